@@ -13,14 +13,14 @@ iteration count.  The default workload is the largest single-problem one, the
   roofline  for the kernel with the most time in the timed steps: algorithmic
           bytes per launch over its average launch duration, timed with HIP
           events on the library's stream, against 8 TB/s HBM.  Per kernel:
-            product over recorded paths  8 B per intersection (particle index,
-                                         K/h^2) + 16 B per ray (row offset,
-                                         FP64 column);
-            recording walk (one walk)    20 B per intersection read (x, y, z,
-                                         h, mu*x in FP32) + 8 B written (the
-                                         entry) + 8 B per ray (its count);
-            chunk compaction             16 B per intersection (entry read and
-                                         written) + 12 B per ray;
+            product over recorded paths  5.5 B per intersection (K/h^2 and the
+                                         particle's slot, in full groups of
+                                         four) + 8 B per ray (FP64 column);
+            recording walk               16 B per intersection read (x, y, z, h
+                                         in FP32) + 0.5 B written (a log word
+                                         per 16 at best);
+            log into paths               16.5 B per intersection read (its log
+                                         word, x, y, z, h) + 5.5 B written;
             traversal without recording  20 B per intersection + 8 B per ray;
   sub-objects  the 262144-particle halo (its own steps, update rules, the
           near/far scheme), forward+adjoint against the plain forward on both
@@ -51,14 +51,13 @@ sys.path.insert(0, ROOT)
 HBM_PEAK_GBS = 8000.0
 BYTES_PER_HIT = 20.0          # x, y, z, h, mu*x (FP32) of each intersected particle
 BYTES_PER_RAY = 8.0           # the FP64 column written per ray
-BYTES_PER_PATH_HIT = 8.0      # recorded (particle index, K/h^2) streamed per intersection
+BYTES_PER_PATH_HIT = 5.5      # recorded K/h^2, slot, share of its group's ray, per intersection
+BYTES_PER_PATH_RAY = 8.0      # the FP64 column written per ray
 BYTES_PER_ROW = 16.0          # row offset read + FP64 column written per ray
 BYTES_PER_TILE_HIT = 6.0      # 16-bit local particle index + FP32 K/h^2 per intersection
 BYTES_PER_TILE_SET = 8.0      # per distinct particle of a tile: its index + its mu*x
-BYTES_PER_WALK_HIT = 28.0     # recording walk: 20 B read + the 8 B entry written
-BYTES_PER_WALK_RAY = 8.0      # its per-ray count
-BYTES_PER_COMPACT_HIT = 16.0  # compaction: each 8 B entry read and written
-BYTES_PER_COMPACT_RAY = 12.0  # row offset and first chunk read per ray
+BYTES_PER_WALK_HIT = 16.5     # recording walk: x, y, z, h read + its share of a log word
+BYTES_PER_BUILD_HIT = 22.0    # log into paths: log word, x, y, z, h read, the entry written
 DEFAULT_WORKLOAD = "lognormal_field_2097152"
 METRIC = "ray-particle intersections/s + particles/s per iteration; fwd+adjoint vs plain"
 
@@ -87,16 +86,16 @@ def make_workload(name: str):
 
 
 # the kernel behind each timed phase (source file, function, counter-name prefix)
-KERNEL_SOURCES = {"recorded_paths": ("paper_1304_4235_amd/csrc/trace.hip", "k_path_stream",
-                                     "k_path_stream<"),
+KERNEL_SOURCES = {"recorded_paths": ("paper_1304_4235_amd/csrc/paths.hip", "k_path_columns",
+                                     "k_path_columns<"),
                   "row_tiles": ("paper_1304_4235_amd/csrc/tiles.hip", "k_tile_columns",
                                 "k_tile_columns<"),
                   "traversal": ("paper_1304_4235_amd/csrc/trace.hip", "k_trace_wave",
                                 "k_trace_wave<0,"),
                   "path_recording_walk": ("paper_1304_4235_amd/csrc/trace.hip", "k_trace_wave",
                                           "k_trace_wave<5,"),
-                  "chunk_compaction": ("paper_1304_4235_amd/csrc/trace.hip", "k_compact_chunks",
-                                       "k_compact_chunks")}
+                  "path_building": ("paper_1304_4235_amd/csrc/paths.hip", "k_build_paths",
+                                    "k_build_paths<")}
 
 
 def kernel_source_sha256(path: str, function: str) -> str:
@@ -244,23 +243,23 @@ def kernel_table(tm, steps, hits_per_iter, rays, wl):
 
     add("traversal", "k_trace_wave<0> (traversal + column, no recorded paths)", tm["trace_ms"],
         tm["n_trace"], BYTES_PER_HIT * hits_per_iter + BYTES_PER_RAY * rays)
-    add("recorded_paths", "k_path_stream (columns from recorded paths, streamed by row blocks)",
+    add("recorded_paths", "k_path_columns (columns from recorded paths, by packets)",
         tm["path_ms"],
-        tm["n_path"], BYTES_PER_PATH_HIT * hits_per_iter + BYTES_PER_ROW * rays)
+        tm["n_path"], BYTES_PER_PATH_HIT * hits_per_iter + BYTES_PER_PATH_RAY * rays)
     add("row_tiles", "k_tile_columns (columns from row tiles)", tm["tile_ms"], tm["n_tile"],
         BYTES_PER_TILE_HIT * hits_per_iter + BYTES_PER_ROW * rays
         + BYTES_PER_TILE_SET * max(tm["tile_set_total"], 0),
         build_ms_per_step=tm["tile_build_ms"] / steps)
     # a recording walk sees every intersection of the geometry once
-    add("path_recording_walk", "k_trace_wave<5> (path recording in one walk into pool chunks)",
+    add("path_recording_walk", "k_trace_wave<5> (path recording: one walk into the log)",
         tm["chunk_walk_ms"], tm["n_chunk_walk"],
-        BYTES_PER_WALK_HIT * hits_per_iter + BYTES_PER_WALK_RAY * rays)
-    add("chunk_compaction", "k_compact_chunks (pool chunks into rows)", tm["compact_ms"],
-        tm["n_chunk_walk"], BYTES_PER_COMPACT_HIT * hits_per_iter + BYTES_PER_COMPACT_RAY * rays)
+        BYTES_PER_WALK_HIT * hits_per_iter)
+    add("path_building", "k_build_paths (the log into segments, with the factors)",
+        tm["compact_ms"], tm["n_chunk_walk"], BYTES_PER_BUILD_HIT * hits_per_iter)
     if tm["other_walk_ms"] > 0:
         kernels["counting_and_recording_walks"] = dict(
-            kernel="k_trace_wave<1>, <3> (a count walk and a record walk: a context's first "
-                   "recording, or a pool that ran short)",
+            kernel="k_trace_wave<3>, <5> (a walk for the sizes and one into the log: a "
+                   "context's first recording, or a log that ran short)",
             total_ms=tm["other_walk_ms"])
     kernels["rate_equilibrium"] = dict(kernel="k_gamma (rate and equilibrium, ALU bound)",
                                        total_ms=tm["rate_ms"])
@@ -368,7 +367,7 @@ def run_single(name, steps, warmup, args, rules=False, near_far=False, adjoint=T
         "phase_ms_per_step": {"tree_build": tm["build_ms"] / steps,
                               "path_recording": tm["record_ms"] / steps,
                               "path_recording_walk": tm["chunk_walk_ms"] / steps,
-                              "chunk_compaction": tm["compact_ms"] / steps,
+                              "path_building": tm["compact_ms"] / steps,
                               "counting_and_recording_walks": tm["other_walk_ms"] / steps,
                               "columns_from_paths": tm["path_ms"] / steps,
                               "columns_from_row_tiles": tm["tile_ms"] / steps,

@@ -89,18 +89,18 @@ typedef struct {
  * kernel chord factor K/h^2 of each) does not depend on x, because the column
  * is linear in the neutral fractions (Sec. 4.1.1, eq. colden).  With path
  * recording the first column evaluation after a tree build traverses the tree
- * and records 8 bytes per intersection (particle index and factor) into the
- * path buffer; every evaluation then forms N = sum (mu x)_j * factor_j by a
- * streaming product over the recorded paths.  Without it, every evaluation
- * traverses the tree.  Both give the same intersections and terms; the two
- * sums differ only in summation order.  The recording takes
- *   - one recording walk, when rrt_count_paths counted the current tree;
- *   - else, when the path buffer has room for the paths and a pool of chunks
- *     beside them (RRT_TUNE_ONE_PASS), one walk that appends each ray's
- *     entries to 32-entry chunks of the pool and counts them, and a copy of
- *     the chunks into rows; if the pool runs short, a second, recording walk
- *     with the counts the first one took;
- *   - else a counting walk and a recording walk. */
+ * and records every intersection (the kernel factor, FP32, and 12 bits that
+ * name the particle) into the path buffer, about 5.9 bytes each; every
+ * evaluation then forms N = sum (mu x)_j * factor_j by a streaming product over
+ * the recorded paths.  Without it, every evaluation traverses the tree.  Both
+ * give the same intersections and terms; the two sums differ only in summation
+ * order.  The recording is a walk that logs its hits in the path buffer and a
+ * pass over the log:
+ *   - one walk, when rrt_count_paths counted the current tree, or when the path
+ *     buffer has room for a log and paths of the last recording's size
+ *     (RRT_TUNE_ONE_PASS); if that log runs short, a second walk with the sizes
+ *     the first one took;
+ *   - else a counting walk and a logging walk. */
 
 /* Library version as major*10000 + minor*100 + patch. */
 int rrt_version(void);
@@ -149,20 +149,21 @@ int rrt_workspace_info(const rrt_ctx* ctx, size_t* out6);
 /* Recorded paths, first step: a counting walk over the current tree (Sec.
  * 4.1.1, eq. colden: which particles each ray intersects).  Host outputs,
  * each nullable: *n_hits, the intersections of every ray (each periodic
- * image separately); *bytes_paths, the path buffer the recorded paths need
- * (8 bytes per intersection and a little padding); *bytes_one_walk, the size
- * with which a later recording of a geometry with up to this many
- * intersections takes one walk (the paths and the chunk pool beside them).
+ * image separately); *bytes_paths, the path buffer that recording the paths
+ * needs (the paths, about 5.9 bytes per intersection, and the walk's log beside
+ * them while recording, 2 to 4); *bytes_one_walk, the size with which a later
+ * recording of a similar geometry takes one walk (with a log a quarter larger).
  * The counts are kept, so the next column evaluation records with one walk.
  * Synchronises. */
 int rrt_count_paths(rrt_ctx* ctx, int64_t* n_hits, size_t* bytes_paths, size_t* bytes_one_walk);
 
 /* Recorded paths, second step: the device memory they are recorded into,
  * owned by the caller, 256-byte aligned (NULL and 0: none).  Besides the
- * paths, the library uses the rest of it for the one-walk chunk pool while
- * recording, and, room permitting, for the reverse mode's transposed paths
- * and kept columns and for row tiles; each of these is optional and has a
- * slower form that needs no memory.  Replacing the buffer drops the recorded
+ * paths, the library uses the rest of it for the walk's log while recording,
+ * and, room permitting, for the reverse mode's transposed paths and kept
+ * columns, for row tiles and for the paths by rows that the density order's
+ * blocks read; each of these is optional and has a slower form that needs no
+ * memory.  Replacing the buffer drops the recorded
  * paths and everything in the old buffer (synchronises the stream first). */
 int rrt_set_path_buffer(rrt_ctx* ctx, void* dev, size_t bytes);
 
@@ -341,8 +342,7 @@ int rrt_backward(rrt_ctx* ctx, const double* dL_dlnG, const double* dL_dx, doubl
  * continue (per-halo masks on the device).  After a first eager iteration
  * (which records the ray paths when they fit in the path buffer; when the
  * whole batch's do not, the halos are solved in groups whose paths fit, after
- * one counting walk, which takes 8 more bytes per ray of workspace; a halo
- * too large alone traverses), the iterations run as replays
+ * one counting walk; a halo too large alone traverses), the iterations run as replays
  * of a HIP graph of per_launch (1..256) iterations captured once per geometry
  * and parameters, on a stream the library owns (ordered after the context's
  * stream by events); the host reads 8 bytes after each replay.  x_out: device
@@ -356,18 +356,16 @@ int rrt_iterate_halos(rrt_ctx* ctx, int32_t max_iter, double tol, int32_t per_la
  *   RRT_TUNE_TRACE_BLOCK  threads per block of the traversal (64, 128, 192, 256)
  *   RRT_TUNE_PACKET       rays walking one node sequence: 64 (a wave-cooperative
  *                         packet, default) or 1 (independent lanes)
- *   RRT_TUNE_PATH_GROUP   lanes per ray in the recorded-path product: 8, 16, 32,
- *                         64, or 0 (default): a full sweep of the plain product
- *                         streams the path array by blocks of rows, and the
- *                         other products (near/far split, halos that stopped,
- *                         per-block source lists) take lanes per ray from the
- *                         mean intersections per ray
+ *   RRT_TUNE_PATH_GROUP   lanes per ray in the products that work by rows (the
+ *                         row tiles and the density order's blocks): 8, 16, 32,
+ *                         64, or 0 (default), from the mean intersections per
+ *                         ray
  *   RRT_TUNE_LEAF         particles per tree leaf (1..16), from the next build
  *   RRT_TUNE_ADJOINT      transposed column product of rrt_backward over
  *                         recorded paths: 0 (default) = gather over paths
  *                         transposed once per geometry when they fit in the
- *                         path buffer (32 bytes per intersection while they are
- *                         built; deterministic), else per row tile in LDS with one
+ *                         path buffer (24 bytes per intersection beside the
+ *                         paths while they are built; deterministic), else per row tile in LDS with one
  *                         atomic add per distinct particle of a tile (when the
  *                         tiles fit), else one atomic add per intersection;
  *                         1 = always one atomic add per intersection;
@@ -376,34 +374,25 @@ int rrt_iterate_halos(rrt_ctx* ctx, int32_t max_iter, double tol, int32_t per_la
  *                         recorded.  1: after a few column evaluations over the
  *                         same recorded paths (and before the graph of a
  *                         batched solve is captured), group consecutive rays
- *                         into tiles whose particle values are staged in LDS,
- *                         so each intersection streams 6 bytes instead of 8 and
- *                         needs no global gather; the columns agree to FP64
- *                         summation order.  The one-time build costs about as
- *                         much as a hundred evaluations save on long rays, so
- *                         it pays for long solves with short rays only.
+ *                         into tiles whose particle values are staged in LDS
+ *                         (6 bytes per intersection); the columns agree to FP64
+ *                         summation order.  The recorded paths stage theirs per
+ *                         segment already, so the tiles no longer pay.
  *   RRT_TUNE_KEEP_COLUMNS 1 (default): rrt_forward keeps every iteration's
  *                         columns for rrt_backward when they fit in the path
  *                         buffer beside the paths (8 n n_ray K bytes); 0:
  *                         rrt_backward recomputes them from the kept states.
  *                         The same columns either way.
- *   RRT_TUNE_ONE_PASS     1 (default): with the wave-cooperative walk,
- *                         record the paths in one walk that appends each
- *                         ray's entries to 32-entry chunks of a pool in the
- *                         path buffer and counts them, then copy the chunks
- *                         into rows; when the pool runs short, record in a
- *                         second walk as with 0.  The pool is sized from the
- *                         context's previous recording or count (so a
- *                         context's first recording takes two walks unless
- *                         rrt_count_paths ran): 5/4 of its entries plus half
- *                         a chunk per ray, in 1024 slices with a counter
- *                         each; after a recording that ran short, half as
- *                         large again (up to 4x).  It is used only when the
- *                         path buffer holds it beside the paths, and freed
- *                         once the paths are in rows.  0: a counting walk,
- *                         then a recording walk.  n > 1: one pass with a pool
- *                         of about n chunks, also on a first recording.  The
- *                         same paths either way.
+ *   RRT_TUNE_ONE_PASS     1 (default): size the recording walk's log from the
+ *                         context's previous recording or count (5/4 of its
+ *                         blocks; after a recording that ran short, half as
+ *                         large again, up to 4x) and record in one walk; when
+ *                         the log runs short, again with the sizes the walk
+ *                         took.  Used only when the path buffer holds the log
+ *                         beside the paths; it is freed once they are recorded.
+ *                         0: a counting walk, then a logging walk.  n > 1: a log
+ *                         of about n times 256 bytes.  The same paths either
+ *                         way.
  *   RRT_TUNE_PACKET_QUEUE 1 (default): the wave-cooperative walk runs as a
  *                         persistent grid of the blocks the device holds at
  *                         once, whose waves take packets (64 sources of one
@@ -512,8 +501,9 @@ int rrt_get_hits(rrt_ctx* ctx, int64_t cap, int64_t* row_off, int32_t* hit_j,
  *   [8] columns from row tiles           [9] number of those launches
  *   [10] row-tile builds                 [11] distinct particles summed over
  *                                             the row tiles (-1 when none)
- *   [12] one-walk chunk walks (inside [4])  [13] number of those walks
- *   [14] chunk compaction (inside [4])   [15] counting and recording walks
+ *   [12] one-walk logging walks (inside [4]) [13] number of those walks
+ *   [14] the passes over the log (inside [4]) [15] counting walks and the
+ *                                             logging walks after a count
  *                                             (inside [4])
  * Timing is recorded only after rrt_enable_timing(ctx, 1): a pair of events
  * on the context's stream around each timed phase, resolved (and the stream
@@ -530,9 +520,9 @@ int rrt_reset_timing(rrt_ctx* ctx);
 int rrt_get_counters(rrt_ctx* ctx, int64_t* out2);
 
 /* Path recordings since rrt_create, host int64 out[n_out] (up to
- * RRT_N_REC_STATS entries): [0] in one walk into the chunk pool, [1] one walk
- * whose pool ran short, finished by a second, recording walk, [2] one
- * recording walk after rrt_count_paths, [3] a counting and a recording walk,
+ * RRT_N_REC_STATS entries): [0] in one walk with the log sized from the last
+ * recording, [1] one walk whose log ran short, and a second, [2] one walk after
+ * rrt_count_paths, [3] a counting and a logging walk,
  * [4] recordings that did not fit the path buffer (traversal instead). */
 enum { RRT_N_REC_STATS = 5 };
 int rrt_get_recording_stats(rrt_ctx* ctx, int64_t* out, int32_t n_out);

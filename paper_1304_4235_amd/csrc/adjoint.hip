@@ -222,25 +222,6 @@ __global__ void k_adj_bins(const double* __restrict__ part2, int n_bins, double*
     acc[b] += s;
 }
 
-// transposed product over recorded paths: y_j += (K/h^2) nu_row for every hit
-__global__ void __launch_bounds__(256)
-k_adj_scatter(const uint64_t* __restrict__ row_off, const int2* __restrict__ path,
-              const float* __restrict__ nu, int64_t n_rows, double* __restrict__ y)
-{
-    const int lane = threadIdx.x & 63;
-    const int64_t stride = (int64_t)gridDim.x * (blockDim.x >> 6);
-    for (int64_t row = (blockIdx.x * (int64_t)blockDim.x + threadIdx.x) >> 6; row < n_rows;
-         row += stride) {
-        const double v = (double)nu[row];
-        if (v == 0.0) continue;
-        const uint64_t a = row_off[row], b = row_off[row + 1];
-        for (uint64_t e = a + lane; e < b; e += 64) {
-            const int2 h = path[e];
-            unsafeAtomicAdd(y + h.x, (double)__int_as_float(h.y) * v);
-        }
-    }
-}
-
 // adjoint of x^{k-1} from the columns, and the density term through mu
 __global__ void k_adj_x(const double* __restrict__ y, const double* __restrict__ mu_s,
                         const float* __restrict__ mu0_s, const float* __restrict__ nH0_s,
@@ -331,16 +312,6 @@ hipError_t launch_adj_rate(Ctx& c, const double* N, const double* lup)
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(k_adj_bins, dim3((c.n_bins + 255) / 256), dim3(256), 0, c.stream, part2,
                        c.n_bins, c.adj_gw);
-    return hipGetLastError();
-}
-
-hipError_t launch_adj_scatter(Ctx& c)
-{
-    const int64_t n_rows = c.n * (int64_t)c.n_ray;
-    hipError_t e = hipMemsetAsync(c.adj_y, 0, sizeof(double) * c.n, c.stream);
-    if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(k_adj_scatter, dim3(stride_blocks(n_rows, 4)), dim3(256), 0,
-                       c.stream, c.row_off, c.path, c.adj_nu, n_rows, c.adj_y);
     return hipGetLastError();
 }
 

@@ -31,17 +31,83 @@ constexpr int kTileMaxSet = 16384;
 // The column products read recorded entries in aligned groups of four, so the
 // arrays holding them are allocated with this many entries to spare.
 constexpr int kPathPad = 4;
-constexpr int kChunkLen = 32;              // entries per chunk of one-pass recording
-constexpr int kChunkShift = 5;             // log2 kChunkLen
-constexpr uint32_t kNoChunk = 0xffffffffu;
-constexpr int kPoolSlices = 1024;          // independent allocation counters
-constexpr int kCtrStride = 16;             // counters 128 bytes apart
-constexpr int kSliceTries = 16;            // slices a chunk request tries
-// Chunks a wave of the persistent recording walk takes from the pool at once;
-// what it holds when the walk ends stays unused, at most kCacheBlock chunks for
-// each of 256 CUs x 32 waves (kCacheAllowance, added to the pool).
-constexpr uint32_t kCacheBlock = 16;
-constexpr uint64_t kCacheAllowance = 256ull * 32 * kCacheBlock;
+// 16-byte words past the segments that the products may read (not use)
+constexpr int kPackedPad = 17;
+
+// ---- recorded paths ----
+// The 64 rays of a packet (one direction, 64 sources consecutive in tree
+// order) walk one node sequence, so their paths are recorded together.  A
+// packet's walk is split into path_parts(c) units; a unit's
+// leaf visits with hits, in order, are cut into segments of at most kSegVisits
+// visits, kSegSlots slots (each visit takes one slot per particle of its leaf)
+// and kSegHits hits.  A ray's hits in a segment, in walk order, fill groups of
+// four.  A segment of the recorded paths (16-byte words):
+//   word 0       visits | slots << 16, groups, size in words, 0
+//   then         leaf word of each visit (u32)
+//   then         per group four factors K/h^2 (FP32, sign bit: the near flag)
+//   then         per group three slots of 10 bits, entries in use less one (2)
+//   then         per group the fourth slot (10 bits) and the ray (6)   (u16)
+// (a group's unused entries repeat its last slot, with factor 0).  Groups are
+// independent of one another, so a wave takes 64 of them at a time whatever
+// rays they belong to: an intersection takes 5.5 bytes, read in order, and its
+// particle's value comes from the slots, staged once per segment.  Lane l of
+// the 64 takes a run of consecutive groups, ray by ray (group_at), so that the
+// lanes add to different rays.
+constexpr int kSegSlots = 1024;
+constexpr int kSegVisits = 128;
+constexpr int kSegHits = 1856;             // >= 64 rays x kLeafMax
+constexpr int kRayPacket = 64;
+constexpr int kSegGroups = kSegHits / 4 + kRayPacket * 3 / 4;   // with the rays' last groups
+// The walk's log: blocks of kLogBlock 8-byte words, the last one the next
+// block's number and the words used (<< 32).  Per segment a header (payload
+// words | visits << 32 | slots << 48; groups; the next segment's header; the 64
+// rays' entries as u16) and its payload: a word per visit, one more for a
+// shifted image, and one per ray that hits.  Neither a header nor a visit's
+// words straddle blocks.
+constexpr uint32_t kLogBlock = 128, kLogData = kLogBlock - 1, kLogHeader = 19;
+constexpr uint32_t kNoBlock = 0xffffffffu;
+// Blocks a wave of the persistent walk takes from the pool at once; what it
+// holds when the walk ends stays unused.
+constexpr uint32_t kLogCache = 8;
+constexpr int64_t kMaxWaves = 256 * 32;    // resident waves of the device
+// |periodic image| along an axis that a log word can hold
+constexpr int kMaxImage = 8191;
+
+__host__ __device__ constexpr uint32_t segment_words(uint32_t visits, uint32_t groups)
+{
+    return 1 + (visits + 3) / 4 + groups + (groups + 3) / 4 + (groups + 7) / 8;
+}
+// the group (in ray order) stored at position pos of n (lane pos % 64 holds a
+// run), and the position of group e
+__host__ __device__ constexpr uint32_t group_at(uint32_t pos, uint32_t n)
+{
+    const uint32_t l = pos & 63u, t = pos >> 6, full = n >> 6, more = n & 63u;
+    return l * full + (l < more ? l : more) + t;
+}
+__host__ __device__ constexpr uint32_t group_place(uint32_t e, uint32_t n)
+{
+    const uint32_t full = n >> 6, more = n & 63u, long_end = more * (full + 1);
+    const uint32_t l = e < long_end ? e / (full + 1) : more + (e - long_end) / full;
+    return ((e - (l * full + (l < more ? l : more))) << 6) + l;
+}
+constexpr int kLogHits = 0, kLogVisit = 1, kLogImage = 2;      // word types, bits 62-63
+__host__ __device__ constexpr uint64_t log_visit_word(int leafw, uint32_t visit)
+{
+    return (uint64_t)(uint32_t)leafw | ((uint64_t)visit << 43) | ((uint64_t)kLogVisit << 62);
+}
+__host__ __device__ constexpr uint64_t log_image_word(int sx, int sy, int sz, uint32_t visit)
+{
+    return (uint64_t)(sx + kMaxImage) | ((uint64_t)(sy + kMaxImage) << 14) |
+           ((uint64_t)(sz + kMaxImage) << 28) | ((uint64_t)visit << 43) |
+           ((uint64_t)kLogImage << 62);
+}
+__host__ __device__ constexpr uint64_t log_hits_word(uint32_t mask, int ray, uint32_t start,
+                                                     uint32_t visit)
+{
+    return (uint64_t)mask | ((uint64_t)ray << 16) | ((uint64_t)start << 22) |
+           ((uint64_t)visit << 43);
+}
+
 // column evaluations over one set of recorded paths before its row tiles are
 // built (the build costs about as much as a few evaluations)
 constexpr int kTileAfter = 8;
@@ -132,8 +198,12 @@ enum {
     kRedConvRel = 5,    // particles of a sweep with |dx| / x < tol
     kRedInput = 6,      // a given x or n_H was non-finite or out of range
     kRedNumeric = 7,    // an update produced a non-finite neutral fraction
-    kRedQueue = 8,      // the persistent walk's next packet
-    kRedSlots = 9
+    kRedQueue = 8,      // the persistent walk's next unit
+    kRedPathSize = 9,   // of a recording's or tally's units: recorded words,
+    kRedPathBlocks = 10,    // log blocks,
+    kRedPathHits = 11,      // intersections,
+    kRedPathSegs = 12,      // segments (recording only)
+    kRedSlots = 13
 };
 
 struct Ctx {
@@ -192,28 +262,34 @@ struct Ctx {
     int32_t* perm = nullptr;     // tree order -> input index
     uint64_t* codes = nullptr;   // sorted keys
 
-    // recorded ray paths (rows = rays in [k][tree position] order)
-    uint64_t* row_off = nullptr;  // [n_ray * n + 1]
-    int2* path = nullptr;         // (tree index, factor K/h^2 bits) per intersection
-    uint64_t path_cap = 0;        // entries allocated
-    int64_t path_hits = 0;        // entries in use
+    // recorded ray paths (paths.hip)
+    uint4* packed = nullptr;      // the segments of every unit
+    uint64_t* seg_off = nullptr;  // first word of each segment
+    uint64_t* unit_seg = nullptr; // [units + 1] first segment of each unit
+    uint64_t path_segs = 0, path_words = 0;
+    int64_t path_hits = 0;        // intersections recorded
     bool paths_valid = false;
     bool paths_unfit = false;     // recording was tried and exceeded the budget
-    // one-pass recording: each ray's hits appended to chunks of kChunkLen
-    // entries from a pool of kPoolSlices slices, linked per row, then
-    // compacted into path
+    // the log of the recording walk, in the path buffer while recording
     bool one_pass = true;
     bool packet_queue = true;    // persistent walk with a global packet queue
-    bool images_fit = true;      // every reachable periodic image codes in 10 bits per axis
-    uint64_t pool_cap = 0;            // > 0: at most this many chunks (tests the fallback)
-    uint64_t last_total = 0;          // entries of the last recording (sizes the pool)
-    int2* pool = nullptr;             // [pool_chunks * kChunkLen]
-    uint32_t* chunk_next = nullptr;   // [pool_chunks] next chunk of the same row
-    uint32_t* row_first = nullptr;    // [pool_rows] first chunk of each row
-    unsigned long long* pool_ctr = nullptr;   // per slice (kCtrStride apart), then overflow
-    uint64_t pool_chunks = 0;         // kPoolSlices * slice_chunks
-    uint64_t slice_chunks = 0;
-    int64_t pool_rows = 0;
+    bool images_fit = true;      // every reachable periodic image fits a log word
+    uint64_t pool_cap = 0;            // > 0: about this many 256-byte chunks of log (tests)
+    uint64_t* path_log = nullptr;     // [log_blocks * kLogBlock]
+    uint2* unit_log = nullptr;        // per unit: first block, segments
+    uint64_t* unit_off = nullptr;     // [units + 1] first word of each unit
+    uint64_t* seg_src = nullptr;      // per segment: its header in the log
+    uint32_t* seg_unit = nullptr;     // per segment: its unit
+    unsigned long long* log_ctr = nullptr;    // next block, pool ran short
+    uint64_t log_blocks = 0;
+    // sizes of the last recording or tally walk: recorded words, log blocks, hits
+    uint64_t last_words = 0, last_blocks = 0, last_total = 0;
+    // the same paths by rows (row = ray), for what needs them that way (row
+    // tiles, the transposition): offsets and (tree index, factor) entries
+    uint64_t* row_off = nullptr;  // [n_ray * n + 1]
+    int2* path = nullptr;         // held while the density order uses it
+    bool rows_unfit = false;      // c.path was tried and did not fit
+    bool rows_valid = false;      // row_off holds the recorded paths' offsets
     uint64_t* tpath = nullptr;    // transposed paths: (factor bits << 32 | row) by particle
     uint64_t* tcol_off = nullptr; // [n + 1] start of each particle's entries
     bool tpaths_valid = false;
@@ -242,10 +318,10 @@ struct Ctx {
     uint8_t* skip_s = nullptr;     // [n] frozen after the first sweep
     uint8_t* want_s = nullptr;     // [n] updated in the current block step
     int32_t* block_s = nullptr;    // [n] block of the density order, tree order
-    int32_t blocks_for = 0;        // rule_blocks that block_s was computed for (0: none)
     int32_t* block_list = nullptr; // [n] tree positions grouped by block (ascending within)
     std::vector<int64_t> block_off;  // [rule_blocks + 1] start of each block in block_list
-    const int32_t* row_list = nullptr;   // the recorded-path product's sources, or null (all)
+    int32_t blocks_for = 0;        // rule_blocks that block_s was computed for (0: none)
+    const int32_t* row_list = nullptr;   // the sources of the running density block, or null
     int64_t row_list_n = 0;
     int path_evals = 0;            // column evaluations since the paths were recorded
     bool capturing = false;        // a graph capture is in progress (no allocation)
@@ -318,12 +394,10 @@ struct Ctx {
     // path recordings since rrt_create: in one walk, one walk that ran short
     // and took a second, after rrt_count_paths, a counting and a recording walk
     int64_t n_rec_one = 0, n_rec_fallback = 0, n_rec_counted = 0, n_rec_two = 0, n_rec_unfit = 0;
-    // row_off holds the exclusive scan of the current geometry's per-ray
-    // counts (rrt_count_paths), count_total their sum
+    // last_words, last_blocks and last_total are those of the current geometry
     bool counts_valid = false;
-    uint64_t count_total = 0;
-    // the one-walk pool holds pool_scale x the last recording's entries (plus
-    // half a chunk per ray); it grows by half after a recording that ran short
+    // the one-walk pool holds pool_scale x the last recording's log blocks; it
+    // grows by half after a recording that ran short
     double pool_scale = 1.25;
     double conv_tol = 0.0;       // tolerance of the running fixed point (convergence counts)
     bool ctx_bufs = false;       // tables, reductions and chunk counters are in the workspace
@@ -339,7 +413,7 @@ struct Ctx {
     double graph_tol = -1.0;
     hipEvent_t ev_a = nullptr, ev_b = nullptr;
 
-    int32_t path_group = 0;       // lanes per ray in the path product (0 = automatic)
+    int32_t path_group = 0;       // lanes per ray in the row-tile products (0 = automatic)
     int32_t adj_scatter = 0;      // 1: atomic scatter, 2: tile scatter, 0: automatic
 
     // counters: intersections of the last iteration and since the last reset
@@ -430,11 +504,9 @@ hipError_t scan_exclusive_u64(Ctx& c, const uint64_t* in, uint64_t* out, int64_t
 // ---- launchers (trace.hip) ----
 void fill_kernel_tables(KernelTables* host);
 hipError_t launch_columns(Ctx& c);
-hipError_t launch_record_paths(Ctx& c, const uint64_t* row_off, int2* path, uint64_t cap);
-hipError_t launch_record_chunks(Ctx& c, uint64_t* row_cnt);
-hipError_t launch_compact_chunks(Ctx& c);
-hipError_t launch_path_columns(Ctx& c, int group);
-hipError_t launch_path_stream(Ctx& c);
+// the recording walk into the log (store), or its sizes only; unit_size
+// receives each unit's recorded words | log blocks << 32
+hipError_t launch_log_walk(Ctx& c, bool store, uint64_t* unit_size);
 void drop_graph(Ctx& c);
 hipError_t build_tiles(Ctx& c);
 hipError_t launch_want(Ctx& c, int block, bool use_skip);
@@ -457,6 +529,27 @@ hipError_t launch_record_rows(Ctx& c, const int32_t* src_list, int32_t src_n,
                               float* hit_fac, uint64_t cap);
 // a count pass of the wave-cooperative walk that also tallies its work
 hipError_t launch_trace_stats(Ctx& c, uint64_t* row_cnt, unsigned long long* stats);
+// ---- recorded paths (paths.hip) ----
+// packets (64 sources of one direction) and the units each is split into
+int64_t path_packets(const Ctx& c);
+int path_parts(const Ctx& c);
+uint32_t log_take(const Ctx& c);
+// the sums of the units' sizes into the reductions (kRedPathSize, Blocks, and
+// with segments Segs)
+hipError_t launch_sum_units(Ctx& c, const uint64_t* unit_size, bool segments);
+// the units' sizes (words | blocks << 32) as words alone, their segments into
+// c.unit_seg
+hipError_t launch_unit_words(Ctx& c);
+hipError_t launch_build_paths(Ctx& c);
+hipError_t launch_path_columns(Ctx& c);
+// the rows of the listed sources (one block of the density order) from c.path
+hipError_t launch_row_columns(Ctx& c, int group);
+hipError_t launch_path_scatter(Ctx& c, const float* nu, double* y);
+// row offsets of the recorded paths into c.row_off
+hipError_t ensure_row_offsets(Ctx& c);
+// the entries by rows: (tree index, factor), or keys and (factor bits, row)
+hipError_t launch_expand_rows(Ctx& c, int2* path);
+hipError_t launch_expand_keys(Ctx& c, uint32_t* key, uint64_t* val);
 // sampled rows (tree-order row ids) of the recorded paths: counts when
 // dst_off is null, else the entries at those offsets
 hipError_t launch_path_rows(Ctx& c, const int64_t* rows, int m, uint64_t* cnt,
@@ -473,7 +566,6 @@ hipError_t launch_gather_cols(Ctx& c);
 // ---- launchers (adjoint.hip) ----
 hipError_t launch_set_density(Ctx& c, const float* nH);
 hipError_t launch_adj_rate(Ctx& c, const double* N, const double* lup);
-hipError_t launch_adj_scatter(Ctx& c);
 hipError_t launch_adj_x(Ctx& c, const double* xprev);
 hipError_t launch_adj_init(Ctx& c, double* part);
 int64_t adj_waves(const Ctx& c);
@@ -494,8 +586,8 @@ hipError_t launch_state_from_input(Ctx& c, const double* src);
 hipError_t launch_mux(Ctx& c);
 hipError_t launch_seg_finalize(Ctx& c, double tol, int max_iter);
 hipError_t launch_seg_init(Ctx& c);
-hipError_t launch_halo_hits(Ctx& c, const uint64_t* row_cnt, unsigned long long* out);
-hipError_t launch_mask_rows(Ctx& c, const uint64_t* row_cnt, const int32_t* mask, uint64_t* row_off);
+// per halo: recorded words and log blocks of the units its rays are in
+hipError_t launch_halo_sizes(Ctx& c, const uint64_t* unit_tally, unsigned long long* out);
 hipError_t launch_seg_group_init(Ctx& c, const int32_t* mask);
 
 }  // namespace rrt

@@ -572,29 +572,28 @@ hipError_t launch_block_ids(Ctx& c, const int32_t* block_in)
     return hipGetLastError();
 }
 
-// intersections per halo from per-ray counts (rows are [direction][tree position])
-__global__ void k_halo_hits(const uint64_t* __restrict__ row_cnt, int64_t n_rows, int64_t n,
-                            const int32_t* __restrict__ seg_of, unsigned long long* __restrict__ out)
+// Per halo the recorded words and log blocks of the units its rays are in
+// (out[2h], out[2h + 1]): an upper bound of what its rays alone take, since a
+// unit that a packet across two halos walks counts for both.
+__global__ void k_halo_sizes(const uint64_t* __restrict__ unit_tally, int64_t packets, int parts,
+                             int64_t n, const int32_t* __restrict__ seg_of,
+                             unsigned long long* __restrict__ out)
 {
-    const int64_t r = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-    const int h = r < n_rows ? seg_of[r % n] : -1;
-    unsigned long long v = r < n_rows ? (unsigned long long)row_cnt[r] : 0ull;
-    const int h0 = __shfl(h, 0, 64);
-    if (h0 >= 0 && __ballot(h != h0 && h >= 0) == 0) {
-        for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
-        if ((threadIdx.x & 63) == 0 && v) atomicAdd(out + h0, v);
-    } else if (h >= 0 && v) {
-        atomicAdd(out + h, v);
+    const int64_t pk = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
+    if (pk >= packets) return;
+    unsigned long long words = 0, blocks = 0;
+    for (int q = 0; q < parts; ++q) {
+        const uint64_t v = unit_tally[pk * parts + q];
+        words += v & 0xffffffffull;
+        blocks += v >> 32;
     }
-}
-
-// per-ray counts of the halos in `mask`, zero for the others
-__global__ void k_mask_rows(const uint64_t* __restrict__ row_cnt, int64_t n_rows, int64_t n,
-                            const int32_t* __restrict__ seg_of, const int32_t* __restrict__ mask,
-                            uint64_t* __restrict__ row_off)
-{
-    const int64_t r = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-    if (r < n_rows) row_off[r] = mask[seg_of[r % n]] ? row_cnt[r] : 0ull;
+    // the halos of the packet's sources (consecutive in tree order)
+    const int64_t p0 = (pk % ((n + 63) / 64)) * 64;
+    const int64_t p1 = p0 + 63 < n ? p0 + 63 : n - 1;
+    for (int h = seg_of[p0]; h <= seg_of[p1]; ++h) {
+        atomicAdd(out + 2 * h, words);
+        atomicAdd(out + 2 * h + 1, blocks);
+    }
 }
 
 // start a group of halos: only the masked ones iterate; iteration counts kept
@@ -623,19 +622,11 @@ __global__ void k_seg_group_init(int n_halo, const int32_t* __restrict__ mask,
     }
 }
 
-hipError_t launch_halo_hits(Ctx& c, const uint64_t* row_cnt, unsigned long long* out)
+hipError_t launch_halo_sizes(Ctx& c, const uint64_t* unit_tally, unsigned long long* out)
 {
-    const int64_t n_rows = c.n * (int64_t)c.n_ray;
-    hipLaunchKernelGGL(k_halo_hits, dim3(nblk(n_rows)), dim3(kBlock), 0, c.stream, row_cnt, n_rows,
-                       c.n, c.seg_of, out);
-    return hipGetLastError();
-}
-
-hipError_t launch_mask_rows(Ctx& c, const uint64_t* row_cnt, const int32_t* mask, uint64_t* row_off)
-{
-    const int64_t n_rows = c.n * (int64_t)c.n_ray;
-    hipLaunchKernelGGL(k_mask_rows, dim3(nblk(n_rows)), dim3(kBlock), 0, c.stream, row_cnt, n_rows,
-                       c.n, c.seg_of, mask, row_off);
+    const int64_t pk = path_packets(c);
+    hipLaunchKernelGGL(k_halo_sizes, dim3(nblk(pk)), dim3(kBlock), 0, c.stream, unit_tally, pk,
+                       path_parts(c), c.n, c.seg_of, out);
     return hipGetLastError();
 }
 

@@ -92,6 +92,7 @@ void free_columns(Ctx& c)
     ws_free(c, &c.N_s);
     ws_free(c, &c.Nn_s);
     ws_free(c, &c.row_off);
+    c.rows_valid = false;
     c.counts_valid = false;
 }
 
@@ -147,7 +148,7 @@ int alloc_particles(Ctx& c, int64_t n)
     return RRT_OK;
 }
 
-// Columns (and near columns) and the recorded paths' row offsets, [n_ray][n].
+// Columns (and near columns) and the row offsets, [n_ray][n].
 int alloc_columns(Ctx& c)
 {
     free_columns(c);
@@ -167,13 +168,13 @@ int alloc_columns(Ctx& c)
     return RRT_OK;
 }
 
-// The context's own small buffers: kernel tables, reductions, chunk counters.
+// The context's own small buffers: kernel tables, reductions, the log's counters.
 int alloc_ctx_buffers(Ctx& c)
 {
     if (c.ctx_bufs) return RRT_OK;
     HIP_OK(ws_alloc(c, &c.tables, 1));
     HIP_OK(ws_alloc(c, &c.red, kRedSlots));
-    HIP_OK(ws_alloc(c, &c.pool_ctr, (size_t)kPoolSlices * kCtrStride + 1));
+    HIP_OK(ws_alloc(c, &c.log_ctr, 2));
     KernelTables host;
     fill_kernel_tables(&host);
     HIP_OK(hipMemcpyAsync(c.tables, &host, sizeof host, hipMemcpyHostToDevice, c.stream));
@@ -285,13 +286,14 @@ void free_tpaths(Ctx& c)
     c.tpaths_unfit = false;
 }
 
-void free_pool(Ctx& c)
+void free_log(Ctx& c)
 {
-    ws_free(c, &c.pool);
-    ws_free(c, &c.chunk_next);
-    ws_free(c, &c.row_first);
-    c.pool_chunks = c.slice_chunks = 0;
-    c.pool_rows = 0;
+    ws_free(c, &c.path_log);
+    ws_free(c, &c.unit_log);
+    ws_free(c, &c.unit_off);
+    ws_free(c, &c.seg_src);
+    ws_free(c, &c.seg_unit);
+    c.log_blocks = 0;
 }
 
 // What is recorded in the path buffer and derived from the recorded paths.
@@ -300,94 +302,152 @@ void free_paths(Ctx& c)
     drop_graph(c);
     free_tpaths(c);
     free_tiles(c);
-    free_pool(c);
+    free_log(c);
     c.path_evals = 0;
+    ws_free(c, &c.packed);
+    ws_free(c, &c.seg_off);
+    ws_free(c, &c.unit_seg);
+    c.path_segs = c.path_words = 0;
     ws_free(c, &c.path);
-    c.path_cap = 0;
+    c.rows_valid = false;
+    c.rows_unfit = false;
     c.path_hits = 0;
     c.paths_valid = false;
     c.paths_unfit = false;
 }
 
-// Chunks of the one-walk pool for a recording expected to hold `entries`
-// entries over n_rows rays: pool_scale x entries plus half a chunk per ray,
-// plus what the walk's waves may hold unused in their caches, rounded up to
-// whole slices (or the tuned pool size).
-uint64_t pool_chunks_for(const Ctx& c, uint64_t entries, int64_t n_rows)
+uint64_t region_bytes(uint64_t b) { return (b + kWsAlign - 1) / kWsAlign * kWsAlign; }
+
+// Log blocks for a recording expected to need `blocks` of them: with what the
+// walk's waves may hold unused (log_take at a time), or the tuned pool size (in
+// chunks of 256 bytes).
+uint64_t log_pool(const Ctx& c, uint64_t blocks, double scale, bool tuned)
 {
-    uint64_t chunks;
-    if (c.pool_cap) {
-        chunks = c.pool_cap;
-    } else {
-        const uint64_t e = (uint64_t)((double)entries * c.pool_scale) +
-                           (uint64_t)n_rows * (kChunkLen / 2);
-        chunks = (e + kChunkLen - 1) / kChunkLen + kCacheAllowance;
-    }
-    const uint64_t per_slice =
-        std::min<uint64_t>((chunks + kPoolSlices - 1) / kPoolSlices, 0xfffffff0ull / kPoolSlices);
-    return per_slice * kPoolSlices;
+    if (tuned && c.pool_cap) return std::max<uint64_t>(c.pool_cap * 256 / (kLogBlock * 8), 1);
+    const uint64_t spare = (log_take(c) - 1) *
+                           (uint64_t)std::min<int64_t>(path_packets(c) * path_parts(c), kMaxWaves);
+    return (uint64_t)((double)blocks * scale) + 1 + spare;
 }
 
-uint64_t pool_bytes(uint64_t chunks, int64_t n_rows)
+// a segment's entries in seg_off, seg_src and seg_unit
+constexpr uint64_t kSegmentBytes = 2 * sizeof(uint64_t) + sizeof(uint32_t);
+
+// Path buffer for a recording of `words` 16-byte words and a log of `blocks`
+// (a full segment takes at least 32 words, and a unit leaves one open).
+uint64_t record_bytes(const Ctx& c, uint64_t words, uint64_t blocks)
 {
-    auto up = [](uint64_t b) { return (b + kWsAlign - 1) / kWsAlign * kWsAlign; };
-    return up(chunks * sizeof(int2) * kChunkLen) + up(chunks * sizeof(uint32_t)) +
-           up((uint64_t)n_rows * sizeof(uint32_t));
+    const uint64_t units = (uint64_t)(path_packets(c) * path_parts(c));
+    const uint64_t segs = units + words / 32;
+    return 2 * region_bytes((units + 1) * sizeof(uint64_t)) + region_bytes(units * sizeof(uint2)) +
+           region_bytes(segs * kSegmentBytes) + 2 * kWsAlign +
+           region_bytes(blocks * kLogBlock * sizeof(uint64_t)) +
+           region_bytes((words + kPackedPad) * 16);
 }
 
-uint64_t path_bytes(uint64_t entries)
+// The log's pool and the units' arrays in the path buffer, when they fit
+// beside paths of `words`.  False (nothing kept) otherwise.
+bool alloc_log(Ctx& c, uint64_t words, uint64_t blocks)
 {
-    return (((entries ? entries : 1) + kPathPad) * sizeof(int2) + kWsAlign - 1) / kWsAlign *
-           kWsAlign;
-}
-
-// The one-walk pool in the path buffer, when it fits beside paths of about the
-// expected size.  No pool (and no error) otherwise.
-void ensure_pool(Ctx& c, int64_t n_rows, uint64_t expect)
-{
-    free_pool(c);
-    if (!c.pool_cap && expect == 0) return;            // nothing to size it from
-    const uint64_t chunks = pool_chunks_for(c, expect, n_rows);
-    if (pool_bytes(chunks, n_rows) + path_bytes(expect) > ws_largest_gap(c, kRegionPath)) return;
-    hipError_t e = ws_alloc(c, &c.pool, chunks * kChunkLen, kRegionPath);
-    if (e == hipSuccess) e = ws_alloc(c, &c.chunk_next, chunks, kRegionPath);
-    if (e == hipSuccess) e = ws_alloc(c, &c.row_first, (size_t)n_rows, kRegionPath);
+    free_log(c);
+    if (blocks > 0xfffffff0ull) return false;          // block numbers are 32-bit
+    const size_t units = (size_t)(path_packets(c) * path_parts(c));
+    hipError_t e = ws_alloc(c, &c.unit_seg, units + 1, kRegionPath);
+    if (e == hipSuccess) e = ws_alloc(c, &c.unit_off, units + 1, kRegionPath);
+    if (e == hipSuccess) e = ws_alloc(c, &c.unit_log, units, kRegionPath);
+    if (e == hipSuccess) e = ws_alloc(c, &c.path_log, (size_t)blocks * kLogBlock, kRegionPath);
+    if (e == hipSuccess && ws_largest_gap(c, kRegionPath) < region_bytes(words * 16))
+        e = hipErrorOutOfMemory;
     if (e != hipSuccess) {
-        free_pool(c);
-        return;
+        free_log(c);
+        ws_free(c, &c.unit_seg);
+        return false;
     }
-    c.pool_chunks = chunks;
-    c.slice_chunks = chunks / kPoolSlices;
-    c.pool_rows = n_rows;
+    c.log_blocks = blocks;
+    return true;
+}
+
+// One walk for its sizes (store false) or into the log: last_words,
+// last_blocks and last_total, and whether the pool ran short.
+int path_walk(Ctx& c, bool store, uint64_t* unit_tally, bool* overflow)
+{
+    HIP_OK(hipMemsetAsync(c.red + kRedPathSize, 0, 4 * sizeof(unsigned long long), c.stream));
+    HIP_OK(hipMemsetAsync(c.log_ctr, 0, 2 * sizeof(unsigned long long), c.stream));
+    // the units' sizes: the recorded paths' offsets to be, the caller's array, or
+    // scratch
+    const size_t units = (size_t)(path_packets(c) * path_parts(c));
+    Scratch<uint64_t> tmp(c);
+    uint64_t* size = store ? c.unit_off : unit_tally;
+    if (!size && c.row_off && units <= (size_t)c.n * c.n_ray) {
+        size = c.row_off;
+        c.rows_valid = false;
+    }
+    if (!size) {
+        HIP_OK(tmp.get(units));
+        size = tmp.p;
+    }
+    HIP_OK(launch_log_walk(c, store, size));
+    HIP_OK(launch_sum_units(c, size, store));
+    HIP_OK(hipMemcpyAsync(c.red_host + kRedPathSize, c.red + kRedPathSize,
+                          4 * sizeof(unsigned long long), hipMemcpyDeviceToHost, c.stream));
+    unsigned long long ctr[2] = {0, 0};
+    HIP_OK(hipMemcpyAsync(ctr, c.log_ctr, sizeof ctr, hipMemcpyDeviceToHost, c.stream));
+    HIP_OK(hipStreamSynchronize(c.stream));
+    c.last_words = c.red_host[kRedPathSize];
+    c.last_blocks = c.red_host[kRedPathBlocks];
+    c.last_total = c.red_host[kRedPathHits];
+    if (store) {
+        c.path_segs = c.red_host[kRedPathSegs];
+        c.path_words = c.last_words;
+    }
+    if (overflow) *overflow = ctr[1] != 0;
+    return RRT_OK;
+}
+
+// The log into the recorded paths; false when they do not fit.
+int build_paths(Ctx& c, bool* fit)
+{
+    const int64_t units = path_packets(c) * path_parts(c);
+    const size_t segs = (size_t)std::max<uint64_t>(c.path_segs, 1);
+    hipError_t e = ws_alloc(c, &c.seg_off, segs, kRegionPath);
+    if (e == hipSuccess) e = ws_alloc(c, &c.seg_src, segs, kRegionPath);
+    if (e == hipSuccess) e = ws_alloc(c, &c.seg_unit, segs, kRegionPath);
+    if (e == hipSuccess)
+        e = ws_alloc(c, &c.packed, (size_t)c.last_words + kPackedPad, kRegionPath);
+    *fit = e == hipSuccess;
+    if (!*fit) return RRT_OK;
+    HIP_OK(launch_unit_words(c));
+    HIP_OK(scan_exclusive_u64(c, c.unit_off, c.unit_off, units + 1));
+    HIP_OK(scan_exclusive_u64(c, c.unit_seg, c.unit_seg, units + 1));
+    HIP_OK(launch_build_paths(c));
+    free_log(c);
+    return RRT_OK;
 }
 
 // The paths do not fit the path buffer: traverse instead, or fail when
 // recording is required.
-int paths_unfit(Ctx& c, uint64_t total)
+int paths_unfit(Ctx& c)
 {
     free_paths(c);
-    c.last_total = total;
     c.n_rec_unfit += 1;
     if (c.prm.record_paths == 1)
         return fail(c, RRT_E_WORKSPACE,
                     "recorded paths need %llu bytes; the path buffer holds %llu "
                     "(rrt_count_paths, rrt_set_path_buffer)",
-                    (unsigned long long)path_bytes(total),
+                    (unsigned long long)record_bytes(c, c.last_words,
+                                                     log_pool(c, c.last_blocks, 1.0, false)),
                     (unsigned long long)c.arena.cap[kRegionPath]);
     c.paths_unfit = true;
     return RRT_OK;
 }
 
-// Record (tree index, K/h^2) per intersection into the path buffer, rows in
-// order, with row offsets in c.row_off: one recording walk when the counts of
-// this tree are known (rrt_count_paths); else one walk into pool chunks, their
-// compaction into rows, and a second, recording walk only when the pool ran
-// short; else a counting walk and a recording walk.  Leaves the paths unfit
-// (and traversal in charge) when they do not fit the path buffer.
+// Record the paths into the path buffer: a walk that logs its hits, then a
+// pass over the log.  The log's size is known from rrt_count_paths, or taken
+// from the last recording (a second walk when that ran short), else from a
+// walk for the sizes alone.  Leaves the paths unfit (and traversal in charge)
+// when they do not fit the path buffer.
 int record_paths(Ctx& c)
 {
     Range range("rrt: record paths");
-    const int64_t n_rows = c.n * (int64_t)c.n_ray;
     free_paths(c);
     if (!c.arena.base[kRegionPath]) {
         c.n_rec_unfit += 1;
@@ -398,73 +458,51 @@ int record_paths(Ctx& c)
         c.paths_unfit = true;
         return RRT_OK;
     }
+    if (!c.images_fit) return paths_unfit(c);
     hipEvent_t ev_rec = ev_begin(c);
-    uint64_t total = 0;
-    int kind = 3;                                   // counting walk + recording walk
-    if (c.counts_valid) {
-        total = c.count_total;
-        kind = 2;
-    } else {
-        bool chunked = false;
-        if (c.one_pass && c.prm.traversal == 0 && c.images_fit) {
-            ensure_pool(c, n_rows, c.last_total);
-            chunked = c.pool != nullptr;
-        }
-        const size_t n_ctr = (size_t)kPoolSlices * kCtrStride + 1;
-        if (chunked) {
-            HIP_OK(hipMemsetAsync(c.pool_ctr, 0, n_ctr * sizeof(unsigned long long), c.stream));
-            hipEvent_t ew = ev_begin(c);
-            HIP_OK(launch_record_chunks(c, c.row_off));
-            ev_end(c, ew, &c.t_chunk_walk);
-            c.n_chunk_walk += c.timing ? 1 : 0;
-        } else {
-            hipEvent_t ew = ev_begin(c);
-            HIP_OK(launch_count_hits(c, c.row_off));
-            ev_end(c, ew, &c.t_other_walk);
-        }
-        HIP_OK(hipMemsetAsync(c.row_off + n_rows, 0, sizeof(uint64_t), c.stream));
-        HIP_OK(scan_exclusive_u64(c, c.row_off, c.row_off, n_rows + 1));
-        unsigned long long overflow = 0;
-        HIP_OK(hipMemcpyAsync(&total, c.row_off + n_rows, sizeof total, hipMemcpyDeviceToHost,
-                              c.stream));
-        if (chunked)
-            HIP_OK(hipMemcpyAsync(&overflow, c.pool_ctr + n_ctr - 1, sizeof overflow,
-                                  hipMemcpyDeviceToHost, c.stream));
-        HIP_OK(hipStreamSynchronize(c.stream));
-        if (chunked) {
-            kind = overflow ? 1 : 0;
-            // a pool that ran short is sized half as large again next time
-            if (overflow) c.pool_scale = std::min(c.pool_scale * 1.5, 4.0);
-        }
-        c.counts_valid = true;                      // row_off holds this tree's offsets
-        c.count_total = total;
-    }
-    // the compaction needs the paths beside the pool; the recording walk only
-    // the paths
-    if (kind == 0 && ws_alloc(c, &c.path, total + kPathPad, kRegionPath) != hipSuccess) kind = 1;
-    if (kind != 0) {
-        free_pool(c);
-        if (ws_alloc(c, &c.path, total + kPathPad, kRegionPath) != hipSuccess) {
-            ev_end(c, ev_rec, &c.t_record);
-            return paths_unfit(c, total);
-        }
-    }
-    c.path_cap = std::max<uint64_t>(total, 1);
-    hipEvent_t ew = ev_begin(c);
-    if (kind == 0) {
-        HIP_OK(launch_compact_chunks(c));
-        ev_end(c, ew, &c.t_compact);
-    } else {
-        HIP_OK(launch_record_paths(c, c.row_off, c.path, total));
+    int kind = c.counts_valid ? 2 : 3;      // after a count; a sizes walk first
+    bool logged = false;
+    if (!c.counts_valid && c.one_pass && c.last_total > 0 &&
+        alloc_log(c, c.last_words, log_pool(c, c.last_blocks, c.pool_scale, true))) {
+        bool overflow = false;
+        hipEvent_t ew = ev_begin(c);
+        if (int r = path_walk(c, true, nullptr, &overflow)) return r;
+        ev_end(c, ew, &c.t_chunk_walk);
+        c.n_chunk_walk += c.timing ? 1 : 0;
+        kind = overflow ? 1 : 0;
+        logged = !overflow;
+        // a pool that ran short is sized half as large again next time
+        if (overflow) c.pool_scale = std::min(c.pool_scale * 1.5, 4.0);
+    } else if (!c.counts_valid) {
+        hipEvent_t ew = ev_begin(c);
+        if (int r = path_walk(c, false, nullptr, nullptr)) return r;
         ev_end(c, ew, &c.t_other_walk);
     }
-    free_pool(c);
+    c.counts_valid = true;
+    if (!logged) {
+        if (!alloc_log(c, c.last_words, log_pool(c, c.last_blocks, 1.0, false))) {
+            ev_end(c, ev_rec, &c.t_record);
+            return paths_unfit(c);
+        }
+        bool overflow = false;
+        hipEvent_t ew = ev_begin(c);
+        if (int r = path_walk(c, true, nullptr, &overflow)) return r;
+        ev_end(c, ew, &c.t_other_walk);
+        if (overflow) return fail(c, RRT_E_HIP, "the recording's log ran past its counted size");
+    }
+    hipEvent_t ew = ev_begin(c);
+    bool fit = false;
+    if (int r = build_paths(c, &fit)) return r;
+    ev_end(c, ew, &c.t_compact);
+    if (!fit) {
+        ev_end(c, ev_rec, &c.t_record);
+        return paths_unfit(c);
+    }
     if (kind == 0) c.n_rec_one += 1;
     else if (kind == 1) c.n_rec_fallback += 1;
     else if (kind == 2) c.n_rec_counted += 1;
     else c.n_rec_two += 1;
-    c.path_hits = (int64_t)total;
-    c.last_total = total;
+    c.path_hits = (int64_t)c.last_total;
     c.paths_valid = true;
     ev_end(c, ev_rec, &c.t_record);
     return RRT_OK;
@@ -480,29 +518,38 @@ int columns_impl(Ctx& c, int64_t* hits)
         if (int r = record_paths(c)) return r;
     }
     if (c.paths_valid) {
-        const int64_t n_rows = c.n * (int64_t)c.n_ray;
-        const double mean = (double)c.path_hits / (double)std::max<int64_t>(n_rows, 1);
-        // measured on MI355X: 32 lanes per ray are fastest from a few tens of
-        // intersections per ray up to hundreds; short rays want fewer lanes
-        const int group = c.path_group ? c.path_group
-                          : mean >= 40 ? 32 : mean >= 16 ? 16 : 8;
-        // a full sweep of the plain product streams the path array by blocks
-        // of rows unless a lane group per ray is asked for
-        const bool stream = c.path_group == 0 && !c.near_far && !c.row_list &&
-                            !c.geom.seg_active && !c.geom.want;
         if (c.use_tiles && !c.near_far && !c.tiles_valid && !c.tiles_unfit && !c.capturing &&
             ++c.path_evals > kTileAfter) {
             hipEvent_t et = ev_begin(c);
             HIP_OK(build_tiles(c));
             ev_end(c, et, &c.t_tile_build);
         }
-        // a source list (one block of the density order) walks only its own
-        // rows in the plain product; the tiles serve full sweeps
+        // One block of the density order runs a few rays of most packets, so it
+        // takes the paths by rows, which walk only its own; without room for
+        // them, the packets' product with the others masked.  The tiles serve
+        // full sweeps.
         const bool tiles = c.tiles_valid && c.use_tiles && !c.near_far && !c.row_list;
+        if (c.row_list && !c.path && !c.rows_unfit) {
+            hipError_t e = ensure_row_offsets(c);
+            if (e == hipSuccess)
+                e = ws_alloc(c, &c.path, (size_t)c.path_hits + kPathPad, kRegionPath);
+            if (e == hipSuccess) e = launch_expand_rows(c, c.path);
+            else if (e == hipErrorOutOfMemory) {
+                c.rows_unfit = true;
+                e = hipSuccess;
+            }
+            HIP_OK(e);
+        }
+        const double mean = (double)c.path_hits /
+                            (double)std::max<int64_t>(c.n * (int64_t)c.n_ray, 1);
+        // measured on MI355X: 32 lanes per ray are fastest from a few tens of
+        // intersections per ray up to hundreds; short rays want fewer lanes
+        const int group = c.path_group ? c.path_group
+                          : mean >= 40 ? 32 : mean >= 16 ? 16 : 8;
         hipEvent_t ep = ev_begin(c);
         if (tiles) HIP_OK(launch_tile_columns(c, tile_group(c)));
-        else if (stream) HIP_OK(launch_path_stream(c));
-        else HIP_OK(launch_path_columns(c, group));
+        else if (c.row_list && c.path) HIP_OK(launch_row_columns(c, group));
+        else HIP_OK(launch_path_columns(c));
         if (c.timing) {
             if (tiles) {
                 ev_end(c, ep, &c.t_tile);
@@ -1084,8 +1131,8 @@ int rrt_build_tree(rrt_ctx* x)
     }
     g.hmax = hmax;
     g.pad = (float)(4e-6 * 2.0 * (maxabs + g.L + (double)hmax + g.box));
-    // the one-walk recording codes a hit's periodic image in 10 bits per axis
-    c.images_fit = !(g.box > 0.0) || (g.L + (double)hmax + ext) / g.box + 2.0 <= 511.0;
+    // the recording's log codes a hit's periodic image in 14 bits per axis
+    c.images_fit = !(g.box > 0.0) || (g.L + (double)hmax + ext) / g.box + 2.0 <= kMaxImage;
     g.n = (int32_t)c.n;
     g.n_ray = c.n_ray;
     g.n_nodes = nn;
@@ -1194,9 +1241,9 @@ int ensure_blocks(Ctx& c)
     for (int b = 0; b < c.rule_blocks; ++b) c.block_off[b + 1] += c.block_off[b];
     std::vector<int64_t> fill(c.block_off.begin(), c.block_off.end() - 1);
     for (int64_t i = 0; i < n; ++i) lst[(size_t)fill[blk[i]]++] = (int32_t)i;
-    HIP_OK(hipMemcpyAsync(c.block_s, blk.data(), sizeof(int32_t) * n, hipMemcpyHostToDevice,
-                          c.stream));
     HIP_OK(hipMemcpyAsync(c.block_list, lst.data(), sizeof(int32_t) * n, hipMemcpyHostToDevice,
+                          c.stream));
+    HIP_OK(hipMemcpyAsync(c.block_s, blk.data(), sizeof(int32_t) * n, hipMemcpyHostToDevice,
                           c.stream));
     HIP_OK(hipStreamSynchronize(c.stream));
     c.blocks_for = c.rule_blocks;
@@ -1400,6 +1447,7 @@ int rrt_forward(rrt_ctx* x, int32_t K, double* lnG_out, double* x_out)
     }
     const size_t nr = n * (size_t)c.n_ray;
     c.fwd_K = -1;
+    ws_free(c, &c.path);               // the density order's: its room may be needed
     HIP_OK(launch_init_state(c, false));
     HIP_OK(hipMemcpyAsync(c.xhist, c.x_s, sizeof(double) * n, hipMemcpyDeviceToDevice,
                           c.stream));
@@ -1505,7 +1553,7 @@ int rrt_backward(rrt_ctx* x, const double* dL_dlnG, const double* dL_dx, double*
         } else if (tile_scatter) {
             HIP_OK(launch_tile_scatter(c, c.adj_nu, c.adj_y));
         } else if (c.paths_valid) {
-            HIP_OK(launch_adj_scatter(c));
+            HIP_OK(launch_path_scatter(c, c.adj_nu, c.adj_y));
         } else {
             HIP_OK(hipMemsetAsync(c.adj_y, 0, sizeof(double) * n, c.stream));
             HIP_OK(launch_scatter_traverse(c, c.adj_nu, c.adj_y));
@@ -1647,54 +1695,69 @@ int run_active_halos(Ctx& c, double tol, int32_t max_iter, int32_t per_launch)
     return RRT_OK;
 }
 
-// Which halos can share recorded paths: per-halo intersection totals from one
-// count pass, packed first-fit by decreasing size into groups whose paths fit
-// the path buffer.  A halo too large for it alone forms a group that
-// traverses every iteration.  Counts stay in row_cnt for the per-group offsets.
-int plan_groups(Ctx& c, uint64_t* row_cnt, std::vector<std::vector<int>>& groups,
-                std::vector<bool>& recordable, uint64_t& max_group)
+// Which halos can share recorded paths: per-halo sizes from one walk, packed
+// first-fit by decreasing size into groups whose paths (and their log) fit the
+// path buffer.  A halo too large for it alone forms a group that traverses
+// every iteration.
+int plan_groups(Ctx& c, std::vector<std::vector<int>>& groups, std::vector<bool>& recordable,
+                uint64_t& max_words, uint64_t& max_blocks)
 {
     const int nh = c.n_halo;
-    std::vector<unsigned long long> hits(nh);
+    const int64_t units = path_packets(c) * path_parts(c);
+    std::vector<unsigned long long> size(2 * (size_t)nh);
     {
-        Scratch<unsigned long long> d_hits(c);
-        HIP_OK(d_hits.get((size_t)nh));
-        HIP_OK(hipMemsetAsync(d_hits.p, 0, sizeof(unsigned long long) * nh, c.stream));
-        HIP_OK(launch_count_hits(c, row_cnt));
-        HIP_OK(launch_halo_hits(c, row_cnt, d_hits.p));
-        HIP_OK(hipMemcpyAsync(hits.data(), d_hits.p, sizeof(unsigned long long) * nh,
+        Scratch<uint64_t> tally(c);
+        Scratch<unsigned long long> d_size(c);
+        HIP_OK(tally.get((size_t)units));
+        HIP_OK(d_size.get(2 * (size_t)nh));
+        HIP_OK(hipMemsetAsync(d_size.p, 0, sizeof(unsigned long long) * 2 * nh, c.stream));
+        if (int r = path_walk(c, false, tally.p, nullptr)) return r;
+        HIP_OK(launch_halo_sizes(c, tally.p, d_size.p));
+        HIP_OK(hipMemcpyAsync(size.data(), d_size.p, sizeof(unsigned long long) * 2 * nh,
                               hipMemcpyDeviceToHost, c.stream));
         HIP_OK(hipStreamSynchronize(c.stream));
     }
-    // entries the path buffer holds (with the padding of one array)
-    const uint64_t room = c.arena.cap[kRegionPath] / sizeof(int2);
-    const uint64_t cap = room > (uint64_t)kPathPad + kWsAlign ? room - kPathPad - kWsAlign : 0;
+    // bytes of each halo's paths and log, and the room beside the fixed arrays
+    auto bytes = [&](int h) {
+        return size[2 * h] * 16 + (size[2 * h] / 32 + 1) * kSegmentBytes +
+               size[2 * h + 1] * kLogBlock * 8;
+    };
+    const uint64_t fixed = record_bytes(c, 0, log_pool(c, 0, 1.0, false)) + 4 * kWsAlign;
+    const uint64_t room = c.arena.cap[kRegionPath];
+    const uint64_t cap = room > fixed && c.images_fit ? room - fixed : 0;
     std::vector<int> order(nh);
     for (int h = 0; h < nh; ++h) order[h] = h;
     std::stable_sort(order.begin(), order.end(),
-                     [&](int a, int b) { return hits[a] > hits[b]; });
-    std::vector<uint64_t> load;
+                     [&](int a, int b) { return bytes(a) > bytes(b); });
+    std::vector<uint64_t> load, words, blocks;
     groups.clear();
     recordable.clear();
-    max_group = 0;
+    max_words = max_blocks = 0;
     for (int h : order) {
-        if (c.prm.record_paths == 0 || hits[h] > cap) {
+        if (c.prm.record_paths == 0 || bytes(h) > cap) {
             groups.push_back({h});
             recordable.push_back(false);
             load.push_back(0);
+            words.push_back(0);
+            blocks.push_back(0);
             continue;
         }
         size_t g = 0;
         for (; g < groups.size(); ++g)
-            if (recordable[g] && load[g] + hits[h] <= cap) break;
+            if (recordable[g] && load[g] + bytes(h) <= cap) break;
         if (g == groups.size()) {
             groups.push_back({});
             recordable.push_back(true);
             load.push_back(0);
+            words.push_back(0);
+            blocks.push_back(0);
         }
         groups[g].push_back(h);
-        load[g] += hits[h];
-        max_group = std::max<uint64_t>(max_group, load[g]);
+        load[g] += bytes(h);
+        words[g] += size[2 * h];
+        blocks[g] += size[2 * h + 1];
+        max_words = std::max<uint64_t>(max_words, words[g]);
+        max_blocks = std::max<uint64_t>(max_blocks, blocks[g]);
     }
     // traversing halos need no memory: run them together as one group
     std::vector<std::vector<int>> gs;
@@ -1721,32 +1784,20 @@ int plan_groups(Ctx& c, uint64_t* row_cnt, std::vector<std::vector<int>>& groups
 // another (the paths held one group at a time are not valid for the batch).
 int run_groups(Ctx& c, double tol, int32_t max_iter, int32_t per_launch)
 {
-    const int64_t n_rows = c.n * (int64_t)c.n_ray;
-    Scratch<uint64_t> row_cnt(c);
     Scratch<int32_t> d_mask(c);
-    HIP_OK(row_cnt.get((size_t)n_rows));
     HIP_OK(d_mask.get((size_t)c.n_halo));
     std::vector<std::vector<int>> groups;
     std::vector<bool> recordable;
-    uint64_t max_group = 0;
-    if (int r = plan_groups(c, row_cnt.p, groups, recordable, max_group)) return r;
+    uint64_t max_words = 0, max_blocks = 0;
+    if (int r = plan_groups(c, groups, recordable, max_words, max_blocks)) return r;
+    const uint64_t batch_total = c.last_total, batch_words = c.last_words,
+                   batch_blocks = c.last_blocks;
     if (groups.size() == 1 && recordable[0]) {
-        // all paths fit: keep the counts, so the first iteration records them
-        // with one walk
-        HIP_OK(hipMemcpyAsync(c.row_off, row_cnt.p, sizeof(uint64_t) * n_rows,
-                              hipMemcpyDeviceToDevice, c.stream));
-        HIP_OK(hipMemsetAsync(c.row_off + n_rows, 0, sizeof(uint64_t), c.stream));
-        HIP_OK(scan_exclusive_u64(c, c.row_off, c.row_off, n_rows + 1));
-        HIP_OK(hipMemcpyAsync(&c.count_total, c.row_off + n_rows, sizeof(uint64_t),
-                              hipMemcpyDeviceToHost, c.stream));
-        HIP_OK(hipStreamSynchronize(c.stream));
+        // all paths fit: the sizes are known, so the first iteration records
+        // them with one walk
         c.counts_valid = true;
         return run_active_halos(c, tol, max_iter, per_launch);
     }
-    free_paths(c);
-    c.counts_valid = false;            // row_off takes each group's offsets
-    if (max_group > 0) HIP_OK(ws_alloc(c, &c.path, (size_t)max_group + kPathPad, kRegionPath));
-    c.path_cap = max_group;
     std::vector<int32_t> mask(c.n_halo);
     int r = RRT_OK;
     for (size_t g = 0; g < groups.size() && r == RRT_OK; ++g) {
@@ -1755,32 +1806,30 @@ int run_groups(Ctx& c, double tol, int32_t max_iter, int32_t per_launch)
         HIP_OK(hipMemcpyAsync(d_mask.p, mask.data(), sizeof(int32_t) * c.n_halo,
                               hipMemcpyHostToDevice, c.stream));
         HIP_OK(launch_seg_group_init(c, d_mask.p));
-        if (recordable[g]) {
-            uint64_t total = 0;
-            HIP_OK(launch_mask_rows(c, row_cnt.p, d_mask.p, c.row_off));
-            HIP_OK(hipMemsetAsync(c.row_off + n_rows, 0, sizeof(uint64_t), c.stream));
-            HIP_OK(scan_exclusive_u64(c, c.row_off, c.row_off, n_rows + 1));
-            HIP_OK(hipMemcpyAsync(&total, c.row_off + n_rows, sizeof total,
-                                  hipMemcpyDeviceToHost, c.stream));
-            HIP_OK(hipStreamSynchronize(c.stream));      // also: mask is read
-            // record only this group's rays: they are the active ones; tiles
-            // and transposed paths of the previous group go
-            free_tpaths(c);
-            free_tiles(c);
-            HIP_OK(launch_record_paths(c, c.row_off, c.path, total));
-            if (!c.paths_valid) drop_graph(c);           // the graph held traversals
+        HIP_OK(hipStreamSynchronize(c.stream));          // mask is read
+        // record only this group's rays: they are the active ones
+        free_paths(c);
+        bool ok = recordable[g] && alloc_log(c, 0, log_pool(c, max_blocks, 1.0, false));
+        if (ok) {
+            bool overflow = false;
+            if ((r = path_walk(c, true, nullptr, &overflow)) != RRT_OK) break;
+            ok = !overflow;
+        }
+        if (ok && (r = build_paths(c, &ok)) != RRT_OK) break;
+        if (ok) {
             c.paths_valid = true;
-            c.paths_unfit = false;
-            c.path_hits = (int64_t)total;
+            c.path_hits = (int64_t)c.last_total;
         } else {
-            HIP_OK(hipStreamSynchronize(c.stream));      // mask is read
-            if (c.paths_valid) drop_graph(c);            // the graph held path products
-            c.paths_valid = false;
+            free_paths(c);
             c.paths_unfit = true;
         }
         r = run_active_halos(c, tol, max_iter, per_launch);
     }
     free_paths(c);
+    c.counts_valid = false;
+    c.last_total = batch_total;
+    c.last_words = batch_words;
+    c.last_blocks = batch_blocks;
     return r;
 }
 
@@ -1810,8 +1859,9 @@ int rrt_iterate_halos(rrt_ctx* x, int32_t max_iter, double tol, int32_t per_laun
     if (c.prm.record_paths != 0 && c.n_halo > 1 && !c.paths_valid && !c.paths_unfit &&
         c.arena.base[kRegionPath]) {
         const uint64_t gap = ws_largest_gap(c, kRegionPath);
-        if (c.counts_valid) grouped = path_bytes(c.count_total) > gap;
-        else grouped = !(c.last_total > 0 && path_bytes(c.last_total) <= gap);
+        const bool known = c.counts_valid || c.last_total > 0;
+        grouped = !known || record_bytes(c, c.last_words, log_pool(c, c.last_blocks, 1.0, false)) >
+                                gap;
     }
     if (int r = grouped ? run_groups(c, tol, max_iter, per_launch)
                         : run_active_halos(c, tol, max_iter, per_launch))
@@ -1854,7 +1904,6 @@ int rrt_set_tuning(rrt_ctx* x, int32_t key, int32_t value)
         if (value < 0) return fail(c, RRT_E_ARG, "one_pass must be >= 0");
         c.one_pass = value != 0;
         c.pool_cap = value > 1 ? (uint64_t)value : 0;
-        free_pool(c);
         return RRT_OK;
     case RRT_TUNE_PACKET_QUEUE:
         if (value != 0 && value != 1) return fail(c, RRT_E_ARG, "packet_queue must be 0 or 1");
@@ -2104,27 +2153,18 @@ int rrt_count_paths(rrt_ctx* x, int64_t* n_hits, size_t* bytes_paths, size_t* by
     if (!x) return RRT_E_ARG;
     Ctx& c = x->c;
     if (int r = need_tree(c)) return r;
-    const int64_t n_rows = c.n * (int64_t)c.n_ray;
     if (!c.counts_valid) {
-        HIP_OK(launch_count_hits(c, c.row_off));
-        HIP_OK(hipMemsetAsync(c.row_off + n_rows, 0, sizeof(uint64_t), c.stream));
-        HIP_OK(scan_exclusive_u64(c, c.row_off, c.row_off, n_rows + 1));
-        HIP_OK(hipMemcpyAsync(&c.count_total, c.row_off + n_rows, sizeof(uint64_t),
-                              hipMemcpyDeviceToHost, c.stream));
-        HIP_OK(hipStreamSynchronize(c.stream));
+        if (int r = path_walk(c, false, nullptr, nullptr)) return r;
         c.counts_valid = true;
     }
-    const uint64_t total = c.count_total;
-    if (c.last_total == 0) c.last_total = total;      // sizes the next one-walk pool
-    if (n_hits) *n_hits = (int64_t)total;
-    if (bytes_paths) *bytes_paths = (size_t)path_bytes(total);
-    if (bytes_one_walk) {
-        Ctx probe;                                      // the pool sizing at this count
-        probe.pool_cap = c.pool_cap;
-        probe.pool_scale = c.pool_scale;
-        *bytes_one_walk =
-            (size_t)(path_bytes(total) + pool_bytes(pool_chunks_for(probe, total, n_rows), n_rows));
-    }
+    if (n_hits) *n_hits = (int64_t)c.last_total;
+    if (bytes_paths)
+        *bytes_paths =
+            (size_t)record_bytes(c, c.last_words, log_pool(c, c.last_blocks, 1.0, false));
+    if (bytes_one_walk)
+        *bytes_one_walk = (size_t)record_bytes(
+            c, c.last_words, std::max(log_pool(c, c.last_blocks, c.pool_scale, true),
+                                      log_pool(c, c.last_blocks, 1.0, false)));
     return RRT_OK;
 }
 

@@ -307,8 +307,14 @@ hipError_t build_tiles(Ctx& c)
     int rows = 16;
     while (rows < 4096 && (double)rows * 2.0 * mean <= 65536.0) rows *= 2;
     std::vector<uint64_t> u;
-    hipError_t e = hipSuccess;
-    for (; rows >= 16; rows /= 2) {
+    // the tiles are built from the paths by rows, expanded for the while
+    hipError_t e = ensure_row_offsets(c);
+    const bool held = c.path != nullptr;
+    if (e == hipSuccess && !held) {
+        e = ws_alloc(c, &c.path, (size_t)m + kPathPad, kRegionPath);
+        if (e == hipSuccess) e = launch_expand_rows(c, c.path);
+    }
+    for (; e == hipSuccess && rows >= 16; rows /= 2) {
         const int64_t nt = (n_rows + rows - 1) / rows;
         if (nt > (int64_t(1) << 24)) break;
         e = ws_alloc(c, &c.tile_off, nt + 1, kRegionPath);
@@ -356,10 +362,10 @@ hipError_t build_tiles(Ctx& c)
             break;
         }
     }
+    if (!held) ws_free(c, &c.path);
     if (!c.tiles_valid) {
-        const bool unfit = true;
         free_tiles(c);
-        c.tiles_unfit = unfit;
+        c.tiles_unfit = true;
         if (e == hipErrorOutOfMemory) {
             (void)hipGetLastError();
             e = hipSuccess;

@@ -17,23 +17,6 @@ constexpr int kRounds = 32;                    // items per thread per tile
 constexpr int kTile = kBlock * kRounds;        // 8192 items per tile
 constexpr int kWaves = kBlock / 64;
 
-// (row, factor) of every recorded intersection, keyed by its particle
-__global__ void k_expand(const uint64_t* __restrict__ row_off, const int2* __restrict__ path,
-                         int64_t n_rows, uint32_t* __restrict__ key, uint64_t* __restrict__ val)
-{
-    const int lane = threadIdx.x & 63;
-    const int64_t stride = (int64_t)gridDim.x * (blockDim.x >> 6);
-    for (int64_t row = (blockIdx.x * (int64_t)blockDim.x + threadIdx.x) >> 6; row < n_rows;
-         row += stride) {
-        const uint64_t a = row_off[row], b = row_off[row + 1];
-        for (uint64_t e = a + lane; e < b; e += 64) {
-            const int2 h = path[e];
-            key[e] = (uint32_t)h.x;
-            val[e] = ((uint64_t)(uint32_t)h.y << 32) | (uint64_t)(uint32_t)row;
-        }
-    }
-}
-
 __global__ void k_hist32(const uint32_t* __restrict__ keys, int64_t n, int shift,
                          uint64_t* __restrict__ hist, int64_t n_tiles)
 {
@@ -151,7 +134,6 @@ hipError_t scan_exclusive_u64(Ctx& c, const uint64_t* in, uint64_t* out, int64_t
 hipError_t build_transposed_paths(Ctx& c)
 {
     const int64_t m = c.path_hits;
-    const int64_t n_rows = c.n * (int64_t)c.n_ray;
     const int64_t n = c.n;
     ws_free(c, &c.tpath);
     ws_free(c, &c.tcol_off);
@@ -167,9 +149,9 @@ hipError_t build_transposed_paths(Ctx& c)
     if (e == hipSuccess) e = vb.get(mm, kRegionPath);
     if (e == hipSuccess) e = hist.get(2 * hn, kRegionPath);
     if (e == hipSuccess && m > 0) {
-        hipLaunchKernelGGL(k_expand, dim3(stride_blocks(n_rows, 4)), dim3(256), 0,
-                           c.stream, c.row_off, c.path, n_rows, ka.p, c.tpath);
-        e = hipGetLastError();
+        // (row, factor) of every recorded intersection, keyed by its particle
+        e = ensure_row_offsets(c);
+        if (e == hipSuccess) e = launch_expand_keys(c, ka.p, c.tpath);
     }
     // sort by particle: enough 8-bit passes to cover the largest index
     int bits = 1;

@@ -121,10 +121,10 @@ uint64_t workspace_bytes(int64_t n, int n_ray, int n_bins, int n_halo, int K, bo
     const uint64_t rays = (uint64_t)std::max(n_ray, 1), bins = (uint64_t)std::max(n_bins, 1);
     const uint64_t H = (uint64_t)std::max(n_halo, 1);
     const uint64_t nr = m * (uint64_t)std::max(n_ray, 0);
-    // context: kernel tables, reductions, chunk counters
+    // context: kernel tables, reductions, the log's counters
     add(sizeof(KernelTables));
     add(kRedSlots * sizeof(unsigned long long));
-    add(((uint64_t)kPoolSlices * kCtrStride + 1) * sizeof(unsigned long long));
+    add(2 * sizeof(unsigned long long));
     // rays, spectrum and its attenuation table
     add(3 * rays * sizeof(double));
     for (int q = 0; q < 3; ++q) add(bins * sizeof(float));

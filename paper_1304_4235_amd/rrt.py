@@ -280,9 +280,10 @@ class Solver:
         have = 0 if self._path is None else self._path.numel()
         budget = self.path_budget or int(0.6 * (self._free_bytes() + have))
         need, one = cnt["bytes_paths"], cnt["bytes_one_walk"]
-        # room for the one-walk pool and, after it, for the reverse mode's
-        # transposed paths (32 bytes per intersection while they are built)
-        want = max(one, 5 * need)
+        # room for the one-walk log and, after it, for the reverse mode's
+        # transposed paths (24 bytes per intersection while they are built,
+        # beside the paths) and its kept columns
+        want = max(one, need, 40 * cnt["hits"])
         if self.record_paths == 1:
             # required: at least the paths, unless an explicit budget says no
             # (then the library reports RRT_E_WORKSPACE)

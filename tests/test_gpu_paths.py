@@ -1,0 +1,105 @@
+"""The recorded paths at the edges of their layout: packets that are not full,
+segments that end by slots, visits or hits, rays without hits, shifted images,
+and packets split into parts."""
+import numpy as np
+import pytest
+import torch
+
+import workloads as W
+
+pytestmark = pytest.mark.gpu
+
+
+def _case(which):
+    """A workload and the leaf size of its tree."""
+    if which == "one":                       # one particle: one ray to a packet
+        return W.isothermal_halo(n=1, n_bins=1, seed=3), 0
+    if which == "packet_less_one":
+        return W.isothermal_halo(n=63, n_bins=1, seed=4), 0
+    if which == "packet":
+        return W.isothermal_halo(n=64, n_bins=1, seed=5), 0
+    if which == "packet_plus_one":
+        return W.isothermal_halo(n=65, n_bins=1, seed=6), 0
+    if which == "visits":                    # one-particle leaves: 128 visits a segment
+        return W.isothermal_halo(n=700, n_bins=1, seed=7), 1
+    if which == "slots":                     # many leaves, few rays in each: 1024 slots
+        wl = W.isothermal_halo(n=6000, n_bins=1, seed=8)
+        wl.h = (wl.h * 0.35).astype(np.float32)
+        return wl, 16
+    if which == "no_hits":                   # kernels that hold their own particle only
+        wl = W.isothermal_halo(n=300, n_bins=1, seed=9)
+        wl.h = (wl.h * 1e-3).astype(np.float32)
+        return wl, 0
+    if which == "images":                    # every ray crosses the box several times
+        return W.uniform_lattice(n_side_lattice=7, box=20.0, l_ray=67.0), 0
+    return W.lognormal_field(n_grid=20, box=1562.5, n_bins=1, n_side=2), 0   # parts = 1
+
+
+CASES = ["one", "packet_less_one", "packet", "packet_plus_one", "visits", "slots", "no_hits",
+         "images", "field"]
+
+
+@pytest.mark.parametrize("near_far", [0, 1])
+@pytest.mark.parametrize("which", CASES)
+def test_recorded_paths_hold_the_walk(which, near_far):
+    """Columns over the recorded paths against the traversal's: the same FP32
+    products, summed in FP64 in another order, so a ray's columns differ by at
+    most its intersections times 2^-53 of their (positive) sum, 1e-11 for any
+    ray here.  The paths by rows against the walk's hit lists: the same
+    particles in the same order, the same factors.  A second recording gives
+    the same columns bit for bit."""
+    from paper_1304_4235_amd import Solver
+    wl, leaf = _case(which)
+    rng = np.random.default_rng(1)
+    x = torch.tensor(rng.uniform(1e-6, 1.0, wl.n))
+    src = np.sort(rng.choice(wl.n, min(wl.n, 130), replace=False))
+    out = []
+    for paths in (1, 0):
+        s = Solver.from_workload(wl, leaf_size=leaf, record_paths=paths, build=False)
+        s.set_scheme(near_far)
+        s.build_tree()
+        s.set_state(x)
+        N, hits = s.compute_columns()
+        near = s.near_columns().cpu().numpy() if near_far else None
+        out.append((N.cpu().numpy(), hits, near))
+        if paths:
+            off, j, fac = s.path_rows(src)
+            ho, hj, _, hf = s.hits_rows(src)
+            np.testing.assert_array_equal(off, ho)
+            np.testing.assert_array_equal(j, hj)
+            np.testing.assert_array_equal(fac, hf)
+            s.build_tree()                               # one walk, sized from the first
+            s.set_state(x)
+            again, _ = s.compute_columns()
+            np.testing.assert_array_equal(again.cpu().numpy(), out[0][0])
+        s.close()
+    (N1, h1, n1), (N0, h0, n0) = out
+    assert h1 == h0
+    np.testing.assert_allclose(N1, N0, rtol=1e-11, atol=0)
+    if near_far:
+        np.testing.assert_allclose(n1, n0, rtol=1e-11, atol=0)
+
+
+def test_row_products_of_the_recorded_paths():
+    """What takes the paths by rows: the density order's blocks (paths expanded
+    into rows) against the same blocks without recorded paths, and the
+    transposed product with one atomic add per intersection against the gather
+    over transposed paths, on a tree whose packets are not full."""
+    from paper_1304_4235_amd import Solver
+    wl = W.isothermal_halo(n=3001, n_bins=8, seed=12)
+    xs = []
+    for paths in (1, 0):
+        s = Solver.from_workload(wl, record_paths=paths)
+        s.set_update_rule(n_blocks=7)
+        xs.append(s.iterate(3, 0.0)["x"].cpu().numpy())
+        s.close()
+    np.testing.assert_allclose(xs[0], xs[1], rtol=1e-9)
+    s = Solver.from_workload(wl, record_paths=1)
+    g = torch.ones(wl.n, dtype=torch.float64, device="cuda")
+    dn = []
+    for mode in (0, 1):
+        s.set_tuning(adjoint_scatter=mode)
+        s.forward(3)
+        dn.append(s.backward(g, None)[1].cpu().numpy())
+    np.testing.assert_allclose(dn[1], dn[0], rtol=1e-9, atol=1e-12 * np.abs(dn[0]).max())
+    s.close()
