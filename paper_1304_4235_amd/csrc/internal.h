@@ -70,6 +70,8 @@ constexpr uint32_t kNoBlock = 0xffffffffu;
 // holds when the walk ends stays unused.
 constexpr uint32_t kLogCache = 8;
 constexpr int64_t kMaxWaves = 256 * 32;    // resident waves of the device
+// the persistent walk's queues (one per XCD), 128 bytes apart
+constexpr int kQueues = 8, kQueueStride = 16;
 // |periodic image| along an axis that a log word can hold
 constexpr int kMaxImage = 8191;
 
@@ -198,12 +200,11 @@ enum {
     kRedConvRel = 5,    // particles of a sweep with |dx| / x < tol
     kRedInput = 6,      // a given x or n_H was non-finite or out of range
     kRedNumeric = 7,    // an update produced a non-finite neutral fraction
-    kRedQueue = 8,      // the persistent walk's next unit
-    kRedPathSize = 9,   // of a recording's or tally's units: recorded words,
-    kRedPathBlocks = 10,    // log blocks,
-    kRedPathHits = 11,      // intersections,
-    kRedPathSegs = 12,      // segments (recording only)
-    kRedSlots = 13
+    kRedPathSize = 8,   // of a recording's or tally's units: recorded words,
+    kRedPathBlocks = 9,    // log blocks,
+    kRedPathHits = 10,      // intersections,
+    kRedPathSegs = 11,      // segments (recording only)
+    kRedSlots = 12
 };
 
 struct Ctx {
@@ -328,6 +329,7 @@ struct Ctx {
 
     // tree
     Node* nodes = nullptr;
+    float4* leaf_ball = nullptr; // [n] at each leaf's first particle: centre, squared radius
     // build scratch
     uint64_t* keys_b = nullptr;
     int32_t* vals_b = nullptr;
@@ -386,6 +388,7 @@ struct Ctx {
 
     // reductions (device, kRedSlots) and a host mirror
     unsigned long long* red = nullptr;
+    unsigned long long* queue = nullptr;     // [kQueues * kQueueStride]
     unsigned long long* red_host = nullptr;  // pinned
     // per sweep of the last rrt_iterate_equilibrium: max |dx| and the
     // particles whose change is below tol, absolutely and relative to x
@@ -497,7 +500,7 @@ hipError_t noalloc_setup(int device);
 hipError_t launch_bounds(Ctx& c, float* part_out /*[nb][8]*/, int nb);
 hipError_t launch_morton(Ctx& c, const double lo[3], double scale, int bits);
 hipError_t radix_sort_pairs(Ctx& c, uint64_t* keys, int32_t* vals, int64_t n);
-hipError_t build_radix_tree(Ctx& c);
+hipError_t build_radix_tree(Ctx& c, float pad);
 hipError_t launch_gather(Ctx& c);
 hipError_t scan_exclusive_u64(Ctx& c, const uint64_t* in, uint64_t* out, int64_t m);
 

@@ -88,13 +88,21 @@ int64_t path_packets(const Ctx& c) { return ((c.n + 63) / 64) * (int64_t)c.n_ray
 
 // A packet is one wave's work in the walk.  With few packets for the device (6
 // waves on each of 1024 SIMDs), each is split: into ranges of the tree's nodes,
-// or in a periodic box into groups of its rays.
+// or in a periodic box into groups of its rays (so that a ray's hits stay in
+// the order of one walk over its images).
+//  * Node ranges, to at least 49152 units (8 a wave, as ranges differ in work):
+//    the 16384-particle halo's walk 574 us at half as many units, 526 us here,
+//    the 65521-particle halo's 2580 and 2323 us.
+//  * Ray groups repeat the packet's node visits, and their segments are shorter,
+//    which the product pays for: the 4096-particle lattice's walk and product at
+//    1, 4, 8, 16 groups 698 (before the queues) and 21, 323 and 21, 360 and 27,
+//    532 and 41 us.
 int path_parts(const Ctx& c)
 {
     const int64_t pk = path_packets(c);
     const int most = c.prm.box > 0.0 ? 4 : 32;
     int p = 1;
-    while (p < most && pk * p < (c.prm.box > 0.0 ? 6144 : 24576)) p *= 2;
+    while (p < most && pk * p < (c.prm.box > 0.0 ? 6144 : 49152)) p *= 2;
     return p;
 }
 

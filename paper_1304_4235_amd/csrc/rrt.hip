@@ -103,7 +103,7 @@ void free_particles(Ctx& c)
                      (void**)&c.nH_s, (void**)&c.mu0_s, (void**)&c.nH0_s, (void**)&c.alpha_s,
                      (void**)&c.gcoll_s, (void**)&c.x_s, (void**)&c.mux_s, (void**)&c.lnG_s,
                      (void**)&c.G_s, (void**)&c.tau_s, (void**)&c.perm, (void**)&c.codes,
-                     (void**)&c.nodes, (void**)&c.keys_b, (void**)&c.vals_b, (void**)&c.k_left,
+                     (void**)&c.nodes, (void**)&c.leaf_ball, (void**)&c.keys_b, (void**)&c.vals_b, (void**)&c.k_left,
                      (void**)&c.k_right, (void**)&c.k_parent, (void**)&c.k_first,
                      (void**)&c.k_last, (void**)&c.k_lo, (void**)&c.k_hi, (void**)&c.k_cnt,
                      (void**)&c.k_dfs, (void**)&c.k_flag, (void**)&c.seg_of, (void**)&c.k_seg,
@@ -128,7 +128,7 @@ int alloc_particles(Ctx& c, int64_t n)
     A(c.pos_in, 3 * m) A(c.h_in, m) A(c.mu_in, m) A(c.nH_in, m) A(c.T_in, m) A(c.x_init, m)
     A(c.p4, m + kLeafMax) A(c.mu_s, m) A(c.mu0_s, m) A(c.nH0_s, m) A(c.nH_s, m) A(c.alpha_s, m) A(c.gcoll_s, m) A(c.x_s, m)
     A(c.mux_s, m) A(c.lnG_s, m) A(c.G_s, m) A(c.tau_s, m) A(c.perm, m) A(c.codes, m)
-    A(c.nodes, 2 * m) A(c.keys_b, m) A(c.vals_b, m) A(c.k_left, mi) A(c.k_right, mi)
+    A(c.nodes, 2 * m) A(c.leaf_ball, m) A(c.keys_b, m) A(c.vals_b, m) A(c.k_left, mi) A(c.k_right, mi)
     A(c.k_parent, 2 * m) A(c.k_first, mi) A(c.k_last, mi) A(c.k_lo, 3 * mi) A(c.k_hi, 3 * mi)
     A(c.k_cnt, mi) A(c.k_dfs, mi) A(c.k_flag, mi) A(c.seg_of, m) A(c.k_seg, mi)
     A(c.alphaB_s, m) A(c.skip_s, m) A(c.want_s, m) A(c.block_s, m) A(c.block_list, m)
@@ -175,6 +175,7 @@ int alloc_ctx_buffers(Ctx& c)
     HIP_OK(ws_alloc(c, &c.tables, 1));
     HIP_OK(ws_alloc(c, &c.red, kRedSlots));
     HIP_OK(ws_alloc(c, &c.log_ctr, 2));
+    HIP_OK(ws_alloc(c, &c.queue, (size_t)kQueues * kQueueStride));
     KernelTables host;
     fill_kernel_tables(&host);
     HIP_OK(hipMemcpyAsync(c.tables, &host, sizeof host, hipMemcpyHostToDevice, c.stream));
@@ -1102,7 +1103,9 @@ int rrt_build_tree(rrt_ctx* x)
     HIP_OK(radix_sort_pairs(c, c.codes, c.perm, c.n));
     if (c.n_halo > 1)                            // every byte 0xff: -1, no halo root yet
         HIP_OK(hipMemsetAsync(c.seg_root, 0xff, sizeof(int32_t) * c.n_halo, c.stream));
-    HIP_OK(build_radix_tree(c));
+    const float pad =
+        (float)(4e-6 * 2.0 * (maxabs + c.prm.l_ray + (double)hmax + c.prm.box));
+    HIP_OK(build_radix_tree(c, pad));
     if (c.n_halo > 1) {
         std::vector<int32_t> roots(c.n_halo);
         HIP_OK(hipMemcpyAsync(roots.data(), c.seg_root, sizeof(int32_t) * c.n_halo,
@@ -1130,7 +1133,7 @@ int rrt_build_tree(rrt_ctx* x)
         g.phi[a] = hi[a];
     }
     g.hmax = hmax;
-    g.pad = (float)(4e-6 * 2.0 * (maxabs + g.L + (double)hmax + g.box));
+    g.pad = pad;
     // the recording's log codes a hit's periodic image in 14 bits per axis
     c.images_fit = !(g.box > 0.0) || (g.L + (double)hmax + ext) / g.box + 2.0 <= kMaxImage;
     g.n = (int32_t)c.n;

@@ -438,7 +438,8 @@ __global__ void k_layout(const float4* __restrict__ p4, int n, int leaf_max,
                          const int32_t* __restrict__ kseg, const int32_t* __restrict__ klast,
                          const int32_t* __restrict__ seg_of, const int64_t* __restrict__ halo_off,
                          int32_t* __restrict__ seg_root, int32_t* __restrict__ seg_end,
-                         Node* __restrict__ nodes, unsigned long long* err)
+                         Node* __restrict__ nodes, float4* __restrict__ leaf_ball, float pad,
+                         unsigned long long* err)
 {
     int v = blockIdx.x * blockDim.x + threadIdx.x;
     int total = 2 * n - 1;
@@ -493,6 +494,30 @@ __global__ void k_layout(const float4* __restrict__ p4, int n, int leaf_max,
     nd.a = make_float4(lo[0], lo[1], lo[2], __int_as_float(idx + dfs));
     nd.b = make_float4(hi[0], hi[1], hi[2], __int_as_float(leafw));
     nodes[idx] = nd;
+    if (!leafy) return;
+    // a ball around the leaf's kernel spheres: the middle of its particles, and
+    // the squared radius that reaches the farthest sphere's far side, widened by
+    // the walk's pad
+    float a0[3] = {INFINITY, INFINITY, INFINITY}, a1[3] = {-INFINITY, -INFINITY, -INFINITY};
+    for (int j = f; j < f + cnt; ++j) {
+        const float4 q = p4[j];
+        const float r[3] = {q.x, q.y, q.z};
+        for (int a = 0; a < 3; ++a) {
+            a0[a] = fminf(a0[a], r[a]);
+            a1[a] = fmaxf(a1[a], r[a]);
+        }
+    }
+    const float m[3] = {0.5f * a0[0] + 0.5f * a1[0], 0.5f * a0[1] + 0.5f * a1[1],
+                        0.5f * a0[2] + 0.5f * a1[2]};
+    double rad = 0.0;
+    for (int j = f; j < f + cnt; ++j) {
+        const float4 q = p4[j];
+        const double d0 = (double)q.x - (double)m[0], d1 = (double)q.y - (double)m[1],
+                     d2 = (double)q.z - (double)m[2];
+        rad = fmax(rad, sqrt(d0 * d0 + d1 * d1 + d2 * d2) + (double)q.w);
+    }
+    rad += (double)pad;
+    leaf_ball[f] = make_float4(m[0], m[1], m[2], (float)(rad * rad * (1.0 + 1e-6)));
 }
 
 __global__ void k_gather_particles(const int32_t* __restrict__ perm, const float* __restrict__ pos,
@@ -565,7 +590,7 @@ hipError_t radix_sort_pairs(Ctx& c, uint64_t* keys, int32_t* vals, int64_t n)
     return hipSuccess;
 }
 
-hipError_t build_radix_tree(Ctx& c)
+hipError_t build_radix_tree(Ctx& c, float pad)
 {
     const int n = (int)c.n;
     hipError_t e;
@@ -590,7 +615,7 @@ hipError_t build_radix_tree(Ctx& c)
     hipLaunchKernelGGL(k_layout, dim3(nblk(2 * n - 1)), dim3(kBlock), 0, c.stream, c.p4, n, c.leaf,
                        c.k_left, c.k_right, c.k_parent, c.k_first, c.k_lo, c.k_hi, c.k_cnt,
                        c.k_dfs, c.k_seg, c.k_last, c.seg_of, c.n_halo > 1 ? c.halo_off : nullptr,
-                       c.seg_root, c.seg_end, c.nodes, c.red + kRedBuild);
+                       c.seg_root, c.seg_end, c.nodes, c.leaf_ball, pad, c.red + kRedBuild);
     return hipGetLastError();
 }
 

@@ -121,10 +121,11 @@ uint64_t workspace_bytes(int64_t n, int n_ray, int n_bins, int n_halo, int K, bo
     const uint64_t rays = (uint64_t)std::max(n_ray, 1), bins = (uint64_t)std::max(n_bins, 1);
     const uint64_t H = (uint64_t)std::max(n_halo, 1);
     const uint64_t nr = m * (uint64_t)std::max(n_ray, 0);
-    // context: kernel tables, reductions, the log's counters
+    // context: kernel tables, reductions, the log's counters, the walk's queues
     add(sizeof(KernelTables));
     add(kRedSlots * sizeof(unsigned long long));
     add(2 * sizeof(unsigned long long));
+    add((uint64_t)kQueues * kQueueStride * sizeof(unsigned long long));
     // rays, spectrum and its attenuation table
     add(3 * rays * sizeof(double));
     for (int q = 0; q < 3; ++q) add(bins * sizeof(float));
@@ -144,6 +145,7 @@ uint64_t workspace_bytes(int64_t n, int n_ray, int n_bins, int n_halo, int K, bo
         for (uint64_t b : per_m) add(b * m);
         add(16 * (m + kLeafMax));                                    // p4
         add(2 * sizeof(Node) * m);                                   // nodes
+        add(16 * m);                                                 // leaf balls
         const uint64_t per_mi[] = {4, 4, 4, 4, 12, 12, 4, 4, 4, 4};  // radix tree (x n - 1)
         for (uint64_t b : per_mi) add(b * mi);
         // columns (and near columns), path row offsets
