@@ -324,6 +324,8 @@ struct Ctx {
     int32_t blocks_for = 0;        // rule_blocks that block_s was computed for (0: none)
     const int32_t* row_list = nullptr;   // the sources of the running density block, or null
     int64_t row_list_n = 0;
+    int row_block = 0;             // its number
+    const uint8_t* row_frozen = nullptr;   // particles left out of a masked sweep, or null
     int path_evals = 0;            // column evaluations since the paths were recorded
     bool capturing = false;        // a graph capture is in progress (no allocation)
 
@@ -512,7 +514,7 @@ hipError_t launch_columns(Ctx& c);
 hipError_t launch_log_walk(Ctx& c, bool store, uint64_t* unit_size);
 void drop_graph(Ctx& c);
 hipError_t build_tiles(Ctx& c);
-hipError_t launch_want(Ctx& c, int block, bool use_skip);
+hipError_t launch_want(Ctx& c, int block);
 hipError_t launch_evolve(Ctx& c, double dt);
 hipError_t launch_block_ids(Ctx& c, const int32_t* block_in);
 void free_tiles(Ctx& c);

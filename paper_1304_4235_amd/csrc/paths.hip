@@ -769,7 +769,7 @@ template <int G>
 __global__ void __launch_bounds__(kBlock)
 k_row_columns(const uint64_t* __restrict__ row_off, const int2* __restrict__ path,
               const float* __restrict__ mux, int64_t n_rows, double* __restrict__ N, int64_t n,
-              const uint8_t* __restrict__ want, const int32_t* __restrict__ list, int64_t list_n)
+              const uint8_t* __restrict__ frozen, const int32_t* __restrict__ list, int64_t list_n)
 {
     const int lane = threadIdx.x & (G - 1);
     const int64_t stride = (int64_t)gridDim.x * (blockDim.x / G);
@@ -778,7 +778,7 @@ k_row_columns(const uint64_t* __restrict__ row_off, const int2* __restrict__ pat
     for (int64_t v = (blockIdx.x * (int64_t)blockDim.x + threadIdx.x) / G; v < n_iter;
          v += stride) {
         const int64_t row = (v / list_n) * n + list[v % list_n];
-        if (want && !want[row % n]) continue;     // not updated in this step
+        if (frozen && frozen[row % n]) continue;  // not updated in this step
         const uint64_t a = row_off[row], b = row_off[row + 1];
         double acc = 0.0;
         // Lanes stride through the row one entry at a time, so the particle
@@ -825,7 +825,7 @@ hipError_t launch_row_columns(Ctx& c, int group)
     if (n_iter == 0) return hipSuccess;
     auto go = [&](auto kernel, int g) {
         hipLaunchKernelGGL(kernel, dim3(stride_blocks(n_iter, kBlock / g)), dim3(kBlock), 0,
-                           c.stream, c.row_off, c.path, c.mux_s, n_rows, c.N_s, c.n, c.geom.want,
+                           c.stream, c.row_off, c.path, c.mux_s, n_rows, c.N_s, c.n, c.row_frozen,
                            c.row_list, c.row_list_n);
     };
     if (group == 64) go(k_row_columns<64>, 64);

@@ -54,6 +54,7 @@ __global__ void k_init_state(const int32_t* __restrict__ perm, const float* __re
 // relative changes for the convergence test.
 struct RateRule {
     const uint8_t* want;      // null = every particle
+    const uint8_t* frozen;    // of a list: those left out (null = none)
     uint8_t* skip;            // first sweep: set for tau_eff < tau_skip (null = none)
     double tau_skip;
     double tau_case_b;        // +inf = case A throughout
@@ -78,9 +79,30 @@ struct RateRule {
 
 enum { kSchemePlain = 0, kSchemeNearMono = 1, kSchemeNearPoly = 2 };
 
-// One thread per particle: rays, then bins; optionally the equilibrium update.
-template <int SCHEME>
-__global__ void __launch_bounds__(256)
+// W threads per particle, each taking every W-th ray (its bins in turn): their
+// log-sum-exps merge in thread order, and the first thread finishes the
+// particle; optionally the equilibrium update.  The block's wave wv takes
+// particles by its low part and rays by its high part, so loads stay coalesced
+// and W = 1 is one thread per particle.
+// A ray's log, exponentials or slab march are one serial chain: its length, not
+// the arithmetic, bounds the kernel below some 100k particles, so W grows up to
+// 4 waves on each of the device's 1024 SIMDs.  Measured on MI355X (us at W = 1,
+// then as chosen): 4096 particles and one bin 12.7, 8.7 (W = 8); 16384 particles
+// and 128 bins 45.6, 17.3 (8); 65521: 47.7, 22.0 (4); 140k in a batch: 52.7,
+// 41.1 (2), and 65.4 at W = 4, beyond the line.  One ray a thread (W = 16 for 12
+// rays) took 9.9 and 18.3 us on the first two: half of its threads are idle in
+// the merge.  The slab march of 18432 particles, one ray: 366 us by one lane, 83
+// by kSlabLanes.  A block of 4096 of 65536 particles: 25.4 us under a mask, 10.0
+// from its list.
+// list: only these particles (the sources of a density block, dense, instead of
+// every particle under a mask).
+constexpr int kRateMaxWays = 16;
+constexpr int64_t kRateWaves = 4096;
+
+constexpr int scheme_lanes(int scheme) { return scheme == kSchemeNearPoly ? kSlabLanes : 1; }
+
+template <int SCHEME, int W>
+__global__ void __launch_bounds__(W > 4 ? 64 * W : 256)
 k_gamma(const double* __restrict__ N, int64_t n, int n_ray, int n_bins,
         const float* __restrict__ ws_rel, const float* __restrict__ dsig_l2, double sigma_min,
         double ln_ws_max, double ln_gthin, double* __restrict__ lnG, double* __restrict__ G,
@@ -89,16 +111,23 @@ k_gamma(const double* __restrict__ N, int64_t n, int n_ray, int n_bins,
         const double* __restrict__ gcoll, double* __restrict__ x_s, float* __restrict__ mux,
         unsigned long long* __restrict__ maxdx_bits, const int32_t* __restrict__ seg_of,
         const int32_t* __restrict__ seg_active, unsigned long long* __restrict__ seg_maxdx,
-        RateRule rule)
+        const int32_t* __restrict__ list, int64_t list_n, RateRule rule)
 {
-    int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
+    constexpr int kB = W > 4 ? 64 * W : 256;
+    constexpr int kPWaves = kB / 64 / W;             // waves over the block's particles
+    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+    const int way = W > 1 ? wv / kPWaves : 0;
+    constexpr int kLanes = scheme_lanes(SCHEME), kPer = 64 / kLanes;
+    const int64_t at = (blockIdx.x * (int64_t)kPWaves + wv % kPWaves) * kPer + lane / kLanes;
+    const bool in = at < list_n;
+    const int64_t i = !in ? n : list ? (int64_t)list[at] : at;
     double dx = 0.0;
     bool conv_a = false, conv_r = false, bad = false;
     const int h = (seg_of && i < n) ? seg_of[i] : -1;
-    const bool live = !(seg_active && h >= 0 && seg_active[h] == 0) &&
-                      !(rule.want && i < n && rule.want[i] == 0);
-    if (i < n && live) {
-        double m = -INFINITY, s = 0.0, l;
+    const bool live = i < n && !(seg_active && h >= 0 && seg_active[h] == 0) &&
+                      !(rule.want && rule.want[i] == 0) && !(rule.frozen && rule.frozen[i]);
+    double m = -INFINITY, s = 0.0;
+    if (live) {
         if (SCHEME != kSchemePlain) {
             // near/far: per ray the slab of near particles lit by the radiation
             // the far particles let through.  Each slab is lit by the ray's
@@ -106,7 +135,7 @@ k_gamma(const double* __restrict__ N, int64_t n, int n_ray, int n_bins,
             // with 4 pi inside w), and the slabs' bottom rates add up.  (The
             // table of binned spectra carries the shift.)
             const double ln_share = -log((double)n_ray);
-            for (int k = 0; k < n_ray; ++k) {
+            for (int k = way; k < n_ray; k += W) {
                 double v;
                 if (SCHEME == kSchemeNearPoly) {
                     v = slab_ln_rate_poly(N[(int64_t)k * n + i], rule.Nn[(int64_t)k * n + i],
@@ -126,7 +155,6 @@ k_gamma(const double* __restrict__ N, int64_t n, int n_ray, int n_bins,
                     s += exp(v - m);
                 }
             }
-            l = (s > 0.0) ? (m + log(s)) : -INFINITY;
         } else {
             // 2^x is the hardware instruction (about 1 ulp), which flushes
             // results below 2^-126 to zero: the bin of smallest cross-section
@@ -139,7 +167,7 @@ k_gamma(const double* __restrict__ N, int64_t n, int n_ray, int n_bins,
             // each term, 1.9e-8 of S_k (S_k >= 0.85 sum_b r_b there): below
             // the FP32 sum's own rounding, for 6 FMAs instead of n_bins
             // exponentials.
-            for (int k = 0; k < n_ray; ++k) {
+            for (int k = way; k < n_ray; k += W) {
                 double Nk = N[(int64_t)k * n + i];
                 float Nf = (float)Nk;
                 double Sd;
@@ -150,6 +178,7 @@ k_gamma(const double* __restrict__ N, int64_t n, int n_ray, int n_bins,
                 } else {
                     float S0 = 0.f, S1 = 0.f, S2 = 0.f, S3 = 0.f;
                     int b = 0;
+#pragma unroll 4
                     for (; b + 3 < n_bins; b += 4) {
                         S0 = fmaf(ws_rel[b], __builtin_amdgcn_exp2f(-dsig_l2[b] * Nf), S0);
                         S1 = fmaf(ws_rel[b + 1], __builtin_amdgcn_exp2f(-dsig_l2[b + 1] * Nf),
@@ -172,8 +201,29 @@ k_gamma(const double* __restrict__ N, int64_t n, int n_ray, int n_bins,
                     s += exp(v - m);
                 }
             }
-            l = (s > 0.0) ? (ln_ws_max + m + log(s / (double)n_ray)) : -INFINITY;
         }
+    }
+    if (W > 1) {
+        __shared__ double s_m[W * kPWaves][64], s_s[W * kPWaves][64];
+        s_m[wv][lane] = m;
+        s_s[wv][lane] = s;
+        __syncthreads();
+        if (way == 0)
+            for (int q = wv + kPWaves; q < W * kPWaves; q += kPWaves) {
+                const double mq = s_m[q][lane], sq = s_s[q][lane];
+                if (sq == 0.0) continue;                      // no ray carried anything
+                if (mq > m) {
+                    s = s * exp(m - mq) + sq;
+                    m = mq;
+                } else {
+                    s += sq * exp(mq - m);
+                }
+            }
+    }
+    if (live && way == 0 && lane % kLanes == 0) {
+        const double l = !(s > 0.0) ? -INFINITY
+                         : SCHEME != kSchemePlain ? m + log(s)
+                                                  : ln_ws_max + m + log(s / (double)n_ray);
         double g = exp(l);
         if (lnG) lnG[i] = l;
         if (G) G[i] = g;
@@ -198,11 +248,10 @@ k_gamma(const double* __restrict__ N, int64_t n, int n_ray, int n_bins,
         // the counts, the flag and the maximum are reduced per block, so each
         // takes one atomic per block on its (single) global word
         const uint64_t ba = __ballot(conv_a), br = __ballot(conv_r), bb = __ballot(bad);
-        __shared__ unsigned long long s_red[kBlockWaves][4];
-        __shared__ int s_hw[kBlockWaves];
-        __shared__ unsigned long long s_hm[kBlockWaves];
-        const int wv = threadIdx.x >> 6;
-        if (seg_maxdx) {
+        __shared__ unsigned long long s_red[kPWaves][4];
+        __shared__ int s_hw[kPWaves];
+        __shared__ unsigned long long s_hm[kPWaves];
+        if (seg_maxdx && way == 0) {
             // per-halo maximum: a wave that holds one halo passes its maximum
             // to the block (below); the lanes of a wave across halos add theirs
             const int h0 = __shfl(h, 0, 64);
@@ -217,7 +266,7 @@ k_gamma(const double* __restrict__ N, int64_t n, int n_ray, int n_bins,
             }
         }
         for (int off = 32; off > 0; off >>= 1) dx = fmax(dx, __shfl_xor(dx, off, 64));
-        if ((threadIdx.x & 63) == 0) {
+        if (lane == 0 && way == 0) {
             s_red[wv][0] = (unsigned long long)__popcll(ba);
             s_red[wv][1] = (unsigned long long)__popcll(br);
             s_red[wv][2] = bb ? 1ull : 0ull;
@@ -226,7 +275,7 @@ k_gamma(const double* __restrict__ N, int64_t n, int n_ray, int n_bins,
         __syncthreads();
         if (seg_maxdx && threadIdx.x == 0) {
             // one atomic per run of the block's waves in the same halo
-            const int nw = (int)(blockDim.x >> 6);
+            const int nw = kPWaves;
             for (int w = 0; w < nw;) {
                 const int hh = s_hw[w];
                 unsigned long long mx = s_hm[w];
@@ -239,7 +288,7 @@ k_gamma(const double* __restrict__ N, int64_t n, int n_ray, int n_bins,
         }
         if (threadIdx.x == 0) {
             unsigned long long na = 0, nr = 0, nb = 0, mx = 0;
-            for (int w = 0; w < (int)(blockDim.x >> 6); ++w) {
+            for (int w = 0; w < kPWaves; ++w) {
                 na += s_red[w][0];
                 nr += s_red[w][1];
                 nb |= s_red[w][2];
@@ -472,7 +521,9 @@ hipError_t launch_init_state(Ctx& c, bool use_given)
 hipError_t launch_gamma(Ctx& c, bool update_x, bool first_sweep)
 {
     RateRule rule;
-    rule.want = c.geom.want;
+    // a density block's list leaves out what the mask would, but the frozen ones
+    rule.want = c.row_list ? nullptr : c.geom.want;
+    rule.frozen = c.row_list ? c.row_frozen : nullptr;
     rule.skip = (first_sweep && c.rule_tau_skip > 0.0) ? c.skip_s : nullptr;
     rule.tau_skip = c.rule_tau_skip;
     rule.tau_case_b = c.rule_tau_case_b;
@@ -498,17 +549,34 @@ hipError_t launch_gamma(Ctx& c, bool update_x, bool first_sweep)
                                     c.att_dt, c.att_tmax, c.att_smax, c.sigma_min,
                                     c.ln_ws_max - shift};
     }
-    auto launch = [&](auto kernel) {
-        hipLaunchKernelGGL(kernel, dim3(nblk(c.n)), dim3(kBlock), 0, c.stream, c.N_s, c.n,
+    const int64_t count = c.row_list ? c.row_list_n : c.n;
+    const int per_wave = 64 / scheme_lanes(scheme);
+    int W = 1;
+    while (W < kRateMaxWays && 2 * W <= c.n_ray && (count + per_wave - 1) / per_wave * W < kRateWaves)
+        W *= 2;
+    auto launch = [&](auto kernel, int ways) {
+        const int threads = ways > 4 ? 64 * ways : 256;
+        const int per = threads / 64 / ways * per_wave;
+        hipLaunchKernelGGL(kernel, dim3((unsigned)((count + per - 1) / per)), dim3(threads), 0,
+                           c.stream, c.N_s, c.n,
                            c.n_ray, c.n_bins, c.ws_rel, c.dsig_l2, c.sigma_min, c.ln_ws_max,
                            std::log(c.gamma_thin), c.lnG_s, c.G_s, c.tau_s, update_x ? 1 : 0,
                            c.nH_s, c.mu_s, c.alpha_s, c.gcoll_s, c.x_s, c.mux_s, c.red,
                            c.geom.seg_of, c.geom.seg_active,
-                           c.geom.seg_active ? c.seg_maxdx : nullptr, rule);
+                           c.geom.seg_active ? c.seg_maxdx : nullptr, c.row_list, count, rule);
     };
-    if (scheme == kSchemePlain) launch(k_gamma<kSchemePlain>);
-    else if (scheme == kSchemeNearMono) launch(k_gamma<kSchemeNearMono>);
-    else launch(k_gamma<kSchemeNearPoly>);
+    auto ways = [&](auto sch) {
+        constexpr int S = decltype(sch)::value;
+        if (W == 1) launch(k_gamma<S, 1>, 1);
+        else if (W == 2) launch(k_gamma<S, 2>, 2);
+        else if (W == 4) launch(k_gamma<S, 4>, 4);
+        else if (W == 8) launch(k_gamma<S, 8>, 8);
+        else launch(k_gamma<S, 16>, 16);
+    };
+    if (count == 0) return hipSuccess;
+    if (scheme == kSchemePlain) ways(std::integral_constant<int, kSchemePlain>{});
+    else if (scheme == kSchemeNearMono) ways(std::integral_constant<int, kSchemeNearMono>{});
+    else ways(std::integral_constant<int, kSchemeNearPoly>{});
     return hipGetLastError();
 }
 
@@ -557,11 +625,11 @@ hipError_t launch_evolve(Ctx& c, double dt)
     return hipGetLastError();
 }
 
-hipError_t launch_want(Ctx& c, int block, bool use_skip)
+hipError_t launch_want(Ctx& c, int block)
 {
     hipLaunchKernelGGL(k_want, dim3(nblk(c.n)), dim3(kBlock), 0, c.stream,
-                       c.rule_blocks > 1 ? c.block_s : nullptr, use_skip ? c.skip_s : nullptr,
-                       c.n, block, c.want_s);
+                       c.rule_blocks > 1 ? c.block_s : nullptr, c.row_frozen, c.n, block,
+                       c.want_s);
     return hipGetLastError();
 }
 

@@ -509,6 +509,15 @@ int record_paths(Ctx& c)
     return RRT_OK;
 }
 
+// The running density block as a mask over all particles, for an evaluation
+// that takes no list.
+hipError_t mask_block(Ctx& c)
+{
+    const hipError_t e = launch_want(c, c.row_block);
+    if (e == hipSuccess) c.geom.want = c.want_s;
+    return e;
+}
+
 // Columns for the current state.  Returns the intersections of this evaluation
 // through *hits when they are known on the host (recorded paths), else -1 (the
 // traversal counts them into red[1]).
@@ -541,6 +550,7 @@ int columns_impl(Ctx& c, int64_t* hits)
             }
             HIP_OK(e);
         }
+        if (c.row_list && !c.path) HIP_OK(mask_block(c));
         const double mean = (double)c.path_hits /
                             (double)std::max<int64_t>(c.n * (int64_t)c.n_ray, 1);
         // measured on MI355X: 32 lanes per ray are fastest from a few tens of
@@ -562,6 +572,7 @@ int columns_impl(Ctx& c, int64_t* hits)
         }
         *hits = c.path_hits;
     } else {
+        if (c.row_list) HIP_OK(mask_block(c));
         hipEvent_t ec = ev_begin(c);
         HIP_OK(launch_columns(c));
         if (c.timing) {
@@ -1262,6 +1273,7 @@ struct WantGuard {
         c.geom.want = nullptr;
         c.row_list = nullptr;
         c.row_list_n = 0;
+        c.row_frozen = nullptr;
     }
 };
 
@@ -1353,13 +1365,15 @@ int rrt_iterate_equilibrium(rrt_ctx* x, int32_t max_iter, double tol, double* x_
         for (int b = 0; b < n_steps; ++b) {
             // one block of the density order (all particles for the
             // order-independent update), frozen particles left out
-            if (masked) {
-                HIP_OK(launch_want(c, b, skipping && it > 0));
-                c.geom.want = c.want_s;
-            }
+            c.geom.want = nullptr;
+            c.row_frozen = skipping && it > 0 ? c.skip_s : nullptr;
             if (ordered) {                    // the product walks only this block's rays
                 c.row_list = c.block_list + c.block_off[b];
                 c.row_list_n = c.block_off[b + 1] - c.block_off[b];
+                c.row_block = b;
+            } else if (masked) {
+                HIP_OK(launch_want(c, 0));
+                c.geom.want = c.want_s;
             }
             if (int r = columns_impl(c, &hits)) return r;
             hipEvent_t eg = ev_begin(c);
@@ -1369,6 +1383,7 @@ int rrt_iterate_equilibrium(rrt_ctx* x, int32_t max_iter, double tol, double* x_
         c.geom.want = nullptr;
         c.row_list = nullptr;
         c.row_list_n = 0;
+        c.row_frozen = nullptr;
         HIP_OK(hipMemcpyAsync(c.red_host, c.red, kRedSlots * sizeof(unsigned long long),
                               hipMemcpyDeviceToHost, c.stream));
         HIP_OK(hipStreamSynchronize(c.stream));

@@ -1,0 +1,56 @@
+"""The rate kernel with several threads per particle, and the density blocks as
+lists of particles."""
+import numpy as np
+import pytest
+import torch
+
+import workloads as W
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("n_ray", [1, 2, 3, 5, 8, 12, 31, 48])
+@pytest.mark.parametrize("n", [1, 65, 300])
+def test_rates_of_shared_particles(n, n_ray):
+    """ln Gamma against an FP64 log-sum-exp over rays and bins of the same
+    columns, at ray counts that take 1, 2, 4, 8 and 16 threads per particle and
+    particles that leave the last block part empty.  The bins' sums are FP32: a
+    term r e^-t has a relative error of at most 3 t 2^-24 from its rounded
+    exponent (t <= 25 where it counts, beyond which its weight hides it) and of
+    2^-23 from the exponential, 33 terms add 33 * 2^-24 at most: 6.5e-6."""
+    from paper_1304_4235_amd import Solver
+    wl = W.isothermal_halo(n=n, n_bins=33, seed=11)
+    rng = np.random.default_rng(n_ray)
+    d = rng.normal(size=(n_ray, 3))
+    s = Solver.from_workload(wl, build=False)
+    s.set_rays(d / np.linalg.norm(d, axis=1)[:, None])
+    s.build_tree()
+    s.set_state(torch.tensor(rng.uniform(1e-5, 1.0, n)))
+    N, _ = s.compute_columns()
+    N = N.cpu().numpy().reshape(n, n_ray) if N.shape[0] == n else N.cpu().numpy().T
+    s.compute_gamma()
+    lnG = s.get_state()["lnG"].cpu().numpy()
+    sg, w = np.asarray(wl.sigma, np.float64), np.asarray(wl.w, np.float64)
+    t = np.log(w * sg)[None, None, :] - sg[None, None, :] * N[:, :, None]
+    m = t.max(axis=(1, 2), keepdims=True)
+    ref = np.log(np.exp(t - m).sum(axis=(1, 2)) / n_ray) + m[:, 0, 0]
+    assert np.abs(lnG - ref).max() <= 6.5e-6
+    s.close()
+
+
+@pytest.mark.parametrize("tau_skip", [0.0, 1.0])
+@pytest.mark.parametrize("n", [5, 65, 700])
+def test_density_blocks_by_list_and_by_mask(n, tau_skip):
+    """Four density blocks over recorded paths (rows and rates of the block's
+    list) and by traversal (every particle under a mask): the same FP32 terms
+    summed in another order, 1e-12 of x a sweep."""
+    from paper_1304_4235_amd import Solver
+    wl = W.isothermal_halo(n=n, n_bins=9, seed=12)
+    out = []
+    for paths in (1, 0):
+        s = Solver.from_workload(wl, record_paths=paths, build=False)
+        s.set_update_rule(tau_skip=tau_skip, n_blocks=4)
+        s.build_tree()
+        out.append(s.iterate(6, 0.0)["x"].cpu().numpy())
+        s.close()
+    np.testing.assert_allclose(out[0], out[1], rtol=1e-10, atol=0)
