@@ -44,13 +44,17 @@ __device__ __forceinline__ double horner(const double* c, double x)
     return r;
 }
 
-// One thread per particle (tree order) at step k: the adjoint of ln Gamma, of
-// x and of every ray's column.  Pass 1 forms ln Gamma from the same terms as
+// W threads per particle (tree order, as in the forward rate kernel) at step k:
+// the adjoint of ln Gamma, of x and of every ray's column.  Pass 1 forms ln Gamma from the same terms as
 // the forward rate kernel (hardware 2^x, or the thin rays' Taylor form),
 // summed in one FP32 accumulator instead of four, so the two agree to FP32
 // rounding; it keeps each ray's S and T for pass 2.  The weights' gradient is accumulated by k_adj_wbins from
 // pis and ell.
-__global__ void __launch_bounds__(256)
+// Bound by the length of a thread's chain of rays, like the forward kernel.
+// Measured on MI355X (us at W = 1, then as chosen): 65521 particles, 12 rays, 128
+// bins 103, 32.5 (W = 4); 110592 particles, 48 rays, 256 bins 100, 76 (4).
+template <int W>
+__global__ void __launch_bounds__(W > 4 ? 64 * W : 256)
 k_adj_rate(const double* __restrict__ N, int64_t n, int n_ray, int n_bins,
            const float* __restrict__ ws_rel, const float* __restrict__ dsig_l2,
            const float* __restrict__ srat, double sigma_min, double ln_ws_max,
@@ -60,11 +64,13 @@ k_adj_rate(const double* __restrict__ N, int64_t n, int n_ray, int n_bins,
            double* __restrict__ gnH, float2* __restrict__ st, double* __restrict__ ell_out,
            ThinSums ts)
 {
-    const int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-    if (i >= n) return;
+    constexpr int kPWaves = (W > 4 ? W : 4) / W;     // waves over the block's particles
+    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+    const int way = wv / kPWaves, pw = wv % kPWaves;
+    const int64_t i = (blockIdx.x * (int64_t)kPWaves + pw) * 64 + lane;
     // pass 1: ln Gamma
     double m = -INFINITY, s = 0.0;
-    for (int k = 0; k < n_ray; ++k) {
+    for (int k = way; k < n_ray && i < n; k += W) {
         const double Nk = N[(int64_t)k * n + i];
         const float Nf = (float)Nk;
         float S = 0.f, T = 0.f;
@@ -72,6 +78,7 @@ k_adj_rate(const double* __restrict__ N, int64_t n, int n_ray, int n_bins,
             S = (float)horner(ts.s, (double)Nf);
             T = (float)horner(ts.t, (double)Nf);
         } else {
+#pragma unroll 8
             for (int b = 0; b < n_bins; ++b) {
                 const float e = ws_rel[b] * __builtin_amdgcn_exp2f(-dsig_l2[b] * Nf);
                 S += e;
@@ -88,6 +95,26 @@ k_adj_rate(const double* __restrict__ N, int64_t n, int n_ray, int n_bins,
             s += exp(v - m);
         }
     }
+    if (W > 1) {
+        // every thread of a particle merges all of them, in order
+        __shared__ double s_m[W * kPWaves][64], s_s[W * kPWaves][64];
+        s_m[wv][lane] = m;
+        s_s[wv][lane] = s;
+        __syncthreads();
+        m = s_m[pw][lane];
+        s = s_s[pw][lane];
+        for (int q = pw + kPWaves; q < W * kPWaves; q += kPWaves) {
+            const double mq = s_m[q][lane], sq = s_s[q][lane];
+            if (sq == 0.0) continue;
+            if (mq > m) {
+                s = s * exp(m - mq) + sq;
+                m = mq;
+            } else {
+                s += sq * exp(mq - m);
+            }
+        }
+    }
+    if (i >= n) return;
     const double l = (s > 0.0) ? (ln_ws_max + m + log(s / (double)n_ray)) : -INFINITY;
     const double G = exp(l);
     const double nh = (double)nH_s[i];
@@ -96,10 +123,12 @@ k_adj_rate(const double* __restrict__ N, int64_t n, int n_ray, int n_bins,
     const double dxdl = (sD > 0.0) ? -G * x / sD : 0.0;
     const double li = lam[i];
     const double ell = (lup ? lup[i] : 0.0) + li * dxdl;
-    gnH[i] += -li * dxdl / nh;
-    ell_out[i] = ell;
+    if (way == 0) {
+        gnH[i] += -li * dxdl / nh;
+        ell_out[i] = ell;
+    }
     // pass 2: adjoint of every ray's column, and pi / S per ray for the bins
-    for (int k = 0; k < n_ray; ++k) {
+    for (int k = way; k < n_ray; k += W) {
         const double Nk = N[(int64_t)k * n + i];
         const float2 ST = st[(int64_t)k * n + i];
         double nk = 0.0, pk = 0.0;
@@ -114,11 +143,15 @@ k_adj_rate(const double* __restrict__ N, int64_t n, int n_ray, int n_bins,
     }
 }
 
-// Weight gradient partials: a wave serves 64 bins (one per lane) for a chunk
-// of kAdjChunk particles.  For each ray, 64 particles' column and ell * pi / S
-// are staged in LDS with coalesced loads, and every lane forms its own bin's
-// factor from the LDS broadcasts.  Per lane the sum runs over rays, then the
-// chunk's particles, in order.
+// Weight gradient partials: a block serves 64 bins (one per lane) for a chunk
+// of kAdjChunk particles, 64 to each of its waves.  For each ray, those 64
+// particles' column and ell * pi / S are staged in LDS with coalesced loads (the
+// next ray's already under way), and every lane forms its own bin's factor from
+// the LDS broadcasts.  Per lane the sum runs over rays, then the wave's
+// particles, in order, then over the waves.
+// Bound by the exponentials of the thick pairs at large sizes, below them by the
+// length of a wave's chain of rays.  Measured on MI355X (us with a wave to the
+// whole chunk, then here): the same two 162, 23 and 136, 51.
 __device__ __forceinline__ void adj_wave_sync()
 {
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
@@ -129,52 +162,55 @@ __device__ __forceinline__ void adj_wave_sync()
 __global__ void __launch_bounds__(256)
 k_adj_wbins(const double* __restrict__ N, const double* __restrict__ pis,
             const double* __restrict__ ell, const float* __restrict__ dsig_l2, int64_t n,
-            int n_ray, int n_bins, int64_t n_chunks, double* __restrict__ part, double nmax)
+            int n_ray, int n_bins, double* __restrict__ part, double nmax)
 {
+    static_assert(kAdjChunk == 256, "64 particles to each of a block's waves");
     __shared__ float sN[4][64];
     __shared__ double sW[4][64];
-    const int64_t wave = (blockIdx.x * (int64_t)blockDim.x + threadIdx.x) >> 6;
+    __shared__ double s_acc[4][64];
     const int lane = threadIdx.x & 63;
     const int wv = threadIdx.x >> 6;
     const int groups = (n_bins + 63) / 64;
-    if (wave >= (int64_t)groups * n_chunks) return;           // whole wave
-    const int g = (int)(wave % groups);
-    const int64_t chunk = wave / groups;
+    const int g = (int)(blockIdx.x % groups);
+    const int64_t chunk = blockIdx.x / groups;
     const int b = g * 64 + lane;
     const float ds = b < n_bins ? dsig_l2[b] : 0.0f;
-    const int64_t i0 = chunk * kAdjChunk;
-    const int64_t i1 = i0 + kAdjChunk < n ? i0 + kAdjChunk : n;
+    const int64_t i = chunk * kAdjChunk + threadIdx.x;
+    const bool in = i < n;
+    const double li = in ? ell[i] : 0.0;
     const uint64_t lt = lane ? (~0ull >> (64 - lane)) : 0ull;
     double acc = 0.0;
     // moments sum W N^j of the thin pairs this lane stages
     double mom[kTaylorTerms] = {};
+    double N1 = in ? N[i] : 0.0, p1 = in ? pis[i] : 0.0;
     for (int k = 0; k < n_ray; ++k) {
-        for (int64_t ib = i0; ib < i1; ib += 64) {
-            const int64_t i = ib + lane;
-            const bool in = i < i1;
-            const float Nf = in ? (float)N[(int64_t)k * n + i] : 0.0f;
-            const double w = in ? ell[i] * pis[(int64_t)k * n + i] : 0.0;
-            const bool thin = (double)Nf <= nmax;
-            if (thin && w != 0.0) {
-                double p = w;
-                for (int j = 0; j < kTaylorTerms; ++j) {
-                    mom[j] += p;
-                    p *= (double)Nf;
-                }
-            }
-            // the thick pairs, packed to the front, go through every bin
-            const uint64_t thick = __builtin_amdgcn_ballot_w64(!thin && w != 0.0);
-            if (!thin && w != 0.0) {
-                const int q = __popcll(thick & lt);
-                sN[wv][q] = Nf;
-                sW[wv][q] = w;
-            }
-            adj_wave_sync();
-            const int m = __popcll(thick);
-            for (int q = 0; q < m; ++q)
-                acc += sW[wv][q] * (double)__builtin_amdgcn_exp2f(-ds * sN[wv][q]);
-            adj_wave_sync();
+        const float Nf = (float)N1;
+        const double w = li * p1;
+        if (in && k + 1 < n_ray) {
+            N1 = N[(int64_t)(k + 1) * n + i];
+            p1 = pis[(int64_t)(k + 1) * n + i];
         }
+        const bool thin = (double)Nf <= nmax;
+        if (thin && w != 0.0) {
+            double p = w;
+            for (int j = 0; j < kTaylorTerms; ++j) {
+                mom[j] += p;
+                p *= (double)Nf;
+            }
+        }
+        // the thick pairs, packed to the front, go through every bin
+        const uint64_t thick = __builtin_amdgcn_ballot_w64(!thin && w != 0.0);
+        if (!thin && w != 0.0) {
+            const int q = __popcll(thick & lt);
+            sN[wv][q] = Nf;
+            sW[wv][q] = w;
+        }
+        adj_wave_sync();
+        const int m = __popcll(thick);
+#pragma unroll 4
+        for (int q = 0; q < m; ++q)
+            acc += sW[wv][q] * (double)__builtin_amdgcn_exp2f(-ds * sN[wv][q]);
+        adj_wave_sync();
     }
     // every bin takes the thin pairs' sum from the wave's moments
     double c = 1.0, tot = 0.0;
@@ -184,8 +220,11 @@ k_adj_wbins(const double* __restrict__ N, const double* __restrict__ pis,
         tot += c * mj;
         c *= -0.6931471805599453 * (double)ds / (double)(j + 1);
     }
-    acc += tot;
-    if (b < n_bins) part[chunk * n_bins + b] = acc;
+    s_acc[wv][lane] = acc + tot;
+    __syncthreads();
+    if (wv == 0 && b < n_bins)
+        part[chunk * n_bins + b] =
+            ((s_acc[0][lane] + s_acc[1][lane]) + s_acc[2][lane]) + s_acc[3][lane];
 }
 
 // The per-chunk partials of every bin summed into the accumulator in two
@@ -291,17 +330,25 @@ hipError_t launch_set_density(Ctx& c, const float* nH)
 
 hipError_t launch_adj_rate(Ctx& c, const double* N, const double* lup)
 {
-    hipLaunchKernelGGL(k_adj_rate, dim3(nblk(c.n)), dim3(kBlock), 0, c.stream, N, c.n, c.n_ray,
-                       c.n_bins, c.ws_rel, c.dsig_l2, c.srat, c.sigma_min, c.ln_ws_max, c.nH_s,
-                       c.alpha_s, c.gcoll_s, c.adj_lam, lup, c.adj_nu, c.adj_pis, c.adj_gnH,
-                       c.adj_st, c.adj_ell, thin_sums(c));
+    auto launch = [&](auto kernel, int ways) {
+        const int threads = ways > 4 ? 64 * ways : kBlock, per = threads / ways;
+        hipLaunchKernelGGL(kernel, dim3((unsigned)((c.n + per - 1) / per)), dim3(threads), 0,
+                           c.stream, N, c.n, c.n_ray, c.n_bins, c.ws_rel, c.dsig_l2, c.srat,
+                           c.sigma_min, c.ln_ws_max, c.nH_s, c.alpha_s, c.gcoll_s, c.adj_lam, lup,
+                           c.adj_nu, c.adj_pis, c.adj_gnH, c.adj_st, c.adj_ell, thin_sums(c));
+    };
+    const int W = ray_ways((c.n + 63) / 64, c.n_ray);
+    if (W == 1) launch(k_adj_rate<1>, 1);
+    else if (W == 2) launch(k_adj_rate<2>, 2);
+    else if (W == 4) launch(k_adj_rate<4>, 4);
+    else if (W == 8) launch(k_adj_rate<8>, 8);
+    else launch(k_adj_rate<16>, 16);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     const int64_t chunks = adj_chunks(c);
-    const int64_t waves = chunks * ((c.n_bins + 63) / 64);
-    hipLaunchKernelGGL(k_adj_wbins, dim3((unsigned)((waves * 64 + kBlock - 1) / kBlock)),
+    hipLaunchKernelGGL(k_adj_wbins, dim3((unsigned)(chunks * ((c.n_bins + 63) / 64))),
                        dim3(kBlock), 0, c.stream, N, c.adj_pis, c.adj_ell, c.dsig_l2, c.n,
-                       c.n_ray, c.n_bins, chunks, c.adj_wpart, c.tay_nmax);
+                       c.n_ray, c.n_bins, c.adj_wpart, c.tay_nmax);
     e = hipGetLastError();
     if (e != hipSuccess) return e;
     // the second level sits behind the per-chunk partials

@@ -575,6 +575,16 @@ hipError_t launch_adj_x(Ctx& c, const double* xprev);
 hipError_t launch_adj_init(Ctx& c, double* part);
 int64_t adj_waves(const Ctx& c);
 int64_t adj_chunks(const Ctx& c);
+
+// Threads per particle of the kernels whose threads take rays, for `waves` of
+// one thread per particle: up to 4 waves on each of the device's 1024 SIMDs and
+// at least two rays each (the reasons are at k_gamma).
+inline int ray_ways(int64_t waves, int n_ray)
+{
+    int w = 1;
+    while (w < 16 && 2 * w <= n_ray && waves * w < 4096) w *= 2;
+    return w;
+}
 // particles per partial of the reverse-mode weight gradient
 constexpr int64_t kAdjChunk = 256;
 constexpr int kAdjSlices = 64;           // second level of the weight-gradient sum

@@ -96,8 +96,6 @@ enum { kSchemePlain = 0, kSchemeNearMono = 1, kSchemeNearPoly = 2 };
 // from its list.
 // list: only these particles (the sources of a density block, dense, instead of
 // every particle under a mask).
-constexpr int kRateMaxWays = 16;
-constexpr int64_t kRateWaves = 4096;
 
 constexpr int scheme_lanes(int scheme) { return scheme == kSchemeNearPoly ? kSlabLanes : 1; }
 
@@ -551,9 +549,7 @@ hipError_t launch_gamma(Ctx& c, bool update_x, bool first_sweep)
     }
     const int64_t count = c.row_list ? c.row_list_n : c.n;
     const int per_wave = 64 / scheme_lanes(scheme);
-    int W = 1;
-    while (W < kRateMaxWays && 2 * W <= c.n_ray && (count + per_wave - 1) / per_wave * W < kRateWaves)
-        W *= 2;
+    const int W = ray_ways((count + per_wave - 1) / per_wave, c.n_ray);
     auto launch = [&](auto kernel, int ways) {
         const int threads = ways > 4 ? 64 * ways : 256;
         const int per = threads / 64 / ways * per_wave;

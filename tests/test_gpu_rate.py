@@ -4,6 +4,7 @@ import numpy as np
 import pytest
 import torch
 
+import oracle
 import workloads as W
 
 pytestmark = pytest.mark.gpu
@@ -54,3 +55,27 @@ def test_density_blocks_by_list_and_by_mask(n, tau_skip):
         out.append(s.iterate(6, 0.0)["x"].cpu().numpy())
         s.close()
     np.testing.assert_allclose(out[0], out[1], rtol=1e-10, atol=0)
+
+
+@pytest.mark.parametrize("n_bins", [1, 33, 70])
+@pytest.mark.parametrize("n_ray", [1, 2, 5, 12, 48])
+@pytest.mark.parametrize("n", [1, 65, 300])
+def test_gradients_of_shared_particles(n, n_ray, n_bins):
+    """Weight and density gradients against the oracle's reverse mode where a
+    particle's rays are shared by 1 to 16 threads, the last chunk of particles
+    and the last group of 64 bins part empty.  The FP32 factors and bin terms
+    (1e-7 each, tens of them in a product of derivatives) allow 1e-5 of a
+    gradient and of the largest of its kind."""
+    from paper_1304_4235_amd import Solver
+    wl = W.isothermal_halo(n=n, n_bins=n_bins, seed=47, n_peak=3.0)
+    rng = np.random.default_rng(n_ray)
+    d = rng.normal(size=(n_ray, 3))
+    wl.dirs = d / np.linalg.norm(d, axis=1)[:, None]
+    gl, gx = rng.uniform(-1, 1, n), rng.uniform(-1, 1, n)
+    ref = oracle.adjoint(wl, 3, gl, gx)
+    s = Solver.from_workload(wl)
+    s.forward(3)
+    dw, dn = s.backward(torch.tensor(gl, device="cuda"), torch.tensor(gx, device="cuda"))
+    for got, want in ((dw, ref["dw"]), (dn.cpu().numpy(), ref["dnH"])):
+        np.testing.assert_allclose(got, want, rtol=1e-5, atol=1e-5 * np.abs(want).max())
+    s.close()
