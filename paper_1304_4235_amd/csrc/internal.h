@@ -80,17 +80,11 @@ __host__ __device__ constexpr uint32_t segment_words(uint32_t visits, uint32_t g
     return 1 + (visits + 3) / 4 + groups + (groups + 3) / 4 + (groups + 7) / 8;
 }
 // the group (in ray order) stored at position pos of n (lane pos % 64 holds a
-// run), and the position of group e
+// run)
 __host__ __device__ constexpr uint32_t group_at(uint32_t pos, uint32_t n)
 {
     const uint32_t l = pos & 63u, t = pos >> 6, full = n >> 6, more = n & 63u;
     return l * full + (l < more ? l : more) + t;
-}
-__host__ __device__ constexpr uint32_t group_place(uint32_t e, uint32_t n)
-{
-    const uint32_t full = n >> 6, more = n & 63u, long_end = more * (full + 1);
-    const uint32_t l = e < long_end ? e / (full + 1) : more + (e - long_end) / full;
-    return ((e - (l * full + (l < more ? l : more))) << 6) + l;
 }
 constexpr int kLogHits = 0, kLogVisit = 1, kLogImage = 2;      // word types, bits 62-63
 __host__ __device__ constexpr uint64_t log_visit_word(int leafw, uint32_t visit)

@@ -79,3 +79,24 @@ def test_gradients_of_shared_particles(n, n_ray, n_bins):
     for got, want in ((dw, ref["dw"]), (dn.cpu().numpy(), ref["dnH"])):
         np.testing.assert_allclose(got, want, rtol=1e-5, atol=1e-5 * np.abs(want).max())
     s.close()
+
+
+@pytest.mark.parametrize("n", [1, 2, 127, 129, 257, 513, 5000, 140000])
+def test_transposed_paths_at_the_sort_edges(n):
+    """The transposed gather against the scatter of a re-traversal (the same
+    FP32 products, summed in another order: 1e-9 of a gradient, or of the
+    largest) where the particle index takes 7, 8 and 9 bits, one and two passes,
+    and tiles end part full; twice the same bits."""
+    from paper_1304_4235_amd import Solver
+    wl = W.isothermal_halo(n=n, n_bins=1, seed=21)
+    wl.l_ray = 5.0 if n > 10000 else wl.l_ray
+    gl = torch.tensor(np.random.default_rng(3).uniform(0.5, 1.0, n), device="cuda")
+    out = []
+    for paths in (1, 0):
+        s = Solver.from_workload(wl, record_paths=paths)
+        for _ in range(2 if paths else 1):
+            s.forward(2)
+            out.append(s.backward(gl, None)[1].cpu().numpy())
+        s.close()
+    np.testing.assert_array_equal(out[0], out[1])
+    np.testing.assert_allclose(out[0], out[2], rtol=1e-9, atol=1e-9 * np.abs(out[2]).max())
