@@ -57,7 +57,11 @@ __device__ __forceinline__ float chord_factor(double sp, double b2, double h2, d
     const float z1 = fmaxf((float)(-sp) * ih, -lh);
     const float z2 = fminf((float)(L - sp) * ih, lh);
     if (!(z2 > z1)) return 0.0f;
-    const double e = -ga * (b2 / h2);
+    // b2 / h2 by the hardware reciprocal (some 2^-27) and one correction, to
+    // about 1 ulp; the division's scaling and special cases, a dozen
+    // instructions, have no use here (0 <= b2 < h2, both normal)
+    const double ir2 = __builtin_amdgcn_rcp(h2), q0 = b2 * ir2;
+    const double e = -ga * fma(fma(-q0, h2, b2), ir2, q0);
     const double en = floor(e);
     const float g = (float)gc * ldexpf(__builtin_amdgcn_exp2f((float)(e - en)), (int)en);
     const float e2 = erf_t_odd(t_erf, z2);
@@ -86,19 +90,8 @@ struct PairGeom {
     double d0, d1, d2, sp;
 };
 
-__device__ __forceinline__ PairGeom pair_geom(const float4 Q, double o0, double o1, double o2,
-                                              const double sh[3], const double u[3])
-{
-    PairGeom pg;
-    pg.d0 = ((double)Q.x - o0) + sh[0];
-    pg.d1 = ((double)Q.y - o1) + sh[1];
-    pg.d2 = ((double)Q.z - o2) + sh[2];
-    pg.sp = dot_u(pg.d0, pg.d1, pg.d2, u);
-    return pg;
-}
-
-// The same from coordinates already in FP64; for an unshifted image
-// (kShifted false, s = 0) the adds of zero are left out, which changes no bit.
+// From coordinates already in FP64; for an unshifted image (kShifted false,
+// s = 0) the adds of zero are left out, which changes no bit.
 template <bool kShifted>
 __device__ __forceinline__ PairGeom pair_geom_d(double qx, double qy, double qz, double o0,
                                                 double o1, double o2, const double sh[3],

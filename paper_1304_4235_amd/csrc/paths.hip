@@ -13,6 +13,7 @@
 #include "pair.h"
 
 #include <algorithm>
+#include <type_traits>
 
 namespace rrt {
 
@@ -137,6 +138,13 @@ struct BuildLds {
 // lane per group in stored order: the four chord factors (the walk's own pair
 // arithmetic, so the factors are those every other evaluation of a hit
 // produces) and coalesced stores.
+// Bound by vector issue (80% of the SIMDs' cycles, 157 instructions to an
+// intersection with the log's share): the factor's arithmetic, without the
+// image shift where no lane of the wave has one.  Measured on MI355X: the 885k-
+// particle field's 3.37e9 intersections 19.4 ms with the shift's adds always and
+// an FP64 division, 18.2 ms here; the 262144-particle halo's 1.57e9 8.25 and
+// 7.72 ms.  Not branching in the factor, so that a lane's four interleave, took
+// 20.5 ms: most chords span their sphere and skip a table lookup.
 template <bool NF>
 __global__ void __launch_bounds__(kBlock)
 k_build_paths(const uint64_t* __restrict__ log, const uint64_t* __restrict__ seg_src,
@@ -274,19 +282,21 @@ k_build_paths(const uint64_t* __restrict__ log, const uint64_t* __restrict__ seg
                     slot[i] = S.base[vis[i]] + (pl & 15u);
                     Q[i] = p4[(S.vis[vis[i]] >> kLeafShift) + (pl & 15u)];
                 }
+                auto factors = [&](auto shifted_tag) {
+                constexpr bool kShifted = decltype(shifted_tag)::value;
 #pragma unroll
                 for (int i = 0; i < 4; ++i) {
-                    // the image shift, 0 for the source's own image as in the walk
                     double sh[3] = {0.0, 0.0, 0.0};
-                    if (B > 0.0) {
+                    if (kShifted) {
                         const uint64_t im = S.img[vis[i]];
-                        if (im != ~0ull) {
-                            sh[0] = (double)((int)(im & 16383u) - kMaxImage) * B;
-                            sh[1] = (double)((int)((im >> 14) & 16383u) - kMaxImage) * B;
-                            sh[2] = (double)((int)((im >> 28) & 16383u) - kMaxImage) * B;
-                        }
+                        const bool own = im == ~0ull;
+                        sh[0] = own ? 0.0 : (double)((int)(im & 16383u) - kMaxImage) * B;
+                        sh[1] = own ? 0.0 : (double)((int)((im >> 14) & 16383u) - kMaxImage) * B;
+                        sh[2] = own ? 0.0 : (double)((int)((im >> 28) & 16383u) - kMaxImage) * B;
                     }
-                    const PairGeom pg = pair_geom(Q[i], o0, o1, o2, sh, u);
+                    const PairGeom pg =
+                        pair_geom_d<kShifted>((double)Q[i].x, (double)Q[i].y, (double)Q[i].z, o0,
+                                              o1, o2, sh, u);
                     bits[i] = (uint32_t)__float_as_int(hit_factor(pg, u, Q[i].w, L, t_erf, gc, ga));
                     if (NF) {
                         const double hj = (double)Q[i].w, h2 = hj * hj;
@@ -295,6 +305,14 @@ k_build_paths(const uint64_t* __restrict__ log, const uint64_t* __restrict__ seg
                     }
                     if ((uint32_t)i >= n_used) bits[i] = 0u;
                 }
+                };
+                // the image shift, 0 for the source's own image as in the walk: few
+                // waves hold a shifted one, the others leave its work out
+                bool any = false;
+                if (B > 0.0)
+                    for (int i = 0; i < 4; ++i) any = any || S.img[vis[i]] != ~0ull;
+                if (wave_ballot(any)) factors(std::true_type{});
+                else factors(std::false_type{});
                 d_fac[at] = make_float4(__int_as_float((int)bits[0]), __int_as_float((int)bits[1]),
                                         __int_as_float((int)bits[2]), __int_as_float((int)bits[3]));
                 d_abc[at] = slot[0] | (slot[1] << 10) | (slot[2] << 20) | ((n_used - 1u) << 30);
