@@ -153,10 +153,10 @@ uint64_t workspace_bytes(int64_t n, int n_ray, int n_bins, int n_halo, int K, bo
         if (near_far) add(8 * nr);
         add(8 * (nr + 1));
         // tree build transients: bounds partials, sort histograms, scan partials
-        const uint64_t tiles = (m + 4095) / 4096;
+        const uint64_t tiles = (m + 2047) / 2048;
         add(1024 * 8 * sizeof(float));
-        add(2 * tiles * 256 * sizeof(uint32_t));
-        add(2 * sizeof(uint64_t) * (std::max<uint64_t>(nr + 1, 2 * tiles * 256) / 1024 + 64) + 4096);
+        add(tiles * 256 * sizeof(uint32_t));
+        add(2 * sizeof(uint64_t) * (std::max<uint64_t>(nr + 1, tiles * 256) / 1024 + 64) + 4096);
         if (n_halo > 1) {                                            // grouping of halos
             add(8 * nr);
             add(H * sizeof(int32_t));
