@@ -200,6 +200,8 @@ enum {
     kRedPathSegs = 11,      // segments (recording only)
     kRedSlots = 12
 };
+// sweeps of a fixed number that run between the host's looks at their results
+constexpr int kSweepBatch = 32;
 
 struct Ctx {
     rrt_params prm{};
@@ -385,7 +387,9 @@ struct Ctx {
     // reductions (device, kRedSlots) and a host mirror
     unsigned long long* red = nullptr;
     unsigned long long* queue = nullptr;     // [kQueues * kQueueStride]
+    unsigned long long* sweep_red = nullptr; // [kSweepBatch] sweeps' slots
     unsigned long long* red_host = nullptr;  // pinned
+    unsigned long long* sweep_host = nullptr;    // behind it: sweep_red's copy
     // per sweep of the last rrt_iterate_equilibrium: max |dx| and the
     // particles whose change is below tol, absolutely and relative to x
     std::vector<double> conv_maxdx;
@@ -509,6 +513,7 @@ hipError_t launch_log_walk(Ctx& c, bool store, uint64_t* unit_size);
 void drop_graph(Ctx& c);
 hipError_t build_tiles(Ctx& c);
 hipError_t launch_want(Ctx& c, int block);
+hipError_t launch_keep_sweep(Ctx& c, int sweep);
 hipError_t launch_evolve(Ctx& c, double dt);
 hipError_t launch_block_ids(Ctx& c, const int32_t* block_in);
 void free_tiles(Ctx& c);

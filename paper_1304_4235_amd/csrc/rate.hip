@@ -578,6 +578,16 @@ hipError_t launch_gamma(Ctx& c, bool update_x, bool first_sweep)
 
 namespace {
 
+// a copy of a sweep's slots, its reductions cleared
+__global__ void k_keep_sweep(unsigned long long* __restrict__ red,
+                             unsigned long long* __restrict__ out)
+{
+    const int t = threadIdx.x;
+    if (t >= kRedSlots) return;
+    out[t] = red[t];
+    if (t < kRedInput) red[t] = 0ull;
+}
+
 // particles of block `block` of the density order that are not frozen
 __global__ void k_want(const int32_t* __restrict__ block_s, const uint8_t* __restrict__ skip,
                        int64_t n, int block, uint8_t* __restrict__ want)
@@ -626,6 +636,13 @@ hipError_t launch_want(Ctx& c, int block)
     hipLaunchKernelGGL(k_want, dim3(nblk(c.n)), dim3(kBlock), 0, c.stream,
                        c.rule_blocks > 1 ? c.block_s : nullptr, c.row_frozen, c.n, block,
                        c.want_s);
+    return hipGetLastError();
+}
+
+hipError_t launch_keep_sweep(Ctx& c, int sweep)
+{
+    hipLaunchKernelGGL(k_keep_sweep, dim3(1), dim3(64), 0, c.stream, c.red,
+                       c.sweep_red + (size_t)sweep * kRedSlots);
     return hipGetLastError();
 }
 

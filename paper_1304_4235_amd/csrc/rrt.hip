@@ -176,6 +176,7 @@ int alloc_ctx_buffers(Ctx& c)
     HIP_OK(ws_alloc(c, &c.red, kRedSlots));
     HIP_OK(ws_alloc(c, &c.log_ctr, 2));
     HIP_OK(ws_alloc(c, &c.queue, (size_t)kQueues * kQueueStride));
+    HIP_OK(ws_alloc(c, &c.sweep_red, (size_t)kSweepBatch * kRedSlots));
     KernelTables host;
     fill_kernel_tables(&host);
     HIP_OK(hipMemcpyAsync(c.tables, &host, sizeof host, hipMemcpyHostToDevice, c.stream));
@@ -737,8 +738,12 @@ int rrt_create(rrt_ctx** out, const rrt_params* params, void* stream)
     // the fixed staging array of rrt_get_hits_rows_noalloc on this device
     if (e == hipSuccess) e = noalloc_setup(c.device);
     if (e == hipSuccess)
-        e = hipHostMalloc((void**)&c.red_host, kRedSlots * sizeof(unsigned long long));
-    if (e == hipSuccess) std::memset(c.red_host, 0, kRedSlots * sizeof(unsigned long long));
+        e = hipHostMalloc((void**)&c.red_host,
+                          (1 + kSweepBatch) * kRedSlots * sizeof(unsigned long long));
+    if (e == hipSuccess) {
+        std::memset(c.red_host, 0, kRedSlots * sizeof(unsigned long long));
+        c.sweep_host = c.red_host + kRedSlots;
+    }
     if (e != hipSuccess) {
         g_create_err = std::string("rrt_create: HIP error: ") + hipGetErrorString(e);
         rrt_destroy(x);
@@ -1358,15 +1363,23 @@ int rrt_iterate_equilibrium(rrt_ctx* x, int32_t max_iter, double tol, double* x_
     c.conv_maxdx.clear();
     c.conv_abs.clear();
     c.conv_rel.clear();
+    // The sweep's reductions; the input flags (slots 6, 7) persist until reported.
+    // Every sweep keeps a copy of its slots and clears them for the next.  With a
+    // tolerance the host needs them to go on; a fixed number of sweeps (tol = 0)
+    // runs kSweepBatch at a time, and the device does not wait for the host's
+    // turn after each (measured on MI355X: 20 sweeps of 16384 particles 3014 us
+    // in all with a look at each, 2869 here; 8 of 4096 1136 and 1087).
+    HIP_OK(hipMemsetAsync(c.red, 0, kRedInput * sizeof(unsigned long long), c.stream));
+    const int batch = tol > 0.0 ? 1 : kSweepBatch;
+    int64_t hits_of[kSweepBatch];
+    int launched = 0;                         // sweeps whose slots are still to be read
     for (it = 0; it < max_iter;) {
-        // the sweep's reductions; the input flags (slots 6, 7) persist until reported
-        HIP_OK(hipMemsetAsync(c.red, 0, kRedInput * sizeof(unsigned long long), c.stream));
         int64_t hits = -1;
         for (int b = 0; b < n_steps; ++b) {
             // one block of the density order (all particles for the
             // order-independent update), frozen particles left out
             c.geom.want = nullptr;
-            c.row_frozen = skipping && it > 0 ? c.skip_s : nullptr;
+            c.row_frozen = skipping && it + launched > 0 ? c.skip_s : nullptr;
             if (ordered) {                    // the product walks only this block's rays
                 c.row_list = c.block_list + c.block_off[b];
                 c.row_list_n = c.block_off[b + 1] - c.block_off[b];
@@ -1377,27 +1390,37 @@ int rrt_iterate_equilibrium(rrt_ctx* x, int32_t max_iter, double tol, double* x_
             }
             if (int r = columns_impl(c, &hits)) return r;
             hipEvent_t eg = ev_begin(c);
-            HIP_OK(launch_gamma(c, true, it == 0));
+            HIP_OK(launch_gamma(c, true, it + launched == 0));
             ev_end(c, eg, &c.t_rate);
         }
         c.geom.want = nullptr;
         c.row_list = nullptr;
         c.row_list_n = 0;
         c.row_frozen = nullptr;
-        HIP_OK(hipMemcpyAsync(c.red_host, c.red, kRedSlots * sizeof(unsigned long long),
+        HIP_OK(launch_keep_sweep(c, launched));
+        hits_of[launched++] = hits;
+        if (launched < batch && it + launched < max_iter) continue;
+        HIP_OK(hipMemcpyAsync(c.sweep_host, c.sweep_red,
+                              sizeof(unsigned long long) * kRedSlots * launched,
                               hipMemcpyDeviceToHost, c.stream));
         HIP_OK(hipStreamSynchronize(c.stream));
-        if (int r = check_flags(c)) return r;
-        ++it;
-        std::memcpy(&mdx, &c.red_host[kRedMaxDx], sizeof mdx);
-        c.conv_maxdx.push_back(mdx);
-        c.conv_abs.push_back((int64_t)c.red_host[kRedConvAbs]);
-        c.conv_rel.push_back((int64_t)c.red_host[kRedConvRel]);
-        // intersections of the sweep: counted by traversal, or all recorded
-        // ones when every ray was evaluated; not counted for masked sweeps
-        // over recorded paths
-        c.last_hits = hits < 0 ? (int64_t)c.red_host[kRedHits] : (masked ? -1 : hits);
-        if (c.last_hits > 0) c.total_hits += c.last_hits;
+        for (int q = 0; q < launched; ++q) {
+            const unsigned long long* red = c.sweep_host + (size_t)q * kRedSlots;
+            c.red_host[kRedInput] = red[kRedInput];
+            c.red_host[kRedNumeric] = red[kRedNumeric];
+            if (int r = check_flags(c)) return r;
+            ++it;
+            std::memcpy(&mdx, &red[kRedMaxDx], sizeof mdx);
+            c.conv_maxdx.push_back(mdx);
+            c.conv_abs.push_back((int64_t)red[kRedConvAbs]);
+            c.conv_rel.push_back((int64_t)red[kRedConvRel]);
+            // intersections of the sweep: counted by traversal, or all recorded
+            // ones when every ray was evaluated; not counted for masked sweeps
+            // over recorded paths
+            c.last_hits = hits_of[q] < 0 ? (int64_t)red[kRedHits] : (masked ? -1 : hits_of[q]);
+            if (c.last_hits > 0) c.total_hits += c.last_hits;
+        }
+        launched = 0;
         if (mdx < tol) break;
     }
     c.have_columns = c.have_gamma = false;

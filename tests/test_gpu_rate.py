@@ -100,3 +100,25 @@ def test_transposed_paths_at_the_sort_edges(n):
         s.close()
     np.testing.assert_array_equal(out[0], out[1])
     np.testing.assert_allclose(out[0], out[2], rtol=1e-9, atol=1e-9 * np.abs(out[2]).max())
+
+
+@pytest.mark.parametrize("blocks,tau_skip", [(1, 0.0), (1, 1.0), (4, 1.0)])
+@pytest.mark.parametrize("sweeps", [1, 31, 32, 33, 70])
+def test_a_fixed_number_of_sweeps(sweeps, blocks, tau_skip):
+    """A fixed number of sweeps, whose results the host reads many at a time,
+    against a tolerance that no sweep meets, where it reads each: the same
+    launches, so the same bits, and every sweep's maximum."""
+    from paper_1304_4235_amd import Solver
+    wl = W.isothermal_halo(n=200, n_bins=3, seed=5, n_peak=3.0)
+    out = []
+    for tol in (0.0, 5e-324):
+        s = Solver.from_workload(wl, build=False)
+        s.set_update_rule(tau_skip=tau_skip, n_blocks=blocks)
+        s.build_tree()
+        r = s.iterate(sweeps, tol)
+        out.append((r["x"].cpu().numpy(), s.convergence()["max_dx"]))
+        s.close()
+    m = len(out[1][1])                      # fewer only if a sweep changed nothing at all
+    assert len(out[0][1]) == sweeps and (m == sweeps or out[1][1][-1] == 0.0)
+    np.testing.assert_array_equal(out[0][1][:m], out[1][1])
+    np.testing.assert_array_equal(out[0][0], out[1][0])
