@@ -149,10 +149,11 @@ int rrt_workspace_info(const rrt_ctx* ctx, size_t* out6);
 /* Recorded paths, first step: a counting walk over the current tree (Sec.
  * 4.1.1, eq. colden: which particles each ray intersects).  Host outputs,
  * each nullable: *n_hits, the intersections of every ray (each periodic
- * image separately); *bytes_paths, the path buffer that recording the paths
- * needs (the paths, about 5.9 bytes per intersection, and the walk's log beside
- * them while recording, 2 to 4); *bytes_one_walk, the size with which a later
- * recording of a similar geometry takes one walk (with a log a quarter larger).
+ * image separately); *bytes_paths, the least path buffer that recording the
+ * paths needs (the paths, about 5.9 bytes per intersection, and a 32nd of the
+ * walk's log, so that they are recorded in pieces); *bytes_one_walk, the size
+ * with which a later recording of a similar geometry takes one walk (the whole
+ * log, 2 to 4 bytes per intersection, beside the paths).
  * The counts are kept, so the next column evaluation records with one walk.
  * Synchronises. */
 int rrt_count_paths(rrt_ctx* ctx, int64_t* n_hits, size_t* bytes_paths, size_t* bytes_one_walk);

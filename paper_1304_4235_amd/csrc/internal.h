@@ -73,7 +73,7 @@ constexpr int64_t kMaxWaves = 256 * 32;    // resident waves of the device
 // the persistent walk's queues (one per XCD), 128 bytes apart
 constexpr int kQueues = 8, kQueueStride = 16;
 // |periodic image| along an axis that a log word can hold
-constexpr int kMaxImage = 8191;
+constexpr int kMaxImage = 131071;
 
 __host__ __device__ constexpr uint32_t segment_words(uint32_t visits, uint32_t groups)
 {
@@ -93,8 +93,8 @@ __host__ __device__ constexpr uint64_t log_visit_word(int leafw, uint32_t visit)
 }
 __host__ __device__ constexpr uint64_t log_image_word(int sx, int sy, int sz, uint32_t visit)
 {
-    return (uint64_t)(sx + kMaxImage) | ((uint64_t)(sy + kMaxImage) << 14) |
-           ((uint64_t)(sz + kMaxImage) << 28) | ((uint64_t)visit << 43) |
+    return (uint64_t)(sx + kMaxImage) | ((uint64_t)(sy + kMaxImage) << 18) |
+           ((uint64_t)(sz + kMaxImage) << 36) | ((uint64_t)visit << 54) |
            ((uint64_t)kLogImage << 62);
 }
 __host__ __device__ constexpr uint64_t log_hits_word(uint32_t mask, int ray, uint32_t start,
@@ -197,8 +197,9 @@ enum {
     kRedPathSize = 8,   // of a recording's or tally's units: recorded words,
     kRedPathBlocks = 9,    // log blocks,
     kRedPathHits = 10,      // intersections,
-    kRedPathSegs = 11,      // segments (recording only)
-    kRedSlots = 12
+    kRedPathSegs = 11,      // segments (where the units' are kept),
+    kRedPathMost = 12,      // log blocks of the largest unit
+    kRedSlots = 13
 };
 // sweeps of a fixed number that run between the host's looks at their results
 constexpr int kSweepBatch = 32;
@@ -280,7 +281,8 @@ struct Ctx {
     unsigned long long* log_ctr = nullptr;    // next block, pool ran short
     uint64_t log_blocks = 0;
     // sizes of the last recording or tally walk: recorded words, log blocks, hits
-    uint64_t last_words = 0, last_blocks = 0, last_total = 0;
+    uint64_t last_words = 0, last_blocks = 0, last_most = 0, last_total = 0;
+    bool log_tight = false;           // short of memory: waves take one block at a time
     // the same paths by rows (row = ray), for what needs them that way (row
     // tiles, the transposition): offsets and (tree index, factor) entries
     uint64_t* row_off = nullptr;  // [n_ray * n + 1]
@@ -510,6 +512,7 @@ hipError_t launch_columns(Ctx& c);
 // the recording walk into the log (store), or its sizes only; unit_size
 // receives each unit's recorded words | log blocks << 32
 hipError_t launch_log_walk(Ctx& c, bool store, uint64_t* unit_size);
+hipError_t launch_log_range(Ctx& c, int64_t unit0, int64_t units);
 void drop_graph(Ctx& c);
 hipError_t build_tiles(Ctx& c);
 hipError_t launch_want(Ctx& c, int block);
@@ -545,6 +548,7 @@ hipError_t launch_sum_units(Ctx& c, const uint64_t* unit_size, bool segments);
 // c.unit_seg
 hipError_t launch_unit_words(Ctx& c);
 hipError_t launch_build_paths(Ctx& c);
+hipError_t launch_build_range(Ctx& c, int64_t unit0, int64_t units, uint64_t seg0, uint64_t segs);
 hipError_t launch_path_columns(Ctx& c);
 // the rows of the listed sources (one block of the density order) from c.path
 hipError_t launch_row_columns(Ctx& c, int group);

@@ -111,7 +111,7 @@ int path_parts(const Ctx& c)
 
 // Log blocks a wave takes at once: the counter they come from is one word, on
 // which the device's waves contend (what a wave holds at the end stays unused).
-uint32_t log_take(const Ctx& c) { return c.packet_queue ? kLogCache : 1u; }
+uint32_t log_take(const Ctx& c) { return c.packet_queue && !c.log_tight ? kLogCache : 1u; }
 
 // ---------------------------------------------------------------------------
 // the log into segments
@@ -228,7 +228,8 @@ k_build_paths(const uint64_t* __restrict__ log, const uint64_t* __restrict__ seg
                     S.img[v] = ~0ull;
                 }
                 wave_sync();
-                if (type == (uint32_t)kLogImage) S.img[v] = w & ((1ull << 42) - 1ull);
+                if (type == (uint32_t)kLogImage)
+                    S.img[(uint32_t)(w >> 54) & (kSegVisits - 1)] = w & ((1ull << 54) - 1ull);
                 if (type == (uint32_t)kLogHits) {
                     uint32_t mask = (uint32_t)w & 0xffffu;
                     const uint32_t ray = (uint32_t)(w >> 16) & 63u;
@@ -290,9 +291,9 @@ k_build_paths(const uint64_t* __restrict__ log, const uint64_t* __restrict__ seg
                     if (kShifted) {
                         const uint64_t im = S.img[vis[i]];
                         const bool own = im == ~0ull;
-                        sh[0] = own ? 0.0 : (double)((int)(im & 16383u) - kMaxImage) * B;
-                        sh[1] = own ? 0.0 : (double)((int)((im >> 14) & 16383u) - kMaxImage) * B;
-                        sh[2] = own ? 0.0 : (double)((int)((im >> 28) & 16383u) - kMaxImage) * B;
+                        sh[0] = own ? 0.0 : (double)((int)(im & 0x3ffffu) - kMaxImage) * B;
+                        sh[1] = own ? 0.0 : (double)((int)((im >> 18) & 0x3ffffu) - kMaxImage) * B;
+                        sh[2] = own ? 0.0 : (double)((int)((im >> 36) & 0x3ffffu) - kMaxImage) * B;
                     }
                     const PairGeom pg =
                         pair_geom_d<kShifted>((double)Q[i].x, (double)Q[i].y, (double)Q[i].z, o0,
@@ -332,22 +333,25 @@ __global__ void __launch_bounds__(kBlock)
 k_sum_units(const uint64_t* __restrict__ unit_size, const uint2* __restrict__ unit_log,
             int64_t n_units, unsigned long long* __restrict__ red)
 {
-    unsigned long long words = 0, blocks = 0, segs = 0;
+    unsigned long long words = 0, blocks = 0, segs = 0, most = 0;
     const int64_t stride = (int64_t)gridDim.x * blockDim.x;
     for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n_units; i += stride) {
         words += unit_size[i] & 0xffffffffull;
         blocks += unit_size[i] >> 32;
+        most = std::max<unsigned long long>(most, unit_size[i] >> 32);
         if (unit_log) segs += unit_log[i].y;
     }
     for (int off = 32; off > 0; off >>= 1) {
         words += __shfl_xor(words, off, 64);
         blocks += __shfl_xor(blocks, off, 64);
         segs += __shfl_xor(segs, off, 64);
+        most = std::max<unsigned long long>(most, __shfl_xor(most, off, 64));
     }
     if ((threadIdx.x & 63) == 0 && words) {
         atomicAdd(red + kRedPathSize, words);
         atomicAdd(red + kRedPathBlocks, blocks);
         atomicAdd(red + kRedPathSegs, segs);
+        atomicMax(red + kRedPathMost, most);
     }
 }
 
@@ -366,11 +370,11 @@ k_unit_words(uint64_t* __restrict__ unit_off, const uint2* __restrict__ unit_log
 __global__ void __launch_bounds__(kBlock)
 k_index_segments(const uint64_t* __restrict__ log, const uint2* __restrict__ unit_log,
                  const uint64_t* __restrict__ unit_off, const uint64_t* __restrict__ unit_seg,
-                 int64_t n_units, uint64_t* __restrict__ seg_src, uint32_t* __restrict__ seg_unit,
-                 uint64_t* __restrict__ seg_off)
+                 int64_t unit0, int64_t n_units, uint64_t* __restrict__ seg_src,
+                 uint32_t* __restrict__ seg_unit, uint64_t* __restrict__ seg_off)
 {
-    const int64_t u = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-    if (u >= n_units) return;
+    const int64_t u = unit0 + blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
+    if (u >= unit0 + n_units) return;
     const uint2 ul = unit_log[u];
     uint64_t at = (uint64_t)ul.x * kLogBlock, w = unit_off[u];
     const uint64_t s = unit_seg[u];
@@ -406,18 +410,24 @@ hipError_t launch_unit_words(Ctx& c)
 
 hipError_t launch_build_paths(Ctx& c)
 {
+    return launch_build_range(c, 0, path_packets(c) * path_parts(c), 0, c.path_segs);
+}
+
+// the log of units unit0 and on, their segments seg0 and on
+hipError_t launch_build_range(Ctx& c, int64_t unit0, int64_t units, uint64_t seg0, uint64_t n_segs)
+{
     const int parts = path_parts(c);
-    const int64_t units = path_packets(c) * parts, segs = (int64_t)c.path_segs;
+    const int64_t segs = (int64_t)n_segs;
     if (segs == 0) return hipSuccess;
     hipLaunchKernelGGL(k_index_segments, dim3((unsigned)((units + kBlock - 1) / kBlock)),
                        dim3(kBlock), 0, c.stream, c.path_log, c.unit_log, c.unit_off, c.unit_seg,
-                       units, c.seg_src, c.seg_unit, c.seg_off);
+                       unit0, units, c.seg_src, c.seg_unit, c.seg_off);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     const unsigned nb = (unsigned)std::min<int64_t>((segs + kWaves - 1) / kWaves, kMaxBlocks);
     auto go = [&](auto kernel) {
-        hipLaunchKernelGGL(kernel, dim3(nb), dim3(kBlock), 0, c.stream, c.path_log, c.seg_src,
-                           c.seg_unit, c.seg_off, segs, parts, c.packed, c.p4, c.dirs, c.tables,
+        hipLaunchKernelGGL(kernel, dim3(nb), dim3(kBlock), 0, c.stream, c.path_log,
+                           c.seg_src + seg0, c.seg_unit + seg0, c.seg_off + seg0, segs, parts, c.packed, c.p4, c.dirs, c.tables,
                            c.geom);
     };
     if (c.near_far) go(k_build_paths<true>);

@@ -346,6 +346,14 @@ uint64_t record_bytes(const Ctx& c, uint64_t words, uint64_t blocks)
            region_bytes((words + kPackedPad) * 16);
 }
 
+// Path buffer for a recording in pieces, the least that holds the paths: a log
+// of a 32nd of the whole, and of the largest unit at least.
+uint64_t piece_blocks(const Ctx& c)
+{
+    return std::max<uint64_t>(std::max<uint64_t>(c.last_most, 1), c.last_blocks / 32 + 1);
+}
+uint64_t record_bytes_least(const Ctx& c) { return record_bytes(c, c.last_words, piece_blocks(c)); }
+
 // The log's pool and the units' arrays in the path buffer, when they fit
 // beside paths of `words`.  False (nothing kept) otherwise.
 bool alloc_log(Ctx& c, uint64_t words, uint64_t blocks)
@@ -372,7 +380,7 @@ bool alloc_log(Ctx& c, uint64_t words, uint64_t blocks)
 // last_blocks and last_total, and whether the pool ran short.
 int path_walk(Ctx& c, bool store, uint64_t* unit_tally, bool* overflow)
 {
-    HIP_OK(hipMemsetAsync(c.red + kRedPathSize, 0, 4 * sizeof(unsigned long long), c.stream));
+    HIP_OK(hipMemsetAsync(c.red + kRedPathSize, 0, 5 * sizeof(unsigned long long), c.stream));
     HIP_OK(hipMemsetAsync(c.log_ctr, 0, 2 * sizeof(unsigned long long), c.stream));
     // the units' sizes: the recorded paths' offsets to be, the caller's array, or
     // scratch
@@ -388,16 +396,17 @@ int path_walk(Ctx& c, bool store, uint64_t* unit_tally, bool* overflow)
         size = tmp.p;
     }
     HIP_OK(launch_log_walk(c, store, size));
-    HIP_OK(launch_sum_units(c, size, store));
+    HIP_OK(launch_sum_units(c, size, c.unit_log != nullptr));
     HIP_OK(hipMemcpyAsync(c.red_host + kRedPathSize, c.red + kRedPathSize,
-                          4 * sizeof(unsigned long long), hipMemcpyDeviceToHost, c.stream));
+                          5 * sizeof(unsigned long long), hipMemcpyDeviceToHost, c.stream));
     unsigned long long ctr[2] = {0, 0};
     HIP_OK(hipMemcpyAsync(ctr, c.log_ctr, sizeof ctr, hipMemcpyDeviceToHost, c.stream));
     HIP_OK(hipStreamSynchronize(c.stream));
     c.last_words = c.red_host[kRedPathSize];
     c.last_blocks = c.red_host[kRedPathBlocks];
     c.last_total = c.red_host[kRedPathHits];
-    if (store) {
+    c.last_most = c.red_host[kRedPathMost];
+    if (c.unit_log) {
         c.path_segs = c.red_host[kRedPathSegs];
         c.path_words = c.last_words;
     }
@@ -435,10 +444,69 @@ int paths_unfit(Ctx& c)
         return fail(c, RRT_E_WORKSPACE,
                     "recorded paths need %llu bytes; the path buffer holds %llu "
                     "(rrt_count_paths, rrt_set_path_buffer)",
-                    (unsigned long long)record_bytes(c, c.last_words,
-                                                     log_pool(c, c.last_blocks, 1.0, false)),
+                    (unsigned long long)record_bytes_least(c),
                     (unsigned long long)c.arena.cap[kRegionPath]);
     c.paths_unfit = true;
+    return RRT_OK;
+}
+
+// The recording where the whole log does not fit beside the paths: a walk for the
+// units' sizes and segments, then walk and build alternately over ranges of the
+// units, each as long as the room left holds its log.  fit: the paths and the
+// largest unit's log do.
+int record_pieces(Ctx& c, bool* fit)
+{
+    *fit = false;
+    free_log(c);
+    ws_free(c, &c.unit_seg);
+    ws_free(c, &c.seg_off);
+    ws_free(c, &c.packed);
+    const int64_t units = path_packets(c) * path_parts(c);
+    hipError_t e = ws_alloc(c, &c.unit_seg, (size_t)units + 1, kRegionPath);
+    if (e == hipSuccess) e = ws_alloc(c, &c.unit_off, (size_t)units + 1, kRegionPath);
+    if (e == hipSuccess) e = ws_alloc(c, &c.unit_log, (size_t)units, kRegionPath);
+    if (e != hipSuccess) return RRT_OK;
+    if (int r = path_walk(c, false, c.unit_off, nullptr)) return r;
+    const size_t segs = (size_t)std::max<uint64_t>(c.path_segs, 1);
+    e = ws_alloc(c, &c.seg_off, segs, kRegionPath);
+    if (e == hipSuccess) e = ws_alloc(c, &c.seg_src, segs, kRegionPath);
+    if (e == hipSuccess) e = ws_alloc(c, &c.seg_unit, segs, kRegionPath);
+    if (e == hipSuccess)
+        e = ws_alloc(c, &c.packed, (size_t)c.last_words + kPackedPad, kRegionPath);
+    const uint64_t room = ws_largest_gap(c, kRegionPath) / (kLogBlock * sizeof(uint64_t));
+    const uint64_t blocks = std::min<uint64_t>(std::min<uint64_t>(room, c.last_blocks + 1),
+                                               0xfffffff0ull);
+    if (e != hipSuccess || blocks < std::max<uint64_t>(c.last_most, 1)) return RRT_OK;
+    if (ws_alloc(c, &c.path_log, (size_t)blocks * kLogBlock, kRegionPath) != hipSuccess)
+        return RRT_OK;
+    c.log_blocks = blocks;
+    HIP_OK(launch_unit_words(c));
+    HIP_OK(scan_exclusive_u64(c, c.unit_off, c.unit_off, units + 1));
+    HIP_OK(scan_exclusive_u64(c, c.unit_seg, c.unit_seg, units + 1));
+    int64_t n = std::max<int64_t>(
+        1, (int64_t)((double)units * (double)blocks / (double)(c.last_blocks + 1)));
+    uint64_t seg0 = 0;
+    for (int64_t u = 0; u < units;) {
+        n = std::min({n, units - u, (int64_t)1 << 24});
+        unsigned long long ctr[2] = {0, 0};
+        uint64_t seg1 = 0;
+        HIP_OK(hipMemsetAsync(c.log_ctr, 0, sizeof ctr, c.stream));
+        HIP_OK(launch_log_range(c, u, n));
+        HIP_OK(hipMemcpyAsync(ctr, c.log_ctr, sizeof ctr, hipMemcpyDeviceToHost, c.stream));
+        HIP_OK(hipMemcpyAsync(&seg1, c.unit_seg + u + n, sizeof seg1, hipMemcpyDeviceToHost,
+                              c.stream));
+        HIP_OK(hipStreamSynchronize(c.stream));
+        if (ctr[1] != 0) {                        // more log than the pool: a shorter range
+            if (n == 1) return fail(c, RRT_E_HIP, "the recording's log ran past its counted size");
+            n = (n + 1) / 2;
+            continue;
+        }
+        HIP_OK(launch_build_range(c, u, n, seg0, seg1 - seg0));
+        seg0 = seg1;
+        u += n;
+    }
+    free_log(c);
+    *fit = true;
     return RRT_OK;
 }
 
@@ -461,6 +529,7 @@ int record_paths(Ctx& c)
         return RRT_OK;
     }
     if (!c.images_fit) return paths_unfit(c);
+    c.log_tight = false;
     hipEvent_t ev_rec = ev_begin(c);
     int kind = c.counts_valid ? 2 : 3;      // after a count; a sizes walk first
     bool logged = false;
@@ -481,21 +550,25 @@ int record_paths(Ctx& c)
         ev_end(c, ew, &c.t_other_walk);
     }
     c.counts_valid = true;
-    if (!logged) {
-        if (!alloc_log(c, c.last_words, log_pool(c, c.last_blocks, 1.0, false))) {
-            ev_end(c, ev_rec, &c.t_record);
-            return paths_unfit(c);
-        }
+    if (!logged && alloc_log(c, c.last_words, log_pool(c, c.last_blocks, 1.0, false))) {
         bool overflow = false;
         hipEvent_t ew = ev_begin(c);
         if (int r = path_walk(c, true, nullptr, &overflow)) return r;
         ev_end(c, ew, &c.t_other_walk);
         if (overflow) return fail(c, RRT_E_HIP, "the recording's log ran past its counted size");
+        logged = true;
     }
-    hipEvent_t ew = ev_begin(c);
     bool fit = false;
-    if (int r = build_paths(c, &fit)) return r;
-    ev_end(c, ew, &c.t_compact);
+    if (logged) {
+        hipEvent_t ew = ev_begin(c);
+        if (int r = build_paths(c, &fit)) return r;
+        ev_end(c, ew, &c.t_compact);
+    }
+    if (!fit) {
+        hipEvent_t ew = ev_begin(c);
+        if (int r = record_pieces(c, &fit)) return r;
+        ev_end(c, ew, &c.t_other_walk);
+    }
     if (!fit) {
         ev_end(c, ev_rec, &c.t_record);
         return paths_unfit(c);
@@ -1150,7 +1223,7 @@ int rrt_build_tree(rrt_ctx* x)
     }
     g.hmax = hmax;
     g.pad = pad;
-    // the recording's log codes a hit's periodic image in 14 bits per axis
+    // the recording's log codes a hit's periodic image in 18 bits per axis
     c.images_fit = !(g.box > 0.0) || (g.L + (double)hmax + ext) / g.box + 2.0 <= kMaxImage;
     g.n = (int32_t)c.n;
     g.n_ray = c.n_ray;
@@ -1758,6 +1831,9 @@ int plan_groups(Ctx& c, std::vector<std::vector<int>>& groups, std::vector<bool>
                               hipMemcpyDeviceToHost, c.stream));
         HIP_OK(hipStreamSynchronize(c.stream));
     }
+    // a buffer that the waves' unused blocks would fill: they take one at a time
+    c.log_tight = false;
+    c.log_tight = log_pool(c, 0, 1.0, false) * kLogBlock * 8 > c.arena.cap[kRegionPath] / 16;
     // bytes of each halo's paths and log, and the room beside the fixed arrays
     auto bytes = [&](int h) {
         return size[2 * h] * 16 + (size[2 * h] / 32 + 1) * kSegmentBytes +
@@ -2200,8 +2276,8 @@ int rrt_count_paths(rrt_ctx* x, int64_t* n_hits, size_t* bytes_paths, size_t* by
     }
     if (n_hits) *n_hits = (int64_t)c.last_total;
     if (bytes_paths)
-        *bytes_paths =
-            (size_t)record_bytes(c, c.last_words, log_pool(c, c.last_blocks, 1.0, false));
+        *bytes_paths = (size_t)record_bytes_least(c);
+    c.log_tight = false;
     if (bytes_one_walk)
         *bytes_one_walk = (size_t)record_bytes(
             c, c.last_words, std::max(log_pool(c, c.last_blocks, c.pool_scale, true),

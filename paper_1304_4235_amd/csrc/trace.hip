@@ -102,6 +102,7 @@ struct RayOut {
     uint2* unit_log;                 // per unit: first block, segments
     uint64_t* unit_size;             // per unit: recorded words | log blocks << 32
     int32_t parts;                   // units each packet's walk is split into
+    int64_t unit0, unit_end;         // a part of the units (without the queues), all if 0
     // sampled sources (count and record modes): only the rays of the sorted
     // tree positions src_list[0..src_n) run, and their outputs go to row
     // i * n_ray + k for the source at src_list[i] (null = every ray, row = ray)
@@ -451,6 +452,9 @@ k_trace_wave(const Node* __restrict__ nodes, const float4* __restrict__ leaf_bal
                                : (int64_t)g.n_ray * waves_per_dir;
         unit = wave * parts + part;
     } else if (kTally) {
+        unit += out.unit0;
+        if (out.unit_end && unit >= out.unit_end)      // past the last: ends the wave
+            unit = (int64_t)g.n_ray * waves_per_dir * parts;
         wave = unit / parts;
         part = __builtin_amdgcn_readfirstlane((int)(unit - wave * parts));
     }
@@ -874,13 +878,14 @@ k_trace_wave(const Node* __restrict__ nodes, const float4* __restrict__ leaf_bal
         if (g_vis) close_segment();
         if (lane == 0) {
             const uint64_t un = ls->unit;
+            if (out.unit_log) out.unit_log[un] = make_uint2(ls->first_blk, ls->n_seg);
             if (kLog) {
-                out.unit_log[un] = make_uint2(ls->first_blk, ls->n_seg);
                 if (blk != kNoBlock)
                     out.log[(uint64_t)blk * kLogBlock + kLogData] =
                         (uint64_t)kNoBlock | ((uint64_t)kLogData << 32);
             }
-            out.unit_size[un] = (uint64_t)ls->size | ((uint64_t)ls->blocks << 32);
+            if (out.unit_size)
+                out.unit_size[un] = (uint64_t)ls->size | ((uint64_t)ls->blocks << 32);
         }
         wave_sync();
     }
@@ -933,7 +938,7 @@ static void launch_wave_nf(Ctx& c, RayOut o, int bs, size_t lds, int64_t waves)
     const unsigned nb = (unsigned)((waves * 64 + bs - 1) / bs);
     // the persistent form for the walks that record, count or evaluate
     constexpr bool kQueued = MODE == kModeColumn || MODE == kModeCount || mode_logs(MODE);
-    if (kQueued && c.packet_queue) {
+    if (kQueued && c.packet_queue && o.unit_end == 0) {
         // a kernel, not a memset, clears the counters (the launch may be captured)
         hipLaunchKernelGGL(k_zero_queues, dim3(1), dim3(64), 0, c.stream, c.queue);
         o.queue = c.queue;
@@ -958,7 +963,8 @@ template <int MODE>
 static void launch_wave(Ctx& c, RayOut o)
 {
     const int bs = c.prm.block_size > 0 ? c.prm.block_size : 128;
-    const int64_t waves = path_packets(c) * (mode_logs(MODE) ? o.parts : 1);
+    const int64_t waves = o.unit_end ? o.unit_end - o.unit0
+                                     : path_packets(c) * (mode_logs(MODE) ? o.parts : 1);
     const size_t lds = wave_lds_bytes(MODE, bs);
     constexpr bool kSplit = MODE == kModeColumn;
     if (kSplit && o.near_far) launch_wave_nf<MODE, kSplit>(c, o, bs, lds, waves);
@@ -1077,6 +1083,24 @@ hipError_t launch_log_walk(Ctx& c, bool store, uint64_t* unit_size)
     o.parts = path_parts(c);
     if (store) launch_wave<kModeLog>(c, o);
     else launch_wave<kModeTally>(c, o);
+    return hipGetLastError();
+}
+
+// The log of a range of the units, whose sizes and segments are known.
+hipError_t launch_log_range(Ctx& c, int64_t unit0, int64_t units)
+{
+    RayOut o{};
+    o.perm = c.perm;
+    o.hits_total = c.red + kRedScratch;
+    o.log = c.path_log;
+    o.log_blocks = c.log_blocks;
+    o.log_take = 1;
+    o.log_ctr = c.log_ctr;
+    o.unit_log = c.unit_log;
+    o.parts = path_parts(c);
+    o.unit0 = unit0;
+    o.unit_end = unit0 + units;
+    launch_wave<kModeLog>(c, o);
     return hipGetLastError();
 }
 

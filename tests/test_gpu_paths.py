@@ -103,3 +103,53 @@ def test_row_products_of_the_recorded_paths():
         dn.append(s.backward(g, None)[1].cpu().numpy())
     np.testing.assert_allclose(dn[1], dn[0], rtol=1e-9, atol=1e-12 * np.abs(dn[0]).max())
     s.close()
+
+
+@pytest.mark.parametrize("which", ["one", "packet_plus_one", "slots", "images", "field"])
+def test_recording_in_pieces(which):
+    """The least path buffer that rrt_count_paths names holds no whole log: the
+    paths are recorded a range of units at a time, to the same columns bit for
+    bit; half of it is refused."""
+    from paper_1304_4235_amd import RRTError, Solver
+    wl, leaf = _case(which)
+    x = torch.tensor(np.random.default_rng(2).uniform(1e-6, 1.0, wl.n))
+    s = Solver.from_workload(wl, leaf_size=leaf, record_paths=1)
+    need = s.count_paths()
+    s.set_state(x)
+    N, hits = s.compute_columns()
+    N = N.clone()
+    assert need["bytes_paths"] < need["bytes_one_walk"]
+    t = Solver.from_workload(wl, leaf_size=leaf, record_paths=1, path_budget=need["bytes_paths"])
+    for _ in range(2):
+        t.build_tree()
+        t.set_state(x)
+        got, h = t.compute_columns()
+        assert h == hits == t.timing()["path_hits"]
+        assert torch.equal(got, N)
+    u = Solver.from_workload(wl, leaf_size=leaf, record_paths=1,
+                             path_budget=need["bytes_paths"] // 2)
+    u.set_state(x)
+    with pytest.raises(RRTError, match="RRT_E_WORKSPACE"):
+        u.compute_columns()
+    for q in (s, t, u):
+        q.close()
+
+
+def test_paths_over_many_images():
+    """Images that a ray reaches up to 9000 box lengths away: columns over the
+    recorded paths against the traversal's (FP64 sums in another order)."""
+    from paper_1304_4235_amd import Solver
+    out = []
+    for paths in (1, 0):
+        s = Solver(l_ray=9000.0, box=1.0, record_paths=paths)
+        s.set_particles(np.array([[0.5, 0.5, 0.5]], np.float32), np.array([0.3], np.float32),
+                        np.array([1e15], np.float32), np.array([1e-2], np.float32),
+                        np.array([1e4], np.float32))
+        s.set_rays(np.array([[1.0, 0.0, 0.0]]))
+        s.set_spectrum(np.array([6e-18]), np.array([1e5]))
+        s.build_tree()
+        N, hits = s.compute_columns()
+        out.append((N.cpu().numpy(), hits))
+        s.close()
+    assert out[0][1] == out[1][1] >= 9000
+    np.testing.assert_allclose(out[0][0], out[1][0], rtol=1e-11)
