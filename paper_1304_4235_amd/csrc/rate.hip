@@ -20,6 +20,7 @@
 // printing them.
 #include "internal.h"
 #include "physics.h"
+#include "slab.h"
 
 namespace rrt {
 
