@@ -397,7 +397,7 @@ int rrt_iterate_halos(rrt_ctx* ctx, int32_t max_iter, double tol, int32_t per_la
  *   RRT_TUNE_PACKET_QUEUE 1 (default): the wave-cooperative walk runs as a
  *                         persistent grid of the blocks the device holds at
  *                         once, whose waves take packets (64 sources of one
- *                         direction, over every halo) from one global counter
+ *                         direction, over every halo) from a counter per XCD
  *                         until none is left; 0: one wave per packet, the
  *                         hardware scheduling them.  The same results either
  *                         way (measured on MI355X: the queue is 5% faster on

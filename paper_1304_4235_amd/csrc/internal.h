@@ -405,7 +405,7 @@ struct Ctx {
     // grows by half after a recording that ran short
     double pool_scale = 1.25;
     double conv_tol = 0.0;       // tolerance of the running fixed point (convergence counts)
-    bool ctx_bufs = false;       // tables, reductions and chunk counters are in the workspace
+    bool ctx_bufs = false;       // tables, reductions and log counters are in the workspace
 
     // geometry
     TraceGeom geom{};
@@ -429,8 +429,8 @@ struct Ctx {
     double t_trace = 0, t_rate = 0, t_build = 0, n_trace = 0;
     double t_record = 0, t_spmv = 0, n_spmv = 0;
     double t_tile = 0, n_tile = 0, t_tile_build = 0;
-    // inside path recording: one-walk chunk walks (and how many), the chunk
-    // compaction, and counting or recording walks
+    // inside path recording: one-walk logging walks (and how many), the pass over
+    // the log, and walks for sizes or after them
     double t_chunk_walk = 0, n_chunk_walk = 0, t_compact = 0, t_other_walk = 0;
     // timing: event pairs recorded around launches on the context's stream and
     // resolved later (no host wait per launch); acc receives the milliseconds

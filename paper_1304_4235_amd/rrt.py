@@ -295,7 +295,7 @@ class Solver:
         else:
             size = min(want, budget) if need <= budget else 0
         # smaller sizes when the device cannot hand out that much: the paths
-        # with the one-walk pool, then the paths alone (a batch: half as much)
+        # with the one-walk log, then the paths alone (a batch: half as much)
         smaller = [f for f in (one, need) if f < size] or ([size // 2] if self.n_halo > 1 else [])
         self.set_path_buffer(size, smaller)
 
