@@ -150,8 +150,9 @@ int rrt_workspace_info(const rrt_ctx* ctx, size_t* out6);
  * 4.1.1, eq. colden: which particles each ray intersects).  Host outputs,
  * each nullable: *n_hits, the intersections of every ray (each periodic
  * image separately); *bytes_paths, the least path buffer that recording the
- * paths needs (the paths, about 5.9 bytes per intersection, and a 32nd of the
- * walk's log, so that they are recorded in pieces); *bytes_one_walk, the size
+ * paths needs (the paths, about 5.9 bytes per intersection where rays have tens
+ * of them, a group of 22 for a ray's one to four where they have few, and a 32nd
+ * of the walk's log, so that they are recorded in pieces); *bytes_one_walk, the size
  * with which a later recording of a similar geometry takes one walk (the whole
  * log, 2 to 4 bytes per intersection, beside the paths).
  * The counts are kept, so the next column evaluation records with one walk.
