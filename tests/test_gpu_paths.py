@@ -153,3 +153,29 @@ def test_paths_over_many_images():
         s.close()
     assert out[0][1] == out[1][1] >= 9000
     np.testing.assert_allclose(out[0][0], out[1][0], rtol=1e-11)
+
+
+@pytest.mark.parametrize("l_ray,n_ray", [(9000.0, 6), (60000.0, 1)])
+def test_least_buffer_holds_a_lone_rays_many_visits(l_ray, n_ray):
+    """One ray to a packet and one pair to a visit, thousands of visits: a
+    segment ends by its slots, visits or hits as everywhere else, so the least
+    buffer that rrt_count_paths names holds the paths here too, to the columns
+    of the full buffer bit for bit."""
+    from paper_1304_4235_amd import Solver
+    axes = np.concatenate([np.eye(3), -np.eye(3)])       # a ray meets one line of images
+    out, need = [], None
+    for budget in (0, 1):
+        s = Solver(l_ray=l_ray, box=1.0, record_paths=1,
+                   path_budget=need["bytes_paths"] if budget else 0)
+        s.set_particles(np.array([[0.5, 0.5, 0.5]], np.float32), np.array([0.3], np.float32),
+                        np.array([1e15], np.float32), np.array([1e-2], np.float32),
+                        np.array([1e4], np.float32))
+        s.set_rays(axes[:n_ray])
+        s.set_spectrum(np.array([6e-18]), np.array([1e5]))
+        s.build_tree()
+        need = s.count_paths()
+        N, hits = s.compute_columns()
+        assert hits == need["hits"] == s.timing()["path_hits"]
+        out.append(N.cpu().numpy())
+        s.close()
+    np.testing.assert_array_equal(out[0], out[1])
