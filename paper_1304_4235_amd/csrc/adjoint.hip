@@ -171,14 +171,15 @@ k_adj_wbins(const double* __restrict__ N, const double* __restrict__ pis,
     const int lane = threadIdx.x & 63;
     const int wv = threadIdx.x >> 6;
     const int groups = (n_bins + 63) / 64;
-    const int g = (int)(blockIdx.x % groups);
-    const int64_t chunk = blockIdx.x / groups;
-    const int b = g * 64 + lane;
+    const uint64_t lt = lane ? (~0ull >> (64 - lane)) : 0ull;
+    const int64_t items = (n + kAdjChunk - 1) / kAdjChunk * groups;
+    for (int64_t it = blockIdx.x; it < items; it += gridDim.x) {
+    const int64_t chunk = it / groups;
+    const int b = (int)(it - chunk * groups) * 64 + lane;
     const float ds = b < n_bins ? dsig_l2[b] : 0.0f;
     const int64_t i = chunk * kAdjChunk + threadIdx.x;
     const bool in = i < n;
     const double li = in ? ell[i] : 0.0;
-    const uint64_t lt = lane ? (~0ull >> (64 - lane)) : 0ull;
     double acc = 0.0;
     // moments sum W N^j of the thin pairs this lane stages
     double mom[kTaylorTerms] = {};
@@ -225,6 +226,8 @@ k_adj_wbins(const double* __restrict__ N, const double* __restrict__ pis,
     if (wv == 0 && b < n_bins)
         part[chunk * n_bins + b] =
             ((s_acc[0][lane] + s_acc[1][lane]) + s_acc[2][lane]) + s_acc[3][lane];
+    __syncthreads();                                  // s_acc is written again
+    }
 }
 
 // The per-chunk partials of every bin summed into the accumulator in two
@@ -346,8 +349,7 @@ hipError_t launch_adj_rate(Ctx& c, const double* N, const double* lup)
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     const int64_t chunks = adj_chunks(c);
-    hipLaunchKernelGGL(k_adj_wbins, dim3((unsigned)(chunks * ((c.n_bins + 63) / 64))),
-                       dim3(kBlock), 0, c.stream, N, c.adj_pis, c.adj_ell, c.dsig_l2, c.n,
+    hipLaunchKernelGGL(k_adj_wbins, dim3(adj_wbins_blocks(c.n, c.n_bins)), dim3(kBlock), 0, c.stream, N, c.adj_pis, c.adj_ell, c.dsig_l2, c.n,
                        c.n_ray, c.n_bins, c.adj_wpart, c.tay_nmax);
     e = hipGetLastError();
     if (e != hipSuccess) return e;

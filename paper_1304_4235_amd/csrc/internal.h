@@ -588,9 +588,30 @@ inline int ray_ways(int64_t waves, int n_ray)
     while (w < 16 && 2 * w <= n_ray && waves * w < 4096) w *= 2;
     return w;
 }
+// Waves per packet of the columns' product, for packets of `segs` segments on
+// average: below 16384 waves, as many as the segments keep busy; beyond, so few
+// that each has several segments to run ahead over, and never so many that the
+// launch has 2^32 work-items.
+// Measured on MI355X (ms per product at 1, 2, 4, 8 waves): the 885k-particle
+// field's 663552 packets of 3.4 segments 4.05, 3.93, 5.02, -; the 262144-
+// particle halo's 49152 of 20: 2.03, -, 1.55, 1.72; 12 halos' 26236 of 9:
+// -, 0.255, -, 0.34.
+inline int path_ways(int64_t packets, double segs)
+{
+    int w = 1;
+    while (w < 8 && packets * 64 * (2 * w) < (int64_t(1) << 32) &&
+           (packets * w < 16384 ? segs > w : segs > (w == 1 ? 3 : 6) * w))
+        w *= 2;
+    return w;
+}
 // particles per partial of the reverse-mode weight gradient
 constexpr int64_t kAdjChunk = 256;
 constexpr int kAdjSlices = 64;           // second level of the weight-gradient sum
+// blocks of the weight gradient's partials, which loop over (chunk, 64 bins)
+inline unsigned adj_wbins_blocks(int64_t n, int n_bins)
+{
+    return stride_blocks((n + kAdjChunk - 1) / kAdjChunk * ((n_bins + 63) / 64), 1);
+}
 
 // ---- launchers (rate.hip) ----
 hipError_t launch_init_state(Ctx& c, bool use_given);

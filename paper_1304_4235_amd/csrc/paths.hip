@@ -602,15 +602,7 @@ template <bool NF, bool STREAM>
 void launch_columns_as(Ctx& c)
 {
     const int64_t pk = path_packets(c);
-    // Waves per packet.  Below 16384 waves, as many as its segments keep busy;
-    // beyond, so few that each has several segments to run ahead over.
-    // Measured on MI355X (ms per product at 1, 2, 4, 8 waves): the 885k-particle
-    // field's 663552 packets of 3.4 segments 4.05, 3.93, 5.02, -; the 262144-
-    // particle halo's 49152 of 20: 2.03, -, 1.55, 1.72; 12 halos' 26236 of 9:
-    // -, 0.255, -, 0.34.
-    const double segs = (double)c.path_segs / (double)std::max<int64_t>(pk, 1);
-    int W = 1;
-    while (W < 8 && (pk * W < 16384 ? segs > W : segs > (W == 1 ? 3 : 6) * W)) W *= 2;
+    const int W = path_ways(pk, (double)c.path_segs / (double)std::max<int64_t>(pk, 1));
     auto go = [&](auto kernel, int64_t blocks, int threads) {
         hipLaunchKernelGGL(kernel, dim3((unsigned)blocks), dim3(threads), 0, c.stream, c.unit_seg,
                            c.seg_off, c.packed, path_parts(c), c.mux_s, pk, c.N_s, (int)c.n,

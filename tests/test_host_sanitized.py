@@ -36,6 +36,18 @@ def test_arena_under_sanitizers(tmp_path):
     assert "arena checks passed" in _run(cmd, exe, tmp_path)
 
 
+@pytest.mark.skipif(shutil.which("g++") is None or not os.path.isdir("/opt/rocm/include"),
+                    reason="needs g++ and the ROCm headers")
+def test_launch_grids_under_sanitizers(tmp_path):
+    exe = str(tmp_path / "grid_check")
+    csrc = os.path.join(ROOT, "paper_1304_4235_amd", "csrc")
+    cmd = ["g++", "-std=c++17", *SAN, "-D__HIP_PLATFORM_AMD__", "-I/opt/rocm/include",
+           "-I" + os.path.join(ROOT, "include"), "-I" + csrc,
+           os.path.join(HOST, "grid_check.cpp"), "-L/opt/rocm/lib", "-lamdhip64",
+           "-Wl,-rpath,/opt/rocm/lib", "-o", exe]
+    assert "grid checks passed" in _run(cmd, exe, tmp_path)
+
+
 @pytest.mark.skipif(shutil.which("gcc") is None, reason="needs gcc")
 def test_oracle_under_sanitizers(tmp_path):
     exe = str(tmp_path / "oracle_check")
