@@ -504,7 +504,8 @@ hipError_t launch_morton(Ctx& c, const double lo[3], double scale, int bits);
 hipError_t radix_sort_pairs(Ctx& c, uint64_t* keys, int32_t* vals, int64_t n);
 hipError_t build_radix_tree(Ctx& c, float pad);
 hipError_t launch_gather(Ctx& c);
-hipError_t scan_exclusive_u64(Ctx& c, const uint64_t* in, uint64_t* out, int64_t m);
+hipError_t scan_exclusive_u64(Ctx& c, const uint64_t* in, uint64_t* out, int64_t m,
+                              int region = kRegionWs);
 
 // ---- launchers (trace.hip) ----
 void fill_kernel_tables(KernelTables* host);

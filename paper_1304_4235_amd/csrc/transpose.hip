@@ -191,11 +191,10 @@ k_gather_cols(const uint64_t* __restrict__ col_off, const uint64_t* __restrict__
 
 }  // namespace
 
-hipError_t scan_exclusive_u64(Ctx& c, const uint64_t* in, uint64_t* out, int64_t m);
-
 // Build the transposed paths into c.tpath / c.tcol_off, in the path buffer.
-// Scratch: two key and one value buffer of path_hits entries and the sort
-// histograms, also from the path buffer, released before returning.
+// Scratch: two key and one value buffer of path_hits entries, the sort
+// histograms and their partial sums, also from the path buffer, released before
+// returning.
 // hipErrorOutOfMemory (nothing kept) when they do not fit beside the paths.
 hipError_t build_transposed_paths(Ctx& c)
 {
@@ -232,7 +231,8 @@ hipError_t build_transposed_paths(Ctx& c)
         hipLaunchKernelGGL(count, dim3((unsigned)n_tiles), dim3(kBlock), 0, c.stream, kin, m, shift,
                            hist.p, n_tiles);
         hipError_t r = hipGetLastError();
-        if (r == hipSuccess) r = scan_exclusive_u64(c, hist.p, hist.p, (int64_t)hn);
+        if (r == hipSuccess)
+            r = scan_exclusive_u64(c, hist.p, hist.p, (int64_t)hn, kRegionPath);
         if (r != hipSuccess) return r;
         hipLaunchKernelGGL(scatter, dim3((unsigned)n_tiles), dim3(kBlock), 0, c.stream, kin, vin,
                            kout, vout, m, shift, hist.p, n_tiles);

@@ -233,11 +233,13 @@ hipError_t scan_rec(hipStream_t st, const T* in, T* out, int64_t m, char* tmp)
     return hipGetLastError();
 }
 
+// region: where the partial sums go (the workspace holds those of up to n_ray n
+// + 1 items; arrays sized by the intersections take theirs from the path buffer)
 template <typename T>
-hipError_t scan_exclusive(Ctx& c, const T* in, T* out, int64_t m)
+hipError_t scan_exclusive(Ctx& c, const T* in, T* out, int64_t m, int region = kRegionWs)
 {
     Scratch<char> tmp(c);
-    hipError_t e = tmp.get(scan_tmp_need<T>(m));
+    hipError_t e = tmp.get(scan_tmp_need<T>(m), region);
     if (e != hipSuccess) return e;
     return scan_rec<T>(c.stream, in, out, m, tmp.p);
 }
@@ -600,9 +602,9 @@ inline unsigned nblk(int64_t n, int b = kBlock) { return (unsigned)((n + b - 1) 
 
 }  // namespace
 
-hipError_t scan_exclusive_u64(Ctx& c, const uint64_t* in, uint64_t* out, int64_t m)
+hipError_t scan_exclusive_u64(Ctx& c, const uint64_t* in, uint64_t* out, int64_t m, int region)
 {
-    return scan_exclusive<uint64_t>(c, in, out, m);
+    return scan_exclusive<uint64_t>(c, in, out, m, region);
 }
 
 hipError_t launch_bounds(Ctx& c, float* part_out, int nb)

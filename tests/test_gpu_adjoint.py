@@ -494,3 +494,35 @@ def test_backward_needs_a_forward_with_the_current_parameters():
     dw, dn = s.backward(torch.ones_like(lnG), None)
     assert np.all(np.isfinite(dw))
     s.close()
+
+
+def test_transposed_paths_fit_an_exact_workspace():
+    """In a workspace of exactly rrt_workspace_size bytes the reverse mode of the
+    full halo (1.6e9 intersections) takes its transposed paths from the path
+    buffer alone: no request falls short, and the gradients repeat bit for bit
+    (the gather's order is fixed, the scatters' is not)."""
+    from paper_1304_4235_amd import Solver, lib
+    import ctypes as C
+
+    class Exact(Solver):
+        def _grow_ws(self, need):
+            if self._ws is not None and need <= self._ws.numel():
+                return
+            ws = torch.empty(need, dtype=torch.uint8, device=self.device)
+            self._check(lib().rrt_set_workspace(self._h, C.c_void_p(ws.data_ptr()), need),
+                        "rrt_set_workspace")
+            self._ws = ws
+
+    wl = W.make_config(1)
+    s = Exact.from_workload(wl, record_paths=1)
+    out = []
+    for _ in range(2):
+        lnG, x = s.forward(1)
+        dw, dn = s.backward(torch.ones_like(lnG), None)
+        out.append((dw, dn.cpu().numpy()))
+    info = s.workspace_info()
+    assert info["ws_size"] == s.workspace_size()
+    assert info["short_bytes"] == 0, info
+    np.testing.assert_array_equal(out[0][0], out[1][0])
+    np.testing.assert_array_equal(out[0][1], out[1][1])
+    s.close()
