@@ -301,12 +301,15 @@ int rrt_set_update_rule(rrt_ctx* ctx, double tau_skip, double tau_case_b, int32_
  * largest change of a sweep is below tol or max_iter sweeps, under the update
  * rule above.  x_out: device double[n] (nullable).  iters_done, max_dx_out:
  * host (nullable).  Returns RRT_NOT_CONVERGED if max_iter was reached without
- * convergence.  Synchronises once per sweep (64 bytes: the largest change,
+ * convergence.  Synchronises once per sweep (104 bytes: the largest change,
  * intersections, the convergence counts of rrt_get_convergence and the input
- * flags) for the convergence test; the first call of rrt_set_update_rule's
- * density order also copies n_H to the host once.  RRT_E_INPUT when a given
- * state or density was out of range, or an update left a neutral fraction
- * outside [0, 1]. */
+ * flags) for the convergence test, with tol = 0 (a fixed number of sweeps) once
+ * per 32; the first call of rrt_set_update_rule's density order also copies n_H
+ * to the host once.  RRT_E_INPUT when a given state or density was out of range,
+ * or an update left a neutral fraction outside [0, 1]: the columns, rates and
+ * state are then those of the first sweep that saw it, whatever tol is (with tol
+ * = 0 the report comes at the next look, up to 31 sweeps later, in which
+ * traversals end at once and recorded paths are read without effect). */
 int rrt_iterate_equilibrium(rrt_ctx* ctx, int32_t max_iter, double tol, double* x_out,
                             int32_t* iters_done, double* max_dx_out);
 

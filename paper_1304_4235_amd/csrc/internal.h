@@ -142,6 +142,9 @@ struct TraceGeom {
     // column evaluations only: rays of sources with want[p] == 0 are skipped
     // (their columns keep their previous values); null = every source
     const uint8_t* want;
+    // column evaluations only: set while a batch of sweeps runs; once it holds
+    // something, columns keep their values
+    const unsigned long long* stop;
     double L;              // segment length
     double box;            // periodic side, 0 = isolated
     double plo[3], phi[3]; // bounds of particle positions
@@ -201,7 +204,9 @@ enum {
     kRedPathMost = 12,      // log blocks of the largest unit
     kRedSlots = 13
 };
-// sweeps of a fixed number that run between the host's looks at their results
+// Sweeps of a fixed number that run between the host's looks at their results.
+// Those after one that raised an error write no column, rate or state (geom.stop),
+// so what the caller finds is that sweep's.
 constexpr int kSweepBatch = 32;
 
 struct Ctx {
@@ -390,6 +395,9 @@ struct Ctx {
     unsigned long long* red = nullptr;
     unsigned long long* queue = nullptr;     // [kQueues * kQueueStride]
     unsigned long long* sweep_red = nullptr; // [kSweepBatch] sweeps' slots
+    // set by a sweep that raised an error (a line of its own, which no sweep
+    // without an error writes)
+    unsigned long long* stop = nullptr;
     unsigned long long* red_host = nullptr;  // pinned
     unsigned long long* sweep_host = nullptr;    // behind it: sweep_red's copy
     // per sweep of the last rrt_iterate_equilibrium: max |dx| and the

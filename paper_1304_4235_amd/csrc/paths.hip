@@ -483,8 +483,8 @@ k_path_columns(const uint64_t* __restrict__ unit_seg, const uint64_t* __restrict
                const uint4* __restrict__ packed, int parts, const float* __restrict__ mux,
                int64_t n_packets, double* __restrict__ N,
                int n, const int32_t* __restrict__ seg_of, const int32_t* __restrict__ seg_active,
-               const uint8_t* __restrict__ want, double* __restrict__ Nn,
-               const double* __restrict__ mu)
+               const uint8_t* __restrict__ want, const unsigned long long* __restrict__ stop,
+               double* __restrict__ Nn, const double* __restrict__ mu)
 {
     constexpr int kW = W == 1 ? kWaves : W;
     constexpr int U = 4;                             // groups in flight per lane
@@ -503,6 +503,7 @@ k_path_columns(const uint64_t* __restrict__ unit_seg, const uint64_t* __restrict
     if (live && seg_active) live = seg_active[seg_of[ps]] != 0;
     if (live && want) live = want[ps] != 0;
     if (wave_ballot(live) == 0) return;              // the whole packet
+    const bool stopped = stop && *stop != 0ull;
     s_acc[wv][lane] = 0.0;
     if (NF) s_accn[wv][lane] = 0.0;
     uint64_t sg = unit_seg[pk * parts] + (W == 1 ? 0 : wv);
@@ -580,13 +581,13 @@ k_path_columns(const uint64_t* __restrict__ unit_seg, const uint64_t* __restrict
     const int64_t row = k * n + ps;
     if (W == 1) {
         wave_sync();
-        if (live) {
+        if (live && !stopped) {
             N[row] = s_acc[wv][lane];
             if (NF) Nn[row] = s_accn[wv][lane];
         }
     } else {
         __syncthreads();
-        if (wv == 0 && live) {
+        if (wv == 0 && live && !stopped) {
             double acc = 0.0, accn = 0.0;
             for (int q = 0; q < W; ++q) {
                 acc += s_acc[q][lane];
@@ -606,7 +607,8 @@ void launch_columns_as(Ctx& c)
     auto go = [&](auto kernel, int64_t blocks, int threads) {
         hipLaunchKernelGGL(kernel, dim3((unsigned)blocks), dim3(threads), 0, c.stream, c.unit_seg,
                            c.seg_off, c.packed, path_parts(c), c.mux_s, pk, c.N_s, (int)c.n,
-                           c.geom.seg_of, c.geom.seg_active, c.geom.want, c.Nn_s, c.mu_s);
+                           c.geom.seg_of, c.geom.seg_active, c.geom.want, c.geom.stop, c.Nn_s,
+                           c.mu_s);
     };
     if (W == 1) go(k_path_columns<NF, 1, STREAM>, (pk + kWaves - 1) / kWaves, kBlock);
     else if (W == 2) go(k_path_columns<NF, 2, STREAM>, pk, 128);
@@ -850,12 +852,14 @@ template <int G>
 __global__ void __launch_bounds__(kBlock)
 k_row_columns(const uint64_t* __restrict__ row_off, const int2* __restrict__ path,
               const float* __restrict__ mux, int64_t n_rows, double* __restrict__ N, int64_t n,
-              const uint8_t* __restrict__ frozen, const int32_t* __restrict__ list, int64_t list_n)
+              const uint8_t* __restrict__ frozen, const int32_t* __restrict__ list, int64_t list_n,
+              const unsigned long long* __restrict__ stop)
 {
     const int lane = threadIdx.x & (G - 1);
     const int64_t stride = (int64_t)gridDim.x * (blockDim.x / G);
     const long long* p = reinterpret_cast<const long long*>(path);
     const int64_t n_iter = list_n * (n_rows / n);
+    const bool stopped = stop && *stop != 0ull;
     for (int64_t v = (blockIdx.x * (int64_t)blockDim.x + threadIdx.x) / G; v < n_iter;
          v += stride) {
         const int64_t row = (v / list_n) * n + list[v % list_n];
@@ -879,7 +883,7 @@ k_row_columns(const uint64_t* __restrict__ row_off, const int2* __restrict__ pat
             acc += (double)(m3 * __int_as_float((int)(v3 >> 32)));
         }
         for (int off = G / 2; off > 0; off >>= 1) acc += __shfl_xor(acc, off, G);
-        if (lane == 0) N[row] = acc;
+        if (lane == 0 && !stopped) N[row] = acc;
     }
 }
 
@@ -907,7 +911,7 @@ hipError_t launch_row_columns(Ctx& c, int group)
     auto go = [&](auto kernel, int g) {
         hipLaunchKernelGGL(kernel, dim3(stride_blocks(n_iter, kBlock / g)), dim3(kBlock), 0,
                            c.stream, c.row_off, c.path, c.mux_s, n_rows, c.N_s, c.n, c.row_frozen,
-                           c.row_list, c.row_list_n);
+                           c.row_list, c.row_list_n, c.geom.stop);
     };
     if (group == 64) go(k_row_columns<64>, 64);
     else if (group == 32) go(k_row_columns<32>, 32);

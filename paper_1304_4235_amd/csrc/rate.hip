@@ -76,6 +76,7 @@ struct RateRule {
     // sum_j tay[j] N^j (the bins' Taylor moments), see k_gamma
     double tay[kTaylorTerms];
     double tay_nmax;
+    const unsigned long long* stop;    // holds something: nothing is written
 };
 
 enum { kSchemePlain = 0, kSchemeNearMono = 1, kSchemeNearPoly = 2 };
@@ -219,16 +220,21 @@ k_gamma(const double* __restrict__ N, int64_t n, int n_ray, int n_bins,
                 }
             }
     }
+    // (read here, its latency hides behind the logarithm and the exponential)
+    const unsigned long long stop = rule.stop ? *rule.stop : 0ull;
     if (live && way == 0 && lane % kLanes == 0) {
         const double l = !(s > 0.0) ? -INFINITY
                          : SCHEME != kSchemePlain ? m + log(s)
                                                   : ln_ws_max + m + log(s / (double)n_ray);
         double g = exp(l);
-        if (lnG) lnG[i] = l;
-        if (G) G[i] = g;
-        if (tau) tau[i] = (float)(ln_gthin - l);
+        const bool go = stop == 0ull;
+        if (lnG && go) lnG[i] = l;
+        if (G && go) G[i] = g;
+        if (tau && go) tau[i] = (float)(ln_gthin - l);
         const double te = ln_gthin - l;              // tau_eff in FP64 decides
-        if (update_x && rule.skip && te < rule.tau_skip) {
+        if (!go) {
+            // an earlier sweep of the batch raised an error: nothing changes
+        } else if (update_x && rule.skip && te < rule.tau_skip) {
             rule.skip[i] = 1;                         // keeps its state for good
         } else if (update_x) {
             const double al = te >= rule.tau_case_b ? rule.alphaB[i] : alpha[i];
@@ -523,6 +529,7 @@ hipError_t launch_gamma(Ctx& c, bool update_x, bool first_sweep)
     // a density block's list leaves out what the mask would, but the frozen ones
     rule.want = c.row_list ? nullptr : c.geom.want;
     rule.frozen = c.row_list ? c.row_frozen : nullptr;
+    rule.stop = c.geom.stop;
     rule.skip = (first_sweep && c.rule_tau_skip > 0.0) ? c.skip_s : nullptr;
     rule.tau_skip = c.rule_tau_skip;
     rule.tau_case_b = c.rule_tau_case_b;
@@ -579,14 +586,17 @@ hipError_t launch_gamma(Ctx& c, bool update_x, bool first_sweep)
 
 namespace {
 
-// a copy of a sweep's slots, its reductions cleared
+// a copy of a sweep's slots, its reductions cleared; an error stops the sweeps
+// that follow
 __global__ void k_keep_sweep(unsigned long long* __restrict__ red,
-                             unsigned long long* __restrict__ out)
+                             unsigned long long* __restrict__ out,
+                             unsigned long long* __restrict__ stop)
 {
     const int t = threadIdx.x;
     if (t >= kRedSlots) return;
     out[t] = red[t];
     if (t < kRedInput) red[t] = 0ull;
+    else if (t <= kRedNumeric && out[t]) *stop = 1ull;
 }
 
 // particles of block `block` of the density order that are not frozen
@@ -643,7 +653,7 @@ hipError_t launch_want(Ctx& c, int block)
 hipError_t launch_keep_sweep(Ctx& c, int sweep)
 {
     hipLaunchKernelGGL(k_keep_sweep, dim3(1), dim3(64), 0, c.stream, c.red,
-                       c.sweep_red + (size_t)sweep * kRedSlots);
+                       c.sweep_red + (size_t)sweep * kRedSlots, c.stop);
     return hipGetLastError();
 }
 

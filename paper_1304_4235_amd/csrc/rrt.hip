@@ -177,10 +177,12 @@ int alloc_ctx_buffers(Ctx& c)
     HIP_OK(ws_alloc(c, &c.log_ctr, 2));
     HIP_OK(ws_alloc(c, &c.queue, (size_t)kQueues * kQueueStride));
     HIP_OK(ws_alloc(c, &c.sweep_red, (size_t)kSweepBatch * kRedSlots));
+    HIP_OK(ws_alloc(c, &c.stop, 1));
     KernelTables host;
     fill_kernel_tables(&host);
     HIP_OK(hipMemcpyAsync(c.tables, &host, sizeof host, hipMemcpyHostToDevice, c.stream));
     HIP_OK(hipMemsetAsync(c.red, 0, kRedSlots * sizeof(unsigned long long), c.stream));
+    HIP_OK(hipMemsetAsync(c.stop, 0, sizeof *c.stop, c.stream));
     HIP_OK(hipStreamSynchronize(c.stream));        // `host` goes out of scope
     c.ctx_bufs = true;
     return RRT_OK;
@@ -1236,6 +1238,7 @@ int rrt_build_tree(rrt_ctx* x)
     g.seg_end = segmented ? c.seg_end : nullptr;
     g.seg_active = nullptr;
     g.want = nullptr;
+    g.stop = nullptr;
     c.blocks_for = 0;            // the density blocks are in tree order
     HIP_OK(launch_init_state(c, c.x_init_given));
     ev_end(c, eb, &c.t_build);
@@ -1344,13 +1347,17 @@ int ensure_blocks(Ctx& c)
     return RRT_OK;
 }
 
-// the per-step particle mask lives only inside one sweep of the driver
+// the per-step particle mask and the stop of a batch live only inside one call of
+// the driver (an early return may leave the stop set)
 struct WantGuard {
     Ctx& c;
+    bool done = false;
     explicit WantGuard(Ctx& cc) : c(cc) {}
     ~WantGuard()
     {
+        if (!done) (void)hipMemsetAsync(c.stop, 0, sizeof *c.stop, c.stream);
         c.geom.want = nullptr;
+        c.geom.stop = nullptr;
         c.row_list = nullptr;
         c.row_list_n = 0;
         c.row_frozen = nullptr;
@@ -1443,9 +1450,11 @@ int rrt_iterate_equilibrium(rrt_ctx* x, int32_t max_iter, double tol, double* x_
     // tolerance the host needs them to go on; a fixed number of sweeps (tol = 0)
     // runs kSweepBatch at a time, and the device does not wait for the host's
     // turn after each (measured on MI355X: 20 sweeps of 16384 particles 3014 us
-    // in all with a look at each, 2869 here; 8 of 4096 1136 and 1087).
+    // in all with a look at each, 2869 here; 8 of 4096 1136 and 1087).  After a
+    // sweep with an error the rest of its batch changes nothing.
     HIP_OK(hipMemsetAsync(c.red, 0, kRedInput * sizeof(unsigned long long), c.stream));
     const int batch = tol > 0.0 ? 1 : kSweepBatch;
+    c.geom.stop = batch > 1 ? c.stop : nullptr;
     int64_t hits_of[kSweepBatch];
     int launched = 0;                         // sweeps whose slots are still to be read
     for (it = 0; it < max_iter;) {
@@ -1498,6 +1507,7 @@ int rrt_iterate_equilibrium(rrt_ctx* x, int32_t max_iter, double tol, double* x_
         launched = 0;
         if (mdx < tol) break;
     }
+    guard.done = true;
     c.have_columns = c.have_gamma = false;
     if (x_out) HIP_OK(launch_to_input_order_d(c, c.x_s, x_out, 1));
     if (iters_done) *iters_done = it;

@@ -216,9 +216,10 @@ k_tile_columns(const uint64_t* __restrict__ row_off, const uint16_t* __restrict_
                const uint32_t* __restrict__ set, const float* __restrict__ mux, int64_t n_rows,
                int tile_rows, int64_t n_tiles, double* __restrict__ N, int64_t n,
                const int32_t* __restrict__ seg_of, const int32_t* __restrict__ seg_active,
-               const uint8_t* __restrict__ want)
+               const uint8_t* __restrict__ want, const unsigned long long* __restrict__ stop)
 {
     extern __shared__ float smux[];
+    const bool stopped = stop && *stop != 0ull;
     const int lane = threadIdx.x & (G - 1);
     const int groups = blockDim.x / G;
     const v4u16* iq = reinterpret_cast<const v4u16*>(idx);
@@ -258,7 +259,7 @@ k_tile_columns(const uint64_t* __restrict__ row_off, const uint16_t* __restrict_
                 }
             }
             for (int off = G / 2; off > 0; off >>= 1) acc += __shfl_xor(acc, off, G);
-            if (lane == 0) N[row] = acc;
+            if (lane == 0 && !stopped) N[row] = acc;
         }
         __syncthreads();
     }
@@ -270,7 +271,7 @@ hipError_t launch_tiles_g(Ctx& c, int64_t n_rows, unsigned nb, size_t lds)
     hipLaunchKernelGGL(k_tile_columns<G>, dim3(nb), dim3(512), lds, c.stream, c.row_off,
                        c.tile_idx, c.tile_fac, c.tile_off, c.tile_set, c.mux_s, n_rows,
                        c.tile_rows, c.n_tiles, c.N_s, c.n, c.geom.seg_of, c.geom.seg_active,
-                       c.geom.want);
+                       c.geom.want, c.geom.stop);
     return hipGetLastError();
 }
 

@@ -139,6 +139,7 @@ k_trace(const Node* __restrict__ nodes, const float4* __restrict__ p4,
         const KernelTables* __restrict__ tabs, TraceGeom g, RayOut out)
 {
     __shared__ float4 t_erf[kTabIntervals];
+    if (MODE == kModeColumn && g.stop && *g.stop != 0ull) return;    // the whole grid
     constexpr bool kTerms = MODE != kModeCount;
     if (kTerms) {
         for (int i = threadIdx.x; i < kTabIntervals; i += blockDim.x) t_erf[i] = tabs->erf_t[i];
@@ -386,6 +387,7 @@ k_trace_wave(const Node* __restrict__ nodes, const float4* __restrict__ leaf_bal
     constexpr bool kCountOnly = MODE == kModeCount || MODE == kModeStats;
     constexpr bool kTerms = mode_factors(MODE);
     extern __shared__ __align__(16) unsigned char s_dyn[];
+    if (MODE == kModeColumn && g.stop && *g.stop != 0ull) return;    // the whole grid
     const int lane = threadIdx.x & 63;
     const int wv = threadIdx.x >> 6;
     const int n_wv = blockDim.x >> 6;

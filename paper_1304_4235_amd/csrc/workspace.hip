@@ -127,6 +127,7 @@ uint64_t workspace_bytes(int64_t n, int n_ray, int n_bins, int n_halo, int K, bo
     add(2 * sizeof(unsigned long long));
     add((uint64_t)kQueues * kQueueStride * sizeof(unsigned long long));
     add((uint64_t)kSweepBatch * kRedSlots * sizeof(unsigned long long));
+    add(sizeof(unsigned long long));
     // rays, spectrum and its attenuation table
     add(3 * rays * sizeof(double));
     for (int q = 0; q < 3; ++q) add(bins * sizeof(float));

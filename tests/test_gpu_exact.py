@@ -341,3 +341,45 @@ def test_convergence_counts_per_sweep():
     assert r["converged"] and cv["n_abs"][0] == wl.n
     full = _solver(wl).iterate(20, tol)
     assert full["iters"] == sweeps
+
+
+@pytest.mark.parametrize("mode", ["paths", "near_far", "traverse", "lanes", "tiles", "blocks",
+                                  "frozen", "blocks_traverse"])
+def test_a_failing_sweep_is_the_last_that_changes_anything(mode):
+    """A state out of range fails the first sweep: what rrt_get_state and the
+    columns hold after the error is that sweep's, whether one sweep was asked
+    for or forty (tol = 0 looks at several sweeps at once), and the solver goes
+    on as a new one once the state is set again."""
+    from paper_1304_4235_amd import RRTError
+    wl = W.isothermal_halo(n=3000, seed=15, n_bins=4, n_peak=3.0)
+    x = np.full(wl.n, 0.01)
+    x[123] = 2.0
+    out = []
+    for sweeps in (1, 40):
+        s = _solver(wl, record_paths=0 if "traverse" in mode or mode == "lanes" else 1,
+                    traversal=1 if mode == "lanes" else 0, build=False)
+        s.set_scheme(1 if mode == "near_far" else 0)
+        s.build_tree()
+        if "blocks" in mode:
+            s.set_update_rule(n_blocks=5)
+        if mode == "frozen":
+            s.set_update_rule(tau_skip=0.05)
+        if mode == "tiles":
+            s.set_tuning(tiles=1)
+            for _ in range(10):
+                s.compute_columns(want_N=False, count=False)
+            assert s.timing()["tile_set_total"] > 0
+        s.set_state(torch.tensor(x))
+        with pytest.raises(RRTError, match="RRT_E_INPUT"):
+            s.iterate(sweeps, 0.0)
+        st = {k: v.cpu().numpy() for k, v in s.get_state().items()}
+        lnG, G, _ = s.compute_gamma()                  # from the columns the sweep left
+        near = s.near_columns().cpu().numpy() if mode == "near_far" else np.zeros(1)
+        s.set_state(None)
+        again = s.iterate(3, 0.0)
+        assert again["iters"] == 3 and s.convergence()["max_dx"].size == 3
+        out.append((st["x"], st["lnG"], st["G"], st["tau"], lnG.cpu().numpy(), near,
+                    again["x"].cpu().numpy()))
+        s.close()
+    for a, b in zip(*out):
+        np.testing.assert_array_equal(a, b)
