@@ -9,7 +9,6 @@
 #include <cstdio>
 #include <cstring>
 #include <new>
-#include <utility>
 #include <vector>
 
 using namespace rrt;
@@ -32,8 +31,6 @@ void rrt::drop_graph(Ctx& c)
     c.graph_exec = nullptr;
     c.graph = nullptr;
     c.graph_iters = 0;
-    c.graph_ways = 0;
-    for (const void*& p : c.graph_paths) p = nullptr;
 }
 
 namespace {
@@ -314,7 +311,6 @@ void free_paths(Ctx& c)
     ws_free(c, &c.packed);
     ws_free(c, &c.seg_off);
     ws_free(c, &c.unit_seg);
-    c.hold_segs = c.hold_words = 0;
     c.path_segs = c.path_words = 0;
     ws_free(c, &c.path);
     c.rows_valid = false;
@@ -354,25 +350,6 @@ uint64_t record_bytes(const Ctx& c, uint64_t words, uint64_t blocks)
            region_bytes((words + kPackedPad) * 16);
 }
 
-// The arrays the recorded paths stay in: those held for groups of halos where
-// they are large enough, else new ones.
-hipError_t alloc_unit_seg(Ctx& c)
-{
-    if (c.hold_words) return hipSuccess;
-    return ws_alloc(c, &c.unit_seg, (size_t)(path_packets(c) * path_parts(c)) + 1, kRegionPath);
-}
-hipError_t alloc_paths(Ctx& c, uint64_t segs, uint64_t words)
-{
-    if (c.hold_words) {
-        if (segs <= c.hold_segs && words <= c.hold_words) return hipSuccess;
-        c.hold_segs = c.hold_words = 0;
-    }
-    hipError_t e = ws_alloc(c, &c.seg_off, (size_t)std::max<uint64_t>(segs, 1), kRegionPath);
-    if (e == hipSuccess)
-        e = ws_alloc(c, &c.packed, (size_t)words + kPackedPad, kRegionPath);
-    return e;
-}
-
 // Path buffer for a recording in pieces, the least that holds the paths: a log
 // of a 32nd of the whole, and of the largest unit at least.
 uint64_t piece_blocks(const Ctx& c)
@@ -388,16 +365,15 @@ bool alloc_log(Ctx& c, uint64_t words, uint64_t blocks)
     free_log(c);
     if (blocks > 0xfffffff0ull) return false;          // block numbers are 32-bit
     const size_t units = (size_t)(path_packets(c) * path_parts(c));
-    hipError_t e = alloc_unit_seg(c);
+    hipError_t e = ws_alloc(c, &c.unit_seg, units + 1, kRegionPath);
     if (e == hipSuccess) e = ws_alloc(c, &c.unit_off, units + 1, kRegionPath);
     if (e == hipSuccess) e = ws_alloc(c, &c.unit_log, units, kRegionPath);
     if (e == hipSuccess) e = ws_alloc(c, &c.path_log, (size_t)blocks * kLogBlock, kRegionPath);
-    if (e == hipSuccess && words > c.hold_words &&
-        ws_largest_gap(c, kRegionPath) < region_bytes(words * 16))
+    if (e == hipSuccess && ws_largest_gap(c, kRegionPath) < region_bytes(words * 16))
         e = hipErrorOutOfMemory;
     if (e != hipSuccess) {
         free_log(c);
-        if (!c.hold_words) ws_free(c, &c.unit_seg);
+        ws_free(c, &c.unit_seg);
         return false;
     }
     c.log_blocks = blocks;
@@ -447,9 +423,11 @@ int build_paths(Ctx& c, bool* fit)
 {
     const int64_t units = path_packets(c) * path_parts(c);
     const size_t segs = (size_t)std::max<uint64_t>(c.path_segs, 1);
-    hipError_t e = alloc_paths(c, segs, c.last_words);
+    hipError_t e = ws_alloc(c, &c.seg_off, segs, kRegionPath);
     if (e == hipSuccess) e = ws_alloc(c, &c.seg_src, segs, kRegionPath);
     if (e == hipSuccess) e = ws_alloc(c, &c.seg_unit, segs, kRegionPath);
+    if (e == hipSuccess)
+        e = ws_alloc(c, &c.packed, (size_t)c.last_words + kPackedPad, kRegionPath);
     *fit = e == hipSuccess;
     if (!*fit) return RRT_OK;
     HIP_OK(launch_unit_words(c));
@@ -484,21 +462,21 @@ int record_pieces(Ctx& c, bool* fit)
 {
     *fit = false;
     free_log(c);
-    if (!c.hold_words) {
-        ws_free(c, &c.unit_seg);
-        ws_free(c, &c.seg_off);
-        ws_free(c, &c.packed);
-    }
+    ws_free(c, &c.unit_seg);
+    ws_free(c, &c.seg_off);
+    ws_free(c, &c.packed);
     const int64_t units = path_packets(c) * path_parts(c);
-    hipError_t e = alloc_unit_seg(c);
+    hipError_t e = ws_alloc(c, &c.unit_seg, (size_t)units + 1, kRegionPath);
     if (e == hipSuccess) e = ws_alloc(c, &c.unit_off, (size_t)units + 1, kRegionPath);
     if (e == hipSuccess) e = ws_alloc(c, &c.unit_log, (size_t)units, kRegionPath);
     if (e != hipSuccess) return RRT_OK;
     if (int r = path_walk(c, false, c.unit_off, nullptr)) return r;
     const size_t segs = (size_t)std::max<uint64_t>(c.path_segs, 1);
-    e = alloc_paths(c, segs, c.last_words);
+    e = ws_alloc(c, &c.seg_off, segs, kRegionPath);
     if (e == hipSuccess) e = ws_alloc(c, &c.seg_src, segs, kRegionPath);
     if (e == hipSuccess) e = ws_alloc(c, &c.seg_unit, segs, kRegionPath);
+    if (e == hipSuccess)
+        e = ws_alloc(c, &c.packed, (size_t)c.last_words + kPackedPad, kRegionPath);
     const uint64_t room = ws_largest_gap(c, kRegionPath) / (kLogBlock * sizeof(uint64_t));
     const uint64_t blocks = std::min<uint64_t>(std::min<uint64_t>(room, c.last_blocks + 1),
                                                0xfffffff0ull);
@@ -1794,15 +1772,8 @@ int run_active_halos(Ctx& c, double tol, int32_t max_iter, int32_t per_launch)
                           hipMemcpyDeviceToHost, c.stream));
     HIP_OK(hipStreamSynchronize(c.stream));
     if (c.seg_state_host[1] <= 0) return RRT_OK;
-    // (a graph stays valid over other paths in the same arrays with the same variant
-    // of the product: groups of halos)
-    const void* paths[3] = {c.paths_valid ? c.unit_seg : nullptr,
-                            c.paths_valid ? c.seg_off : nullptr,
-                            c.paths_valid ? c.packed : nullptr};
-    const int ways = c.paths_valid ? path_variant(c) : 0;
     if (!c.graph_exec || c.graph_iters != per_launch || c.graph_tol != tol ||
-        c.graph_max_iter != max_iter || c.graph_ways != ways ||
-        !std::equal(paths, paths + 3, c.graph_paths)) {
+        c.graph_max_iter != max_iter) {
         drop_graph(c);
         // the replays should use the row tiles when the solve is long enough to
         // pay for them; nothing may be allocated during the capture
@@ -1836,8 +1807,6 @@ int run_active_halos(Ctx& c, double tol, int32_t max_iter, int32_t per_launch)
         c.graph_iters = per_launch;
         c.graph_tol = tol;
         c.graph_max_iter = max_iter;
-        c.graph_ways = ways;
-        std::copy(paths, paths + 3, c.graph_paths);
     }
     HIP_OK(hipEventRecord(c.ev_a, c.stream));
     HIP_OK(hipStreamWaitEvent(c.gstream, c.ev_a, 0));
@@ -1852,128 +1821,91 @@ int run_active_halos(Ctx& c, double tol, int32_t max_iter, int32_t per_launch)
     return RRT_OK;
 }
 
-// Which halos can share recorded paths: the sizes of every 64 sources' paths from
-// one walk, and halos packed first-fit by decreasing size into groups whose paths
-// and log fit the path buffer.  A group's size counts the packets of its halos
-// once, also those that two halos (or halos of another group) share.  A halo whose
-// paths fit alone, but not their log, is a group of its own, recorded in pieces;
-// one whose paths do not fit traverses every iteration.
-// Groups by the paths alone, all recorded in pieces, are fewer but slower: twelve
-// halos of 379M intersections with 3.6 bytes of buffer for each took 59.4 ms in two
-// such groups and 40.1 in three with their logs, with 7.2 bytes 39.5 in one and
-// 35.6 in two.
-struct HaloGroup {
-    std::vector<int> halos;
-    bool recorded = false;
-    uint64_t words = 0, blocks = 0;
-    std::vector<int64_t> shared;          // packets counted that may reach into other halos
-};
-
-int plan_groups(Ctx& c, std::vector<HaloGroup>& groups)
+// Which halos can share recorded paths: per-halo sizes from one walk, packed
+// first-fit by decreasing size into groups whose paths (and their log) fit the
+// path buffer.  A halo too large for it alone forms a group that traverses
+// every iteration.
+int plan_groups(Ctx& c, std::vector<std::vector<int>>& groups, std::vector<bool>& recordable,
+                uint64_t& max_words, uint64_t& max_blocks)
 {
     const int nh = c.n_halo;
-    const int64_t units = path_packets(c) * path_parts(c), wpd = (c.n + 63) / 64;
-    std::vector<unsigned long long> size(2 * (size_t)wpd);
+    const int64_t units = path_packets(c) * path_parts(c);
+    std::vector<unsigned long long> size(2 * (size_t)nh);
     {
         Scratch<uint64_t> tally(c);
         Scratch<unsigned long long> d_size(c);
         HIP_OK(tally.get((size_t)units));
-        HIP_OK(d_size.get(2 * (size_t)wpd));
+        HIP_OK(d_size.get(2 * (size_t)nh));
+        HIP_OK(hipMemsetAsync(d_size.p, 0, sizeof(unsigned long long) * 2 * nh, c.stream));
         if (int r = path_walk(c, false, tally.p, nullptr)) return r;
-        HIP_OK(launch_packet_sizes(c, tally.p, d_size.p));
-        HIP_OK(hipMemcpyAsync(size.data(), d_size.p, sizeof(unsigned long long) * 2 * wpd,
+        HIP_OK(launch_halo_sizes(c, tally.p, d_size.p));
+        HIP_OK(hipMemcpyAsync(size.data(), d_size.p, sizeof(unsigned long long) * 2 * nh,
                               hipMemcpyDeviceToHost, c.stream));
         HIP_OK(hipStreamSynchronize(c.stream));
     }
-    std::vector<uint64_t> words(wpd + 1, 0), blocks(wpd + 1, 0);     // before each packet
-    for (int64_t b = 0; b < wpd; ++b) {
-        words[b + 1] = words[b] + size[2 * b];
-        blocks[b + 1] = blocks[b] + size[2 * b + 1];
-    }
-    // what halo h adds to group g: its packets (consecutive in tree order), those at
-    // its ends only if the group has not counted them yet
-    auto add = [&](const HaloGroup& g, int h) {
-        const int64_t b0 = c.halo_off_host[h] / 64, b1 = (c.halo_off_host[h + 1] - 1) / 64;
-        HaloGroup a;
-        auto take = [&](int64_t from, int64_t to) {
-            a.words += words[to] - words[from];
-            a.blocks += blocks[to] - blocks[from];
-        };
-        auto end = [&](int64_t b) {
-            if (std::find(g.shared.begin(), g.shared.end(), b) != g.shared.end()) return;
-            a.shared.push_back(b);
-            take(b, b + 1);
-        };
-        end(b0);
-        if (b1 > b0) end(b1);
-        if (b1 > b0 + 1) take(b0 + 1, b1);
-        return a;
-    };
-    const uint64_t room = c.images_fit ? ws_largest_gap(c, kRegionPath) : 0;
     // a buffer that the waves' unused blocks would fill: they take one at a time
     c.log_tight = false;
-    c.log_tight = log_pool(c, 0, 1.0, false) * kLogBlock * 8 > room / 16;
-    auto bytes = [&](uint64_t w, uint64_t b) {
-        return record_bytes(c, w, log_pool(c, b, 1.0, false)) + 4 * kWsAlign;
+    c.log_tight = log_pool(c, 0, 1.0, false) * kLogBlock * 8 > c.arena.cap[kRegionPath] / 16;
+    // bytes of each halo's paths and log, and the room beside the fixed arrays
+    auto bytes = [&](int h) {
+        return size[2 * h] * 16 + (size[2 * h] / 32 + 1) * kSegmentBytes +
+               size[2 * h + 1] * kLogBlock * 8;
     };
-    auto bytes_pieces = [&](uint64_t w, uint64_t b) {
-        return record_bytes(c, w, std::max<uint64_t>(c.last_most, b / 32) + 1) + 4 * kWsAlign;
-    };
-    std::vector<uint64_t> alone(nh);
-    for (int h = 0; h < nh; ++h) alone[h] = add(HaloGroup(), h).words;
+    const uint64_t fixed = record_bytes(c, 0, log_pool(c, 0, 1.0, false)) + 4 * kWsAlign;
+    const uint64_t room = c.arena.cap[kRegionPath];
+    const uint64_t cap = room > fixed && c.images_fit ? room - fixed : 0;
     std::vector<int> order(nh);
     for (int h = 0; h < nh; ++h) order[h] = h;
     std::stable_sort(order.begin(), order.end(),
-                     [&](int a, int b) { return alone[a] > alone[b]; });
+                     [&](int a, int b) { return bytes(a) > bytes(b); });
+    std::vector<uint64_t> load, words, blocks;
     groups.clear();
-    HaloGroup trav;                       // they need no memory: all at once
+    recordable.clear();
+    max_words = max_blocks = 0;
     for (int h : order) {
-        size_t at = 0;
-        HaloGroup a;
-        for (;; ++at) {
-            const HaloGroup none, &g = at < groups.size() ? groups[at] : none;
-            a = add(g, h);
-            if (bytes(g.words + a.words, g.blocks + a.blocks) <= room || at >= groups.size())
-                break;
+        if (c.prm.record_paths == 0 || bytes(h) > cap) {
+            groups.push_back({h});
+            recordable.push_back(false);
+            load.push_back(0);
+            words.push_back(0);
+            blocks.push_back(0);
+            continue;
         }
-        if (at == groups.size()) {
-            if (bytes(a.words, a.blocks) > room && bytes_pieces(a.words, a.blocks) > room) {
-                trav.halos.push_back(h);
-                continue;
-            }
-            groups.emplace_back();
-            groups.back().recorded = true;
+        size_t g = 0;
+        for (; g < groups.size(); ++g)
+            if (recordable[g] && load[g] + bytes(h) <= cap) break;
+        if (g == groups.size()) {
+            groups.push_back({});
+            recordable.push_back(true);
+            load.push_back(0);
+            words.push_back(0);
+            blocks.push_back(0);
         }
-        HaloGroup& g = groups[at];
-        g.halos.push_back(h);
-        g.words += a.words;
-        g.blocks += a.blocks;
-        g.shared.insert(g.shared.end(), a.shared.begin(), a.shared.end());
+        groups[g].push_back(h);
+        load[g] += bytes(h);
+        words[g] += size[2 * h];
+        blocks[g] += size[2 * h + 1];
+        max_words = std::max<uint64_t>(max_words, words[g]);
+        max_blocks = std::max<uint64_t>(max_blocks, blocks[g]);
     }
-    if (!trav.halos.empty()) groups.push_back(std::move(trav));
-    return RRT_OK;
-}
-
-// Record the rays of the active halos, whose paths and log take at most the
-// group's: the whole log where it fits, else in pieces.
-int record_group(Ctx& c, const HaloGroup& g, bool* fit)
-{
-    free_tpaths(c);
-    free_tiles(c);
-    free_log(c);
-    ws_free(c, &c.path);
-    c.rows_valid = c.rows_unfit = false;
-    c.path_evals = 0;
-    c.paths_valid = c.paths_unfit = *fit = false;
-    if (!g.recorded) return RRT_OK;
-    if (alloc_log(c, g.words, log_pool(c, g.blocks, 1.0, false))) {
-        bool overflow = false;
-        if (int r = path_walk(c, true, nullptr, &overflow)) return r;
-        if (!overflow)
-            if (int r = build_paths(c, fit)) return r;
+    // traversing halos need no memory: run them together as one group
+    std::vector<std::vector<int>> gs;
+    std::vector<bool> rs;
+    std::vector<int> trav;
+    for (size_t g = 0; g < groups.size(); ++g) {
+        if (recordable[g]) {
+            gs.push_back(groups[g]);
+            rs.push_back(true);
+        } else {
+            trav.insert(trav.end(), groups[g].begin(), groups[g].end());
+        }
     }
-    if (!*fit)
-        if (int r = record_pieces(c, fit)) return r;
+    if (!trav.empty()) {
+        gs.push_back(trav);
+        rs.push_back(false);
+    }
+    groups.swap(gs);
+    recordable.swap(rs);
     return RRT_OK;
 }
 
@@ -1983,59 +1915,50 @@ int run_groups(Ctx& c, double tol, int32_t max_iter, int32_t per_launch)
 {
     Scratch<int32_t> d_mask(c);
     HIP_OK(d_mask.get((size_t)c.n_halo));
-    std::vector<HaloGroup> groups;
-    if (int r = plan_groups(c, groups)) return r;
-    if (groups.size() == 1 && groups[0].recorded) {
+    std::vector<std::vector<int>> groups;
+    std::vector<bool> recordable;
+    uint64_t max_words = 0, max_blocks = 0;
+    if (int r = plan_groups(c, groups, recordable, max_words, max_blocks)) return r;
+    const uint64_t batch_total = c.last_total, batch_words = c.last_words,
+                   batch_blocks = c.last_blocks;
+    if (groups.size() == 1 && recordable[0]) {
         // all paths fit: the sizes are known, so the first iteration records
         // them with one walk
         c.counts_valid = true;
         return run_active_halos(c, tol, max_iter, per_launch);
     }
-    const uint64_t batch_total = c.last_total, batch_words = c.last_words,
-                   batch_blocks = c.last_blocks, batch_most = c.last_most;
-    // where every group's log fits beside the paths of the largest, its arrays for
-    // all of them: the captured graph stays valid where the product's variant does
-    free_paths(c);
-    uint64_t words = 0, blocks = 0;
-    for (const HaloGroup& g : groups) {
-        words = std::max(words, g.words);
-        blocks = std::max(blocks, g.blocks);
-    }
-    const uint64_t segs = (uint64_t)(path_packets(c) * path_parts(c)) + words / 32;
-    if (words > 0 &&
-        record_bytes(c, words, log_pool(c, blocks, 1.0, false)) + 4 * kWsAlign <=
-            ws_largest_gap(c, kRegionPath) &&
-        alloc_unit_seg(c) == hipSuccess && alloc_paths(c, segs, words) == hipSuccess) {
-        c.hold_segs = segs;
-        c.hold_words = words;
-    }
     std::vector<int32_t> mask(c.n_halo);
     int r = RRT_OK;
     for (size_t g = 0; g < groups.size() && r == RRT_OK; ++g) {
         std::fill(mask.begin(), mask.end(), 0);
-        for (int h : groups[g].halos) mask[h] = 1;
+        for (int h : groups[g]) mask[h] = 1;
         HIP_OK(hipMemcpyAsync(d_mask.p, mask.data(), sizeof(int32_t) * c.n_halo,
                               hipMemcpyHostToDevice, c.stream));
         HIP_OK(launch_seg_group_init(c, d_mask.p));
         HIP_OK(hipStreamSynchronize(c.stream));          // mask is read
         // record only this group's rays: they are the active ones
-        bool ok = false;
-        if ((r = record_group(c, groups[g], &ok)) != RRT_OK) break;
+        free_paths(c);
+        bool ok = recordable[g] && alloc_log(c, 0, log_pool(c, max_blocks, 1.0, false));
+        if (ok) {
+            bool overflow = false;
+            if ((r = path_walk(c, true, nullptr, &overflow)) != RRT_OK) break;
+            ok = !overflow;
+        }
+        if (ok && (r = build_paths(c, &ok)) != RRT_OK) break;
         if (ok) {
             c.paths_valid = true;
             c.path_hits = (int64_t)c.last_total;
         } else {
+            free_paths(c);
             c.paths_unfit = true;
         }
         r = run_active_halos(c, tol, max_iter, per_launch);
     }
     free_paths(c);
     c.counts_valid = false;
-    c.log_tight = false;
     c.last_total = batch_total;
     c.last_words = batch_words;
     c.last_blocks = batch_blocks;
-    c.last_most = batch_most;
     return r;
 }
 
