@@ -634,8 +634,8 @@ hipError_t launch_state_from_input(Ctx& c, const double* src);
 hipError_t launch_mux(Ctx& c);
 hipError_t launch_seg_finalize(Ctx& c, double tol, int max_iter);
 hipError_t launch_seg_init(Ctx& c);
-// per halo: recorded words and log blocks of the units its rays are in
-hipError_t launch_halo_sizes(Ctx& c, const uint64_t* unit_tally, unsigned long long* out);
+// per 64 consecutive sources: recorded words and log blocks over every direction
+hipError_t launch_packet_sizes(Ctx& c, const uint64_t* unit_tally, unsigned long long* out);
 hipError_t launch_seg_group_init(Ctx& c, const int32_t* mask);
 
 }  // namespace rrt

@@ -664,28 +664,22 @@ hipError_t launch_block_ids(Ctx& c, const int32_t* block_in)
     return hipGetLastError();
 }
 
-// Per halo the recorded words and log blocks of the units its rays are in
-// (out[2h], out[2h + 1]): an upper bound of what its rays alone take, since a
-// unit that a packet across two halos walks counts for both.
-__global__ void k_halo_sizes(const uint64_t* __restrict__ unit_tally, int64_t packets, int parts,
-                             int64_t n, const int32_t* __restrict__ seg_of,
-                             unsigned long long* __restrict__ out)
+// Per 64 consecutive sources (their packets of every direction) the recorded
+// words and log blocks (out[2b], out[2b + 1]).
+__global__ void k_packet_sizes(const uint64_t* __restrict__ unit_tally, int64_t wpd, int n_ray,
+                               int parts, unsigned long long* __restrict__ out)
 {
-    const int64_t pk = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-    if (pk >= packets) return;
+    const int64_t b = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
+    if (b >= wpd) return;
     unsigned long long words = 0, blocks = 0;
-    for (int q = 0; q < parts; ++q) {
-        const uint64_t v = unit_tally[pk * parts + q];
-        words += v & 0xffffffffull;
-        blocks += v >> 32;
-    }
-    // the halos of the packet's sources (consecutive in tree order)
-    const int64_t p0 = (pk % ((n + 63) / 64)) * 64;
-    const int64_t p1 = p0 + 63 < n ? p0 + 63 : n - 1;
-    for (int h = seg_of[p0]; h <= seg_of[p1]; ++h) {
-        atomicAdd(out + 2 * h, words);
-        atomicAdd(out + 2 * h + 1, blocks);
-    }
+    for (int k = 0; k < n_ray; ++k)
+        for (int q = 0; q < parts; ++q) {
+            const uint64_t v = unit_tally[(k * wpd + b) * parts + q];
+            words += v & 0xffffffffull;
+            blocks += v >> 32;
+        }
+    out[2 * b] = words;
+    out[2 * b + 1] = blocks;
 }
 
 // start a group of halos: only the masked ones iterate; iteration counts kept
@@ -714,11 +708,11 @@ __global__ void k_seg_group_init(int n_halo, const int32_t* __restrict__ mask,
     }
 }
 
-hipError_t launch_halo_sizes(Ctx& c, const uint64_t* unit_tally, unsigned long long* out)
+hipError_t launch_packet_sizes(Ctx& c, const uint64_t* unit_tally, unsigned long long* out)
 {
-    const int64_t pk = path_packets(c);
-    hipLaunchKernelGGL(k_halo_sizes, dim3(nblk(pk)), dim3(kBlock), 0, c.stream, unit_tally, pk,
-                       path_parts(c), c.n, c.seg_of, out);
+    const int64_t wpd = (c.n + 63) / 64;
+    hipLaunchKernelGGL(k_packet_sizes, dim3(nblk(wpd)), dim3(kBlock), 0, c.stream, unit_tally, wpd,
+                       c.n_ray, path_parts(c), out);
     return hipGetLastError();
 }
 

@@ -9,6 +9,7 @@
 #include <cstdio>
 #include <cstring>
 #include <new>
+#include <utility>
 #include <vector>
 
 using namespace rrt;
@@ -1821,91 +1822,114 @@ int run_active_halos(Ctx& c, double tol, int32_t max_iter, int32_t per_launch)
     return RRT_OK;
 }
 
-// Which halos can share recorded paths: per-halo sizes from one walk, packed
-// first-fit by decreasing size into groups whose paths (and their log) fit the
-// path buffer.  A halo too large for it alone forms a group that traverses
-// every iteration.
-int plan_groups(Ctx& c, std::vector<std::vector<int>>& groups, std::vector<bool>& recordable,
-                uint64_t& max_words, uint64_t& max_blocks)
+// Which halos can share recorded paths: the sizes of every 64 sources' paths from
+// one walk, and halos packed first-fit by decreasing size into groups whose paths
+// and log fit the path buffer.  A group's size counts the packets of its halos
+// once, also those that two halos (or halos of another group) share.  A halo too
+// large for the buffer alone traverses every iteration.
+struct HaloGroup {
+    std::vector<int> halos;
+    bool recorded = false;
+    uint64_t words = 0, blocks = 0;
+    std::vector<int64_t> shared;          // packets counted that may reach into other halos
+};
+
+int plan_groups(Ctx& c, std::vector<HaloGroup>& groups)
 {
     const int nh = c.n_halo;
-    const int64_t units = path_packets(c) * path_parts(c);
-    std::vector<unsigned long long> size(2 * (size_t)nh);
+    const int64_t units = path_packets(c) * path_parts(c), wpd = (c.n + 63) / 64;
+    std::vector<unsigned long long> size(2 * (size_t)wpd);
     {
         Scratch<uint64_t> tally(c);
         Scratch<unsigned long long> d_size(c);
         HIP_OK(tally.get((size_t)units));
-        HIP_OK(d_size.get(2 * (size_t)nh));
-        HIP_OK(hipMemsetAsync(d_size.p, 0, sizeof(unsigned long long) * 2 * nh, c.stream));
+        HIP_OK(d_size.get(2 * (size_t)wpd));
         if (int r = path_walk(c, false, tally.p, nullptr)) return r;
-        HIP_OK(launch_halo_sizes(c, tally.p, d_size.p));
-        HIP_OK(hipMemcpyAsync(size.data(), d_size.p, sizeof(unsigned long long) * 2 * nh,
+        HIP_OK(launch_packet_sizes(c, tally.p, d_size.p));
+        HIP_OK(hipMemcpyAsync(size.data(), d_size.p, sizeof(unsigned long long) * 2 * wpd,
                               hipMemcpyDeviceToHost, c.stream));
         HIP_OK(hipStreamSynchronize(c.stream));
     }
+    std::vector<uint64_t> words(wpd + 1, 0), blocks(wpd + 1, 0);     // before each packet
+    for (int64_t b = 0; b < wpd; ++b) {
+        words[b + 1] = words[b] + size[2 * b];
+        blocks[b + 1] = blocks[b] + size[2 * b + 1];
+    }
+    // what halo h adds to group g: its packets (consecutive in tree order), those at
+    // its ends only if the group has not counted them yet
+    auto add = [&](const HaloGroup& g, int h) {
+        const int64_t b0 = c.halo_off_host[h] / 64, b1 = (c.halo_off_host[h + 1] - 1) / 64;
+        HaloGroup a;
+        auto take = [&](int64_t from, int64_t to) {
+            a.words += words[to] - words[from];
+            a.blocks += blocks[to] - blocks[from];
+        };
+        auto end = [&](int64_t b) {
+            if (std::find(g.shared.begin(), g.shared.end(), b) != g.shared.end()) return;
+            a.shared.push_back(b);
+            take(b, b + 1);
+        };
+        end(b0);
+        if (b1 > b0) end(b1);
+        if (b1 > b0 + 1) take(b0 + 1, b1);
+        return a;
+    };
+    const uint64_t room = c.images_fit ? ws_largest_gap(c, kRegionPath) : 0;
     // a buffer that the waves' unused blocks would fill: they take one at a time
     c.log_tight = false;
-    c.log_tight = log_pool(c, 0, 1.0, false) * kLogBlock * 8 > c.arena.cap[kRegionPath] / 16;
-    // bytes of each halo's paths and log, and the room beside the fixed arrays
-    auto bytes = [&](int h) {
-        return size[2 * h] * 16 + (size[2 * h] / 32 + 1) * kSegmentBytes +
-               size[2 * h + 1] * kLogBlock * 8;
+    c.log_tight = log_pool(c, 0, 1.0, false) * kLogBlock * 8 > room / 16;
+    auto bytes = [&](uint64_t w, uint64_t b) {
+        return record_bytes(c, w, log_pool(c, b, 1.0, false)) + 4 * kWsAlign;
     };
-    const uint64_t fixed = record_bytes(c, 0, log_pool(c, 0, 1.0, false)) + 4 * kWsAlign;
-    const uint64_t room = c.arena.cap[kRegionPath];
-    const uint64_t cap = room > fixed && c.images_fit ? room - fixed : 0;
+    std::vector<uint64_t> alone(nh);
+    for (int h = 0; h < nh; ++h) alone[h] = add(HaloGroup(), h).words;
     std::vector<int> order(nh);
     for (int h = 0; h < nh; ++h) order[h] = h;
     std::stable_sort(order.begin(), order.end(),
-                     [&](int a, int b) { return bytes(a) > bytes(b); });
-    std::vector<uint64_t> load, words, blocks;
+                     [&](int a, int b) { return alone[a] > alone[b]; });
     groups.clear();
-    recordable.clear();
-    max_words = max_blocks = 0;
+    HaloGroup trav;                       // they need no memory: all at once
     for (int h : order) {
-        if (c.prm.record_paths == 0 || bytes(h) > cap) {
-            groups.push_back({h});
-            recordable.push_back(false);
-            load.push_back(0);
-            words.push_back(0);
-            blocks.push_back(0);
-            continue;
+        size_t at = 0;
+        HaloGroup a;
+        for (;; ++at) {
+            const HaloGroup none, &g = at < groups.size() ? groups[at] : none;
+            a = add(g, h);
+            if (bytes(g.words + a.words, g.blocks + a.blocks) <= room || at >= groups.size())
+                break;
         }
-        size_t g = 0;
-        for (; g < groups.size(); ++g)
-            if (recordable[g] && load[g] + bytes(h) <= cap) break;
-        if (g == groups.size()) {
-            groups.push_back({});
-            recordable.push_back(true);
-            load.push_back(0);
-            words.push_back(0);
-            blocks.push_back(0);
+        if (at == groups.size()) {
+            if (bytes(a.words, a.blocks) > room) {
+                trav.halos.push_back(h);
+                continue;
+            }
+            groups.emplace_back();
+            groups.back().recorded = true;
         }
-        groups[g].push_back(h);
-        load[g] += bytes(h);
-        words[g] += size[2 * h];
-        blocks[g] += size[2 * h + 1];
-        max_words = std::max<uint64_t>(max_words, words[g]);
-        max_blocks = std::max<uint64_t>(max_blocks, blocks[g]);
+        HaloGroup& g = groups[at];
+        g.halos.push_back(h);
+        g.words += a.words;
+        g.blocks += a.blocks;
+        g.shared.insert(g.shared.end(), a.shared.begin(), a.shared.end());
     }
-    // traversing halos need no memory: run them together as one group
-    std::vector<std::vector<int>> gs;
-    std::vector<bool> rs;
-    std::vector<int> trav;
-    for (size_t g = 0; g < groups.size(); ++g) {
-        if (recordable[g]) {
-            gs.push_back(groups[g]);
-            rs.push_back(true);
-        } else {
-            trav.insert(trav.end(), groups[g].begin(), groups[g].end());
-        }
+    if (!trav.halos.empty()) groups.push_back(std::move(trav));
+    return RRT_OK;
+}
+
+// Record the rays of the active halos, whose paths and log take at most the
+// group's.
+int record_group(Ctx& c, const HaloGroup& g, bool* fit)
+{
+    free_paths(c);
+    *fit = false;
+    if (!g.recorded) return RRT_OK;
+    if (alloc_log(c, g.words, log_pool(c, g.blocks, 1.0, false))) {
+        bool overflow = false;
+        if (int r = path_walk(c, true, nullptr, &overflow)) return r;
+        if (!overflow)
+            if (int r = build_paths(c, fit)) return r;
     }
-    if (!trav.empty()) {
-        gs.push_back(trav);
-        rs.push_back(false);
-    }
-    groups.swap(gs);
-    recordable.swap(rs);
+    if (!*fit) free_paths(c);
     return RRT_OK;
 }
 
@@ -1915,50 +1939,43 @@ int run_groups(Ctx& c, double tol, int32_t max_iter, int32_t per_launch)
 {
     Scratch<int32_t> d_mask(c);
     HIP_OK(d_mask.get((size_t)c.n_halo));
-    std::vector<std::vector<int>> groups;
-    std::vector<bool> recordable;
-    uint64_t max_words = 0, max_blocks = 0;
-    if (int r = plan_groups(c, groups, recordable, max_words, max_blocks)) return r;
-    const uint64_t batch_total = c.last_total, batch_words = c.last_words,
-                   batch_blocks = c.last_blocks;
-    if (groups.size() == 1 && recordable[0]) {
+    std::vector<HaloGroup> groups;
+    if (int r = plan_groups(c, groups)) return r;
+    if (groups.size() == 1 && groups[0].recorded) {
         // all paths fit: the sizes are known, so the first iteration records
         // them with one walk
         c.counts_valid = true;
         return run_active_halos(c, tol, max_iter, per_launch);
     }
+    const uint64_t batch_total = c.last_total, batch_words = c.last_words,
+                   batch_blocks = c.last_blocks, batch_most = c.last_most;
     std::vector<int32_t> mask(c.n_halo);
     int r = RRT_OK;
     for (size_t g = 0; g < groups.size() && r == RRT_OK; ++g) {
         std::fill(mask.begin(), mask.end(), 0);
-        for (int h : groups[g]) mask[h] = 1;
+        for (int h : groups[g].halos) mask[h] = 1;
         HIP_OK(hipMemcpyAsync(d_mask.p, mask.data(), sizeof(int32_t) * c.n_halo,
                               hipMemcpyHostToDevice, c.stream));
         HIP_OK(launch_seg_group_init(c, d_mask.p));
         HIP_OK(hipStreamSynchronize(c.stream));          // mask is read
         // record only this group's rays: they are the active ones
-        free_paths(c);
-        bool ok = recordable[g] && alloc_log(c, 0, log_pool(c, max_blocks, 1.0, false));
-        if (ok) {
-            bool overflow = false;
-            if ((r = path_walk(c, true, nullptr, &overflow)) != RRT_OK) break;
-            ok = !overflow;
-        }
-        if (ok && (r = build_paths(c, &ok)) != RRT_OK) break;
+        bool ok = false;
+        if ((r = record_group(c, groups[g], &ok)) != RRT_OK) break;
         if (ok) {
             c.paths_valid = true;
             c.path_hits = (int64_t)c.last_total;
         } else {
-            free_paths(c);
             c.paths_unfit = true;
         }
         r = run_active_halos(c, tol, max_iter, per_launch);
     }
     free_paths(c);
     c.counts_valid = false;
+    c.log_tight = false;
     c.last_total = batch_total;
     c.last_words = batch_words;
     c.last_blocks = batch_blocks;
+    c.last_most = batch_most;
     return r;
 }
 

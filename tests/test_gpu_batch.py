@@ -200,3 +200,31 @@ def test_packet_queue_gives_the_grid_results(paths):
             np.testing.assert_array_equal(a, b)
         else:
             assert a == b
+
+
+@pytest.mark.parametrize("sizes,frac,most", [
+    ([9, 1, 30, 5, 64, 3, 17] * 20, 1.0, 3),     # packets of many halos
+    ([20] * 600, 0.9, 3),
+    ([640, 64, 128] * 6, 0.9, 3)])        # halos that end with their packets
+def test_groups_record_every_halo_that_fits(sizes, frac, most):
+    """A batch larger than its buffer: halos whose paths fit are recorded (none
+    traverses), in few groups where packets hold several halos, and each halo gives
+    the results of the batch in one.  A second call on the same solver does too."""
+    wl, _ = _batch(sizes, [1.0 + (i % 5) for i in range(len(sizes))], seed=14)
+    probe = _solver(wl, record_paths=-1)
+    need = probe.count_paths()
+    probe.close()
+    ref = _solver(wl).iterate_halos(200, 1e-3, per_launch=8)
+    s = _solver(wl, record_paths=-1, path_budget=int(need["bytes_paths"] * frac))
+    for _ in range(2):
+        s.set_state(None)
+        s.enable_timing(True)
+        s.reset_timing()
+        r = s.iterate_halos(200, 1e-3, per_launch=8)
+        tm = s.timing()
+        assert tm["n_trace"] == 0 and tm["n_path"] <= most, (tm["n_trace"], tm["n_path"])
+        np.testing.assert_array_equal(r["halo_iters"], ref["halo_iters"])
+        np.testing.assert_allclose(r["x"].cpu().numpy(), ref["x"].cpu().numpy(), rtol=1e-9)
+    N1, h1 = s.compute_columns()
+    assert h1 == need["hits"]
+    s.close()
