@@ -203,6 +203,7 @@ def test_packet_queue_gives_the_grid_results(paths):
 
 
 @pytest.mark.parametrize("sizes,frac,most", [
+    ([5000, 9, 40], 1.0, 2),              # the largest halo's paths fit, not its log
     ([9, 1, 30, 5, 64, 3, 17] * 20, 1.0, 3),     # packets of many halos
     ([20] * 600, 0.9, 3),
     ([640, 64, 128] * 6, 0.9, 3)])        # halos that end with their packets
