@@ -270,6 +270,7 @@ struct Ctx {
     uint64_t* seg_off = nullptr;  // first word of each segment
     uint64_t* unit_seg = nullptr; // [units + 1] first segment of each unit
     uint64_t path_segs = 0, path_words = 0;
+    int64_t path_live = 0;        // packets recorded (those of a group of halos)
     int64_t path_hits = 0;        // intersections recorded
     bool paths_valid = false;
     bool paths_unfit = false;     // recording was tried and exceeded the budget
@@ -597,19 +598,21 @@ inline int ray_ways(int64_t waves, int n_ray)
     while (w < 16 && 2 * w <= n_ray && waves * w < 4096) w *= 2;
     return w;
 }
-// Waves per packet of the columns' product, for packets of `segs` segments on
-// average: below 16384 waves, as many as the segments keep busy; beyond, so few
+// Waves per packet of the columns' product over `live` packets of `segs` segments
+// in all (the other packets of the launch end at once): below 16384 waves, as many as the segments keep busy; beyond, so few
 // that each has several segments to run ahead over, and never so many that the
 // launch has 2^32 work-items.
 // Measured on MI355X (ms per product at 1, 2, 4, 8 waves): the 885k-particle
 // field's 663552 packets of 3.4 segments 4.05, 3.93, 5.02, -; the 262144-
 // particle halo's 49152 of 20: 2.03, -, 1.55, 1.72; 12 halos' 26236 of 9:
-// -, 0.255, -, 0.34.
-inline int path_ways(int64_t packets, double segs)
+// -, 0.255, -, 0.34; 640-particle halos in groups, 936 packets of which some 250
+// are recorded, us at 1, 8: 20, 9.
+inline int path_ways(int64_t packets, int64_t live, uint64_t segs)
 {
+    const double mean = (double)segs / (double)(live > 0 ? live : 1);
     int w = 1;
     while (w < 8 && packets * 64 * (2 * w) < (int64_t(1) << 32) &&
-           (packets * w < 16384 ? segs > w : segs > (w == 1 ? 3 : 6) * w))
+           (live * w < 16384 ? mean > w : mean > (w == 1 ? 3 : 6) * w))
         w *= 2;
     return w;
 }

@@ -603,7 +603,7 @@ template <bool NF, bool STREAM>
 void launch_columns_as(Ctx& c)
 {
     const int64_t pk = path_packets(c);
-    const int W = path_ways(pk, (double)c.path_segs / (double)std::max<int64_t>(pk, 1));
+    const int W = path_ways(pk, c.path_live, c.path_segs);
     auto go = [&](auto kernel, int64_t blocks, int threads) {
         hipLaunchKernelGGL(kernel, dim3((unsigned)blocks), dim3(threads), 0, c.stream, c.unit_seg,
                            c.seg_off, c.packed, path_parts(c), c.mux_s, pk, c.N_s, (int)c.n,

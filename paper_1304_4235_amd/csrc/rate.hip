@@ -669,15 +669,20 @@ hipError_t launch_block_ids(Ctx& c, const int32_t* block_in)
 __global__ void k_packet_sizes(const uint64_t* __restrict__ unit_tally, int64_t wpd, int n_ray,
                                int parts, unsigned long long* __restrict__ out)
 {
-    const int64_t b = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
+    // a wave per 64 sources
+    const int64_t b = (blockIdx.x * (int64_t)blockDim.x + threadIdx.x) >> 6;
     if (b >= wpd) return;
     unsigned long long words = 0, blocks = 0;
-    for (int k = 0; k < n_ray; ++k)
-        for (int q = 0; q < parts; ++q) {
-            const uint64_t v = unit_tally[(k * wpd + b) * parts + q];
-            words += v & 0xffffffffull;
-            blocks += v >> 32;
-        }
+    for (int i = threadIdx.x & 63; i < n_ray * parts; i += 64) {
+        const uint64_t v = unit_tally[((int64_t)(i / parts) * wpd + b) * parts + i % parts];
+        words += v & 0xffffffffull;
+        blocks += v >> 32;
+    }
+    for (int off = 32; off > 0; off >>= 1) {
+        words += __shfl_xor(words, off, 64);
+        blocks += __shfl_xor(blocks, off, 64);
+    }
+    if ((threadIdx.x & 63) != 0) return;
     out[2 * b] = words;
     out[2 * b + 1] = blocks;
 }
@@ -711,7 +716,7 @@ __global__ void k_seg_group_init(int n_halo, const int32_t* __restrict__ mask,
 hipError_t launch_packet_sizes(Ctx& c, const uint64_t* unit_tally, unsigned long long* out)
 {
     const int64_t wpd = (c.n + 63) / 64;
-    hipLaunchKernelGGL(k_packet_sizes, dim3(nblk(wpd)), dim3(kBlock), 0, c.stream, unit_tally, wpd,
+    hipLaunchKernelGGL(k_packet_sizes, dim3(nblk(64 * wpd)), dim3(kBlock), 0, c.stream, unit_tally, wpd,
                        c.n_ray, path_parts(c), out);
     return hipGetLastError();
 }

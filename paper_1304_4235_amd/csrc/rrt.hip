@@ -583,6 +583,7 @@ int record_paths(Ctx& c)
     else if (kind == 2) c.n_rec_counted += 1;
     else c.n_rec_two += 1;
     c.path_hits = (int64_t)c.last_total;
+    c.path_live = path_packets(c);
     c.paths_valid = true;
     ev_end(c, ev_rec, &c.t_record);
     return RRT_OK;
@@ -1836,6 +1837,7 @@ struct HaloGroup {
     std::vector<int> halos;
     bool recorded = false;
     uint64_t words = 0, blocks = 0;
+    int64_t packets = 0;                  // of one direction
     std::vector<int64_t> shared;          // packets counted that may reach into other halos
 };
 
@@ -1866,6 +1868,7 @@ int plan_groups(Ctx& c, std::vector<HaloGroup>& groups)
         const int64_t b0 = c.halo_off_host[h] / 64, b1 = (c.halo_off_host[h + 1] - 1) / 64;
         HaloGroup a;
         auto take = [&](int64_t from, int64_t to) {
+            a.packets += to - from;
             a.words += words[to] - words[from];
             a.blocks += blocks[to] - blocks[from];
         };
@@ -1918,6 +1921,7 @@ int plan_groups(Ctx& c, std::vector<HaloGroup>& groups)
         g.halos.push_back(h);
         g.words += a.words;
         g.blocks += a.blocks;
+        g.packets += a.packets;
         g.shared.insert(g.shared.end(), a.shared.begin(), a.shared.end());
     }
     if (!trav.halos.empty()) groups.push_back(std::move(trav));
@@ -1973,6 +1977,7 @@ int run_groups(Ctx& c, double tol, int32_t max_iter, int32_t per_launch)
         if (ok) {
             c.paths_valid = true;
             c.path_hits = (int64_t)c.last_total;
+            c.path_live = groups[g].packets * c.n_ray;
         } else {
             c.paths_unfit = true;
         }

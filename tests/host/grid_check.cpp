@@ -27,11 +27,14 @@ int main()
     for (int64_t pk : {int64_t(1), int64_t(16383), int64_t(16384), int64_t(663552),
                        int64_t(1) << 22, int64_t(1) << 23, int64_t(1) << 24, int64_t(1) << 25,
                        kMaxRows / 64 + kMaxRays})
-        for (double segs : {0.0, 1.0, 3.5, 7.0, 13.0, 25.0, 1e6})
-            below("path_ways", pk, segs, (double)pk * 64.0 * path_ways(pk, segs));
+        for (uint64_t segs : {0, 1, 4, 7, 13, 25, 1000000})
+            for (int64_t live : {int64_t(0), int64_t(1), pk / 3, pk})
+                below("path_ways", pk, (double)segs,
+                      (double)pk * 64.0 * path_ways(pk, live, segs * (uint64_t)live));
     // the measured choices
-    if (path_ways(663552, 3.4) != 2 || path_ways(49152, 20.0) != 4 || path_ways(26236, 9.0) != 2 ||
-        path_ways(100, 9.0) != 8 || path_ways(100, 1.0) != 1) {
+    if (path_ways(663552, 663552, 2256077) != 2 || path_ways(49152, 49152, 983040) != 4 ||
+        path_ways(26236, 26236, 236124) != 2 || path_ways(100, 100, 900) != 8 ||
+        path_ways(100, 100, 100) != 1 || path_ways(936, 250, 900) != 4) {
         std::fprintf(stderr, "path_ways: not the measured choices\n");
         return 1;
     }
