@@ -271,6 +271,9 @@ struct Ctx {
     uint64_t* unit_seg = nullptr; // [units + 1] first segment of each unit
     uint64_t path_segs = 0, path_words = 0;
     int64_t path_live = 0;        // packets recorded (those of a group of halos)
+    // > 0 while groups of halos run: segments and words that unit_seg, seg_off and
+    // packed hold for the largest group, so that they stay where they are
+    uint64_t hold_segs = 0, hold_words = 0;
     int64_t path_hits = 0;        // intersections recorded
     bool paths_valid = false;
     bool paths_unfit = false;     // recording was tried and exceeded the budget
@@ -423,6 +426,8 @@ struct Ctx {
     hipStream_t gstream = nullptr;
     hipGraph_t graph = nullptr;
     hipGraphExec_t graph_exec = nullptr;
+    const void* graph_paths[3] = {};  // the recorded paths it reads (null: it traverses),
+    int graph_ways = 0;               // and their product's variant
     int32_t graph_iters = 0, graph_max_iter = 0;
     double graph_tol = -1.0;
     hipEvent_t ev_a = nullptr, ev_b = nullptr;
@@ -560,6 +565,8 @@ hipError_t launch_unit_words(Ctx& c);
 hipError_t launch_build_paths(Ctx& c);
 hipError_t launch_build_range(Ctx& c, int64_t unit0, int64_t units, uint64_t seg0, uint64_t segs);
 hipError_t launch_path_columns(Ctx& c);
+// the variant of its kernel that the recorded paths take
+int path_variant(const Ctx& c);
 // the rows of the listed sources (one block of the density order) from c.path
 hipError_t launch_row_columns(Ctx& c, int group);
 hipError_t launch_path_scatter(Ctx& c, const float* nu, double* y);

@@ -600,10 +600,9 @@ k_path_columns(const uint64_t* __restrict__ unit_seg, const uint64_t* __restrict
 }
 
 template <bool NF, bool STREAM>
-void launch_columns_as(Ctx& c)
+void launch_columns_as(Ctx& c, int W)
 {
     const int64_t pk = path_packets(c);
-    const int W = path_ways(pk, c.path_live, c.path_segs);
     auto go = [&](auto kernel, int64_t blocks, int threads) {
         hipLaunchKernelGGL(kernel, dim3((unsigned)blocks), dim3(threads), 0, c.stream, c.unit_seg,
                            c.seg_off, c.packed, path_parts(c), c.mux_s, pk, c.N_s, (int)c.n,
@@ -616,14 +615,12 @@ void launch_columns_as(Ctx& c)
     else go(k_path_columns<NF, 8, STREAM>, pk, 512);
 }
 
-// Paths that stay in the 256 MB last-level cache from one sweep to the next are
-// read with ordinary loads (the 16384-particle halo's 250 MB: 55 us a product
-// against 68 with non-temporal ones), larger ones stream past it.
 template <bool NF>
 void launch_columns_nf(Ctx& c)
 {
-    if (c.path_words * 16 > (uint64_t)256 << 20) launch_columns_as<NF, true>(c);
-    else launch_columns_as<NF, false>(c);
+    const int v = path_variant(c);
+    if (v > 8) launch_columns_as<NF, true>(c, v - 8);
+    else launch_columns_as<NF, false>(c, v);
 }
 
 // Visit every group of a packet's segments as stored, a lane per group: f(its
@@ -894,6 +891,16 @@ unsigned packet_blocks(int64_t packets)
 }
 
 }  // namespace
+
+// Waves per packet, and 8 more where the paths are read past the cache.  Paths
+// that stay in the 256 MB last-level cache from one sweep to the next are read with
+// ordinary loads (the 16384-particle halo's 250 MB: 55 us a product against 68 with
+// non-temporal ones), larger ones stream past it.
+int path_variant(const Ctx& c)
+{
+    return path_ways(path_packets(c), c.path_live, c.path_segs) +
+           (c.path_words * 16 > (uint64_t)256 << 20 ? 8 : 0);
+}
 
 hipError_t launch_path_columns(Ctx& c)
 {

@@ -32,6 +32,8 @@ void rrt::drop_graph(Ctx& c)
     c.graph_exec = nullptr;
     c.graph = nullptr;
     c.graph_iters = 0;
+    c.graph_ways = 0;
+    for (const void*& p : c.graph_paths) p = nullptr;
 }
 
 namespace {
@@ -312,6 +314,7 @@ void free_paths(Ctx& c)
     ws_free(c, &c.packed);
     ws_free(c, &c.seg_off);
     ws_free(c, &c.unit_seg);
+    c.hold_segs = c.hold_words = 0;
     c.path_segs = c.path_words = 0;
     ws_free(c, &c.path);
     c.rows_valid = false;
@@ -351,6 +354,25 @@ uint64_t record_bytes(const Ctx& c, uint64_t words, uint64_t blocks)
            region_bytes((words + kPackedPad) * 16);
 }
 
+// The arrays the recorded paths stay in: those held for groups of halos where
+// they are large enough, else new ones.
+hipError_t alloc_unit_seg(Ctx& c)
+{
+    if (c.hold_words) return hipSuccess;
+    return ws_alloc(c, &c.unit_seg, (size_t)(path_packets(c) * path_parts(c)) + 1, kRegionPath);
+}
+hipError_t alloc_paths(Ctx& c, uint64_t segs, uint64_t words)
+{
+    if (c.hold_words) {
+        if (segs <= c.hold_segs && words <= c.hold_words) return hipSuccess;
+        c.hold_segs = c.hold_words = 0;
+    }
+    hipError_t e = ws_alloc(c, &c.seg_off, (size_t)std::max<uint64_t>(segs, 1), kRegionPath);
+    if (e == hipSuccess)
+        e = ws_alloc(c, &c.packed, (size_t)words + kPackedPad, kRegionPath);
+    return e;
+}
+
 // Path buffer for a recording in pieces, the least that holds the paths: a log
 // of a 32nd of the whole, and of the largest unit at least.
 uint64_t piece_blocks(const Ctx& c)
@@ -366,15 +388,16 @@ bool alloc_log(Ctx& c, uint64_t words, uint64_t blocks)
     free_log(c);
     if (blocks > 0xfffffff0ull) return false;          // block numbers are 32-bit
     const size_t units = (size_t)(path_packets(c) * path_parts(c));
-    hipError_t e = ws_alloc(c, &c.unit_seg, units + 1, kRegionPath);
+    hipError_t e = alloc_unit_seg(c);
     if (e == hipSuccess) e = ws_alloc(c, &c.unit_off, units + 1, kRegionPath);
     if (e == hipSuccess) e = ws_alloc(c, &c.unit_log, units, kRegionPath);
     if (e == hipSuccess) e = ws_alloc(c, &c.path_log, (size_t)blocks * kLogBlock, kRegionPath);
-    if (e == hipSuccess && ws_largest_gap(c, kRegionPath) < region_bytes(words * 16))
+    if (e == hipSuccess && words > c.hold_words &&
+        ws_largest_gap(c, kRegionPath) < region_bytes(words * 16))
         e = hipErrorOutOfMemory;
     if (e != hipSuccess) {
         free_log(c);
-        ws_free(c, &c.unit_seg);
+        if (!c.hold_words) ws_free(c, &c.unit_seg);
         return false;
     }
     c.log_blocks = blocks;
@@ -424,11 +447,9 @@ int build_paths(Ctx& c, bool* fit)
 {
     const int64_t units = path_packets(c) * path_parts(c);
     const size_t segs = (size_t)std::max<uint64_t>(c.path_segs, 1);
-    hipError_t e = ws_alloc(c, &c.seg_off, segs, kRegionPath);
+    hipError_t e = alloc_paths(c, segs, c.last_words);
     if (e == hipSuccess) e = ws_alloc(c, &c.seg_src, segs, kRegionPath);
     if (e == hipSuccess) e = ws_alloc(c, &c.seg_unit, segs, kRegionPath);
-    if (e == hipSuccess)
-        e = ws_alloc(c, &c.packed, (size_t)c.last_words + kPackedPad, kRegionPath);
     *fit = e == hipSuccess;
     if (!*fit) return RRT_OK;
     HIP_OK(launch_unit_words(c));
@@ -463,21 +484,21 @@ int record_pieces(Ctx& c, bool* fit)
 {
     *fit = false;
     free_log(c);
-    ws_free(c, &c.unit_seg);
-    ws_free(c, &c.seg_off);
-    ws_free(c, &c.packed);
+    if (!c.hold_words) {
+        ws_free(c, &c.unit_seg);
+        ws_free(c, &c.seg_off);
+        ws_free(c, &c.packed);
+    }
     const int64_t units = path_packets(c) * path_parts(c);
-    hipError_t e = ws_alloc(c, &c.unit_seg, (size_t)units + 1, kRegionPath);
+    hipError_t e = alloc_unit_seg(c);
     if (e == hipSuccess) e = ws_alloc(c, &c.unit_off, (size_t)units + 1, kRegionPath);
     if (e == hipSuccess) e = ws_alloc(c, &c.unit_log, (size_t)units, kRegionPath);
     if (e != hipSuccess) return RRT_OK;
     if (int r = path_walk(c, false, c.unit_off, nullptr)) return r;
     const size_t segs = (size_t)std::max<uint64_t>(c.path_segs, 1);
-    e = ws_alloc(c, &c.seg_off, segs, kRegionPath);
+    e = alloc_paths(c, segs, c.last_words);
     if (e == hipSuccess) e = ws_alloc(c, &c.seg_src, segs, kRegionPath);
     if (e == hipSuccess) e = ws_alloc(c, &c.seg_unit, segs, kRegionPath);
-    if (e == hipSuccess)
-        e = ws_alloc(c, &c.packed, (size_t)c.last_words + kPackedPad, kRegionPath);
     const uint64_t room = ws_largest_gap(c, kRegionPath) / (kLogBlock * sizeof(uint64_t));
     const uint64_t blocks = std::min<uint64_t>(std::min<uint64_t>(room, c.last_blocks + 1),
                                                0xfffffff0ull);
@@ -1774,8 +1795,15 @@ int run_active_halos(Ctx& c, double tol, int32_t max_iter, int32_t per_launch)
                           hipMemcpyDeviceToHost, c.stream));
     HIP_OK(hipStreamSynchronize(c.stream));
     if (c.seg_state_host[1] <= 0) return RRT_OK;
+    // (a graph stays valid over other paths in the same arrays with the same variant
+    // of the product: groups of halos)
+    const void* paths[3] = {c.paths_valid ? c.unit_seg : nullptr,
+                            c.paths_valid ? c.seg_off : nullptr,
+                            c.paths_valid ? c.packed : nullptr};
+    const int ways = c.paths_valid ? path_variant(c) : 0;
     if (!c.graph_exec || c.graph_iters != per_launch || c.graph_tol != tol ||
-        c.graph_max_iter != max_iter) {
+        c.graph_max_iter != max_iter || c.graph_ways != ways ||
+        !std::equal(paths, paths + 3, c.graph_paths)) {
         drop_graph(c);
         // the replays should use the row tiles when the solve is long enough to
         // pay for them; nothing may be allocated during the capture
@@ -1809,6 +1837,8 @@ int run_active_halos(Ctx& c, double tol, int32_t max_iter, int32_t per_launch)
         c.graph_iters = per_launch;
         c.graph_tol = tol;
         c.graph_max_iter = max_iter;
+        c.graph_ways = ways;
+        std::copy(paths, paths + 3, c.graph_paths);
     }
     HIP_OK(hipEventRecord(c.ev_a, c.stream));
     HIP_OK(hipStreamWaitEvent(c.gstream, c.ev_a, 0));
@@ -1932,8 +1962,13 @@ int plan_groups(Ctx& c, std::vector<HaloGroup>& groups)
 // group's: the whole log where it fits, else in pieces.
 int record_group(Ctx& c, const HaloGroup& g, bool* fit)
 {
-    free_paths(c);
-    *fit = false;
+    free_tpaths(c);
+    free_tiles(c);
+    free_log(c);
+    ws_free(c, &c.path);
+    c.rows_valid = c.rows_unfit = false;
+    c.path_evals = 0;
+    c.paths_valid = c.paths_unfit = *fit = false;
     if (!g.recorded) return RRT_OK;
     if (alloc_log(c, g.words, log_pool(c, g.blocks, 1.0, false))) {
         bool overflow = false;
@@ -1962,6 +1997,22 @@ int run_groups(Ctx& c, double tol, int32_t max_iter, int32_t per_launch)
     }
     const uint64_t batch_total = c.last_total, batch_words = c.last_words,
                    batch_blocks = c.last_blocks, batch_most = c.last_most;
+    // where every group's log fits beside the paths of the largest, its arrays for
+    // all of them: the captured graph stays valid where the product's variant does
+    free_paths(c);
+    uint64_t words = 0, blocks = 0;
+    for (const HaloGroup& g : groups) {
+        words = std::max(words, g.words);
+        blocks = std::max(blocks, g.blocks);
+    }
+    const uint64_t segs = (uint64_t)(path_packets(c) * path_parts(c)) + words / 32;
+    if (words > 0 &&
+        record_bytes(c, words, log_pool(c, blocks, 1.0, false)) + 4 * kWsAlign <=
+            ws_largest_gap(c, kRegionPath) &&
+        alloc_unit_seg(c) == hipSuccess && alloc_paths(c, segs, words) == hipSuccess) {
+        c.hold_segs = segs;
+        c.hold_words = words;
+    }
     std::vector<int32_t> mask(c.n_halo);
     int r = RRT_OK;
     for (size_t g = 0; g < groups.size() && r == RRT_OK; ++g) {
