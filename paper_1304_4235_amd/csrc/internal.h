@@ -459,12 +459,15 @@ struct Ctx {
 // ---- device memory (workspace.hip) ----
 // Carve `bytes` for *owner from a region (what *owner held is released
 // first).  hipErrorOutOfMemory when no gap is large enough; the request is
-// recorded in c.arena.short_*.
-hipError_t ws_alloc(Ctx& c, void** owner, size_t bytes, int region);
+// recorded in c.arena.short_*.  high: from the top of the highest gap instead of
+// the bottom of the lowest, for what goes again before the blocks below it (so
+// that it leaves no hole between them).
+hipError_t ws_alloc(Ctx& c, void** owner, size_t bytes, int region, bool high = false);
 template <typename T>
-inline hipError_t ws_alloc(Ctx& c, T** owner, size_t count, int region = kRegionWs)
+inline hipError_t ws_alloc(Ctx& c, T** owner, size_t count, int region = kRegionWs,
+                           bool high = false)
 {
-    return ws_alloc(c, reinterpret_cast<void**>(owner), count * sizeof(T), region);
+    return ws_alloc(c, reinterpret_cast<void**>(owner), count * sizeof(T), region, high);
 }
 void ws_free(Ctx& c, void** owner);
 template <typename T>

@@ -382,16 +382,18 @@ uint64_t piece_blocks(const Ctx& c)
 uint64_t record_bytes_least(const Ctx& c) { return record_bytes(c, c.last_words, piece_blocks(c)); }
 
 // The log's pool and the units' arrays in the path buffer, when they fit
-// beside paths of `words`.  False (nothing kept) otherwise.
+// beside paths of `words`.  False (nothing kept) otherwise.  What the recording gives
+// back lies at the buffer's end, so the room after it is one piece.
 bool alloc_log(Ctx& c, uint64_t words, uint64_t blocks)
 {
     free_log(c);
     if (blocks > 0xfffffff0ull) return false;          // block numbers are 32-bit
     const size_t units = (size_t)(path_packets(c) * path_parts(c));
     hipError_t e = alloc_unit_seg(c);
-    if (e == hipSuccess) e = ws_alloc(c, &c.unit_off, units + 1, kRegionPath);
-    if (e == hipSuccess) e = ws_alloc(c, &c.unit_log, units, kRegionPath);
-    if (e == hipSuccess) e = ws_alloc(c, &c.path_log, (size_t)blocks * kLogBlock, kRegionPath);
+    if (e == hipSuccess) e = ws_alloc(c, &c.unit_off, units + 1, kRegionPath, true);
+    if (e == hipSuccess) e = ws_alloc(c, &c.unit_log, units, kRegionPath, true);
+    if (e == hipSuccess)
+        e = ws_alloc(c, &c.path_log, (size_t)blocks * kLogBlock, kRegionPath, true);
     if (e == hipSuccess && words > c.hold_words &&
         ws_largest_gap(c, kRegionPath) < region_bytes(words * 16))
         e = hipErrorOutOfMemory;
@@ -448,8 +450,8 @@ int build_paths(Ctx& c, bool* fit)
     const int64_t units = path_packets(c) * path_parts(c);
     const size_t segs = (size_t)std::max<uint64_t>(c.path_segs, 1);
     hipError_t e = alloc_paths(c, segs, c.last_words);
-    if (e == hipSuccess) e = ws_alloc(c, &c.seg_src, segs, kRegionPath);
-    if (e == hipSuccess) e = ws_alloc(c, &c.seg_unit, segs, kRegionPath);
+    if (e == hipSuccess) e = ws_alloc(c, &c.seg_src, segs, kRegionPath, true);
+    if (e == hipSuccess) e = ws_alloc(c, &c.seg_unit, segs, kRegionPath, true);
     *fit = e == hipSuccess;
     if (!*fit) return RRT_OK;
     HIP_OK(launch_unit_words(c));
@@ -491,19 +493,19 @@ int record_pieces(Ctx& c, bool* fit)
     }
     const int64_t units = path_packets(c) * path_parts(c);
     hipError_t e = alloc_unit_seg(c);
-    if (e == hipSuccess) e = ws_alloc(c, &c.unit_off, (size_t)units + 1, kRegionPath);
-    if (e == hipSuccess) e = ws_alloc(c, &c.unit_log, (size_t)units, kRegionPath);
+    if (e == hipSuccess) e = ws_alloc(c, &c.unit_off, (size_t)units + 1, kRegionPath, true);
+    if (e == hipSuccess) e = ws_alloc(c, &c.unit_log, (size_t)units, kRegionPath, true);
     if (e != hipSuccess) return RRT_OK;
     if (int r = path_walk(c, false, c.unit_off, nullptr)) return r;
     const size_t segs = (size_t)std::max<uint64_t>(c.path_segs, 1);
     e = alloc_paths(c, segs, c.last_words);
-    if (e == hipSuccess) e = ws_alloc(c, &c.seg_src, segs, kRegionPath);
-    if (e == hipSuccess) e = ws_alloc(c, &c.seg_unit, segs, kRegionPath);
+    if (e == hipSuccess) e = ws_alloc(c, &c.seg_src, segs, kRegionPath, true);
+    if (e == hipSuccess) e = ws_alloc(c, &c.seg_unit, segs, kRegionPath, true);
     const uint64_t room = ws_largest_gap(c, kRegionPath) / (kLogBlock * sizeof(uint64_t));
     const uint64_t blocks = std::min<uint64_t>(std::min<uint64_t>(room, c.last_blocks + 1),
                                                0xfffffff0ull);
     if (e != hipSuccess || blocks < std::max<uint64_t>(c.last_most, 1)) return RRT_OK;
-    if (ws_alloc(c, &c.path_log, (size_t)blocks * kLogBlock, kRegionPath) != hipSuccess)
+    if (ws_alloc(c, &c.path_log, (size_t)blocks * kLogBlock, kRegionPath, true) != hipSuccess)
         return RRT_OK;
     c.log_blocks = blocks;
     HIP_OK(launch_unit_words(c));

@@ -27,7 +27,7 @@ void ws_free(Ctx& c, void** owner)
     *owner = nullptr;
 }
 
-hipError_t ws_alloc(Ctx& c, void** owner, size_t bytes, int region)
+hipError_t ws_alloc(Ctx& c, void** owner, size_t bytes, int region, bool high)
 {
     ws_free(c, owner);
     Arena& a = c.arena;
@@ -37,16 +37,18 @@ hipError_t ws_alloc(Ctx& c, void** owner, size_t bytes, int region)
     for (const Arena::Block& b : a.blocks)
         if (b.region == region) used.push_back({b.off, b.off + b.size});
     std::sort(used.begin(), used.end());
-    uint64_t at = 0;
+    const uint64_t cap = a.base[region] ? a.cap[region] / kWsAlign * kWsAlign : 0;
+    used.push_back({cap, cap});
+    uint64_t at = 0, from = 0;
     bool found = false;
     for (const auto& u : used) {
-        if (u.first >= at + need) {
+        if (u.first >= from + need) {
             found = true;
-            break;
+            at = high ? u.first - need : from;
+            if (!high) break;
         }
-        at = std::max(at, u.second);
+        from = std::max(from, u.second);
     }
-    if (!found) found = a.base[region] && at + need <= a.cap[region];
     if (!found) {
         a.short_bytes = need;
         a.short_region = region;

@@ -38,14 +38,16 @@ def test_arena_under_sanitizers(tmp_path):
 
 @pytest.mark.skipif(shutil.which("g++") is None or not os.path.isdir("/opt/rocm/include"),
                     reason="needs g++ and the ROCm headers")
-def test_launch_grids_under_sanitizers(tmp_path):
-    exe = str(tmp_path / "grid_check")
+@pytest.mark.parametrize("name,says", [("grid_check", "grid checks passed"),
+                                       ("arena_high_check", "arena checks from the top passed")])
+def test_host_rules_under_sanitizers(tmp_path, name, says):
+    exe = str(tmp_path / name)
     csrc = os.path.join(ROOT, "paper_1304_4235_amd", "csrc")
     cmd = ["g++", "-std=c++17", *SAN, "-D__HIP_PLATFORM_AMD__", "-I/opt/rocm/include",
            "-I" + os.path.join(ROOT, "include"), "-I" + csrc,
-           os.path.join(HOST, "grid_check.cpp"), "-L/opt/rocm/lib", "-lamdhip64",
+           os.path.join(HOST, name + ".cpp"), "-L/opt/rocm/lib", "-lamdhip64",
            "-Wl,-rpath,/opt/rocm/lib", "-o", exe]
-    assert "grid checks passed" in _run(cmd, exe, tmp_path)
+    assert says in _run(cmd, exe, tmp_path)
 
 
 @pytest.mark.skipif(shutil.which("gcc") is None, reason="needs gcc")
