@@ -12,6 +12,7 @@
 // those of the plain product over the recorded paths up to FP64 summation
 // order (the same products, assigned to lanes in groups of four).
 #include "internal.h"
+#include "segment.h"
 
 #include <vector>
 
@@ -29,45 +30,125 @@ __device__ inline uint32_t hash_slot(uint32_t j)
     return (j * 2654435761u) >> (32 - kHashBits);
 }
 
-// Insert every particle index of the tile's entries into the LDS set; *count
-// receives the number of distinct indices, or stops growing once it passes
-// kTileMaxSet (the caller treats that as overflow).
-__device__ void tile_collect(uint32_t* tab, uint32_t* count, const int2* __restrict__ path,
-                             uint64_t a, uint64_t b)
+// A tile of rows r0..r1 - 1 (row = k n + p) over the packets whose rows it holds.
+struct Tile {
+    int64_t r0, r1, pk0, pk1;             // its packets, the last one included
+};
+
+__device__ __forceinline__ Tile tile_of(int64_t t, int tile_rows, int64_t n_rows, int n)
 {
-    for (int i = threadIdx.x; i < kHashSlots; i += blockDim.x) tab[i] = kEmpty;
-    if (threadIdx.x == 0) *count = 0;
+    Tile T;
+    const int64_t wpd = (n + 63) / 64;
+    T.r0 = t * tile_rows;
+    T.r1 = T.r0 + tile_rows < n_rows ? T.r0 + tile_rows : n_rows;
+    T.pk0 = T.r0 / n * wpd + T.r0 % n / 64;
+    T.pk1 = (T.r1 - 1) / n * wpd + (T.r1 - 1) % n / 64;
+    return T;
+}
+
+// the rays of a packet that are rows of the tile: lo..hi - 1
+__device__ __forceinline__ void tile_rays(const Tile& T, int64_t pk, int n, int64_t* row0, int* lo,
+                                          int* hi)
+{
+    const int64_t wpd = (n + 63) / 64, k = pk / wpd, p0 = (pk - k * wpd) * 64;
+    *row0 = k * n + p0;
+    int64_t h = n - p0 < 64 ? n - p0 : 64;
+    if (T.r1 - *row0 < h) h = T.r1 - *row0;
+    *lo = T.r0 > *row0 ? (int)(T.r0 - *row0) : 0;
+    *hi = (int)h;
+}
+
+constexpr int kBuildWaves = kBuildBlock / 64;
+
+// LDS of a block: the hash set, and per wave which of a segment's slots the tile's
+// rays hit, or (entries) one segment in ray order.
+struct alignas(16) TileLds {
+    uint32_t tab[kHashSlots];
+    union {
+        uint8_t hit[kBuildWaves][kSegSlots];
+        struct {
+            float fac[4 * (kSegGroups + kSegGroups / 8)];
+            uint32_t abc[kSegGroups];
+            uint16_t dr[kSegGroups];
+            uint16_t id[kSegSlots];       // a slot's particle in the tile's set
+            // per ray, of this and the next segment in turn: where its next entry
+            // goes, its first group and its entries
+            uint64_t to[2][kRayPacket];
+            uint32_t first[2][kRayPacket], cnt[2][kRayPacket];
+        } seg;
+    };
+    uint32_t count;
+};
+
+// The particles of the tile's entries into the LDS set; S.count receives the number
+// of distinct ones, or stops growing once it passes kTileMaxSet (the caller treats
+// that as overflow).  A wave per segment marks the slots that the tile's rays hit
+// and inserts their particles: a slot is some 0.4 of the entries, and the factors
+// are not read.
+__device__ void tile_collect(TileLds& S, const Tile& T, const uint64_t* __restrict__ unit_seg,
+                             const uint64_t* __restrict__ seg_off,
+                             const uint4* __restrict__ packed, int parts, int n)
+{
+    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+    for (int i = threadIdx.x; i < kHashSlots; i += blockDim.x) S.tab[i] = kEmpty;
+    if (threadIdx.x == 0) S.count = 0;
     __syncthreads();
-    for (uint64_t e = a + threadIdx.x; e < b; e += blockDim.x) {
-        if (*(volatile uint32_t*)count > (uint32_t)kTileMaxSet) break;
-        const uint32_t j = (uint32_t)path[e].x;
-        uint32_t s = hash_slot(j);
-        for (int probe = 0; probe < kHashSlots; ++probe) {
-            const uint32_t prev = atomicCAS(&tab[s], kEmpty, j);
-            if (prev == kEmpty) {
-                atomicAdd(count, 1u);
-                break;
-            }
-            if (prev == j) break;
-            s = (s + 1) & (kHashSlots - 1);
+    const uint64_t end = unit_seg[(T.pk1 + 1) * parts];
+    const uint64_t first_end = unit_seg[(T.pk0 + 1) * parts];     // of the first packet
+    const uint64_t last = unit_seg[T.pk1 * parts];                // the last one's first
+    uint8_t* hit = S.hit[wv];
+    for (uint64_t sg = unit_seg[T.pk0 * parts] + wv; sg < end; sg += kBuildWaves) {
+        if (__builtin_amdgcn_readfirstlane(*(volatile uint32_t*)&S.count) >
+            (uint32_t)kTileMaxSet)
+            break;
+        const Segment g = segment_at(packed + seg_off[sg]);
+        // (packets between the first and the last are rows of the tile as a whole)
+        int64_t row0;
+        int lo = 0, hi = 64, q;
+        if (sg < first_end) tile_rays(T, T.pk0, n, &row0, &lo, &q);
+        if (sg >= last) tile_rays(T, T.pk1, n, &row0, &q, &hi);
+        for (int i = lane; i < kSegSlots / 16; i += 64)
+            reinterpret_cast<uint4*>(hit)[i] = make_uint4(0u, 0u, 0u, 0u);
+        wave_sync();
+        for (uint32_t at = lane; at < g.n_groups; at += 64) {
+            const uint32_t a = g.abc[at], d = g.dr[at];
+            const int ray = (int)(d >> 10);
+            if (ray < lo || ray >= hi) continue;
+            hit[a & 1023u] = 1;
+            hit[(a >> 10) & 1023u] = 1;
+            hit[(a >> 20) & 1023u] = 1;
+            hit[d & 1023u] = 1;
         }
+        wave_sync();
+        for_slots(g, lane, (uint32_t)lane < g.n_vis ? g.vis[lane] : 0u, [&](uint32_t slot, int j) {
+            if (!hit[slot]) return;
+            uint32_t s = hash_slot((uint32_t)j);
+            for (int probe = 0; probe < kHashSlots; ++probe) {
+                const uint32_t prev = atomicCAS(&S.tab[s], kEmpty, (uint32_t)j);
+                if (prev == kEmpty) {
+                    atomicAdd(&S.count, 1u);
+                    break;
+                }
+                if (prev == (uint32_t)j) break;
+                s = (s + 1) & (kHashSlots - 1);
+            }
+        });
+        wave_sync();
     }
     __syncthreads();
 }
 
 // distinct particles per tile (kTileMaxSet + 1 marks a tile that overflowed)
 __global__ void __launch_bounds__(kBuildBlock)
-k_tile_count(const uint64_t* __restrict__ row_off, const int2* __restrict__ path, int64_t n_rows,
-             int tile_rows, int64_t n_tiles, uint64_t* __restrict__ tile_u)
+k_tile_count(const uint64_t* __restrict__ unit_seg, const uint64_t* __restrict__ seg_off,
+             const uint4* __restrict__ packed, int parts, int n, int64_t n_rows, int tile_rows,
+             int64_t n_tiles, uint64_t* __restrict__ tile_u)
 {
-    __shared__ uint32_t tab[kHashSlots];
-    __shared__ uint32_t count;
+    __shared__ TileLds S;
     for (int64_t t = blockIdx.x; t < n_tiles; t += gridDim.x) {
-        const int64_t r0 = t * tile_rows;
-        const int64_t r1 = r0 + tile_rows < n_rows ? r0 + tile_rows : n_rows;
-        tile_collect(tab, &count, path, row_off[r0], row_off[r1]);
+        tile_collect(S, tile_of(t, tile_rows, n_rows, n), unit_seg, seg_off, packed, parts, n);
         if (threadIdx.x == 0)
-            tile_u[t] = count > (uint32_t)kTileMaxSet ? (uint64_t)kTileMaxSet + 1 : count;
+            tile_u[t] = S.count > (uint32_t)kTileMaxSet ? (uint64_t)kTileMaxSet + 1 : S.count;
         __syncthreads();
     }
 }
@@ -81,30 +162,39 @@ __device__ __forceinline__ uint32_t slot_id(const uint32_t* occ, const uint32_t*
     return pre[s >> 5] + __popc(occ[s >> 5] & ((1u << (s & 31)) - 1u));
 }
 
+// The entries come from the segments, so that nothing but the tiles (6 B per
+// intersection) is needed beside the recorded paths: the block takes one segment at a
+// time through LDS into ray order, as k_path_rows does, with its slots looked up once
+// in the set.  Bound by a segment's chain of steps, one block being all that the set's
+// LDS leaves room for.  Measured on MI355X, the 2.1M-particle field's 7.3e9
+// intersections, ms: paths by rows expanded, counted and built from 31, 36 and 61 (8 B
+// per intersection more); here 20 and 72 (76 without loading ahead), and 4 for the
+// rows' sizes in both.
 __global__ void __launch_bounds__(kBuildBlock)
-k_tile_build(const uint64_t* __restrict__ row_off, const int2* __restrict__ path, int64_t n_rows,
-             int tile_rows, int64_t n_tiles, const uint64_t* __restrict__ set_off,
-             uint32_t* __restrict__ set, uint16_t* __restrict__ idx, float* __restrict__ fac)
+k_tile_build(const uint64_t* __restrict__ unit_seg, const uint64_t* __restrict__ seg_off,
+             const uint4* __restrict__ packed, int parts, int n,
+             const uint64_t* __restrict__ row_off, int64_t n_rows, int tile_rows, int64_t n_tiles,
+             const uint64_t* __restrict__ set_off, uint32_t* __restrict__ set,
+             uint16_t* __restrict__ idx, float* __restrict__ fac)
 {
     constexpr int kWords = kHashSlots / 32;           // 1024 bitmap words
-    __shared__ uint32_t tab[kHashSlots];
+    __shared__ TileLds S;
     __shared__ uint32_t occ[kWords];
     __shared__ uint32_t pre[kWords];
-    __shared__ uint32_t count;
-    for (int64_t t = blockIdx.x; t < n_tiles; t += gridDim.x) {
-        const int64_t r0 = t * tile_rows;
-        const int64_t r1 = r0 + tile_rows < n_rows ? r0 + tile_rows : n_rows;
-        const uint64_t a = row_off[r0], b = row_off[r1];
-        tile_collect(tab, &count, path, a, b);
-        for (int w = threadIdx.x; w < kWords; w += blockDim.x) {
+    const uint32_t t = threadIdx.x;
+    const int lane = t & 63;
+    for (int64_t tile = blockIdx.x; tile < n_tiles; tile += gridDim.x) {
+        const Tile T = tile_of(tile, tile_rows, n_rows, n);
+        tile_collect(S, T, unit_seg, seg_off, packed, parts, n);
+        for (int w = t; w < kWords; w += blockDim.x) {
             uint32_t m = 0;
             for (int q = 0; q < 32; ++q)
-                if (tab[32 * w + q] != kEmpty) m |= 1u << q;
+                if (S.tab[32 * w + ((q + w) & 31)] != kEmpty) m |= 1u << ((q + w) & 31);
             occ[w] = m;
         }
         __syncthreads();
-        if (threadIdx.x < 64) {                       // one wave: 16 words per lane
-            const int l = threadIdx.x;
+        if (t < 64) {                                 // one wave: 16 words per lane
+            const int l = t;
             uint32_t loc[kWords / 64];
             uint32_t sum = 0;
             for (int q = 0; q < kWords / 64; ++q) {
@@ -120,19 +210,98 @@ k_tile_build(const uint64_t* __restrict__ row_off, const int2* __restrict__ path
             for (int q = 0; q < kWords / 64; ++q) pre[l * (kWords / 64) + q] = base + loc[q];
         }
         __syncthreads();
-        const uint64_t so = set_off[t];
-        for (int sl = threadIdx.x; sl < kHashSlots; sl += blockDim.x) {
-            const uint32_t key = tab[sl];
+        const uint64_t so = set_off[tile];
+        for (int sl = t; sl < kHashSlots; sl += blockDim.x) {
+            const uint32_t key = S.tab[sl];
             if (key != kEmpty) set[so + slot_id(occ, pre, (uint32_t)sl)] = key;
         }
-        for (uint64_t e = a + threadIdx.x; e < b; e += blockDim.x) {
-            const int2 h = path[e];
-            const uint32_t j = (uint32_t)h.x;
-            uint32_t sl = hash_slot(j);
-            for (int probe = 0; probe < kHashSlots && tab[sl] != j; ++probe)
-                sl = (sl + 1) & (kHashSlots - 1);
-            idx[e] = (uint16_t)slot_id(occ, pre, sl);
-            fac[e] = __int_as_float(h.y);
+        static_assert(kSegGroups <= kBuildBlock, "a thread per group");
+        // The next segment's visits and groups (one to a thread) are loaded while one
+        // is placed, the header after it too.
+        uint64_t sg = unit_seg[T.pk0 * parts];
+        const uint64_t end = unit_seg[(T.pk1 + 1) * parts];
+        uint4 h = make_uint4(0u, 0u, 0u, 0u), h1 = h;
+        uint64_t o = 0, o1 = 0, o2 = 0;
+        float4 f = make_float4(0.f, 0.f, 0.f, 0.f);
+        uint32_t a = 0, d = 0, w = 0;
+        auto load = [&](uint64_t off, const uint4 head) {
+            const Segment g = segment_of(packed + off, head);
+            w = (uint32_t)lane < g.n_vis ? g.vis[lane] : 0u;
+            if (t >= g.n_groups) return;
+            f = g.fac[t];
+            a = g.abc[t];
+            d = g.dr[t];
+        };
+        if (sg < end) {
+            o = seg_off[sg];
+            h = packed[o];
+            if (sg + 1 < end) o1 = seg_off[sg + 1], h1 = packed[o1];
+            if (sg + 2 < end) o2 = seg_off[sg + 2];
+            load(o, h);
+        }
+        int cur = 0, lo = 0, hi = 0;
+        int64_t pk = T.pk0 - 1;
+        for (uint64_t pk_end = sg; sg < end; ++sg) {
+            if (sg >= pk_end) {                       // the next packet with segments
+                do pk_end = unit_seg[(++pk + 1) * parts];
+                while (sg >= pk_end);
+                int64_t row0;
+                tile_rays(T, pk, n, &row0, &lo, &hi);
+                if (t < (uint32_t)kRayPacket) {
+                    S.seg.to[cur][t] = (int)t >= lo && (int)t < hi ? row_off[row0 + t] : 0ull;
+                    S.seg.first[cur][t] = ~0u;
+                    S.seg.cnt[cur][t] = 0u;
+                }
+                __syncthreads();
+            }
+            const Segment g = segment_of(packed + o, h);
+            // (a gap after every eight groups spreads a lane's run over the banks)
+            if (t < g.n_groups) {
+                const uint32_t e = group_at(t, g.n_groups);
+                *reinterpret_cast<float4*>(S.seg.fac + 4 * (e + (e >> 3))) = f;
+                S.seg.abc[e] = a;
+                S.seg.dr[e] = (uint16_t)d;
+                atomicMin(&S.seg.first[cur][d >> 10], e);
+                atomicAdd(&S.seg.cnt[cur][d >> 10], (a >> 30) + 1u);
+            }
+            for_slots(g, lane, w, [&](uint32_t slot, int j) {
+                uint32_t sl = hash_slot((uint32_t)j);
+                uint32_t key = S.tab[sl];
+                for (int probe = 1; probe < kHashSlots && key != (uint32_t)j && key != kEmpty;
+                     ++probe) {
+                    sl = (sl + 1) & (kHashSlots - 1);
+                    key = S.tab[sl];
+                }
+                // (a particle that no ray of the tile hits has no place)
+                S.seg.id[slot] = key == (uint32_t)j ? (uint16_t)slot_id(occ, pre, sl) : 0;
+            }, t >> 6, kBuildWaves);
+            __syncthreads();
+            if (sg + 1 < end) {
+                o = o1;
+                h = h1;
+                load(o, h);
+                if (sg + 2 < end) {
+                    o1 = o2;
+                    h1 = packed[o1];
+                    if (sg + 3 < end) o2 = seg_off[sg + 3];
+                }
+            }
+            for (uint32_t x = t; x < 4 * g.n_groups; x += kBuildBlock) {
+                const uint32_t e = x >> 2, q = x & 3u;
+                const uint32_t ea = S.seg.abc[e], ed = S.seg.dr[e], ray = ed >> 10;
+                if (q > (ea >> 30) || (int)ray < lo || (int)ray >= hi) continue;
+                const uint32_t slot = (q == 3u ? ed : ea >> (10 * q)) & 1023u;
+                const uint64_t at = S.seg.to[cur][ray] + 4u * (e - S.seg.first[cur][ray]) + q;
+                idx[at] = S.seg.id[slot];
+                fac[at] = S.seg.fac[4 * (e + (e >> 3)) + q];
+            }
+            if (t < (uint32_t)kRayPacket) {
+                S.seg.to[cur ^ 1][t] = S.seg.to[cur][t] + S.seg.cnt[cur][t];
+                S.seg.first[cur ^ 1][t] = ~0u;
+                S.seg.cnt[cur ^ 1][t] = 0u;
+            }
+            __syncthreads();
+            cur ^= 1;
         }
         __syncthreads();
     }
@@ -308,13 +477,8 @@ hipError_t build_tiles(Ctx& c)
     int rows = 16;
     while (rows < 4096 && (double)rows * 2.0 * mean <= 65536.0) rows *= 2;
     std::vector<uint64_t> u;
-    // the tiles are built from the paths by rows, expanded for the while
+    const int parts = path_parts(c);
     hipError_t e = ensure_row_offsets(c);
-    const bool held = c.path != nullptr;
-    if (e == hipSuccess && !held) {
-        e = ws_alloc(c, &c.path, (size_t)m + kPathPad, kRegionPath);
-        if (e == hipSuccess) e = launch_expand_rows(c, c.path);
-    }
     for (; e == hipSuccess && rows >= 16; rows /= 2) {
         const int64_t nt = (n_rows + rows - 1) / rows;
         if (nt > (int64_t(1) << 24)) break;
@@ -322,8 +486,8 @@ hipError_t build_tiles(Ctx& c)
         if (e != hipSuccess) break;
         uint64_t* d_u = c.tile_off;
         hipLaunchKernelGGL(k_tile_count, dim3((unsigned)std::min<int64_t>(nt, 2048)),
-                           dim3(kBuildBlock), 0, c.stream, c.row_off, c.path, n_rows, rows, nt,
-                           d_u);
+                           dim3(kBuildBlock), 0, c.stream, c.unit_seg, c.seg_off, c.packed, parts,
+                           (int)c.n, n_rows, rows, nt, d_u);
         e = hipGetLastError();
         if (e != hipSuccess) break;
         u.assign(nt + 1, 0);
@@ -349,8 +513,9 @@ hipError_t build_tiles(Ctx& c)
             if (e == hipSuccess) e = ws_alloc(c, &c.tile_fac, m + kPathPad, kRegionPath);
             if (e != hipSuccess) break;                 // keep the plain product
             hipLaunchKernelGGL(k_tile_build, dim3((unsigned)std::min<int64_t>(nt, 2048)),
-                               dim3(kBuildBlock), 0, c.stream, c.row_off, c.path, n_rows, rows,
-                               nt, d_u, c.tile_set, c.tile_idx, c.tile_fac);
+                               dim3(kBuildBlock), 0, c.stream, c.unit_seg, c.seg_off, c.packed,
+                               parts, (int)c.n, c.row_off, n_rows, rows, nt, d_u, c.tile_set,
+                               c.tile_idx, c.tile_fac);
             e = hipGetLastError();
             if (e == hipSuccess) e = hipStreamSynchronize(c.stream);
             if (e != hipSuccess) break;
@@ -363,7 +528,6 @@ hipError_t build_tiles(Ctx& c)
             break;
         }
     }
-    if (!held) ws_free(c, &c.path);
     if (!c.tiles_valid) {
         free_tiles(c);
         c.tiles_unfit = true;

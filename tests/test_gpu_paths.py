@@ -179,3 +179,59 @@ def test_least_buffer_holds_a_lone_rays_many_visits(l_ray, n_ray):
         out.append(N.cpu().numpy())
         s.close()
     np.testing.assert_array_equal(out[0], out[1])
+
+
+def _tile_case(which):
+    if which == "long":                      # over 2000 hits a ray: 16 rows to a tile
+        return W.uniform_lattice(n_side_lattice=5, box=20.0, l_ray=700.0), 0
+    if which == "mid":                       # a packet in two tiles of 32 rows
+        return W.uniform_lattice(n_side_lattice=5, box=20.0, l_ray=300.0), 0
+    return _case(which)
+
+
+@pytest.mark.parametrize("which", ["one", "packet_less_one", "packet", "packet_plus_one", "visits",
+                                   "slots", "no_hits", "images", "field", "mid", "long"])
+def test_row_tiles_hold_the_recorded_paths(which):
+    """Row tiles whose rows begin and end inside packets and directions: columns
+    over the tiles against the recorded paths' (the same products in another FP64
+    order: 1e-11, as above), and the reverse mode's sums over the tiles against
+    the gather over the transposed paths."""
+    from paper_1304_4235_amd import Solver
+    wl, leaf = _tile_case(which)
+    x = torch.tensor(np.random.default_rng(4).uniform(1e-6, 1.0, wl.n))
+    s = Solver.from_workload(wl, leaf_size=leaf, record_paths=1)
+    s.set_state(x)
+    N, hits = s.compute_columns()
+    N = N.clone()
+    s.set_tuning(tiles=1)
+    for _ in range(10):
+        s.set_state(x)
+        got, h = s.compute_columns()
+    assert h == hits and s.timing()["tile_set_total"] > 0
+    np.testing.assert_allclose(got.cpu().numpy(), N.cpu().numpy(), rtol=1e-11, atol=0)
+    s.set_tuning(tiles=0)
+    g = torch.ones(wl.n, dtype=torch.float64, device="cuda")
+    dn = []
+    for mode in (0, 2):
+        s.set_tuning(adjoint_scatter=mode)
+        s.forward(2)
+        dn.append(s.backward(g, None)[1].cpu().numpy())
+    np.testing.assert_allclose(dn[1], dn[0], rtol=1e-9, atol=1e-12 * np.abs(dn[0]).max())
+    s.close()
+
+
+def test_row_tiles_need_six_bytes_beside_the_paths():
+    """The reverse mode's scatter over row tiles runs where the path buffer holds
+    the paths and 7 bytes per intersection: nothing else is laid out beside them
+    while the tiles are built."""
+    from paper_1304_4235_amd import Solver
+    wl = W.isothermal_halo(n=8192, n_bins=8, seed=46)
+    s = Solver.from_workload(wl, record_paths=1)
+    need = s.count_paths()
+    s.close()
+    s = Solver.from_workload(wl, record_paths=1, path_budget=need["bytes_paths"] + 7 * need["hits"])
+    s.set_tuning(keep_columns=0, adjoint_scatter=2)
+    lnG, x = s.forward(2)
+    s.backward(torch.ones_like(lnG), None)
+    assert s.timing()["tile_set_total"] > 0
+    s.close()
