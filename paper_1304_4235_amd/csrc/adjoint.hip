@@ -172,10 +172,11 @@ k_adj_wbins(const double* __restrict__ N, const double* __restrict__ pis,
     const int wv = threadIdx.x >> 6;
     const int groups = (n_bins + 63) / 64;
     const uint64_t lt = lane ? (~0ull >> (64 - lane)) : 0ull;
-    const int64_t items = (n + kAdjChunk - 1) / kAdjChunk * groups;
-    for (int64_t it = blockIdx.x; it < items; it += gridDim.x) {
-    const int64_t chunk = it / groups;
-    const int b = (int)(it - chunk * groups) * 64 + lane;
+    // (at most 2^19 chunks of 64 groups of bins)
+    const uint32_t items = (uint32_t)((n + kAdjChunk - 1) / kAdjChunk) * (uint32_t)groups;
+    for (uint32_t it = blockIdx.x; it < items; it += gridDim.x) {
+    const int64_t chunk = it / (uint32_t)groups;
+    const int b = (int)(it % (uint32_t)groups) * 64 + lane;
     const float ds = b < n_bins ? dsig_l2[b] : 0.0f;
     const int64_t i = chunk * kAdjChunk + threadIdx.x;
     const bool in = i < n;
