@@ -142,9 +142,6 @@ struct TraceGeom {
     // column evaluations only: rays of sources with want[p] == 0 are skipped
     // (their columns keep their previous values); null = every source
     const uint8_t* want;
-    // column evaluations only: set while a batch of sweeps runs; once it holds
-    // something, columns keep their values
-    const unsigned long long* stop;
     double L;              // segment length
     double box;            // periodic side, 0 = isolated
     double plo[3], phi[3]; // bounds of particle positions
@@ -205,7 +202,7 @@ enum {
     kRedSlots = 13
 };
 // Sweeps of a fixed number that run between the host's looks at their results.
-// Those after one that raised an error write no column, rate or state (geom.stop),
+// Those after one that raised an error write no column, rate or state (batch_stop),
 // so what the caller finds is that sweep's.
 constexpr int kSweepBatch = 32;
 
@@ -402,6 +399,7 @@ struct Ctx {
     // set by a sweep that raised an error (a line of its own, which no sweep
     // without an error writes)
     unsigned long long* stop = nullptr;
+    const unsigned long long* batch_stop = nullptr;   // the same while a batch of sweeps runs
     unsigned long long* red_host = nullptr;  // pinned
     unsigned long long* sweep_host = nullptr;    // behind it: sweep_red's copy
     // per sweep of the last rrt_iterate_equilibrium: max |dx| and the

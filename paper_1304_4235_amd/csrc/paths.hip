@@ -544,7 +544,7 @@ void launch_columns_as(Ctx& c, int W)
     auto go = [&](auto kernel, int64_t blocks, int threads) {
         hipLaunchKernelGGL(kernel, dim3((unsigned)blocks), dim3(threads), 0, c.stream, c.unit_seg,
                            c.seg_off, c.packed, path_parts(c), c.mux_s, pk, c.N_s, (int)c.n,
-                           c.geom.seg_of, c.geom.seg_active, c.geom.want, c.geom.stop, c.Nn_s,
+                           c.geom.seg_of, c.geom.seg_active, c.geom.want, c.batch_stop, c.Nn_s,
                            c.mu_s);
     };
     if (W == 1) go(k_path_columns<NF, 1, STREAM>, (pk + kWaves - 1) / kWaves, kBlock);
@@ -856,7 +856,7 @@ hipError_t launch_row_columns(Ctx& c, int group)
     auto go = [&](auto kernel, int g) {
         hipLaunchKernelGGL(kernel, dim3(stride_blocks(n_iter, kBlock / g)), dim3(kBlock), 0,
                            c.stream, c.row_off, c.path, c.mux_s, n_rows, c.N_s, c.n, c.row_frozen,
-                           c.row_list, c.row_list_n, c.geom.stop);
+                           c.row_list, c.row_list_n, c.batch_stop);
     };
     if (group == 64) go(k_row_columns<64>, 64);
     else if (group == 32) go(k_row_columns<32>, 32);

@@ -529,7 +529,7 @@ hipError_t launch_gamma(Ctx& c, bool update_x, bool first_sweep)
     // a density block's list leaves out what the mask would, but the frozen ones
     rule.want = c.row_list ? nullptr : c.geom.want;
     rule.frozen = c.row_list ? c.row_frozen : nullptr;
-    rule.stop = c.geom.stop;
+    rule.stop = c.batch_stop;
     rule.skip = (first_sweep && c.rule_tau_skip > 0.0) ? c.skip_s : nullptr;
     rule.tau_skip = c.rule_tau_skip;
     rule.tau_case_b = c.rule_tau_case_b;
@@ -594,9 +594,10 @@ __global__ void k_keep_sweep(unsigned long long* __restrict__ red,
 {
     const int t = threadIdx.x;
     if (t >= kRedSlots) return;
-    out[t] = red[t];
+    const unsigned long long v = red[t];
+    out[t] = v;
     if (t < kRedInput) red[t] = 0ull;
-    else if (t <= kRedNumeric && out[t]) *stop = 1ull;
+    if (t >= kRedInput && t <= kRedNumeric && v) *stop = 1ull;
 }
 
 // particles of block `block` of the density order that are not frozen

@@ -1263,7 +1263,6 @@ int rrt_build_tree(rrt_ctx* x)
     g.seg_end = segmented ? c.seg_end : nullptr;
     g.seg_active = nullptr;
     g.want = nullptr;
-    g.stop = nullptr;
     c.blocks_for = 0;            // the density blocks are in tree order
     HIP_OK(launch_init_state(c, c.x_init_given));
     ev_end(c, eb, &c.t_build);
@@ -1382,7 +1381,7 @@ struct WantGuard {
     {
         if (!done) (void)hipMemsetAsync(c.stop, 0, sizeof *c.stop, c.stream);
         c.geom.want = nullptr;
-        c.geom.stop = nullptr;
+        c.batch_stop = nullptr;
         c.row_list = nullptr;
         c.row_list_n = 0;
         c.row_frozen = nullptr;
@@ -1479,7 +1478,7 @@ int rrt_iterate_equilibrium(rrt_ctx* x, int32_t max_iter, double tol, double* x_
     // sweep with an error the rest of its batch changes nothing.
     HIP_OK(hipMemsetAsync(c.red, 0, kRedInput * sizeof(unsigned long long), c.stream));
     const int batch = tol > 0.0 ? 1 : kSweepBatch;
-    c.geom.stop = batch > 1 ? c.stop : nullptr;
+    c.batch_stop = batch > 1 ? c.stop : nullptr;
     int64_t hits_of[kSweepBatch];
     int launched = 0;                         // sweeps whose slots are still to be read
     for (it = 0; it < max_iter;) {

@@ -440,7 +440,7 @@ hipError_t launch_tiles_g(Ctx& c, int64_t n_rows, unsigned nb, size_t lds)
     hipLaunchKernelGGL(k_tile_columns<G>, dim3(nb), dim3(512), lds, c.stream, c.row_off,
                        c.tile_idx, c.tile_fac, c.tile_off, c.tile_set, c.mux_s, n_rows,
                        c.tile_rows, c.n_tiles, c.N_s, c.n, c.geom.seg_of, c.geom.seg_active,
-                       c.geom.want, c.geom.stop);
+                       c.geom.want, c.batch_stop);
     return hipGetLastError();
 }
 

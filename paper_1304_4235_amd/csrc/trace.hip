@@ -117,6 +117,7 @@ struct RayOut {
     // counters, kQueueStride apart, each over its share of the sources; null =
     // one wave per unit
     unsigned long long* queue;
+    const unsigned long long* stop;   // column mode: holds something: nothing is written
 };
 
 // Place of tree position ps among the sorted sampled sources, or -1.
@@ -139,7 +140,7 @@ k_trace(const Node* __restrict__ nodes, const float4* __restrict__ p4,
         const KernelTables* __restrict__ tabs, TraceGeom g, RayOut out)
 {
     __shared__ float4 t_erf[kTabIntervals];
-    if (MODE == kModeColumn && g.stop && *g.stop != 0ull) return;    // the whole grid
+    if (MODE == kModeColumn && out.stop && *out.stop != 0ull) return;    // the whole grid
     constexpr bool kTerms = MODE != kModeCount;
     if (kTerms) {
         for (int i = threadIdx.x; i < kTabIntervals; i += blockDim.x) t_erf[i] = tabs->erf_t[i];
@@ -387,7 +388,8 @@ k_trace_wave(const Node* __restrict__ nodes, const float4* __restrict__ leaf_bal
     constexpr bool kCountOnly = MODE == kModeCount || MODE == kModeStats;
     constexpr bool kTerms = mode_factors(MODE);
     extern __shared__ __align__(16) unsigned char s_dyn[];
-    if (MODE == kModeColumn && g.stop && *g.stop != 0ull) return;    // the whole grid
+    // the whole grid (the queues of the persistent form are spent then)
+    if (MODE == kModeColumn && !PQ && out.stop && *out.stop != 0ull) return;
     const int lane = threadIdx.x & 63;
     const int wv = threadIdx.x >> 6;
     const int n_wv = blockDim.x >> 6;
@@ -923,9 +925,12 @@ k_trace_wave(const Node* __restrict__ nodes, const float4* __restrict__ leaf_bal
 
 #pragma clang fp contract(on)
 
-__global__ void k_zero_queues(unsigned long long* p)
+// Every queue from its start, or spent where a column evaluation is stopped (the
+// walk itself reads no more than its queues: the test there cost it 2%).
+__global__ void k_zero_queues(unsigned long long* p, const unsigned long long* stop)
 {
-    if (threadIdx.x < kQueues) p[(size_t)threadIdx.x * kQueueStride] = 0ull;
+    const unsigned long long from = stop && *stop != 0ull ? 1ull << 31 : 0ull;
+    if (threadIdx.x < kQueues) p[(size_t)threadIdx.x * kQueueStride] = from;
 }
 
 }  // namespace
@@ -950,7 +955,8 @@ static void launch_wave_nf(Ctx& c, RayOut o, int bs, size_t lds, int64_t waves)
     constexpr bool kQueued = MODE == kModeColumn || MODE == kModeCount || mode_logs(MODE);
     if (kQueued && c.packet_queue && o.unit_end == 0) {
         // a kernel, not a memset, clears the counters (the launch may be captured)
-        hipLaunchKernelGGL(k_zero_queues, dim3(1), dim3(64), 0, c.stream, c.queue);
+        hipLaunchKernelGGL(k_zero_queues, dim3(1), dim3(64), 0, c.stream, c.queue,
+                           o.stop);
         o.queue = c.queue;
         int per_cu = 0, cus = 0, dev = 0;
         if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k_trace_wave<MODE, NF, kQueued>,
@@ -1016,6 +1022,7 @@ hipError_t launch_columns(Ctx& c)
     o.near_far = c.near_far;
     o.Nn = c.Nn_s;
     o.mu = c.mu_s;
+    o.stop = c.batch_stop;
     return launch_mode(c, kModeColumn, o);
 }
 
