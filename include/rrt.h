@@ -369,7 +369,7 @@ int rrt_iterate_halos(rrt_ctx* ctx, int32_t max_iter, double tol, int32_t per_la
  *   RRT_TUNE_ADJOINT      transposed column product of rrt_backward over
  *                         recorded paths: 0 (default) = gather over paths
  *                         transposed once per geometry when they fit in the
- *                         path buffer (24 bytes per intersection beside the
+ *                         path buffer (25 bytes per intersection beside the
  *                         paths while they are built; deterministic), else per row tile in LDS with one
  *                         atomic add per distinct particle of a tile (when the
  *                         tiles fit), else one atomic add per intersection;

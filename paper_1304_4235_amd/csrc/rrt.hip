@@ -1683,7 +1683,7 @@ int rrt_backward(rrt_ctx* x, const double* dL_dlnG, const double* dL_dx, double*
         }
         HIP_OK(launch_adj_rate(c, Nk, (k == K && dL_dlnG) ? c.adj_lup : nullptr));
         if (c.paths_valid && !c.tpaths_valid && !c.tpaths_unfit && c.adj_scatter == 0) {
-            // transposed paths (8 B per intersection) plus sort scratch (24 B)
+            // transposed paths (8 B per intersection) plus sort scratch (17 B)
             // in the path buffer, when they fit beside the paths
             const hipError_t e = build_transposed_paths(c);
             if (e == hipSuccess) c.tpaths_valid = true;

@@ -281,9 +281,12 @@ class Solver:
         budget = self.path_budget or int(0.6 * (self._free_bytes() + have))
         need, one = cnt["bytes_paths"], cnt["bytes_one_walk"]
         # room for the one-walk log and, after it, for the reverse mode's
-        # transposed paths (24 bytes per intersection while they are built,
-        # beside the paths) and its kept columns
-        want = max(one, need, 40 * cnt["hits"])
+        # transposed paths (8 bytes per intersection; keys, values and counts of
+        # their sort take 17 more while they are built) beside the paths, whose own
+        # size per intersection depends on how many a ray has; what is left of 32
+        # takes some iterations' kept columns
+        hits = cnt["hits"]
+        want = max(one, 40 * hits, need + 32 * hits + 8 * (self.n + 1) + (1 << 16))
         if self.record_paths == 1:
             # required: at least the paths, unless an explicit budget says no
             # (then the library reports RRT_E_WORKSPACE)

@@ -526,3 +526,32 @@ def test_transposed_paths_fit_an_exact_workspace():
     np.testing.assert_array_equal(out[0][0], out[1][0])
     np.testing.assert_array_equal(out[0][1], out[1][1])
     s.close()
+
+
+def test_default_buffer_holds_the_transposed_paths_of_sparse_rays():
+    """Rays with one or two intersections, whose paths take twice the bytes of the
+    usual: the binding's own buffer still has room for the transposed paths, so
+    the reverse mode takes neither the row tiles nor the atomic scatter (the
+    gradients repeat bit for bit)."""
+    from paper_1304_4235_amd import Solver, healpix_dirs
+    rng = np.random.default_rng(3)
+    n = 900_000
+    s = Solver(l_ray=0.05, box=0.0)
+    s.set_particles(rng.uniform(0, 100, (n, 3)).astype(np.float32), np.full(n, 0.55, np.float32),
+                    np.full(n, 1e18, np.float32), rng.uniform(0.5, 2, n).astype(np.float32),
+                    np.full(n, 1e4, np.float32))
+    s.set_rays(healpix_dirs(1))
+    s.set_spectrum(np.array([6.3e-18, 1e-18]), np.array([1e5, 1e5]))
+    s.build_tree()
+    hits = s.count_paths()["hits"]
+    assert hits < 2.5 * n * 12
+    out = []
+    for _ in range(2):
+        lnG, x = s.forward(1)
+        dw, dn = s.backward(torch.ones_like(lnG), None)
+        assert s.timing()["tile_set_total"] == -1
+        out.append((dw, dn.cpu().numpy()))
+    assert s.workspace_info()["path_used"] > 8 * hits
+    np.testing.assert_array_equal(out[0][0], out[1][0])
+    np.testing.assert_array_equal(out[0][1], out[1][1])
+    s.close()
