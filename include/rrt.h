@@ -360,7 +360,9 @@ int rrt_iterate_halos(rrt_ctx* ctx, int32_t max_iter, double tol, int32_t per_la
 /* Launch knobs for the autotuner (results never change, only speed):
  *   RRT_TUNE_TRACE_BLOCK  threads per block of the traversal (64, 128, 192, 256)
  *   RRT_TUNE_PACKET       rays walking one node sequence: 64 (a wave-cooperative
- *                         packet, default) or 1 (independent lanes)
+ *                         packet, default) or 1 (independent lanes), in the
+ *                         walks that evaluate columns, count or list hits; the
+ *                         recording of paths always takes packets
  *   RRT_TUNE_PATH_GROUP   lanes per ray in the products that work by rows (the
  *                         row tiles and the density order's blocks): 8, 16, 32,
  *                         64, or 0 (default), from the mean intersections per

@@ -4,11 +4,14 @@ It times the phases that the knobs affect, on the workload itself, with the
 library's HIP-event timers (median of repeats), and keeps the fastest setting
 of each knob:
 
-* leaf size, traversal block and ray packet (1 ray per lane, or a packet of 64
-  rays walking one node sequence): the count + record traversals of path
-  recording (or, without recorded paths, a column traversal);
-* lanes per ray of the recorded-path product;
+* leaf size and traversal block: the walks of path recording (or, without
+  recorded paths, a column traversal);
+* ray packet (1 ray per lane, or a packet of 64 rays walking one node sequence):
+  column traversals only, as recordings always take packets;
 * iterations per graph replay of the batched fixed point.
+
+Lanes per ray (path_group) act on row tiles and density blocks, which a batched
+solve does not run by itself: the pick is the library's default.
 
 The phases run on a sample of at most max_n particles, which need not rank
 the knobs as the whole workload does, so one solve of the whole workload with
@@ -30,7 +33,7 @@ import numpy as np
 import torch
 
 DEFAULT_SPACE = dict(leaf=[8, 16], trace_block=[64, 128, 256], packet=[64, 1],
-                     path_group=[16, 32, 64], per_launch=[4, 16, 64])
+                     per_launch=[4, 16, 64])
 # the library's own settings (and the benchmark's iterations per graph replay)
 DEFAULTS = dict(leaf=16, trace_block=128, packet=64, path_group=0, per_launch=8)
 DEFAULT_CACHE = os.path.join(os.path.expanduser("~"), ".cache", "rrt_autotune.json")
@@ -89,7 +92,9 @@ def tune(wl, space: Optional[dict] = None, reps: int = 3, cache_path: str = DEFA
     probe.close()
     rec = -1 if paths else 0
 
-    # 1. traversal shape: time path recording (count + record) or a column traversal
+    # 1. traversal shape: time path recording or a column traversal (which alone
+    #    takes the packet)
+    packets = [DEFAULTS["packet"]] if paths else space["packet"]
     best_tr, best_t = None, float("inf")
     for leaf in space["leaf"]:
         s = Solver.from_workload(wl, record_paths=rec)
@@ -98,7 +103,7 @@ def tune(wl, space: Optional[dict] = None, reps: int = 3, cache_path: str = DEFA
         if x_probe is None:
             x_probe = torch.full((wl.n,), 0.01, dtype=torch.float64)
         for block in space["trace_block"]:
-            for packet in space["packet"]:
+            for packet in packets:
                 s.set_tuning(trace_block=block, packet=packet)
                 ts = []
                 for _ in range(reps):
@@ -117,33 +122,10 @@ def tune(wl, space: Optional[dict] = None, reps: int = 3, cache_path: str = DEFA
                     best_t, best_tr = t, dict(leaf=leaf, trace_block=block, packet=packet)
         s.close()
 
-    # 2. lanes per ray of the recorded-path product
-    best_g = 0
-    if not paths:
-        space = dict(space, path_group=[])
-    s = Solver.from_workload(wl, record_paths=rec)
-    s.set_tuning(**best_tr)
-    s.build_tree()
-    s.set_state(x_probe)
-    s.compute_columns(want_N=False, count=False)           # records the paths
-    best_gt = float("inf")
-    for group in space["path_group"]:
-        s.set_tuning(path_group=group)
-        s.enable_timing(True)
-        s.reset_timing()
-        for _ in range(max(reps, 3)):
-            s.compute_columns(want_N=False, count=False)
-        t = s.timing()["path_ms"] / max(reps, 3)
-        table.append(dict(phase="paths", path_group=group, ms=t))
-        say(f"paths group={group}: {t:.3f} ms")
-        if t < best_gt:
-            best_gt, best_g = t, group
-    s.close()
-
-    # 3. iterations per graph replay of the batched fixed point
+    # 2. iterations per graph replay of the batched fixed point
     best_pl, best_plt = space["per_launch"][0], float("inf")
     s = Solver.from_workload(wl)
-    s.set_tuning(path_group=best_g, **best_tr)
+    s.set_tuning(**best_tr)
     s.build_tree()
     for per in space["per_launch"]:
         ts = []
@@ -161,9 +143,9 @@ def tune(wl, space: Optional[dict] = None, reps: int = 3, cache_path: str = DEFA
             best_plt, best_pl = t, per
     s.close()
 
-    best = dict(best_tr, path_group=best_g, per_launch=best_pl)
+    best = dict(best_tr, path_group=DEFAULTS["path_group"], per_launch=best_pl)
 
-    # 4. the phases above time a sample of the workload, which need not rank the
+    # 3. the phases above time a sample of the workload, which need not rank the
     #    knobs as the whole does: one solve of the whole workload with the picks
     #    and one with the defaults decide (the first solve of each records its
     #    paths and is not timed)

@@ -229,3 +229,27 @@ def test_groups_record_every_halo_that_fits(sizes, frac, most):
     N1, h1 = s.compute_columns()
     assert h1 == need["hits"]
     s.close()
+
+
+@pytest.mark.parametrize("paths", [-1, 0])
+def test_autotuner_times_only_knobs_that_act(tmp_path, monkeypatch, paths):
+    """Over recorded paths the walk is the same for either ray packet and the
+    product for any lanes per ray: neither is timed, and the picks leave both at
+    the library's settings.  Without paths (here: none may be recorded) the packet
+    is timed."""
+    from paper_1304_4235_amd import Solver, autotune
+    wl, _ = _batch([300, 500], [1.0, 3.0])
+    if paths == 0:
+        make = Solver.from_workload.__func__
+        monkeypatch.setattr(Solver, "from_workload", classmethod(
+            lambda cls, w, **k: make(cls, w, **dict(k, record_paths=0))))
+    space = dict(leaf=[16], trace_block=[128], packet=[64, 1], path_group=[8, 64], per_launch=[8])
+    res = autotune.tune(wl, space=space, reps=1, cache_path=str(tmp_path / "t.json"),
+                        use_cache=False)
+    assert res["recorded_paths"] == (paths != 0)
+    timed = [t["packet"] for t in res["timings"] if t["phase"] == "record"]
+    assert timed == ([64] if paths else [64, 1])
+    assert all(t["phase"] in ("record", "solve") for t in res["timings"])
+    assert res["best"]["path_group"] == autotune.DEFAULTS["path_group"]
+    if paths:
+        assert res["best"]["packet"] == autotune.DEFAULTS["packet"]
