@@ -772,7 +772,7 @@ k_trace_wave(const Node* __restrict__ nodes, const float4* __restrict__ leaf_bal
             // quotient is at least 1/(2 k_hit) >= 1/128 away from an integer,
             // far beyond the error of the reciprocal and product (< 2^-12)
             const float rk = __builtin_amdgcn_rcpf((float)k_hit);
-            uint32_t v_hits = 0;           // this visit's hits (log modes)
+            uint32_t v_hits = 0;           // at least this visit's hits (log modes)
             // two copies of the pair loop: with and without the image shift
             // (a select per component would cost more than the adds it saves)
             auto pair_loop = [&](auto shifted_tag) {
@@ -784,9 +784,8 @@ k_trace_wave(const Node* __restrict__ nodes, const float4* __restrict__ leaf_bal
                 sh[2] = (double)sz * B;
             }
             // Every lane runs every iteration; spare lanes repeat the last pair,
-            // which changes no hit (the same bit, the same factor); the log modes'
-            // count of hits leaves them out afterwards.
-            uint64_t in_lanes = 0;
+            // which changes no hit (the same bit, the same factor) but counts in
+            // v_hits.
             for (int t0 = 0; t0 < pairs; t0 += 64) {
                 const int t = min(t0 + lane, pairs - 1);
                 const int q = (int)(((float)t + 0.5f) * rk);
@@ -803,10 +802,7 @@ k_trace_wave(const Node* __restrict__ nodes, const float4* __restrict__ leaf_bal
                 double hj = pq[3];
                 double h2 = hj * hj;
                 const bool in = D2 < h2;
-                if (kTally) {
-                    in_lanes = wave_ballot(in);
-                    v_hits += (uint32_t)__popcll(in_lanes);
-                }
+                if (kTally) v_hits += (uint32_t)__popcll(wave_ballot(in));
                 if (in) {
                     bool near = false;
                     if (NF) near = (pg.d0 * pg.d0 + pg.d1 * pg.d1 + pg.d2 * pg.d2) < h2;
@@ -814,9 +810,6 @@ k_trace_wave(const Node* __restrict__ nodes, const float4* __restrict__ leaf_bal
                     atomicOr(&s_mask[r], (near ? 0x10001u : 1u) << q);
                 }
             }
-            // lane 63 of the last iteration and the spare lanes before it hold
-            // the same pair
-            if (kTally && (in_lanes >> 63)) v_hits -= (uint32_t)(-pairs & 63);
             };
             if (shifted) pair_loop(std::true_type{});
             else pair_loop(std::false_type{});
@@ -828,9 +821,16 @@ k_trace_wave(const Node* __restrict__ nodes, const float4* __restrict__ leaf_bal
                 const uint32_t m = hit ? s_mask[rank] & 0xffffu : 0u;
                 const uint64_t rays = wave_ballot(m != 0u);
                 if (rays) {
-                    if (g_vis && (g_slots + c > kSegSlots || g_hits + v_hits > kSegHits ||
-                                  g_vis == kSegVisits))
-                        close_segment();
+                    bool full = g_slots + c > kSegSlots || g_vis == kSegVisits;
+                    if (!full && g_hits + v_hits > kSegHits) {
+                        // with the spare lanes' repeats: the hits themselves decide
+                        uint32_t hits = g_cnt + (uint32_t)__popc(m);
+                        for (int off = 32; off > 0; off >>= 1) hits += __shfl_xor(hits, off, 64);
+                        hits = (uint32_t)__builtin_amdgcn_readfirstlane((int)hits);
+                        full = hits > kSegHits;
+                        g_hits = hits - v_hits;
+                    }
+                    if (g_vis && full) close_segment();
                     if (g_vis == 0) open_segment();
                     const uint32_t hw = shifted ? 2u : 1u;
                     const uint32_t need = hw + (uint32_t)__popcll(rays);
