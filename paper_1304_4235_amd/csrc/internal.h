@@ -62,7 +62,8 @@ constexpr int kSegGroups = kSegHits / 4 + kRayPacket * 3 / 4;   // with the rays
 // block's number and the words used (<< 32).  Per segment a header (payload
 // words | visits << 32 | slots << 48; groups; the next segment's header; the 64
 // rays' entries as u16) and its payload: a word per visit, one more for a
-// shifted image, and one per ray that hits.  Neither a header nor a visit's
+// shifted image (three for one that does not fit 18 bits per axis), and one per ray
+// that hits.  Neither a header nor a visit's
 // words straddle blocks.
 constexpr uint32_t kLogBlock = 128, kLogData = kLogBlock - 1, kLogHeader = 19;
 constexpr uint32_t kNoBlock = 0xffffffffu;
@@ -72,8 +73,9 @@ constexpr uint32_t kLogCache = 8;
 constexpr int64_t kMaxWaves = 256 * 32;    // resident waves of the device
 // the persistent walk's queues (one per XCD), 128 bytes apart
 constexpr int kQueues = 8, kQueueStride = 16;
-// |periodic image| along an axis that a log word can hold
-constexpr int kMaxImage = 131071;
+// |periodic image| along an axis that a log word for all three can hold, and that
+// one for a single axis can
+constexpr int kMaxImage = 131071, kMaxAxisImage = 1 << 30;
 
 __host__ __device__ constexpr uint32_t segment_words(uint32_t visits, uint32_t groups)
 {
@@ -96,6 +98,12 @@ __host__ __device__ constexpr uint64_t log_image_word(int sx, int sy, int sz, ui
     return (uint64_t)(sx + kMaxImage) | ((uint64_t)(sy + kMaxImage) << 18) |
            ((uint64_t)(sz + kMaxImage) << 36) | ((uint64_t)visit << 54) |
            ((uint64_t)kLogImage << 62);
+}
+// one axis of an image, told from the above by bit 61
+__host__ __device__ constexpr uint64_t log_axis_word(int s, int axis, uint32_t visit)
+{
+    return (uint64_t)(uint32_t)s | ((uint64_t)axis << 32) | ((uint64_t)visit << 54) |
+           (1ull << 61) | ((uint64_t)kLogImage << 62);
 }
 __host__ __device__ constexpr uint64_t log_hits_word(uint32_t mask, int ray, uint32_t start,
                                                      uint32_t visit)
@@ -277,7 +285,7 @@ struct Ctx {
     // the log of the recording walk, in the path buffer while recording
     bool one_pass = true;
     bool packet_queue = true;    // persistent walk with a global packet queue
-    bool images_fit = true;      // every reachable periodic image fits a log word
+    bool images_fit = true;      // every reachable periodic image fits the log's words
     uint64_t pool_cap = 0;            // > 0: about this many 256-byte chunks of log (tests)
     uint64_t* path_log = nullptr;     // [log_blocks * kLogBlock]
     uint2* unit_log = nullptr;        // per unit: first block, segments

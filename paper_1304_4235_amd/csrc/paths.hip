@@ -59,10 +59,11 @@ uint32_t log_take(const Ctx& c) { return c.packet_queue && !c.log_tight ? kLogCa
 namespace {
 
 // per wave: which hit each entry is, the rays' groups and the visits
+constexpr int32_t kOwnImage = INT32_MIN;
 constexpr uint32_t kPlaceFill = 0x8000u;       // no hit: the last one's slot, factor 0
 
 struct BuildLds {
-    uint64_t img[kSegVisits];
+    int32_t img[3][kSegVisits];       // periodic image, kOwnImage for none
     uint32_t vis[kSegVisits];
     float org[3 * kRayPacket];
     uint16_t place[4 * kSegGroups];   // particle of the leaf | visit << 4, by group in ray order
@@ -163,11 +164,19 @@ k_build_paths(const uint64_t* __restrict__ log, const uint64_t* __restrict__ seg
                 const uint32_t v = (uint32_t)(w >> 43) & (kSegVisits - 1);
                 if (type == (uint32_t)kLogVisit) {
                     S.vis[v] = (uint32_t)w;
-                    S.img[v] = ~0ull;
+                    S.img[0][v] = kOwnImage;
                 }
                 wave_sync();
-                if (type == (uint32_t)kLogImage)
-                    S.img[(uint32_t)(w >> 54) & (kSegVisits - 1)] = w & ((1ull << 54) - 1ull);
+                if (type == (uint32_t)kLogImage) {
+                    const uint32_t iv = (uint32_t)(w >> 54) & (kSegVisits - 1);
+                    if ((w >> 61) & 1ull) {
+                        S.img[(uint32_t)(w >> 32) & 3u][iv] = (int32_t)(uint32_t)w;
+                    } else {
+                        S.img[0][iv] = (int)(w & 0x3ffffu) - kMaxImage;
+                        S.img[1][iv] = (int)((w >> 18) & 0x3ffffu) - kMaxImage;
+                        S.img[2][iv] = (int)((w >> 36) & 0x3ffffu) - kMaxImage;
+                    }
+                }
                 if (type == (uint32_t)kLogHits) {
                     uint32_t mask = (uint32_t)w & 0xffffu;
                     const uint32_t ray = (uint32_t)(w >> 16) & 63u;
@@ -227,11 +236,11 @@ k_build_paths(const uint64_t* __restrict__ log, const uint64_t* __restrict__ seg
                 for (int i = 0; i < 4; ++i) {
                     double sh[3] = {0.0, 0.0, 0.0};
                     if (kShifted) {
-                        const uint64_t im = S.img[vis[i]];
-                        const bool own = im == ~0ull;
-                        sh[0] = own ? 0.0 : (double)((int)(im & 0x3ffffu) - kMaxImage) * B;
-                        sh[1] = own ? 0.0 : (double)((int)((im >> 18) & 0x3ffffu) - kMaxImage) * B;
-                        sh[2] = own ? 0.0 : (double)((int)((im >> 36) & 0x3ffffu) - kMaxImage) * B;
+                        const int s0 = S.img[0][vis[i]];
+                        const bool own = s0 == kOwnImage;
+                        sh[0] = own ? 0.0 : (double)s0 * B;
+                        sh[1] = own ? 0.0 : (double)S.img[1][vis[i]] * B;
+                        sh[2] = own ? 0.0 : (double)S.img[2][vis[i]] * B;
                     }
                     const PairGeom pg =
                         pair_geom_d<kShifted>((double)Q[i].x, (double)Q[i].y, (double)Q[i].z, o0,
@@ -249,7 +258,7 @@ k_build_paths(const uint64_t* __restrict__ log, const uint64_t* __restrict__ seg
                 // waves hold a shifted one, the others leave its work out
                 bool any = false;
                 if (B > 0.0)
-                    for (int i = 0; i < 4; ++i) any = any || S.img[vis[i]] != ~0ull;
+                    for (int i = 0; i < 4; ++i) any = any || S.img[0][vis[i]] != kOwnImage;
                 if (wave_ballot(any)) factors(std::true_type{});
                 else factors(std::false_type{});
                 d_fac[at] = make_float4(__int_as_float((int)bits[0]), __int_as_float((int)bits[1]),

@@ -468,6 +468,10 @@ int paths_unfit(Ctx& c)
 {
     free_paths(c);
     c.n_rec_unfit += 1;
+    if (c.prm.record_paths == 1 && !c.images_fit)
+        return fail(c, RRT_E_WORKSPACE, "the rays reach over more than %d periodic images: their "
+                                        "paths cannot be recorded in a buffer of any size",
+                    kMaxAxisImage);
     if (c.prm.record_paths == 1)
         return fail(c, RRT_E_WORKSPACE,
                     "recorded paths need %llu bytes; the path buffer holds %llu "
@@ -1252,8 +1256,10 @@ int rrt_build_tree(rrt_ctx* x)
     }
     g.hmax = hmax;
     g.pad = pad;
-    // the recording's log codes a hit's periodic image in 18 bits per axis
-    c.images_fit = !(g.box > 0.0) || (g.L + (double)hmax + ext) / g.box + 2.0 <= kMaxImage;
+    // the recording's log codes a visit's periodic image in 18 bits per axis, or in
+    // a word per axis
+    const double images = g.box > 0.0 ? (g.L + (double)hmax + ext) / g.box + 2.0 : 0.0;
+    c.images_fit = images <= kMaxAxisImage;
     g.n = (int32_t)c.n;
     g.n_ray = c.n_ray;
     g.n_nodes = nn;

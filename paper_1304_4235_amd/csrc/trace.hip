@@ -660,7 +660,11 @@ k_trace_wave(const Node* __restrict__ nodes, const float4* __restrict__ leaf_bal
         // the segment's end in the slab test; below the start for lanes that
         // do not walk this image, so their test always fails
         const float t_end = mine ? 1.0f : -1.0f;
-        const bool shifted = (sx | sy | sz) != 0;            // wave-uniform
+        // the log's words of a visit before its rays': one, two with a shifted image,
+        // four with one that does not fit a word (wave-uniform)
+        const uint32_t hw = (sx | sy | sz) == 0 ? 1u
+                            : max(max(abs(sx), abs(sy)), abs(sz)) <= kMaxImage ? 2u : 4u;
+        const bool shifted = hw > 1u;
         // slab offsets of the entry and exit faces: the low face is padded
         // by -pad, the high face by +pad
         float oin[3], oout[3], of[3];
@@ -832,13 +836,15 @@ k_trace_wave(const Node* __restrict__ nodes, const float4* __restrict__ leaf_bal
                     }
                     if (g_vis && full) close_segment();
                     if (g_vis == 0) open_segment();
-                    const uint32_t hw = shifted ? 2u : 1u;
                     const uint32_t need = hw + (uint32_t)__popcll(rays);
                     reserve(need);
                     if (kLog && blk != kNoBlock) {
                         uint64_t* at = out.log + ((uint64_t)blk * kLogBlock + pos);
                         if (lane == 0) at[0] = log_visit_word(leafw, g_vis);
-                        if (shifted && lane == 1) at[1] = log_image_word(sx, sy, sz, g_vis);
+                        if (hw == 2u && lane == 1) at[1] = log_image_word(sx, sy, sz, g_vis);
+                        if (hw == 4u && lane > 0 && lane < 4)
+                            at[lane] = log_axis_word(lane == 1 ? sx : lane == 2 ? sy : sz,
+                                                     lane - 1, g_vis);
                         if (m)
                             at[hw + (uint32_t)__popcll(rays & lt_mask)] =
                                 log_hits_word(m, lane, g_cnt, g_vis);

@@ -235,3 +235,29 @@ def test_row_tiles_need_six_bytes_beside_the_paths():
     s.backward(torch.ones_like(lnG), None)
     assert s.timing()["tile_set_total"] > 0
     s.close()
+
+
+def test_paths_over_images_beyond_a_word():
+    """Images more than 131071 box lengths away along an axis: recorded (the image
+    takes a log word per axis), to the traversal's columns and hit lists."""
+    from paper_1304_4235_amd import Solver
+    out = []
+    for paths in (1, 0):
+        s = Solver(l_ray=140000.0, box=1.0, record_paths=paths)
+        s.set_particles(np.array([[0.5, 0.5, 0.5], [0.75, 0.5, 0.25]], np.float32),
+                        np.array([0.3, 0.35], np.float32), np.array([1e12, 2e12], np.float32),
+                        np.array([1e-2, 1e-2], np.float32), np.array([1e4, 1e4], np.float32))
+        s.set_rays(np.array([[1.0, 0.0, 0.0], [0.0, -1.0, 0.0], [0.0, 0.0, -1.0]]))
+        s.set_spectrum(np.array([6e-18]), np.array([1e5]))
+        s.build_tree()
+        N, hits = s.compute_columns()
+        out.append((N.cpu().numpy(), hits))
+        if paths:
+            off, j, fac = s.path_rows([0, 1])
+            ho, hj, _, hf = s.hits_rows([0, 1])
+            np.testing.assert_array_equal(off, ho)
+            np.testing.assert_array_equal(j, hj)
+            np.testing.assert_array_equal(fac, hf)
+        s.close()
+    assert out[0][1] == out[1][1] >= 6 * 140000
+    np.testing.assert_allclose(out[0][0], out[1][0], rtol=1e-9)
