@@ -4,6 +4,7 @@
 #pragma once
 
 #include "internal.h"
+#include "quotient.h"
 
 namespace rrt {
 
@@ -57,11 +58,7 @@ __device__ __forceinline__ float chord_factor(double sp, double b2, double h2, d
     const float z1 = fmaxf((float)(-sp) * ih, -lh);
     const float z2 = fminf((float)(L - sp) * ih, lh);
     if (!(z2 > z1)) return 0.0f;
-    // b2 / h2 by the hardware reciprocal (some 2^-27) and one correction, to
-    // about 1 ulp; the division's scaling and special cases, a dozen
-    // instructions, have no use here (0 <= b2 < h2, both normal)
-    const double ir2 = __builtin_amdgcn_rcp(h2), q0 = b2 * ir2;
-    const double e = -ga * fma(fma(-q0, h2, b2), ir2, q0);
+    const double e = -ga * quotient_from(b2, h2, __builtin_amdgcn_rcp(h2));
     const double en = floor(e);
     const float g = (float)gc * ldexpf(__builtin_amdgcn_exp2f((float)(e - en)), (int)en);
     const float e2 = erf_t_odd(t_erf, z2);

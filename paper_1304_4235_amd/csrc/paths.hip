@@ -81,8 +81,8 @@ struct BuildLds {
 // intersection with the log's share): the factor's arithmetic, without the
 // image shift where no lane of the wave has one.  Measured on MI355X: the 885k-
 // particle field's 3.37e9 intersections 19.4 ms with the shift's adds always and
-// an FP64 division, 18.2 ms here; the 262144-particle halo's 1.57e9 8.25 and
-// 7.72 ms.  Not branching in the factor, so that a lane's four interleave, took
+// the FP64 division, 18.2 ms here; the 262144-particle halo's 1.57e9 8.25 and
+// 7.6 ms.  Not branching in the factor, so that a lane's four interleave, took
 // 20.5 ms: most chords span their sphere and skip a table lookup.
 template <bool NF>
 __global__ void __launch_bounds__(kBlock)

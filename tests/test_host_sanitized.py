@@ -39,12 +39,13 @@ def test_arena_under_sanitizers(tmp_path):
 @pytest.mark.skipif(shutil.which("g++") is None or not os.path.isdir("/opt/rocm/include"),
                     reason="needs g++ and the ROCm headers")
 @pytest.mark.parametrize("name,says", [("grid_check", "grid checks passed"),
-                                       ("arena_high_check", "arena checks from the top passed")])
+                                       ("arena_high_check", "arena checks from the top passed"),
+                                       ("quotient_check", "quotient checks passed")])
 def test_host_rules_under_sanitizers(tmp_path, name, says):
     exe = str(tmp_path / name)
     csrc = os.path.join(ROOT, "paper_1304_4235_amd", "csrc")
-    cmd = ["g++", "-std=c++17", *SAN, "-D__HIP_PLATFORM_AMD__", "-I/opt/rocm/include",
-           "-I" + os.path.join(ROOT, "include"), "-I" + csrc,
+    cmd = ["g++", "-std=c++17", *SAN, "-ffp-contract=off", "-D__HIP_PLATFORM_AMD__",
+           "-I/opt/rocm/include", "-I" + os.path.join(ROOT, "include"), "-I" + csrc,
            os.path.join(HOST, name + ".cpp"), "-L/opt/rocm/lib", "-lamdhip64",
            "-Wl,-rpath,/opt/rocm/lib", "-o", exe]
     assert says in _run(cmd, exe, tmp_path)
