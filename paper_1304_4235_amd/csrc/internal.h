@@ -28,8 +28,8 @@ constexpr int64_t kMaxRows = 2147483647;
 // distinct particles a row tile of the recorded paths may touch (its mu*x is
 // staged in LDS: 64 KiB)
 constexpr int kTileMaxSet = 16384;
-// The column products read recorded entries in aligned groups of four, so the
-// arrays holding them are allocated with this many entries to spare.
+// The row tiles' products read entries in aligned groups of four, so their arrays
+// are allocated with this many entries to spare.
 constexpr int kPathPad = 4;
 // 16-byte words past the segments that the products may read (not use)
 constexpr int kPackedPad = 17;
@@ -622,7 +622,8 @@ inline int ray_ways(int64_t waves, int n_ray)
 // field's 663552 packets of 3.4 segments 4.05, 3.93, 5.02, -; the 262144-
 // particle halo's 49152 of 20: 2.03, -, 1.55, 1.72; 12 halos' 26236 of 9:
 // -, 0.255, -, 0.34; 640-particle halos in groups, 936 packets of which some 250
-// are recorded, us at 1, 8: 20, 9.
+// are recorded, us at 1, 8: 20, 9.  (The limits between those points are taken from
+// them, not measured one by one.)
 inline int path_ways(int64_t packets, int64_t live, uint64_t segs)
 {
     const double mean = (double)segs / (double)(live > 0 ? live : 1);

@@ -412,10 +412,11 @@ typedef float v4f __attribute__((ext_vector_type(4)));
 // block of four waves takes four packets).  A segment's mux is staged in LDS
 // once; then each lane takes groups, whose four products sum in FP64 and are
 // added to their ray's sum in LDS.  The groups are independent, so every lane
-// is busy and the loads run ahead.  The lanes of one instruction add in lane
-// order, a wave's instructions in order and the waves' sums in theirs, so the
-// columns do not depend on the run.  Rows of sources that are not evaluated
-// keep their columns.
+// is busy and the loads run ahead.  A wave's instructions add in order and the
+// waves' sums in theirs; the lanes of one LDS atomic that add to the same ray were
+// always seen to add in the same order (no document promises it), and with that the
+// columns do not depend on the run, which the tests hold to the bit.  Rows of sources
+// that are not evaluated keep their columns.
 __device__ __forceinline__ void lds_add(double* p, double v) { unsafeAtomicAdd(p, v); }
 
 template <bool STREAM, typename T>

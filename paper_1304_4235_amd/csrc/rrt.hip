@@ -649,7 +649,7 @@ int columns_impl(Ctx& c, int64_t* hits)
         if (c.row_list && !c.path && !c.rows_unfit) {
             hipError_t e = ensure_row_offsets(c);
             if (e == hipSuccess)
-                e = ws_alloc(c, &c.path, (size_t)c.path_hits + kPathPad, kRegionPath);
+                e = ws_alloc(c, &c.path, (size_t)c.path_hits, kRegionPath);
             if (e == hipSuccess) e = launch_expand_rows(c, c.path);
             else if (e == hipErrorOutOfMemory) {
                 c.rows_unfit = true;

@@ -311,8 +311,7 @@ k_trace(const Node* __restrict__ nodes, const float4* __restrict__ p4,
 //  * what the log modes need only when a segment opens or closes, a block ends
 //    or a unit does lives in LDS: scalar registers are short, and a spilled one
 //    costs two vector instructions each time;
-//  * the ranges of periodic images are packed, and the shift itself is only
-//    formed where a shifted image's pairs need it;
+//  * the shift of a periodic image is only formed where its pairs need it;
 //  * the image shift's three adds only run for a shifted image: for the
 //    unshifted one they add zero, which changes no bit of the predicate;
 //  * the near test only exists in the near/far variant (NF).
