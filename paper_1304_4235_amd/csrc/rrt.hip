@@ -1119,8 +1119,10 @@ int rrt_set_spectrum(rrt_ctx* x, int32_t n_bins, const double* sigma, const doub
         srt.push_back((float)(sigma[b] / smin));
     }
     int m = (int)rel.size();
+    // the rate's arguments are baked into a captured graph: its polynomial, its
+    // smallest cross-section and scale, the tables' addresses
+    drop_graph(c);
     if (m != c.n_bins || !c.ws_rel || !c.srat) {
-        drop_graph(c);
         HIP_OK(ws_alloc(c, &c.ws_rel, m));
         HIP_OK(ws_alloc(c, &c.dsig_l2, m));
         HIP_OK(ws_alloc(c, &c.srat, m));
@@ -1132,7 +1134,6 @@ int rrt_set_spectrum(rrt_ctx* x, int32_t n_bins, const double* sigma, const doub
     HIP_OK(hipMemcpyAsync(c.srat, srt.data(), sizeof(float) * m, hipMemcpyHostToDevice,
                           c.stream));
     HIP_OK(hipStreamSynchronize(c.stream));     // host vectors go out of scope
-    if (m != c.n_bins) drop_graph(c);
     c.n_bins = m;
     // Taylor moments of the bins as the rate kernel sums them (the FP32
     // tables r_b, d_b with exponent d_b N in base 2): S(N) = sum_b r_b

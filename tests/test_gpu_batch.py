@@ -253,3 +253,20 @@ def test_autotuner_times_only_knobs_that_act(tmp_path, monkeypatch, paths):
     assert res["best"]["path_group"] == autotune.DEFAULTS["path_group"]
     if paths:
         assert res["best"]["packet"] == autotune.DEFAULTS["packet"]
+
+
+@pytest.mark.parametrize("paths", [-1, 0])
+def test_a_new_spectrum_reaches_the_captured_iterations(paths):
+    """A second spectrum of as many bins: the batch solves with it as a new solver
+    does, also where a graph of the first spectrum's iterations is at hand."""
+    wl, _ = _batch([400, 900, 64], [2.0, 0.3, 1.0], seed=21)
+    s = _solver(wl, record_paths=paths)
+    s.iterate_halos(200, 1e-3, per_launch=4)
+    sigma, w = wl.sigma * 0.4, wl.w * np.linspace(3.0, 0.5, wl.w.size)
+    s.set_spectrum(sigma, w)
+    s.set_state(None)
+    got = s.iterate_halos(200, 1e-3, per_launch=4)
+    wl.sigma, wl.w = sigma, w
+    ref = _solver(wl, record_paths=paths).iterate_halos(200, 1e-3, per_launch=4)
+    np.testing.assert_array_equal(got["halo_iters"], ref["halo_iters"])
+    np.testing.assert_array_equal(got["x"].cpu().numpy(), ref["x"].cpu().numpy())
