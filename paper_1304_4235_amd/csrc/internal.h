@@ -39,7 +39,7 @@ constexpr int kPackedPad = 17;
 // order) walk one node sequence, so their paths are recorded together.  A
 // packet's walk is split into path_parts(c) units; a unit's
 // leaf visits with hits, in order, are cut into segments of at most kSegVisits
-// visits, kSegSlots slots (each visit takes one slot per particle of its leaf)
+// visits, kSegFill slots (each visit takes one slot per particle of its leaf)
 // and kSegHits hits.  A ray's hits in a segment, in walk order, fill groups of
 // four.  A segment of the recorded paths (16-byte words):
 //   word 0       visits | slots << 16, groups, size in words, 0
@@ -47,13 +47,14 @@ constexpr int kPackedPad = 17;
 //   then         per group four factors K/h^2 (FP32, sign bit: the near flag)
 //   then         per group three slots of 10 bits, entries in use less one (2)
 //   then         per group the fourth slot (10 bits) and the ray (6)   (u16)
-// (a group's unused entries repeat its last slot, with factor 0).  Groups are
+// (a group's unused entries have the slot kSegFill, whose particle has value 0,
+// and factor 0).  Groups are
 // independent of one another, so a wave takes 64 of them at a time whatever
 // rays they belong to: an intersection takes 5.5 bytes, read in order, and its
 // particle's value comes from the slots, staged once per segment.  Lane l of
 // the 64 takes a run of consecutive groups, ray by ray (group_at), so that the
 // lanes add to different rays.
-constexpr int kSegSlots = 1024;
+constexpr int kSegSlots = 1024, kSegFill = kSegSlots - 1;
 constexpr int kSegVisits = 128;
 constexpr int kSegHits = 1856;             // >= 64 rays x kLeafMax
 constexpr int kRayPacket = 64;

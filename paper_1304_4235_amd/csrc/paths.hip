@@ -60,7 +60,7 @@ namespace {
 
 // per wave: which hit each entry is, the rays' groups and the visits
 constexpr int32_t kOwnImage = INT32_MIN;
-constexpr uint32_t kPlaceFill = 0x8000u;       // no hit: the last one's slot, factor 0
+constexpr uint32_t kPlaceFill = 0x8000u;       // no hit: slot kSegFill, factor 0
 
 struct BuildLds {
     int32_t img[3][kSegVisits];       // periodic image, kOwnImage for none
@@ -227,7 +227,7 @@ k_build_paths(const uint64_t* __restrict__ log, const uint64_t* __restrict__ seg
                         ++n_used;
                     }
                     vis[i] = pl >> 4;
-                    slot[i] = S.base[vis[i]] + (pl & 15u);
+                    slot[i] = x & kPlaceFill ? kSegFill : S.base[vis[i]] + (pl & 15u);
                     Q[i] = p4[(S.vis[vis[i]] >> kLeafShift) + (pl & 15u)];
                 }
                 auto factors = [&](auto shifted_tag) {
@@ -457,6 +457,7 @@ k_path_columns(const uint64_t* __restrict__ unit_seg, const uint64_t* __restrict
     uint64_t sg = unit_seg[pk * parts] + (W == 1 ? 0 : wv);
     const uint64_t end = unit_seg[(pk + 1) * parts];
     float* sx = s_mux[wv];
+    if (lane == 0) sx[kSegFill] = 0.0f;              // of the groups' unused entries
     float* sn = NF ? s_mu[wv] : nullptr;
     // the next segment's header and visits are loaded while one is worked on
     // (64 visits' words, of which the header says how many there are)

@@ -342,7 +342,7 @@ constexpr uint64_t kSegmentBytes = 2 * sizeof(uint64_t) + sizeof(uint32_t);
 
 // Path buffer for a recording of `words` 16-byte words and a log of `blocks`.  A
 // unit leaves one segment open; one that closed takes at least 32 words: ended by
-// its slots it has 64 visits or more, with a hit each (39 words where one ray
+// its slots it has 63 visits or more, with a hit each (39 words where one ray
 // takes them all), by its visits 128 (77 words), by its hits 833 of them.
 uint64_t record_bytes(const Ctx& c, uint64_t words, uint64_t blocks)
 {

@@ -824,7 +824,7 @@ k_trace_wave(const Node* __restrict__ nodes, const float4* __restrict__ leaf_bal
                 const uint32_t m = hit ? s_mask[rank] & 0xffffu : 0u;
                 const uint64_t rays = wave_ballot(m != 0u);
                 if (rays) {
-                    bool full = g_slots + c > kSegSlots || g_vis == kSegVisits;
+                    bool full = g_slots + c > kSegFill || g_vis == kSegVisits;
                     if (!full && g_hits + v_hits > kSegHits) {
                         // with the spare lanes' repeats: the hits themselves decide
                         uint32_t hits = g_cnt + (uint32_t)__popc(m);

@@ -261,3 +261,37 @@ def test_paths_over_images_beyond_a_word():
         s.close()
     assert out[0][1] == out[1][1] >= 6 * 140000
     np.testing.assert_allclose(out[0][0], out[1][0], rtol=1e-9)
+
+
+@pytest.mark.parametrize("near_far", [0, 1])
+def test_an_overflowing_particle_blocks_its_rays_only(near_far):
+    """A density so large that a particle's content leaves the FP32 range (valid
+    input): the rays that meet it get an infinite column, as the traversal gives
+    them, and no ray becomes NaN."""
+    from paper_1304_4235_amd import Solver
+    wl = W.isothermal_halo(n=900, n_bins=4, seed=31)
+    mu = wl.mu.astype(np.float32).copy()
+    nH = wl.n_H.astype(np.float32).copy()
+    big = [17, 500, 899]
+    mu[big] = 1e38
+    dense = nH.copy()
+    dense[big] *= 1e6
+    out = []
+    for paths in (1, 0):
+        s = Solver(l_ray=wl.l_ray, box=0.0, record_paths=paths)
+        s.set_particles(wl.pos, wl.h, mu, nH, wl.T)
+        s.set_rays(wl.dirs)
+        s.set_spectrum(wl.sigma, wl.w)
+        s.set_scheme(near_far)
+        s.build_tree()
+        s.set_density(torch.tensor(dense))
+        s.set_state(torch.full((wl.n,), 0.5, dtype=torch.float64))
+        N, _ = s.compute_columns()
+        N = N.cpu().numpy()
+        if near_far:
+            N = np.concatenate([N, s.near_columns().cpu().numpy()])
+        out.append(N)
+        s.close()
+    assert not np.isnan(out[1]).any() and np.isinf(out[1]).any()
+    np.testing.assert_array_equal(np.isinf(out[0]), np.isinf(out[1]))
+    np.testing.assert_allclose(out[0], out[1], rtol=1e-11)
