@@ -72,6 +72,9 @@ constexpr uint32_t kNoBlock = 0xffffffffu;
 // holds when the walk ends stays unused.
 constexpr uint32_t kLogCache = 8;
 constexpr int64_t kMaxWaves = 256 * 32;    // resident waves of the device
+// parts a packet's walk is split into, at most, and where the log's room is short (a
+// unit takes a block of it at least)
+constexpr int kPartsMost = 32, kPartsTight = 4;
 // the persistent walk's queues (one per XCD), 128 bytes apart
 constexpr int kQueues = 8, kQueueStride = 16;
 // |periodic image| along an axis that a log word for all three can hold, and that
@@ -277,6 +280,8 @@ struct Ctx {
     uint64_t* unit_seg = nullptr; // [units + 1] first segment of each unit
     uint64_t path_segs = 0, path_words = 0;
     int64_t path_live = 0;        // packets recorded (those of a group of halos)
+    int parts_most = kPartsMost;  // parts of a packet's walk at most (path_parts)
+    bool was_grouped = false;     // the last batch did not fit the path buffer at once
     // > 0 while groups of halos run: segments and words that unit_seg, seg_off and
     // packed hold for the largest group, so that they stay where they are
     uint64_t hold_segs = 0, hold_words = 0;

@@ -41,7 +41,7 @@ int64_t path_packets(const Ctx& c) { return ((c.n + 63) / 64) * (int64_t)c.n_ray
 int path_parts(const Ctx& c)
 {
     const int64_t pk = path_packets(c);
-    const int most = c.prm.box > 0.0 ? 4 : 32;
+    const int most = c.prm.box > 0.0 ? std::min(4, c.parts_most) : c.parts_most;
     int p = 1;
     while (p < most && pk * p < (c.prm.box > 0.0 ? 6144 : 49152)) p *= 2;
     return p;

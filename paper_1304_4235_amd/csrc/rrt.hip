@@ -1185,6 +1185,10 @@ int rrt_build_tree(rrt_ctx* x)
     // a new geometry: the recorded paths and their counts no longer apply
     free_paths(c);
     c.counts_valid = false;
+    if (c.parts_most != kPartsMost) {
+        c.parts_most = kPartsMost;
+        c.last_total = 0;              // the last sizes are of other parts
+    }
     c.have_tree = c.have_columns = c.have_gamma = false;
     hipEvent_t eb = ev_begin(c);
     // bounds and validation
@@ -1996,7 +2000,18 @@ int run_groups(Ctx& c, double tol, int32_t max_iter, int32_t per_launch)
     Scratch<int32_t> d_mask(c);
     HIP_OK(d_mask.get((size_t)c.n_halo));
     std::vector<HaloGroup> groups;
+    // Few packets are each split to fill the device (path_parts); with fewer parts the
+    // log, a block of it per part at least, and so the groups take less room: 600
+    // halos of 20 particles with 4 bytes of buffer per intersection took 6.1 ms in four
+    // groups and 4.0 in three, 18 of 64 to 640 particles 8.2 in four and 5.8 in three.
+    auto several = [&]() { return groups.size() > 1 || !groups[0].recorded; };
+    if (c.was_grouped) c.parts_most = kPartsTight;
     if (int r = plan_groups(c, groups)) return r;
+    if (several() && path_parts(c) > kPartsTight) {
+        c.parts_most = kPartsTight;
+        if (int r = plan_groups(c, groups)) return r;
+    }
+    c.was_grouped = several();
     if (groups.size() == 1 && groups[0].recorded) {
         // all paths fit: the sizes are known, so the first iteration records
         // them with one walk

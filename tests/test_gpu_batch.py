@@ -270,3 +270,33 @@ def test_a_new_spectrum_reaches_the_captured_iterations(paths):
     ref = _solver(wl, record_paths=paths).iterate_halos(200, 1e-3, per_launch=4)
     np.testing.assert_array_equal(got["halo_iters"], ref["halo_iters"])
     np.testing.assert_array_equal(got["x"].cpu().numpy(), ref["x"].cpu().numpy())
+
+
+@pytest.mark.parametrize("sizes", [[20] * 600, [640, 64, 128] * 6])
+def test_small_halos_run_in_three_groups_with_four_bytes_each(sizes):
+    """Four bytes of path buffer per intersection, half of what paths without a log
+    took at 8: three groups, on a first tree and on the next, with the results of the
+    batch in one."""
+    wl, _ = _batch(sizes, [1.0 + (i % 5) for i in range(len(sizes))], seed=14)
+    probe = _solver(wl, record_paths=-1)
+    hits = probe.count_paths()["hits"]
+    probe.close()
+    ref = _solver(wl).iterate_halos(200, 1e-3, per_launch=8)
+    s = _solver(wl, record_paths=-1, path_budget=4 * hits, build=False)
+    for _ in range(2):
+        s.build_tree()
+        s.set_state(None)
+        s.enable_timing(True)
+        s.reset_timing()
+        r = s.iterate_halos(200, 1e-3, per_launch=8)
+        tm = s.timing()
+        assert tm["n_trace"] == 0 and tm["n_path"] <= 3, (tm["n_trace"], tm["n_path"])
+        np.testing.assert_array_equal(r["halo_iters"], ref["halo_iters"])
+        np.testing.assert_allclose(r["x"].cpu().numpy(), ref["x"].cpu().numpy(), rtol=1e-9)
+    # the same context with room for all of it: one group, the paths stay
+    s.set_path_buffer(64 * hits + (128 << 20))
+    s.build_tree()
+    r = s.iterate_halos(200, 1e-3, per_launch=8)
+    assert s.timing()["path_hits"] == hits
+    np.testing.assert_array_equal(r["halo_iters"], ref["halo_iters"])
+    s.close()
