@@ -372,10 +372,12 @@ int rrt_iterate_halos(rrt_ctx* ctx, int32_t max_iter, double tol, int32_t per_la
  *                         recorded paths: 0 (default) = gather over paths
  *                         transposed once per geometry when they fit in the
  *                         path buffer (25 bytes per intersection beside the
- *                         paths while they are built; deterministic), else per row tile in LDS with one
- *                         atomic add per distinct particle of a tile (when the
- *                         tiles fit), else one atomic add per intersection;
- *                         1 = always one atomic add per intersection;
+ *                         paths while they are built; deterministic), else
+ *                         per row tile in LDS with one atomic add per distinct
+ *                         particle of a tile (6 bytes per intersection and the
+ *                         tiles' particles, when they fit), else per segment of
+ *                         the paths in LDS with one atomic add per particle it
+ *                         holds; 1 = always per segment;
  *                         2 = always per row tile (when the tiles fit)
  *   RRT_TUNE_TILES        0 (default): columns from the recorded paths as
  *                         recorded.  1: after a few column evaluations over the

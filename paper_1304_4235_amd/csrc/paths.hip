@@ -724,32 +724,49 @@ k_path_rows(const uint64_t* __restrict__ unit_seg, const uint64_t* __restrict__ 
     }
 }
 
-// Transposed product, one atomic add per intersection: y_j += (K/h^2) nu_row.
+// Transposed product: y_j += (K/h^2) nu_row over every entry.  A wave per packet:
+// a segment's entries add to its slots in LDS, then each slot that got something
+// adds to its particle, 16 neighbouring ones of a visit at a time.  Bound by the
+// atomics.  Measured on MI355X, the 65521-particle halo's 258M intersections in 12
+// directions: 7.6 ms with a global atomic per entry (4.1 over paths by rows), 0.76
+// here.
 __global__ void __launch_bounds__(kBlock)
 k_path_scatter(const uint64_t* __restrict__ unit_seg, const uint64_t* __restrict__ seg_off,
-             const uint4* __restrict__ packed,
-               int64_t n_packets, int parts, int n, const float* __restrict__ nu,
-               double* __restrict__ y)
+               const uint4* __restrict__ packed, int64_t n_packets, int parts, int n,
+               const float* __restrict__ nu, double* __restrict__ y)
 {
-    __shared__ int32_t s_j[kWaves][kSegSlots];
+    __shared__ double s_y[kWaves][kSegSlots];
     __shared__ double s_nu[kWaves][64];
     const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
     const int64_t wpd = (n + 63) / 64;
     const int64_t stride = (int64_t)gridDim.x * kWaves;
+    double* acc = s_y[wv];
     for (int64_t pk = blockIdx.x * (int64_t)kWaves + wv; pk < n_packets; pk += stride) {
         const int64_t k = pk / wpd, p0 = (pk - k * wpd) * 64;
         s_nu[wv][lane] = p0 + lane < n ? (double)nu[k * n + p0 + lane] : 0.0;
-        auto none = [](const Segment&) {};
-        for_groups(
-            unit_seg, seg_off, packed, pk, parts, lane, s_j[wv], none,
-            [&](uint32_t, int ray, const int* j, const uint32_t* b, uint32_t used) {
-                const double v = s_nu[wv][ray];
-                if (v == 0.0) return;
-                for (uint32_t q = 0; q < used; ++q)
-                    unsafeAtomicAdd(y + j[q], (double)__int_as_float((int)b[q]) * v);
-            },
-            none);
-        wave_sync();
+        const uint64_t end = unit_seg[(pk + 1) * parts];
+        for (uint64_t sg = unit_seg[pk * parts]; sg < end; ++sg) {
+            const Segment g = segment_at(packed + seg_off[sg]);
+            const uint32_t w0 = (uint32_t)lane < g.n_vis ? g.vis[lane] : 0u;
+            for (uint32_t i = lane; i < g.n_slots; i += 64) acc[i] = 0.0;
+            wave_sync();
+            for (uint32_t at = lane; at < g.n_groups; at += 64) {
+                const float4 f = g.fac[at];
+                const uint32_t a = g.abc[at], d = g.dr[at], used = (a >> 30) + 1u;
+                const double v = s_nu[wv][d >> 10];
+                if (v == 0.0) continue;
+                const float fq[4] = {f.x, f.y, f.z, f.w};
+                const uint32_t sl[4] = {a & 1023u, (a >> 10) & 1023u, (a >> 20) & 1023u, d & 1023u};
+#pragma unroll
+                for (uint32_t q = 0; q < 4; ++q)
+                    if (q < used) lds_add(acc + sl[q], (double)fq[q] * v);
+            }
+            wave_sync();
+            for_slots(g, lane, w0, [&](uint32_t slot, int j) {
+                if (acc[slot] != 0.0) unsafeAtomicAdd(y + j, acc[slot]);
+            });
+            wave_sync();
+        }
     }
 }
 

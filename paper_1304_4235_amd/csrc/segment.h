@@ -10,7 +10,7 @@ namespace rrt {
 
 // One wave's view of a segment.
 struct Segment {
-    uint32_t n_vis, n_groups, words;
+    uint32_t n_vis, n_slots, n_groups, words;
     const uint32_t* vis;
     const float4* fac;
     const uint32_t* abc;                  // three slots, entries in use less one
@@ -21,6 +21,7 @@ __device__ __forceinline__ Segment segment_of(const uint4* __restrict__ s, const
 {
     Segment g;
     g.n_vis = __builtin_amdgcn_readfirstlane(h.x & 0xffffu);
+    g.n_slots = __builtin_amdgcn_readfirstlane(h.x >> 16);
     g.n_groups = __builtin_amdgcn_readfirstlane(h.y);
     g.words = __builtin_amdgcn_readfirstlane(h.z);
     const uint4* p = s + 1 + (g.n_vis + 3) / 4;

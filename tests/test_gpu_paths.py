@@ -194,8 +194,8 @@ def _tile_case(which):
 def test_row_tiles_hold_the_recorded_paths(which):
     """Row tiles whose rows begin and end inside packets and directions: columns
     over the tiles against the recorded paths' (the same products in another FP64
-    order: 1e-11, as above), and the reverse mode's sums over the tiles against
-    the gather over the transposed paths."""
+    order: 1e-11, as above), and the reverse mode's sums over the tiles and over the
+    segments' slots against the gather over the transposed paths."""
     from paper_1304_4235_amd import Solver
     wl, leaf = _tile_case(which)
     x = torch.tensor(np.random.default_rng(4).uniform(1e-6, 1.0, wl.n))
@@ -212,11 +212,12 @@ def test_row_tiles_hold_the_recorded_paths(which):
     s.set_tuning(tiles=0)
     g = torch.ones(wl.n, dtype=torch.float64, device="cuda")
     dn = []
-    for mode in (0, 2):
+    for mode in (0, 1, 2):
         s.set_tuning(adjoint_scatter=mode)
         s.forward(2)
         dn.append(s.backward(g, None)[1].cpu().numpy())
-    np.testing.assert_allclose(dn[1], dn[0], rtol=1e-9, atol=1e-12 * np.abs(dn[0]).max())
+    for q in (1, 2):
+        np.testing.assert_allclose(dn[q], dn[0], rtol=1e-9, atol=1e-12 * np.abs(dn[0]).max())
     s.close()
 
 
