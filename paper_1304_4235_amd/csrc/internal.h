@@ -542,7 +542,8 @@ hipError_t launch_columns(Ctx& c);
 // the recording walk into the log (store), or its sizes only; unit_size
 // receives each unit's recorded words | log blocks << 32
 hipError_t launch_log_walk(Ctx& c, bool store, uint64_t* unit_size);
-hipError_t launch_log_range(Ctx& c, int64_t unit0, int64_t units);
+// (take: blocks a wave takes at once)
+hipError_t launch_log_range(Ctx& c, int64_t unit0, int64_t units, uint32_t take);
 void drop_graph(Ctx& c);
 hipError_t build_tiles(Ctx& c);
 hipError_t launch_want(Ctx& c, int block);

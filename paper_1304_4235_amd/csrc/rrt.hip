@@ -406,6 +406,18 @@ bool alloc_log(Ctx& c, uint64_t words, uint64_t blocks)
     return true;
 }
 
+// Whether a log for the last sizes has room beside their paths (the buffer holds
+// nothing of a recording but the units' arrays, at most).
+bool log_fits(const Ctx& c)
+{
+    const uint64_t units = (uint64_t)(path_packets(c) * path_parts(c));
+    const uint64_t held = (c.unit_seg && !c.hold_words ? region_bytes((units + 1) * 8) : 0) +
+                          (c.unit_off ? region_bytes((units + 1) * 8) : 0) +
+                          (c.unit_log ? region_bytes(units * sizeof(uint2)) : 0);
+    return record_bytes(c, c.last_words, log_pool(c, c.last_blocks, 1.0, false)) <=
+           ws_largest_gap(c, kRegionPath) + held;
+}
+
 // One walk for its sizes (store false) or into the log: last_words,
 // last_blocks and last_total, and whether the pool ran short.
 int path_walk(Ctx& c, bool store, uint64_t* unit_tally, bool* overflow)
@@ -482,27 +494,43 @@ int paths_unfit(Ctx& c)
     return RRT_OK;
 }
 
-// The recording where the whole log does not fit beside the paths: a walk for the
-// units' sizes and segments, then walk and build alternately over ranges of the
-// units, each as long as the room left holds its log.  fit: the paths and the
-// largest unit's log do.
-int record_pieces(Ctx& c, bool* fit)
+// A walk for the sizes that keeps each unit's size and segments, in the arrays the
+// recording uses; done: the path buffer has room for them.
+int size_units(Ctx& c, bool* done)
 {
-    *fit = false;
-    free_log(c);
-    if (!c.hold_words) {
-        ws_free(c, &c.unit_seg);
-        ws_free(c, &c.seg_off);
-        ws_free(c, &c.packed);
-    }
     const int64_t units = path_packets(c) * path_parts(c);
+    free_log(c);
+    if (!c.hold_words) ws_free(c, &c.unit_seg);
     hipError_t e = alloc_unit_seg(c);
     if (e == hipSuccess) e = ws_alloc(c, &c.unit_off, (size_t)units + 1, kRegionPath, true);
     if (e == hipSuccess) e = ws_alloc(c, &c.unit_log, (size_t)units, kRegionPath, true);
-    if (e != hipSuccess) return RRT_OK;
-    if (int r = path_walk(c, false, c.unit_off, nullptr)) return r;
+    *done = e == hipSuccess;
+    if (!*done) {
+        free_log(c);
+        if (!c.hold_words) ws_free(c, &c.unit_seg);
+        return RRT_OK;
+    }
+    return path_walk(c, false, c.unit_off, nullptr);
+}
+
+// The recording where the whole log does not fit beside the paths: a walk for the
+// units' sizes and segments, then walk and build alternately over ranges of the
+// units, each as long as the room left holds its log.  fit: the paths and the
+// largest unit's log do.  sized: size_units has made that walk just now.
+int record_pieces(Ctx& c, bool* fit, bool sized)
+{
+    *fit = false;
+    if (!sized) {
+        if (!c.hold_words) {
+            ws_free(c, &c.seg_off);
+            ws_free(c, &c.packed);
+        }
+        if (int r = size_units(c, &sized)) return r;
+        if (!sized) return RRT_OK;
+    }
+    const int64_t units = path_packets(c) * path_parts(c);
     const size_t segs = (size_t)std::max<uint64_t>(c.path_segs, 1);
-    e = alloc_paths(c, segs, c.last_words);
+    hipError_t e = alloc_paths(c, segs, c.last_words);
     if (e == hipSuccess) e = ws_alloc(c, &c.seg_src, segs, kRegionPath, true);
     if (e == hipSuccess) e = ws_alloc(c, &c.seg_unit, segs, kRegionPath, true);
     const uint64_t room = ws_largest_gap(c, kRegionPath) / (kLogBlock * sizeof(uint64_t));
@@ -515,27 +543,46 @@ int record_pieces(Ctx& c, bool* fit)
     HIP_OK(launch_unit_words(c));
     HIP_OK(scan_exclusive_u64(c, c.unit_off, c.unit_off, units + 1));
     HIP_OK(scan_exclusive_u64(c, c.unit_seg, c.unit_seg, units + 1));
-    int64_t n = std::max<int64_t>(
-        1, (int64_t)((double)units * (double)blocks / (double)(c.last_blocks + 1)));
+    // blocks a wave takes at once: as many as leave what the waves hold unused at a
+    // quarter of the log at most (the counter is one word for all of them)
+    const uint64_t waves = (uint64_t)std::min<int64_t>(units, kMaxWaves);
+    uint32_t take = kLogCache;
+    while (take > 1 && (!c.packet_queue || (take - 1) * waves > blocks / 4)) take /= 2;
+    const int parts = path_parts(c);
+    const int64_t per_dir = (c.n + 63) / 64 * parts;
+    // units from u on, some n of them: whole directions, else packets of one direction,
+    // else (a packet's log does not fit) units of one packet
+    int64_t n = (int64_t)((double)units * (double)(blocks - (take - 1) * waves) /
+                          (double)(c.last_blocks + 1));
+    auto range = [&](int64_t u) {
+        if (u % parts != 0 || n < parts)
+            return std::min<int64_t>(std::max<int64_t>(n, 1), parts - u % parts);
+        if (u % per_dir == 0 && n >= per_dir)
+            return std::min<int64_t>(n / per_dir * per_dir, units - u);
+        return std::min<int64_t>(n / parts * parts, per_dir - u % per_dir);
+    };
+    n = std::max<int64_t>(n, parts);
     uint64_t seg0 = 0;
     for (int64_t u = 0; u < units;) {
-        n = std::min({n, units - u, (int64_t)1 << 24});
+        const int64_t m = range(u);
         unsigned long long ctr[2] = {0, 0};
         uint64_t seg1 = 0;
         HIP_OK(hipMemsetAsync(c.log_ctr, 0, sizeof ctr, c.stream));
-        HIP_OK(launch_log_range(c, u, n));
+        HIP_OK(launch_log_range(c, u, m, take));
         HIP_OK(hipMemcpyAsync(ctr, c.log_ctr, sizeof ctr, hipMemcpyDeviceToHost, c.stream));
-        HIP_OK(hipMemcpyAsync(&seg1, c.unit_seg + u + n, sizeof seg1, hipMemcpyDeviceToHost,
+        HIP_OK(hipMemcpyAsync(&seg1, c.unit_seg + u + m, sizeof seg1, hipMemcpyDeviceToHost,
                               c.stream));
         HIP_OK(hipStreamSynchronize(c.stream));
         if (ctr[1] != 0) {                        // more log than the pool: a shorter range
-            if (n == 1) return fail(c, RRT_E_HIP, "the recording's log ran past its counted size");
-            n = (n + 1) / 2;
+            if (m == 1) return fail(c, RRT_E_HIP, "the recording's log ran past its counted size");
+            if (m <= parts && take > 1) take = 1;
+            else n = m / 2;
             continue;
         }
-        HIP_OK(launch_build_range(c, u, n, seg0, seg1 - seg0));
+        HIP_OK(launch_build_range(c, u, m, seg0, seg1 - seg0));
         seg0 = seg1;
-        u += n;
+        u += m;
+        if (u % parts == 0) n = std::max<int64_t>(n, parts);
     }
     free_log(c);
     *fit = true;
@@ -564,7 +611,7 @@ int record_paths(Ctx& c)
     c.log_tight = false;
     hipEvent_t ev_rec = ev_begin(c);
     int kind = c.counts_valid ? 2 : 3;      // after a count; a sizes walk first
-    bool logged = false;
+    bool logged = false, sized = false;
     if (!c.counts_valid && c.one_pass && c.last_total > 0 &&
         alloc_log(c, c.last_words, log_pool(c, c.last_blocks, c.pool_scale, true))) {
         bool overflow = false;
@@ -578,17 +625,23 @@ int record_paths(Ctx& c)
         if (overflow) c.pool_scale = std::min(c.pool_scale * 1.5, 4.0);
     } else if (!c.counts_valid) {
         hipEvent_t ew = ev_begin(c);
-        if (int r = path_walk(c, false, nullptr, nullptr)) return r;
+        if (int r = size_units(c, &sized)) return r;
+        if (!sized)
+            if (int r = path_walk(c, false, nullptr, nullptr)) return r;
         ev_end(c, ew, &c.t_other_walk);
     }
     c.counts_valid = true;
-    if (!logged && alloc_log(c, c.last_words, log_pool(c, c.last_blocks, 1.0, false))) {
-        bool overflow = false;
-        hipEvent_t ew = ev_begin(c);
-        if (int r = path_walk(c, true, nullptr, &overflow)) return r;
-        ev_end(c, ew, &c.t_other_walk);
-        if (overflow) return fail(c, RRT_E_HIP, "the recording's log ran past its counted size");
-        logged = true;
+    if (!logged && log_fits(c)) {
+        sized = false;                       // (the log's own arrays take their place)
+        logged = alloc_log(c, c.last_words, log_pool(c, c.last_blocks, 1.0, false));
+        if (logged) {
+            bool overflow = false;
+            hipEvent_t ew = ev_begin(c);
+            if (int r = path_walk(c, true, nullptr, &overflow)) return r;
+            ev_end(c, ew, &c.t_other_walk);
+            if (overflow)
+                return fail(c, RRT_E_HIP, "the recording's log ran past its counted size");
+        }
     }
     bool fit = false;
     if (logged) {
@@ -598,7 +651,7 @@ int record_paths(Ctx& c)
     }
     if (!fit) {
         hipEvent_t ew = ev_begin(c);
-        if (int r = record_pieces(c, &fit)) return r;
+        if (int r = record_pieces(c, &fit, sized)) return r;
         ev_end(c, ew, &c.t_other_walk);
     }
     if (!fit) {
@@ -1989,7 +2042,7 @@ int record_group(Ctx& c, const HaloGroup& g, bool* fit)
             if (int r = build_paths(c, fit)) return r;
     }
     if (!*fit)
-        if (int r = record_pieces(c, fit)) return r;
+        if (int r = record_pieces(c, fit, false)) return r;
     return RRT_OK;
 }
 

@@ -118,6 +118,8 @@ struct RayOut {
     // one wave per unit
     unsigned long long* queue;
     const unsigned long long* stop;   // column mode: holds something: nothing is written
+    // the queues' share of the packets: directions and, of each, packets of 64 sources
+    int32_t dir0, n_dir, pk0, n_pk;
 };
 
 // Place of tree position ps among the sorted sampled sources, or -1.
@@ -436,11 +438,12 @@ k_trace_wave(const Node* __restrict__ nodes, const float4* __restrict__ leaf_bal
     int64_t unit = wave;
     int part = 0;
     if (PQ) {
-        const uint32_t per = (uint32_t)(g.n_ray * parts);
+        const uint32_t per = (uint32_t)(out.n_dir * parts);
         uint32_t v = 0, b0 = 0;
         for (; spent < kQueues; ++spent, que = (que + 1) & (kQueues - 1)) {
-            b0 = (uint32_t)(waves_per_dir * que / kQueues);
-            const uint32_t len = (uint32_t)(waves_per_dir * (que + 1) / kQueues) - b0;
+            const uint32_t n_pk = (uint32_t)out.n_pk, at = n_pk * (uint32_t)que / kQueues;
+            const uint32_t len = n_pk * (uint32_t)(que + 1) / kQueues - at;
+            b0 = (uint32_t)out.pk0 + at;
             unsigned long long t = 0;
             if (lane == 0) t = atomicAdd(out.queue + (size_t)que * kQueueStride, 1ull);
             t = __shfl(t, 0, 64);
@@ -451,7 +454,7 @@ k_trace_wave(const Node* __restrict__ nodes, const float4* __restrict__ leaf_bal
         const uint32_t kk = kp / (uint32_t)parts;
         part = __builtin_amdgcn_readfirstlane((int)(kp - kk * (uint32_t)parts));
         // (every queue spent: past the last direction, which ends the wave)
-        wave = spent < kQueues ? (int64_t)kk * waves_per_dir + b0 + b
+        wave = spent < kQueues ? (int64_t)(kk + (uint32_t)out.dir0) * waves_per_dir + b0 + b
                                : (int64_t)g.n_ray * waves_per_dir;
         unit = wave * parts + part;
     } else if (kTally) {
@@ -980,12 +983,16 @@ static void launch_wave_nf(Ctx& c, RayOut o, int bs, size_t lds, int64_t waves)
                        c.nodes, c.leaf_ball, c.p4, c.mux_s, c.dirs, c.tables, c.geom, o);
 }
 
+// (units: of a range of them, whose part of the packets is in o already)
 template <int MODE>
-static void launch_wave(Ctx& c, RayOut o)
+static void launch_wave(Ctx& c, RayOut o, int64_t units = 0)
 {
     const int bs = c.prm.block_size > 0 ? c.prm.block_size : 128;
-    const int64_t waves = o.unit_end ? o.unit_end - o.unit0
-                                     : path_packets(c) * (mode_logs(MODE) ? o.parts : 1);
+    const int64_t waves = units ? units : path_packets(c) * (mode_logs(MODE) ? o.parts : 1);
+    if (!units) {
+        o.n_dir = c.n_ray;
+        o.n_pk = (int32_t)((c.n + 63) / 64);
+    }
     const size_t lds = wave_lds_bytes(MODE, bs);
     constexpr bool kSplit = MODE == kModeColumn;
     if (kSplit && o.near_far) launch_wave_nf<MODE, kSplit>(c, o, bs, lds, waves);
@@ -1108,21 +1115,36 @@ hipError_t launch_log_walk(Ctx& c, bool store, uint64_t* unit_size)
     return hipGetLastError();
 }
 
-// The log of a range of the units, whose sizes and segments are known.
-hipError_t launch_log_range(Ctx& c, int64_t unit0, int64_t units)
+// The log of a range of the units, whose sizes and segments are known: by the queues
+// where it is whole directions or whole packets of one, else a wave to a unit (whose
+// kernel spills and is three times as slow on many units).
+hipError_t launch_log_range(Ctx& c, int64_t unit0, int64_t units, uint32_t take)
 {
     RayOut o{};
     o.perm = c.perm;
     o.hits_total = c.red + kRedScratch;
     o.log = c.path_log;
     o.log_blocks = c.log_blocks;
-    o.log_take = 1;
+    o.log_take = take;
     o.log_ctr = c.log_ctr;
     o.unit_log = c.unit_log;
     o.parts = path_parts(c);
-    o.unit0 = unit0;
-    o.unit_end = unit0 + units;
-    launch_wave<kModeLog>(c, o);
+    const int64_t wpd = (c.n + 63) / 64, per_dir = wpd * o.parts, last = unit0 + units - 1;
+    const bool packets = unit0 % o.parts == 0 && units % o.parts == 0;
+    o.dir0 = (int32_t)(unit0 / per_dir);
+    if (c.packet_queue && unit0 % per_dir == 0 && units % per_dir == 0) {
+        o.n_dir = (int32_t)(units / per_dir);
+        o.n_pk = (int32_t)wpd;
+    } else if (c.packet_queue && packets && unit0 / per_dir == last / per_dir) {
+        o.n_dir = 1;
+        o.pk0 = (int32_t)(unit0 % per_dir / o.parts);
+        o.n_pk = (int32_t)(units / o.parts);
+    } else {
+        o.unit0 = unit0;
+        o.unit_end = unit0 + units;
+        o.log_take = 1;                   // a wave's blocks end with its unit
+    }
+    launch_wave<kModeLog>(c, o, units);
     return hipGetLastError();
 }
 

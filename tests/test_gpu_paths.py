@@ -296,3 +296,36 @@ def test_an_overflowing_particle_blocks_its_rays_only(near_far):
     assert not np.isnan(out[1]).any() and np.isinf(out[1]).any()
     np.testing.assert_array_equal(np.isinf(out[0]), np.isinf(out[1]))
     np.testing.assert_allclose(out[0], out[1], rtol=1e-11)
+
+
+@pytest.mark.parametrize("queue", [1, 0])
+@pytest.mark.parametrize("which", ["one", "packet_plus_one", "slots", "images", "field", "rays"])
+def test_pieces_of_every_size_give_the_same_paths(which, queue):
+    """From the least buffer to one that holds the whole log: pieces of single units,
+    packets, one direction and several directions, by the walk's queues or by a wave
+    to a unit, and recordings of a tree whose sizes are known, are not, or are the
+    last tree's: the same columns bit for bit."""
+    from paper_1304_4235_amd import Solver
+    if which == "rays":                                  # many directions of few packets
+        wl, leaf = W.uniform_lattice(n_side_lattice=7, box=20.0, l_ray=30.0, n_side=4), 0
+    else:
+        wl, leaf = _case(which)
+    x = torch.tensor(np.random.default_rng(5).uniform(1e-6, 1.0, wl.n))
+    s = Solver.from_workload(wl, leaf_size=leaf, record_paths=1)
+    need = s.count_paths()
+    s.set_state(x)
+    N = s.compute_columns()[0].clone()
+    s.close()
+    for extra in (0.0, 0.15, 0.6, 2.0, 5.0):
+        t = Solver.from_workload(wl, leaf_size=leaf, record_paths=1, build=False,
+                                 path_budget=need["bytes_paths"] + int(extra * need["hits"]))
+        t.set_tuning(packet_queue=queue)
+        for k in range(3):
+            t.build_tree()                               # counted, then the last tree's sizes
+            if k == 2:
+                t.set_tuning(one_pass=0)                 # a walk for the sizes
+            t.set_state(x)
+            got, h = t.compute_columns()
+            assert h == need["hits"] == t.timing()["path_hits"]
+            assert torch.equal(got, N), (extra, k)
+        t.close()
