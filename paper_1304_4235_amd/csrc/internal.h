@@ -307,7 +307,9 @@ struct Ctx {
     // tiles, the transposition): offsets and (tree index, factor) entries
     uint64_t* row_off = nullptr;  // [n_ray * n + 1]
     int2* path = nullptr;         // held while the density order uses it
-    bool rows_unfit = false;      // c.path was tried and did not fit
+    bool rows_unfit = false;      // c.path was tried and did not fit beside the paths,
+    bool rows_alone_unfit = false;    // nor without them
+    bool rows_only = false;       // the paths are held by rows alone
     bool rows_valid = false;      // row_off holds the recorded paths' offsets
     uint64_t* tpath = nullptr;    // transposed paths: (factor bits << 32 | row) by particle
     uint64_t* tcol_off = nullptr; // [n + 1] start of each particle's entries
@@ -343,6 +345,7 @@ struct Ctx {
     const int32_t* row_list = nullptr;   // the sources of the running density block, or null
     int64_t row_list_n = 0;
     int row_block = 0;             // its number
+    int row_sweeps = 0;            // sweeps the running solve may have ahead
     const uint8_t* row_frozen = nullptr;   // particles left out of a masked sweep, or null
     int path_evals = 0;            // column evaluations since the paths were recorded
     bool capturing = false;        // a graph capture is in progress (no allocation)
@@ -583,13 +586,16 @@ hipError_t launch_build_range(Ctx& c, int64_t unit0, int64_t units, uint64_t seg
 hipError_t launch_path_columns(Ctx& c);
 // the variant of its kernel that the recorded paths take
 int path_variant(const Ctx& c);
-// the rows of the listed sources (one block of the density order) from c.path
+// rows from c.path: those of the listed sources (one block of the density order), or
+// all that are wanted
 hipError_t launch_row_columns(Ctx& c, int group);
 hipError_t launch_path_scatter(Ctx& c, const float* nu, double* y);
 // row offsets of the recorded paths into c.row_off
 hipError_t ensure_row_offsets(Ctx& c);
 // the entries by rows: (tree index, factor), or keys and (factor bits, row)
 hipError_t launch_expand_rows(Ctx& c, int2* path);
+// those of the packets from pk0 to pk1 - 1
+hipError_t launch_expand_packets(Ctx& c, int2* path, int64_t pk0, int64_t pk1);
 hipError_t launch_expand_keys(Ctx& c, uint32_t* key, uint64_t* val);
 // sampled rows (tree-order row ids) of the recorded paths: counts when
 // dst_off is null, else the entries at those offsets

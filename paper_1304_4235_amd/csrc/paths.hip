@@ -666,7 +666,7 @@ struct RowsLds {
 template <bool KEYS>
 __global__ void __launch_bounds__(kBlock)
 k_path_rows(const uint64_t* __restrict__ unit_seg, const uint64_t* __restrict__ seg_off,
-            const uint4* __restrict__ packed, int64_t n_packets, int parts, int n,
+            const uint4* __restrict__ packed, int64_t pk0, int64_t n_packets, int parts, int n,
             const uint64_t* __restrict__ row_off, int2* __restrict__ path,
             uint32_t* __restrict__ key, uint64_t* __restrict__ val)
 {
@@ -674,7 +674,7 @@ k_path_rows(const uint64_t* __restrict__ unit_seg, const uint64_t* __restrict__ 
     const uint32_t t = threadIdx.x;
     const int lane = t & 63;
     const int64_t wpd = (n + 63) / 64;
-    for (int64_t pk = blockIdx.x; pk < n_packets; pk += gridDim.x) {
+    for (int64_t pk = pk0 + blockIdx.x; pk < n_packets; pk += gridDim.x) {
         const int64_t k = pk / wpd, p0 = (pk - k * wpd) * 64;
         if (t < 64) S.to[t] = p0 + t < n ? row_off[k * n + p0 + t] : 0ull;
         const uint32_t row0 = (uint32_t)(k * n + p0);
@@ -810,22 +810,24 @@ k_path_sampled(const uint64_t* __restrict__ unit_seg, const uint64_t* __restrict
 
 // The rows of a density block's sources (list), G lanes per row, from the paths
 // by rows: few rows of a packet run at a time there, and a packet's segments
-// would be staged for each.
+// would be staged for each.  Without a list every row, where the paths are held by
+// rows alone.
 template <int G>
 __global__ void __launch_bounds__(kBlock)
 k_row_columns(const uint64_t* __restrict__ row_off, const int2* __restrict__ path,
               const float* __restrict__ mux, int64_t n_rows, double* __restrict__ N, int64_t n,
               const uint8_t* __restrict__ frozen, const int32_t* __restrict__ list, int64_t list_n,
-              const unsigned long long* __restrict__ stop)
+              const uint8_t* __restrict__ want, const unsigned long long* __restrict__ stop)
 {
     const int lane = threadIdx.x & (G - 1);
     const int64_t stride = (int64_t)gridDim.x * (blockDim.x / G);
     const long long* p = reinterpret_cast<const long long*>(path);
-    const int64_t n_iter = list_n * (n_rows / n);
+    const int64_t n_iter = list ? list_n * (n_rows / n) : n_rows;
     const bool stopped = stop && *stop != 0ull;
     for (int64_t v = (blockIdx.x * (int64_t)blockDim.x + threadIdx.x) / G; v < n_iter;
          v += stride) {
-        const int64_t row = (v / list_n) * n + list[v % list_n];
+        const int64_t row = list ? (v / list_n) * n + list[v % list_n] : v;
+        if (want && !want[row % n]) continue;     // not evaluated
         if (frozen && frozen[row % n]) continue;  // not updated in this step
         const uint64_t a = row_off[row], b = row_off[row + 1];
         double acc = 0.0;
@@ -879,12 +881,13 @@ hipError_t launch_path_columns(Ctx& c)
 hipError_t launch_row_columns(Ctx& c, int group)
 {
     const int64_t n_rows = c.n * (int64_t)c.n_ray;
-    const int64_t n_iter = c.row_list_n * (int64_t)c.n_ray;
+    const int64_t n_iter = c.row_list ? c.row_list_n * (int64_t)c.n_ray : n_rows;
     if (n_iter == 0) return hipSuccess;
     auto go = [&](auto kernel, int g) {
         hipLaunchKernelGGL(kernel, dim3(stride_blocks(n_iter, kBlock / g)), dim3(kBlock), 0,
                            c.stream, c.row_off, c.path, c.mux_s, n_rows, c.N_s, c.n, c.row_frozen,
-                           c.row_list, c.row_list_n, c.batch_stop);
+                           c.row_list, c.row_list_n, c.row_list ? nullptr : c.geom.want,
+                           c.batch_stop);
     };
     if (group == 64) go(k_row_columns<64>, 64);
     else if (group == 32) go(k_row_columns<32>, 32);
@@ -908,19 +911,23 @@ hipError_t ensure_row_offsets(Ctx& c)
 
 hipError_t launch_expand_rows(Ctx& c, int2* path)
 {
-    const int64_t pk = path_packets(c);
-    hipLaunchKernelGGL(k_path_rows<false>, dim3((unsigned)std::min<int64_t>(pk, kMaxBlocks)), dim3(kBlock), 0, c.stream,
-                       c.unit_seg, c.seg_off, c.packed, pk, path_parts(c), (int)c.n, c.row_off, path, nullptr,
-                       nullptr);
+    return launch_expand_packets(c, path, 0, path_packets(c));
+}
+
+hipError_t launch_expand_packets(Ctx& c, int2* path, int64_t pk0, int64_t pk1)
+{
+    hipLaunchKernelGGL(k_path_rows<false>, dim3((unsigned)std::min<int64_t>(pk1 - pk0, kMaxBlocks)),
+                       dim3(kBlock), 0, c.stream, c.unit_seg, c.seg_off, c.packed, pk0, pk1,
+                       path_parts(c), (int)c.n, c.row_off, path, nullptr, nullptr);
     return hipGetLastError();
 }
 
 hipError_t launch_expand_keys(Ctx& c, uint32_t* key, uint64_t* val)
 {
     const int64_t pk = path_packets(c);
-    hipLaunchKernelGGL(k_path_rows<true>, dim3((unsigned)std::min<int64_t>(pk, kMaxBlocks)), dim3(kBlock), 0, c.stream,
-                       c.unit_seg, c.seg_off, c.packed, pk, path_parts(c), (int)c.n, c.row_off, nullptr, key,
-                       val);
+    hipLaunchKernelGGL(k_path_rows<true>, dim3((unsigned)std::min<int64_t>(pk, kMaxBlocks)),
+                       dim3(kBlock), 0, c.stream, c.unit_seg, c.seg_off, c.packed, (int64_t)0, pk,
+                       path_parts(c), (int)c.n, c.row_off, nullptr, key, val);
     return hipGetLastError();
 }
 

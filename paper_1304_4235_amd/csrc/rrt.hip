@@ -318,7 +318,7 @@ void free_paths(Ctx& c)
     c.path_segs = c.path_words = 0;
     ws_free(c, &c.path);
     c.rows_valid = false;
-    c.rows_unfit = false;
+    c.rows_unfit = c.rows_alone_unfit = c.rows_only = false;
     c.path_hits = 0;
     c.paths_valid = false;
     c.paths_unfit = false;
@@ -429,7 +429,7 @@ int path_walk(Ctx& c, bool store, uint64_t* unit_tally, bool* overflow)
     const size_t units = (size_t)(path_packets(c) * path_parts(c));
     Scratch<uint64_t> tmp(c);
     uint64_t* size = store ? c.unit_off : unit_tally;
-    if (!size && c.row_off && units <= (size_t)c.n * c.n_ray) {
+    if (!size && c.row_off && !c.path && units <= (size_t)c.n * c.n_ray) {
         size = c.row_off;
         c.rows_valid = false;
     }
@@ -669,6 +669,151 @@ int record_paths(Ctx& c)
     return RRT_OK;
 }
 
+// The paths by rows alone, where they have no room beside the packed ones: the
+// packed paths go, and are recorded again a range of packets at a time, each into
+// rows.  Leaves the packed paths (and rows_alone_unfit) where that has no room
+// either.  (A block of the density order evaluates a few rays of many packets: from
+// the packed paths each of its products reads those packets whole.)
+// Only where the sweeps ahead pay for it: on the 65536-particle halo in 16 blocks a
+// sweep takes 1.6 ms over the masked packets and 0.66 over rows, and the change 7, 11
+// and 38 ms in 2, 5 and 30 pieces (13, 10 and 8.3 bytes of buffer per intersection).
+int hold_rows_alone(Ctx& c)
+{
+    const int64_t hits = c.path_hits, wpd = (c.n + 63) / 64;
+    const int parts = path_parts(c);
+    const int64_t packets = wpd * c.n_ray, units = packets * parts;
+    // rows, the units' arrays and pieces of a 64th of the whole at least
+    const uint64_t whole = c.path_words * 16 + c.path_segs * kSegmentBytes +
+                           c.last_blocks * kLogBlock * 8;
+    const uint64_t fixed = region_bytes(std::max<int64_t>(hits, 1) * sizeof(int2)) +
+                           2 * region_bytes((units + 1) * sizeof(uint64_t)) +
+                           region_bytes(units * sizeof(uint2)) + 16 * kWsAlign;
+    const uint64_t kept = c.Nhist ? region_bytes(sizeof(double) * (uint64_t)c.Nhist_cap * c.n *
+                                                 c.n_ray) : 0;
+    const uint64_t room = c.arena.cap[kRegionPath] > fixed + kept
+                              ? c.arena.cap[kRegionPath] - fixed - kept : 0;
+    if (!c.rows_valid || room < whole / 64) {
+        c.rows_alone_unfit = true;
+        return RRT_OK;
+    }
+    if ((double)c.row_sweeps < 5.0 + 1.2 * (double)whole / (double)room) return RRT_OK;
+    Range range("rrt: paths by rows");
+    const bool counted = c.counts_valid;
+    free_paths(c);
+    c.rows_valid = true;                     // (row_off stays what it was)
+    int r = RRT_OK;
+    bool ok = ws_alloc(c, &c.path, (size_t)hits, kRegionPath) == hipSuccess;
+    if (ok) r = size_units(c, &ok);
+    std::vector<uint64_t> size(ok ? units : 0), seg(ok ? units + 1 : 0);
+    if (r == RRT_OK && ok) {
+        HIP_OK(hipMemcpyAsync(size.data(), c.unit_off, sizeof(uint64_t) * units,
+                              hipMemcpyDeviceToHost, c.stream));
+        HIP_OK(launch_unit_words(c));
+        HIP_OK(scan_exclusive_u64(c, c.unit_off, c.unit_off, units + 1));
+        HIP_OK(scan_exclusive_u64(c, c.unit_seg, c.unit_seg, units + 1));
+        HIP_OK(hipMemcpyAsync(seg.data(), c.unit_seg, sizeof(uint64_t) * (units + 1),
+                              hipMemcpyDeviceToHost, c.stream));
+        HIP_OK(hipStreamSynchronize(c.stream));
+        // the room in shares of the whole, each piece's arrays and log
+        const double share = 0.98 * (double)ws_largest_gap(c, kRegionPath) / (double)(whole + 1);
+        auto part_of = [&](uint64_t v) { return (uint64_t)(share * (double)v); };
+        const uint64_t cap_words = std::min<uint64_t>(part_of(c.path_words), c.path_words) + 64,
+                       cap_segs = std::min<uint64_t>(part_of(c.path_segs), c.path_segs) + 4,
+                       cap_blocks =
+                           std::min<uint64_t>(std::min<uint64_t>(part_of(c.last_blocks),
+                                                                 c.last_blocks) + 8, 0xfffffff0ull);
+        ok = ws_alloc(c, &c.packed, (size_t)cap_words + kPackedPad, kRegionPath) == hipSuccess &&
+             ws_alloc(c, &c.seg_off, (size_t)cap_segs, kRegionPath) == hipSuccess &&
+             ws_alloc(c, &c.seg_src, (size_t)cap_segs, kRegionPath) == hipSuccess &&
+             ws_alloc(c, &c.seg_unit, (size_t)cap_segs, kRegionPath) == hipSuccess &&
+             ws_alloc(c, &c.path_log, (size_t)cap_blocks * kLogBlock, kRegionPath) == hipSuccess;
+        c.log_blocks = cap_blocks;
+        // blocks that the walk's waves may hold unused, and so take at once
+        const uint64_t waves = (uint64_t)std::min<int64_t>(units, kMaxWaves);
+        const uint64_t spare = std::min<uint64_t>((kLogCache - 1) * waves, cap_blocks / 4);
+        const uint32_t take = c.packet_queue ? 1 + (uint32_t)(spare / waves) : 1;
+        HIP_OK(hipMemsetAsync(c.log_ctr, 0, 2 * sizeof(unsigned long long), c.stream));
+        uint64_t word0 = 0;
+        for (int64_t pk = 0; ok && pk < packets;) {
+            // packets from pk on (of one direction, or whole directions) whose segments,
+            // words and log fit
+            int64_t end = pk;
+            uint64_t w = 0, blocks = 0;
+            auto fits = [&](int64_t to, uint64_t ws, uint64_t bs) {
+                return ws <= cap_words && bs + (take - 1) * waves <= cap_blocks &&
+                       seg[to * parts] - seg[pk * parts] <= cap_segs;
+            };
+            int64_t whole_dirs = pk;         // the last end of a direction that fits
+            uint64_t whole_words = 0;
+            while (end < packets) {
+                uint64_t pw = 0, pb = 0;
+                for (int q = 0; q < parts; ++q) {
+                    pw += size[end * parts + q] & 0xffffffffull;
+                    pb += size[end * parts + q] >> 32;
+                }
+                if (!fits(end + 1, w + pw, blocks + pb)) break;
+                w += pw;
+                blocks += pb;
+                ++end;
+                if (end % wpd == 0) {
+                    whole_dirs = end;
+                    whole_words = w;
+                    if (pk % wpd != 0) break;          // the rest of a direction
+                }
+            }
+            if (pk % wpd == 0 && whole_dirs > pk) {
+                end = whole_dirs;
+                w = whole_words;
+            }
+            ok = end > pk;
+            if (!ok) break;
+            // the piece's arrays in place of the whole's
+            const uint64_t s0 = seg[pk * parts], s1 = seg[end * parts];
+            c.packed -= word0;
+            c.seg_off -= s0;
+            c.seg_src -= s0;
+            c.seg_unit -= s0;
+            hipError_t e = hipMemsetAsync(c.log_ctr, 0, sizeof(unsigned long long), c.stream);
+            if (e == hipSuccess)
+                e = launch_log_range(c, pk * parts, (end - pk) * parts, take);
+            if (e == hipSuccess)
+                e = launch_build_range(c, pk * parts, (end - pk) * parts, s0, s1 - s0);
+            if (e == hipSuccess) e = launch_expand_packets(c, c.path, pk, end);
+            c.packed += word0;
+            c.seg_off += s0;
+            c.seg_src += s0;
+            c.seg_unit += s0;
+            HIP_OK(e);
+            word0 += w;
+            pk = end;
+        }
+        unsigned long long ctr[2] = {0, 0};
+        HIP_OK(hipMemcpyAsync(ctr, c.log_ctr, sizeof ctr, hipMemcpyDeviceToHost, c.stream));
+        HIP_OK(hipStreamSynchronize(c.stream));
+        if (ctr[1]) return fail(c, RRT_E_HIP, "the rows' log ran past its counted size");
+    }
+    if (r == RRT_OK && ok) {
+        free_log(c);
+        ws_free(c, &c.packed);
+        ws_free(c, &c.seg_off);
+        ws_free(c, &c.unit_seg);
+        c.path_hits = hits;
+        c.rows_only = true;
+        return RRT_OK;
+    }
+    c.counts_valid = counted;
+    if (int q = record_paths(c)) return q;   // as they were
+    c.rows_unfit = c.rows_alone_unfit = true;
+    return r;
+}
+
+// Packed paths again where they are held by rows alone.
+int packed_again(Ctx& c)
+{
+    if (!c.rows_only) return RRT_OK;
+    return record_paths(c);
+}
+
 // The running density block as a mask over all particles, for an evaluation
 // that takes no list.
 hipError_t mask_block(Ctx& c)
@@ -684,20 +829,20 @@ hipError_t mask_block(Ctx& c)
 int columns_impl(Ctx& c, int64_t* hits)
 {
     *hits = -1;
-    if (c.prm.record_paths != 0 && !c.paths_valid && !c.paths_unfit) {
+    if (c.prm.record_paths != 0 && !c.paths_valid && !c.paths_unfit && !c.rows_only) {
         if (int r = record_paths(c)) return r;
     }
-    if (c.paths_valid) {
-        if (c.use_tiles && !c.near_far && !c.tiles_valid && !c.tiles_unfit && !c.capturing &&
+    if (c.paths_valid || c.rows_only) {
+        if (c.use_tiles && c.paths_valid && !c.near_far && !c.tiles_valid && !c.tiles_unfit && !c.capturing &&
             ++c.path_evals > kTileAfter) {
             hipEvent_t et = ev_begin(c);
             HIP_OK(build_tiles(c));
             ev_end(c, et, &c.t_tile_build);
         }
         // One block of the density order runs a few rays of most packets, so it
-        // takes the paths by rows, which walk only its own; without room for
-        // them, the packets' product with the others masked.  The tiles serve
-        // full sweeps.
+        // takes the paths by rows, which walk only its own: beside the packed ones,
+        // or in their place; without room for them, the packets' product with the
+        // others masked.  The tiles serve full sweeps.
         const bool tiles = c.tiles_valid && c.use_tiles && !c.near_far && !c.row_list;
         if (c.row_list && !c.path && !c.rows_unfit) {
             hipError_t e = ensure_row_offsets(c);
@@ -710,6 +855,8 @@ int columns_impl(Ctx& c, int64_t* hits)
             }
             HIP_OK(e);
         }
+        if (c.row_list && !c.path && !c.rows_alone_unfit)
+            if (int r = hold_rows_alone(c)) return r;
         if (c.row_list && !c.path) HIP_OK(mask_block(c));
         const double mean = (double)c.path_hits /
                             (double)std::max<int64_t>(c.n * (int64_t)c.n_ray, 1);
@@ -719,7 +866,7 @@ int columns_impl(Ctx& c, int64_t* hits)
                           : mean >= 40 ? 32 : mean >= 16 ? 16 : 8;
         hipEvent_t ep = ev_begin(c);
         if (tiles) HIP_OK(launch_tile_columns(c, tile_group(c)));
-        else if (c.row_list && c.path) HIP_OK(launch_row_columns(c, group));
+        else if (c.rows_only || (c.row_list && c.path)) HIP_OK(launch_row_columns(c, group));
         else HIP_OK(launch_path_columns(c));
         if (c.timing) {
             if (tiles) {
@@ -1547,6 +1694,8 @@ int rrt_iterate_equilibrium(rrt_ctx* x, int32_t max_iter, double tol, double* x_
     int launched = 0;                         // sweeps whose slots are still to be read
     for (it = 0; it < max_iter;) {
         int64_t hits = -1;
+        // (a solve to a tolerance usually ends within some tens of sweeps)
+        c.row_sweeps = tol > 0.0 ? std::min(max_iter, 30) - it : max_iter - it - launched;
         for (int b = 0; b < n_steps; ++b) {
             // one block of the density order (all particles for the
             // order-independent update), frozen particles left out
@@ -1661,6 +1810,7 @@ int rrt_forward(rrt_ctx* x, int32_t K, double* lnG_out, double* x_out)
     }
     const size_t nr = n * (size_t)c.n_ray;
     c.fwd_K = -1;
+    if (c.rows_only) free_paths(c);
     ws_free(c, &c.path);               // the density order's: its room may be needed
     HIP_OK(launch_init_state(c, false));
     HIP_OK(hipMemcpyAsync(c.xhist, c.x_s, sizeof(double) * n, hipMemcpyDeviceToDevice,
@@ -1708,6 +1858,7 @@ int rrt_backward(rrt_ctx* x, const double* dL_dlnG, const double* dL_dx, double*
     if (c.fwd_K < 1) return fail(c, RRT_E_STATE, "rrt_forward must precede rrt_backward");
     if (!c.all_bins_weighted)
         return fail(c, RRT_E_ARG, "gradients need every bin weight w_b > 0");
+    if (int r = packed_again(c)) return r;
     const size_t n = (size_t)c.n, nr = n * (size_t)c.n_ray;
     const int64_t waves = adj_waves(c);
     if (!c.adj_lam || c.adj_n != n || c.adj_nr != nr) {
@@ -2135,6 +2286,7 @@ int rrt_iterate_halos(rrt_ctx* x, int32_t max_iter, double tol, int32_t per_laun
         return fail(c, RRT_E_STATE, "batched halos use the plain order-independent case A "
                                     "update: reset the update rule and the scheme");
     if (int r = ensure_seg_buffers(c)) return r;
+    if (c.rows_only) free_paths(c);
     SegGuard guard(c);
     HIP_OK(launch_seg_init(c));
     c.conv_tol = tol > 0.0 ? tol : 1e-3;
@@ -2376,6 +2528,7 @@ int rrt_get_path_rows(rrt_ctx* x, int32_t n_src, const int64_t* src, int64_t cap
     Ctx& c = x->c;
     if (int r = need_tree(c)) return r;
     if (!row_off) return fail(c, RRT_E_ARG, "row_off is required");
+    if (int r = packed_again(c)) return r;
     if (!c.paths_valid) return fail(c, RRT_E_STATE, "no recorded paths");
     std::vector<int32_t> pos;
     if (int r = tree_positions(c, n_src, src, pos)) return r;
@@ -2513,7 +2666,7 @@ int rrt_get_timing(rrt_ctx* x, double* out, int32_t n_out)
     ev_flush(c);
     const double v[RRT_N_TIMING] = {
         c.t_trace, c.t_rate, c.t_build, c.n_trace, c.t_record, c.t_spmv, c.n_spmv,
-        c.paths_valid ? (double)c.path_hits : -1.0, c.t_tile, c.n_tile, c.t_tile_build,
+        c.paths_valid || c.rows_only ? (double)c.path_hits : -1.0, c.t_tile, c.n_tile, c.t_tile_build,
         c.tiles_valid ? (double)c.tile_set_total : -1.0, c.t_chunk_walk, c.n_chunk_walk,
         c.t_compact, c.t_other_walk};
     for (int32_t i = 0; i < std::min<int32_t>(n_out, RRT_N_TIMING); ++i) out[i] = v[i];

@@ -164,3 +164,47 @@ def test_rule_over_row_tiles(halo, blocks):
         res.append(r["x"].cpu().numpy())
         s.close()
     np.testing.assert_allclose(res[1], res[0], rtol=1e-9)
+
+
+@pytest.mark.parametrize("extra", [7.0, 8.3, 10.0, 13.0])
+def test_density_blocks_over_rows_alone(extra):
+    """The density order (enough sweeps of it) where the paths by rows have no room beside the packed ones
+    (under some 14 bytes of buffer per intersection): held alone from 8 bytes on, else
+    the packed paths with the other blocks masked.  The blocks' results are those of a
+    buffer with room for both, and everything else that reads recorded paths goes on:
+    plain sweeps, columns, the paths by rows, gradients, the blocks again."""
+    from paper_1304_4235_amd import Solver
+    halo = W.isothermal_halo(n=9000, seed=72, n_bins=8, n_peak=1.0)
+    src = np.arange(0, halo.n, 97)
+    out = []
+    hits = None
+    for budget in (0, 1):
+        s = Solver.from_workload(halo, record_paths=1,
+                                 path_budget=int(extra * hits) + (1 << 16) if budget else 0)
+        hits = s.count_paths()["hits"]
+        s.set_update_rule(n_blocks=7, tau_skip=0.02)
+        a = s.iterate(60, 0.0)["x"].cpu().numpy()
+        assert s.timing()["path_hits"] == hits
+        s.set_update_rule()
+        N, h = s.compute_columns()
+        assert h == hits
+        b = s.iterate(3, 0.0)["x"].cpu().numpy()
+        s.set_update_rule(tau_skip=0.02)
+        m = s.iterate(2, 0.0)["x"].cpu().numpy()
+        off, j, fac = s.path_rows(src)
+        s.set_update_rule(n_blocks=3)
+        c = s.iterate(2, 0.0)["x"].cpu().numpy()
+        s.set_update_rule()
+        lnG, x = s.forward(2)
+        s.set_update_rule(n_blocks=3)
+        s.set_state(None)
+        s.iterate(1, 0.0)
+        s.set_update_rule()
+        dw, dn = s.backward(torch.ones_like(lnG), None)
+        out.append((a, N.cpu().numpy(), b, m, c, x.cpu().numpy(), dw, dn.cpu().numpy(), off, j, fac))
+        s.close()
+    for p, q in zip(*out):
+        if p.dtype.kind == "f":
+            np.testing.assert_allclose(q, p, rtol=1e-9, atol=1e-12 * np.abs(p).max())
+        else:
+            np.testing.assert_array_equal(q, p)
