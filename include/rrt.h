@@ -164,8 +164,9 @@ int rrt_count_paths(rrt_ctx* ctx, int64_t* n_hits, size_t* bytes_paths, size_t* 
  * paths, the library uses the rest of it for the walk's log while recording,
  * and, room permitting, for the reverse mode's transposed paths and kept
  * columns, for row tiles and for the paths by rows that the density order's
- * blocks read; each of these is optional and has a slower form that needs no
- * memory.  Replacing the buffer drops the recorded
+ * blocks read (8 bytes per intersection beside the paths, or in their place
+ * where a solve has the sweeps to pay for it); each of these is optional and
+ * has a slower form that needs no memory.  Replacing the buffer drops the recorded
  * paths and everything in the old buffer (synchronises the stream first). */
 int rrt_set_path_buffer(rrt_ctx* ctx, void* dev, size_t bytes);
 

@@ -168,7 +168,7 @@ def test_rule_over_row_tiles(halo, blocks):
 
 @pytest.mark.parametrize("extra", [7.0, 8.3, 10.0, 13.0])
 def test_density_blocks_over_rows_alone(extra):
-    """The density order (enough sweeps of it) where the paths by rows have no room beside the packed ones
+    """The density order (enough sweeps of it) where rows have no room beside the packed paths
     (under some 14 bytes of buffer per intersection): held alone from 8 bytes on, else
     the packed paths with the other blocks masked.  The blocks' results are those of a
     buffer with room for both, and everything else that reads recorded paths goes on:
