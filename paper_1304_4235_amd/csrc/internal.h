@@ -628,21 +628,28 @@ inline int ray_ways(int64_t waves, int n_ray)
     return w;
 }
 // Waves per packet of the columns' product over `live` packets of `segs` segments
-// in all (the other packets of the launch end at once): below 16384 waves, as many as the segments keep busy; beyond, so few
-// that each has several segments to run ahead over, and never so many that the
-// launch has 2^32 work-items.
+// in all (the other packets of the launch end at once): below 16384 waves, as many as
+// the segments keep busy; beyond, so few that each has several segments to run ahead
+// over; and never so many that the launch has 2^32 work-items.
 // Measured on MI355X (ms per product at 1, 2, 4, 8 waves): the 885k-particle
 // field's 663552 packets of 3.4 segments 4.05, 3.93, 5.02, -; the 262144-
 // particle halo's 49152 of 20: 2.03, -, 1.55, 1.72; 12 halos' 26236 of 9:
 // -, 0.255, -, 0.34; 640-particle halos in groups, 936 packets of which some 250
 // are recorded, us at 1, 8: 20, 9.  (The limits between those points are taken from
 // them, not measured one by one.)
+// A wave that ends at once takes 0.13 ns of the launch, a doubling of the waves spares
+// a lone packet some half microsecond per segment and wave: so the packets that are not
+// recorded count, against that gain where waves are few and in the mean where they are
+// many (64 halos in two groups, 1.34M packets: 10.03 ms with 2 waves, 10.49 with 4).
 inline int path_ways(int64_t packets, int64_t live, uint64_t segs)
 {
     const double mean = (double)segs / (double)(live > 0 ? live : 1);
+    const double over_all = (double)segs / (double)(packets > 0 ? packets : 1);
+    const double idle = (double)(packets - live);
     int w = 1;
     while (w < 8 && packets * 64 * (2 * w) < (int64_t(1) << 32) &&
-           (live * w < 16384 ? mean > w : mean > (w == 1 ? 3 : 6) * w))
+           (live * w < 16384 ? mean > w && idle * w * w < 4000 * mean
+                             : over_all > (w == 1 ? 3 : 6) * w))
         w *= 2;
     return w;
 }

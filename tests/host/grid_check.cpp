@@ -38,6 +38,12 @@ int main()
         std::fprintf(stderr, "path_ways: not the measured choices\n");
         return 1;
     }
+    // packets that are not recorded: their waves count against the gain
+    if (path_ways(1335724, 667862, 13357240) != 2 || path_ways(1335724, 250, 5000) != 1 ||
+        path_ways(26236, 8745, 78705) != 2) {
+        std::fprintf(stderr, "path_ways: packets that are not recorded do not count\n");
+        return 1;
+    }
     std::printf("grid checks passed\n");
     return 0;
 }
